@@ -3,7 +3,7 @@
 // (Sec. 3.2):
 //   A_a1(q) = sum_i1 G[q1][i1] sum_i2 B[q2][i2] x_a(i1,i2),
 //   A_a2(q) = sum_i1 B[q1][i1] sum_i2 G[q2][i2] x_a(i1,i2).
-// Pencil sweeps with the 1D tables read from the kernel arguments (scalar
+// Pencil sweeps with the 1D tables read from the kernel arguments (Tab, scalar
 // operands).  LDS per workgroup:
 //   X   [EPB][2][NI^2]          element nodes (or v_E)
 //   R1  [EPB][2][2][NI][NQ]     after the axis-1 contraction (B, G variants)
@@ -60,58 +60,53 @@ __device__ __forceinline__ int node2(const Geom &g, int e, int i1, int i2, int &
 // [e][c][i] on general meshes, the exploded grid [c][ey*NI+i2][ex*NI+i1] on
 // the structured box (the layout the node gather expects).
 template <int P>
-__device__ __forceinline__ long ev_index2(const Geom &g, int e, int c, int i1, int i2)
+__device__ __forceinline__ uint32_t ev_index2(const Geom &g, int e, int c, int i1, int i2)
 {
+    // the E-vector has fewer than 2^31 entries (checked when a mesh is taken)
     constexpr int NI = P + 1, NP = NI * NI;
-    if (g.e2n) return ((long)e * 2 + c) * NP + i1 + NI * i2;
+    if (g.e2n) return (e * 2 + c) * NP + i1 + NI * i2;
     int ex, ey, ez;
     box_elem<2>(g, e, ex, ey, ez);
-    const long EX = (long)g.nel[0] * NI;
-    return (long)c * g.ne * NP + (long)(ey * NI + i2) * EX + ex * NI + i1;
+    const int EX = g.nel[0] * NI;
+    return c * (g.ne * NP) + (ey * NI + i2) * EX + ex * NI + i1;
 }
 
 // Gather 2 components of a global vector into X (masked: fixed DoFs as zero;
-// sub: a vector subtracted entry by entry).
+// sub: a vector subtracted entry by entry).  A lane takes one node and its two
+// components (EPB NP <= 256), so the node's place is worked out once.
 template <int P, int NQ, typename CT>
 __device__ __forceinline__ void gather2(const Geom &g, const double *__restrict__ vec, int e0, int nel,
                                CT *sX, bool masked, const double *__restrict__ sub = nullptr)
 {
     using S = S2<P, NQ>;
     constexpr int NI = S::NI, NP = S::NP;
-    constexpr int NIT = (S::EPB * 2 * NP + BLOCK - 1) / BLOCK;
-    const int n = nel * 2 * NP;
-    double val[NIT];
-    bool fix[NIT];
+    static_assert(S::EPB * NP <= BLOCK, "one node per lane");
+    const int i = threadIdx.x % NP, el = threadIdx.x / NP;
+    if ((int)threadIdx.x < nel * NP) {
+        int gx, gy;
+        const int node = node2<P>(g, e0 + el, i % NI, i / NI, gx, gy);
+        double val[2];
+        bool fix[2];
 #pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-        const int idx = threadIdx.x + it * BLOCK;
-        val[it] = 0.0;
-        fix[it] = false;
-        if (idx < n) {
-            const int i = idx % NP;
-            const int r = idx / NP;  // el*2 + c
-            const int c = r % 2, el = r / 2;
-            int gx, gy;
-            const int node = node2<P>(g, e0 + el, i % NI, i / NI, gx, gy);
-            val[it] = vec[(size_t)c * g.nx + node];
-            if (sub) val[it] -= sub[(size_t)c * g.nx + node];
-            fix[it] = masked && is_fixed(g, c, node, gx, gy, 0);
+        for (int c = 0; c < 2; ++c) {
+            const size_t at = (size_t)c * g.nx + node;
+            val[c] = vec[at];
+            if (sub) val[c] -= sub[at];
+            fix[c] = masked && is_fixed(g, c, node, gx, gy, 0);
         }
-    }
 #pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-        const int idx = threadIdx.x + it * BLOCK;
-        if (idx < n) sX[idx] = fix[it] ? (CT)0 : (CT)val[it];
+        for (int c = 0; c < 2; ++c) sX[(el * 2 + c) * NP + i] = fix[c] ? (CT)0 : (CT)val[c];
     }
 }
 
 // Forward sweeps X -> R1 -> RY: J (plane el*NR + c*2 + b), with VAL also the
 // value of component c (plane el*NR + 4 + c).
 template <int P, int NQ, typename CT, int NR = 4, bool VAL = false>
-__device__ __forceinline__ void forward2(const Tables &tb, const CT *X, CT *R1, CT *RY, int nel)
+__device__ __forceinline__ void forward2(const Tab &tables, const CT *X, CT *R1, CT *RY, int nel)
 {
     using S = S2<P, NQ>;
     constexpr int NI = S::NI, NP = S::NP, L1 = S::L1, NQ2 = S::NQ2;
+    Tab tb = tables.again();
     // axis 1: pencils (r, i2), r = el*2 + c
     for (int pen = threadIdx.x; pen < nel * 2 * NI; pen += BLOCK) {
         const int i2 = pen % NI, r = pen / NI;
@@ -133,6 +128,7 @@ __device__ __forceinline__ void forward2(const Tables &tb, const CT *X, CT *R1, 
         }
     }
     __syncthreads();
+    tb = tables.again();
     // axis 2: pencils (r, q1)
     for (int pen = threadIdx.x; pen < nel * 2 * NQ; pen += BLOCK) {
         const int q1 = pen % NQ, r = pen / NQ;
@@ -167,11 +163,12 @@ __device__ __forceinline__ void forward2(const Tables &tb, const CT *X, CT *R1, 
 // Backward (transposed) sweeps RY -> R1 -> E-vector:
 //   y_c(i) = sum_q sum_b RY[c][b](q) d w_i/d xbar_b (q)  (+ RY[4+c](q) w_i(q) with VAL).
 template <int P, int NQ, typename CT, typename OT, int NR = 4, bool VAL = false>
-__device__ __forceinline__ void backward2(const Tables &tb, const Geom &g, int e0, const CT *RY, CT *R1,
+__device__ __forceinline__ void backward2(const Tab &tables, const Geom &g, int e0, const CT *RY, CT *R1,
                                  int nel, OT *__restrict__ out)
 {
     using S = S2<P, NQ>;
     constexpr int NI = S::NI, L1 = S::L1, NQ2 = S::NQ2;
+    Tab tb = tables.again();
     // axis 2: pencils (r, q1)
     for (int pen = threadIdx.x; pen < nel * 2 * NQ; pen += BLOCK) {
         const int q1 = pen % NQ, r = pen / NQ;
@@ -201,6 +198,7 @@ __device__ __forceinline__ void backward2(const Tables &tb, const Geom &g, int e
         }
     }
     __syncthreads();
+    tb = tables.again();
     // axis 1: pencils (r, i2) -> NI consecutive outputs
     for (int pen = threadIdx.x; pen < nel * 2 * NI; pen += BLOCK) {
         const int i2 = pen % NI, r = pen / NI;
@@ -233,14 +231,14 @@ __device__ __forceinline__ void point_J2(const CT *RY, int el, int q, CT *J)
 }
 
 template <int NQ>
-__device__ __forceinline__ double qweight2(const Tables &tb, int q)
+__device__ __forceinline__ double qweight2(const double *sw, int q)
 {
-    return tab_w<NQ>(tb, q % NQ) * tab_w<NQ>(tb, q / NQ);
+    return sw[q % NQ] * sw[q / NQ];
 }
 
 // Values of x - x0 at the points into U[el][c][q] (limiting term).
 template <int P, int NQ, typename L2>
-__device__ __forceinline__ void lim_values2(const Geom &g, const Tables &tb, const double *__restrict__ x,
+__device__ __forceinline__ void lim_values2(const Geom &g, const Tab &tb, const double *__restrict__ x,
                                    int e0, int nel, L2 &L, double *U)
 {
     using S = S2<P, NQ>;
@@ -256,10 +254,10 @@ __device__ __forceinline__ void lim_values2(const Geom &g, const Tables &tb, con
 
 // Limiting term in the Hessian action: value planes v_c(q) -> 2 w_q lim v_c(q).
 template <int NQ, typename CT, int NR>
-__device__ __forceinline__ void lim_point2(const Tables &tb, const Geom &g, int el, int q, CT *RY)
+__device__ __forceinline__ void lim_point2(const double *sw, const Geom &g, int el, int q, CT *RY)
 {
     constexpr int NQ2 = NQ * NQ;
-    const CT f = (CT)(2.0 * g.lim * qweight2<NQ>(tb, q));
+    const CT f = (CT)(2.0 * g.lim * qweight2<NQ>(sw, q));
 #pragma unroll
     for (int c = 0; c < 2; ++c) RY[(el * NR + 4 + c) * NQ2 + q] *= f;
 }
@@ -269,7 +267,7 @@ __device__ __forceinline__ void lim_point2(const Tables &tb, const Geom &g, int 
 // ------------------------------------------------------------------------
 
 template <int P, int NQ, bool LIM = false>
-__device__ __forceinline__ void b2_energy(const Geom &g, const Tables &tb, const Target &tg,
+__device__ __forceinline__ void b2_energy(const Geom &g, const Tab &tb, const Target &tg,
                                  const double *__restrict__ x, double *__restrict__ part, int e0,
                                  int nel)
 {
@@ -278,6 +276,8 @@ __device__ __forceinline__ void b2_energy(const Geom &g, const Tables &tb, const
     __shared__ Lds2<P, NQ, double, NR> L;
     __shared__ double U[LIM ? S::EPB * 2 * S::NQ2 : 1];
     __shared__ double red[3 * (BLOCK / 64)];
+    __shared__ double sw[NQ];
+    weights_to_lds<NQ>(tb, sw);
     if (LIM) lim_values2<P, NQ>(g, tb, x, e0, nel, L, U);
     gather2<P, NQ>(g, x, e0, nel, L.X, false);
     __syncthreads();
@@ -288,14 +288,14 @@ __device__ __forceinline__ void b2_energy(const Geom &g, const Tables &tb, const
         double J[4], Pm[4], mu;
         point_J2<P, NQ, double, NR>(L.RY, el, q, J);
         dmin = fmin(dmin, det_only<2>(J));
-        const double z = qweight2<NQ>(tb, q) * tg.detW;
+        const double z = qweight2<NQ>(sw, q) * tg.detW;
         if (metric_first<2>(tg, J, z, &mu, Pm))
             esum += z * mu;
         else
             bad += 1.0;
         if (LIM) {
             const double u0 = U[(el * 2) * S::NQ2 + q], u1 = U[(el * 2 + 1) * S::NQ2 + q];
-            esum += qweight2<NQ>(tb, q) * g.lim * (u0 * u0 + u1 * u1);
+            esum += qweight2<NQ>(sw, q) * g.lim * (u0 * u0 + u1 * u1);
         }
     }
     block_energy3(esum, dmin, bad, red);
@@ -308,7 +308,7 @@ __device__ __forceinline__ void b2_energy(const Geom &g, const Tables &tb, const
 
 // EN: also the energy partials of b2_energy, as in b3_gradient.
 template <int P, int NQ, bool LIM = false, bool EN = false>
-__device__ __forceinline__ void b2_gradient(const Geom &g, const Tables &tb, const Target &tg,
+__device__ __forceinline__ void b2_gradient(const Geom &g, const Tab &tb, const Target &tg,
                                    const double *__restrict__ x, double *__restrict__ gE,
                                    double *__restrict__ bad, int e0, int nel)
 {
@@ -317,6 +317,8 @@ __device__ __forceinline__ void b2_gradient(const Geom &g, const Tables &tb, con
     __shared__ Lds2<P, NQ, double, NR> L;
     __shared__ double U[LIM ? S::EPB * 2 * S::NQ2 : 1];
     __shared__ double red[3 * (BLOCK / 64)];
+    __shared__ double sw[NQ];
+    weights_to_lds<NQ>(tb, sw);
     if (LIM) lim_values2<P, NQ>(g, tb, x, e0, nel, L, U);
     gather2<P, NQ>(g, x, e0, nel, L.X, false);
     __syncthreads();
@@ -327,7 +329,7 @@ __device__ __forceinline__ void b2_gradient(const Geom &g, const Tables &tb, con
         double J[4], Pm[4], mu;
         point_J2<P, NQ, double, NR>(L.RY, el, q, J);
         if (EN) dmin = fmin(dmin, det_only<2>(J));
-        const double z = qweight2<NQ>(tb, q) * tg.detW;
+        const double z = qweight2<NQ>(sw, q) * tg.detW;
         if (!metric_first<2>(tg, J, z, &mu, Pm)) {
             nbad += 1.0;
 #pragma unroll
@@ -337,7 +339,7 @@ __device__ __forceinline__ void b2_gradient(const Geom &g, const Tables &tb, con
         }
         if (EN && LIM) {
             const double u0 = U[(el * 2) * S::NQ2 + q], u1 = U[(el * 2 + 1) * S::NQ2 + q];
-            esum += qweight2<NQ>(tb, q) * g.lim * (u0 * u0 + u1 * u1);
+            esum += qweight2<NQ>(sw, q) * g.lim * (u0 * u0 + u1 * u1);
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) L.RY[(el * NR + k) * S::NQ2 + q] = Pm[k];
@@ -345,7 +347,7 @@ __device__ __forceinline__ void b2_gradient(const Geom &g, const Tables &tb, con
 #pragma unroll
             for (int c = 0; c < 2; ++c)
                 L.RY[(el * NR + 4 + c) * S::NQ2 + q] =
-                    2.0 * qweight2<NQ>(tb, q) * g.lim * U[(el * 2 + c) * S::NQ2 + q];
+                    2.0 * qweight2<NQ>(sw, q) * g.lim * U[(el * 2 + c) * S::NQ2 + q];
         }
     }
     __syncthreads();
@@ -364,13 +366,15 @@ __device__ __forceinline__ void b2_gradient(const Geom &g, const Tables &tb, con
 }
 
 template <int P, int NQ, typename TT>
-__device__ __forceinline__ void b2_setup(const Geom &g, const Tables &tb, const Target &tg,
+__device__ __forceinline__ void b2_setup(const Geom &g, const Tab &tb, const Target &tg,
                                 const double *__restrict__ x, TT *__restrict__ H,
                                 double *__restrict__ bad, int e0, int nel)
 {
     using S = S2<P, NQ>;
     __shared__ Lds2<P, NQ, double> L;
     __shared__ double red[BLOCK / 64];
+    __shared__ double sw[NQ];
+    weights_to_lds<NQ>(tb, sw);
     gather2<P, NQ>(g, x, e0, nel, L.X, false);
     __syncthreads();
     forward2<P, NQ, double>(tb, L.X, L.R1, L.RY, nel);
@@ -379,7 +383,7 @@ __device__ __forceinline__ void b2_setup(const Geom &g, const Tables &tb, const 
         const int el = idx / S::NQ2, q = idx % S::NQ2;
         double J[4], Hp[10];
         point_J2<P, NQ>(L.RY, el, q, J);
-        const double z = qweight2<NQ>(tb, q) * tg.detW;
+        const double z = qweight2<NQ>(sw, q) * tg.detW;
         if (!metric_second<2>(tg, J, z, Hp)) {
             nbad += 1.0;
 #pragma unroll
@@ -394,12 +398,14 @@ __device__ __forceinline__ void b2_setup(const Geom &g, const Tables &tb, const 
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM = false>
-__device__ __forceinline__ void b2_apply(const Geom &g, const Tables &tb, const TT *__restrict__ H,
+__device__ __forceinline__ void b2_apply(const Geom &g, const Tab &tb, const TT *__restrict__ H,
                                 const double *__restrict__ v, CT *__restrict__ yE, int e0, int nel)
 {
     using S = S2<P, NQ>;
     constexpr int NR = Planes2<LIM>::NR;
     __shared__ Lds2<P, NQ, CT, NR> L;
+    __shared__ double sw[LIM ? NQ : 1];
+    if (LIM) weights_to_lds<NQ>(tb, sw);
     gather2<P, NQ>(g, v, e0, nel, L.X, true);
     __syncthreads();
     forward2<P, NQ, CT, NR, LIM>(tb, L.X, L.R1, L.RY, nel);
@@ -418,7 +424,7 @@ __device__ __forceinline__ void b2_apply(const Geom &g, const Tables &tb, const 
             for (int c = 0; c < 4; ++c) s += hv[sym_index<4>(r, c)] * J[c];
             L.RY[(el * NR + r) * S::NQ2 + q] = s;
         }
-        if (LIM) lim_point2<NQ, CT, NR>(tb, g, el, q, L.RY);
+        if (LIM) lim_point2<NQ, CT, NR>(sw, g, el, q, L.RY);
     }
     __syncthreads();
     backward2<P, NQ, CT, CT, NR, LIM>(tb, g, e0, L.RY, L.R1, nel, yE);
@@ -464,13 +470,15 @@ __device__ __forceinline__ void mul_winv2(const Target &t, const CT *in, CT *out
 
 
 template <int P, int NQ, typename TT>
-__device__ __forceinline__ void b2_setupc(const Geom &g, const Tables &tb, const Target &tg,
+__device__ __forceinline__ void b2_setupc(const Geom &g, const Tab &tb, const Target &tg,
                                  const double *__restrict__ x, TT *__restrict__ Q,
                                  double *__restrict__ bad, int e0, int nel)
 {
     using S = S2<P, NQ>;
     __shared__ Lds2<P, NQ, double> L;
     __shared__ double red[BLOCK / 64];
+    __shared__ double sw[NQ];
+    weights_to_lds<NQ>(tb, sw);
     gather2<P, NQ>(g, x, e0, nel, L.X, false);
     __syncthreads();
     forward2<P, NQ, double>(tb, L.X, L.R1, L.RY, nel);
@@ -481,7 +489,7 @@ __device__ __forceinline__ void b2_setupc(const Geom &g, const Tables &tb, const
         point_J2<P, NQ>(L.RY, el, q, J);
         apply_winv<2>(tg, J, T);
         const double tau = det_cof<2>(T, C);
-        const double z = qweight2<NQ>(tb, q) * tg.detW;
+        const double z = qweight2<NQ>(sw, q) * tg.detW;
         if (tau > 0.0) {
             double I1 = 0.0;
 #pragma unroll
@@ -507,13 +515,15 @@ __device__ __forceinline__ void b2_setupc(const Geom &g, const Tables &tb, const
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM = false>
-__device__ __forceinline__ void b2_applyc(const Geom &g, const Tables &tb, const Target &tg,
+__device__ __forceinline__ void b2_applyc(const Geom &g, const Tab &tb, const Target &tg,
                                  const TT *__restrict__ Q, const double *__restrict__ v,
                                  CT *__restrict__ yE, int e0, int nel)
 {
     using S = S2<P, NQ>;
     constexpr int NR = Planes2<LIM>::NR;
     __shared__ Lds2<P, NQ, CT, NR> L;
+    __shared__ double sw[LIM ? NQ : 1];
+    if (LIM) weights_to_lds<NQ>(tb, sw);
     gather2<P, NQ>(g, v, e0, nel, L.X, true);
     __syncthreads();
     forward2<P, NQ, CT, NR, LIM>(tb, L.X, L.R1, L.RY, nel);
@@ -535,7 +545,7 @@ __device__ __forceinline__ void b2_applyc(const Geom &g, const Tables &tb, const
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) L.RY[(el * NR + r) * S::NQ2 + q] = Y[r];
-        if (LIM) lim_point2<NQ, CT, NR>(tb, g, el, q, L.RY);
+        if (LIM) lim_point2<NQ, CT, NR>(sw, g, el, q, L.RY);
     }
     __syncthreads();
     backward2<P, NQ, CT, CT, NR, LIM>(tb, g, e0, L.RY, L.R1, nel, yE);
@@ -555,13 +565,13 @@ struct DiagLds2 {
 };
 
 template <int P, int NQ, bool LIM>
-__device__ __forceinline__ void diag_contract2(const Tables &tb, const Geom &g, int e0,
+__device__ __forceinline__ void diag_contract2(const Tab &tb, const Geom &g, int e0,
                                       DiagLds2<P, NQ, LIM> &L, int nel, double *__restrict__ dE)
 {
     using S = S2<P, NQ>;
     constexpr int NI = S::NI, NQ2 = S::NQ2, NP = S::NP, NPR = DiagLds2<P, NQ, LIM>::NPR;
     for (int k = threadIdx.x; k < NQ * NI; k += BLOCK) {
-        const double b = tb.B[k], gg = tb.G[k];
+        const double b = tb.t->B[k], gg = tb.t->G[k];
         L.T[0][k] = b * b;
         L.T[1][k] = b * gg;
         L.T[2][k] = gg * gg;
@@ -603,23 +613,28 @@ __device__ __forceinline__ void diag_contract2(const Tables &tb, const Geom &g, 
 }
 
 template <int P, int NQ, bool LIM>
-__device__ __forceinline__ void diag_lim2(const Tables &tb, const Geom &g, DiagLds2<P, NQ, LIM> &L, int el,
+__device__ __forceinline__ void diag_lim2(const double *sw, const Geom &g, DiagLds2<P, NQ, LIM> &L, int el,
                                  int q)
 {
     if (!LIM) return;
     constexpr int NQ2 = NQ * NQ, NPR = DiagLds2<P, NQ, LIM>::NPR;
-    const double f = 2.0 * g.lim * qweight2<NQ>(tb, q);
+    const double f = 2.0 * g.lim * qweight2<NQ>(sw, q);
 #pragma unroll
     for (int a = 0; a < 2; ++a) L.sQ[((el * NPR + 3) * 2 + a) * NQ2 + q] = f;
 }
 
 template <int P, int NQ, typename TT, bool LIM = false>
-__device__ __forceinline__ void b2_diag(const Geom &g, const Tables &tb, const TT *__restrict__ H,
+__device__ __forceinline__ void b2_diag(const Geom &g, const Tab &tb, const TT *__restrict__ H,
                                double *__restrict__ dE, int e0, int nel)
 {
     using S = S2<P, NQ>;
     constexpr int NPR = DiagLds2<P, NQ, LIM>::NPR;
     __shared__ DiagLds2<P, NQ, LIM> L;
+    __shared__ double sw[LIM ? NQ : 1];
+    if (LIM) {
+        weights_to_lds<NQ>(tb, sw);
+        __syncthreads();
+    }
     for (int idx = threadIdx.x; idx < nel * S::NQ2; idx += BLOCK) {
         const int el = idx / S::NQ2, q = idx % S::NQ2;
         const TT *h = H + (size_t)(e0 + el) * qdata_stride(10, S::NQ2, sizeof(TT)) + q;
@@ -632,18 +647,23 @@ __device__ __forceinline__ void b2_diag(const Geom &g, const Tables &tb, const T
                 L.sQ[((el * NPR + pr) * 2 + a) * S::NQ2 + q] =
                     f * (double)h[sym_index<4>(a * 2 + n, a * 2 + p) * S::NQ2];
         }
-        diag_lim2<P, NQ, LIM>(tb, g, L, el, q);
+        diag_lim2<P, NQ, LIM>(sw, g, L, el, q);
     }
     diag_contract2<P, NQ, LIM>(tb, g, e0, L, nel, dE);
 }
 
 template <int P, int NQ, typename TT, bool LIM = false>
-__device__ __forceinline__ void b2_diagc(const Geom &g, const Tables &tb, const Target &tg,
+__device__ __forceinline__ void b2_diagc(const Geom &g, const Tab &tb, const Target &tg,
                                 const TT *__restrict__ Q, double *__restrict__ dE, int e0, int nel)
 {
     using S = S2<P, NQ>;
     constexpr int NPR = DiagLds2<P, NQ, LIM>::NPR;
     __shared__ DiagLds2<P, NQ, LIM> L;
+    __shared__ double sw[LIM ? NQ : 1];
+    if (LIM) {
+        weights_to_lds<NQ>(tb, sw);
+        __syncthreads();
+    }
     for (int idx = threadIdx.x; idx < nel * S::NQ2; idx += BLOCK) {
         const int el = idx / S::NQ2, q = idx % S::NQ2;
         const TT *h = Q + (size_t)(e0 + el) * qdata_stride(NC2, S::NQ2, sizeof(TT)) + q;
@@ -680,7 +700,7 @@ __device__ __forceinline__ void b2_diagc(const Geom &g, const Tables &tb, const 
                 L.sQ[((el * NPR + pr) * 2 + a) * S::NQ2 + q] = f * hv;
             }
         }
-        diag_lim2<P, NQ, LIM>(tb, g, L, el, q);
+        diag_lim2<P, NQ, LIM>(sw, g, L, el, q);
     }
     diag_contract2<P, NQ, LIM>(tb, g, e0, L, nel, dE);
 }
@@ -693,72 +713,81 @@ __device__ __forceinline__ void b2_diagc(const Geom &g, const Tables &tb, const 
 // ------------------------------------------------------------------------
 
 template <int P, int NQ, bool LIM>
-__global__ __launch_bounds__(BLOCK) void k2_energy(Geom g, Tables tb, Target tg, const double *__restrict__ x, double *__restrict__ part)
+__global__ __launch_bounds__(BLOCK) void k2_energy(Geom g, Tables tba, Target tg, const double *__restrict__ x, double *__restrict__ part)
 {
+    const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S2<P, NQ>::EPB;
     const int e0 = blockIdx.x * EPB;
     b2_energy<P, NQ, LIM>(g, tb, tg, x, part, e0, min(EPB, g.ne - e0));
 }
 
 template <int P, int NQ, bool LIM, bool EN = false>
-__global__ __launch_bounds__(BLOCK) void k2_gradient(Geom g, Tables tb, Target tg, const double *__restrict__ x, double *__restrict__ gE, double *__restrict__ bad)
+__global__ __launch_bounds__(BLOCK) void k2_gradient(Geom g, Tables tba, Target tg, const double *__restrict__ x, double *__restrict__ gE, double *__restrict__ bad)
 {
+    const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S2<P, NQ>::EPB;
     const int e0 = blockIdx.x * EPB;
     b2_gradient<P, NQ, LIM, EN>(g, tb, tg, x, gE, bad, e0, min(EPB, g.ne - e0));
 }
 
 template <int P, int NQ, typename TT>
-__global__ __launch_bounds__(BLOCK) void k2_setup(Geom g, Tables tb, Target tg, const double *__restrict__ x, TT *__restrict__ H, double *__restrict__ bad)
+__global__ __launch_bounds__(BLOCK) void k2_setup(Geom g, Tables tba, Target tg, const double *__restrict__ x, TT *__restrict__ H, double *__restrict__ bad)
 {
+    const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S2<P, NQ>::EPB;
     const int e0 = blockIdx.x * EPB;
     b2_setup<P, NQ, TT>(g, tb, tg, x, H, bad, e0, min(EPB, g.ne - e0));
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM>
-__global__ __launch_bounds__(BLOCK) void k2_apply(Geom g, Tables tb, const TT *__restrict__ H, const double *__restrict__ v, CT *__restrict__ yE)
+__global__ __launch_bounds__(BLOCK) void k2_apply(Geom g, Tables tba, const TT *__restrict__ H, const double *__restrict__ v, CT *__restrict__ yE)
 {
+    const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S2<P, NQ>::EPB;
     const int e0 = blockIdx.x * EPB;
     b2_apply<P, NQ, TT, CT, LIM>(g, tb, H, v, yE, e0, min(EPB, g.ne - e0));
 }
 
 template <int P, int NQ, typename TT>
-__global__ __launch_bounds__(BLOCK) void k2_setupc(Geom g, Tables tb, Target tg, const double *__restrict__ x, TT *__restrict__ Q, double *__restrict__ bad)
+__global__ __launch_bounds__(BLOCK) void k2_setupc(Geom g, Tables tba, Target tg, const double *__restrict__ x, TT *__restrict__ Q, double *__restrict__ bad)
 {
+    const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S2<P, NQ>::EPB;
     const int e0 = blockIdx.x * EPB;
     b2_setupc<P, NQ, TT>(g, tb, tg, x, Q, bad, e0, min(EPB, g.ne - e0));
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM>
-__global__ __launch_bounds__(BLOCK) void k2_applyc(Geom g, Tables tb, Target tg, const TT *__restrict__ Q, const double *__restrict__ v, CT *__restrict__ yE)
+__global__ __launch_bounds__(BLOCK) void k2_applyc(Geom g, Tables tba, Target tg, const TT *__restrict__ Q, const double *__restrict__ v, CT *__restrict__ yE)
 {
+    const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S2<P, NQ>::EPB;
     const int e0 = blockIdx.x * EPB;
     b2_applyc<P, NQ, TT, CT, LIM>(g, tb, tg, Q, v, yE, e0, min(EPB, g.ne - e0));
 }
 
 template <int P, int NQ, typename TT, bool LIM>
-__global__ __launch_bounds__(BLOCK) void k2_diag(Geom g, Tables tb, const TT *__restrict__ H, double *__restrict__ dE)
+__global__ __launch_bounds__(BLOCK) void k2_diag(Geom g, Tables tba, const TT *__restrict__ H, double *__restrict__ dE)
 {
+    const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S2<P, NQ>::EPB;
     const int e0 = blockIdx.x * EPB;
     b2_diag<P, NQ, TT, LIM>(g, tb, H, dE, e0, min(EPB, g.ne - e0));
 }
 
 template <int P, int NQ, typename TT, bool LIM>
-__global__ __launch_bounds__(BLOCK) void k2_diagc(Geom g, Tables tb, Target tg, const TT *__restrict__ Q, double *__restrict__ dE)
+__global__ __launch_bounds__(BLOCK) void k2_diagc(Geom g, Tables tba, Target tg, const TT *__restrict__ Q, double *__restrict__ dE)
 {
+    const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S2<P, NQ>::EPB;
     const int e0 = blockIdx.x * EPB;
     b2_diagc<P, NQ, TT, LIM>(g, tb, tg, Q, dE, e0, min(EPB, g.ne - e0));
 }
 
 template <int P, int NQ, bool LIM = false>
-__global__ __launch_bounds__(BLOCK) void kb2_energy(Tables tb, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ part)
+__global__ __launch_bounds__(BLOCK) void kb2_energy(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ part)
 {
+    const Tab tb = kernel_tables<0>();
     constexpr int EPB = S2<P, NQ>::EPB;
     const Tile t = tiles[blockIdx.x];
     if (gate && !gate[t.slot]) return;
@@ -767,8 +796,9 @@ __global__ __launch_bounds__(BLOCK) void kb2_energy(Tables tb, const Tile *__res
 }
 
 template <int P, int NQ, bool LIM = false, bool EN = false>
-__global__ __launch_bounds__(BLOCK) void kb2_gradient(Tables tb, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ bad)
+__global__ __launch_bounds__(BLOCK) void kb2_gradient(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ bad)
 {
+    const Tab tb = kernel_tables<0>();
     constexpr int EPB = S2<P, NQ>::EPB;
     const Tile t = tiles[blockIdx.x];
     if (gate && !gate[t.slot]) return;
@@ -777,8 +807,9 @@ __global__ __launch_bounds__(BLOCK) void kb2_gradient(Tables tb, const Tile *__r
 }
 
 template <int P, int NQ, typename TT>
-__global__ __launch_bounds__(BLOCK) void kb2_setup(Tables tb, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ bad)
+__global__ __launch_bounds__(BLOCK) void kb2_setup(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ bad)
 {
+    const Tab tb = kernel_tables<0>();
     constexpr int EPB = S2<P, NQ>::EPB;
     const Tile t = tiles[blockIdx.x];
     if (gate && !gate[t.slot]) return;
@@ -787,8 +818,9 @@ __global__ __launch_bounds__(BLOCK) void kb2_setup(Tables tb, const Tile *__rest
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM = false>
-__global__ __launch_bounds__(BLOCK) void kb2_apply(Tables tb, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
+__global__ __launch_bounds__(BLOCK) void kb2_apply(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
 {
+    const Tab tb = kernel_tables<0>();
     constexpr int EPB = S2<P, NQ>::EPB;
     const Tile t = tiles[blockIdx.x];
     if (gate && !gate[t.slot]) return;
@@ -797,8 +829,9 @@ __global__ __launch_bounds__(BLOCK) void kb2_apply(Tables tb, const Tile *__rest
 }
 
 template <int P, int NQ, typename TT>
-__global__ __launch_bounds__(BLOCK) void kb2_setupc(Tables tb, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ bad)
+__global__ __launch_bounds__(BLOCK) void kb2_setupc(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ bad)
 {
+    const Tab tb = kernel_tables<0>();
     constexpr int EPB = S2<P, NQ>::EPB;
     const Tile t = tiles[blockIdx.x];
     if (gate && !gate[t.slot]) return;
@@ -807,8 +840,9 @@ __global__ __launch_bounds__(BLOCK) void kb2_setupc(Tables tb, const Tile *__res
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM = false>
-__global__ __launch_bounds__(BLOCK) void kb2_applyc(Tables tb, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
+__global__ __launch_bounds__(BLOCK) void kb2_applyc(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
 {
+    const Tab tb = kernel_tables<0>();
     constexpr int EPB = S2<P, NQ>::EPB;
     const Tile t = tiles[blockIdx.x];
     if (gate && !gate[t.slot]) return;
@@ -817,8 +851,9 @@ __global__ __launch_bounds__(BLOCK) void kb2_applyc(Tables tb, const Tile *__res
 }
 
 template <int P, int NQ, typename TT, bool LIM = false>
-__global__ __launch_bounds__(BLOCK) void kb2_diag(Tables tb, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate)
+__global__ __launch_bounds__(BLOCK) void kb2_diag(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate)
 {
+    const Tab tb = kernel_tables<0>();
     constexpr int EPB = S2<P, NQ>::EPB;
     const Tile t = tiles[blockIdx.x];
     if (gate && !gate[t.slot]) return;
@@ -827,8 +862,9 @@ __global__ __launch_bounds__(BLOCK) void kb2_diag(Tables tb, const Tile *__restr
 }
 
 template <int P, int NQ, typename TT, bool LIM = false>
-__global__ __launch_bounds__(BLOCK) void kb2_diagc(Tables tb, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate)
+__global__ __launch_bounds__(BLOCK) void kb2_diagc(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate)
 {
+    const Tab tb = kernel_tables<0>();
     constexpr int EPB = S2<P, NQ>::EPB;
     const Tile t = tiles[blockIdx.x];
     if (gate && !gate[t.slot]) return;

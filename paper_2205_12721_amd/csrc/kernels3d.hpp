@@ -8,7 +8,7 @@
 // Each contraction stage is a loop over "pencils": one work item loads one 1D
 // line of its input from LDS once and produces the whole 1D line of outputs.
 // The 1D tables are indexed with compile-time constants in the kernel
-// arguments, so they are read into scalar registers instead of from LDS.
+// arguments (Tab), so they are read into scalar registers instead of from LDS.
 //
 // LDS per workgroup (CT = compute type, double or float):
 //   X   [EPB][3][NI^3]            element nodes (or v_E)
@@ -91,39 +91,57 @@ __device__ __forceinline__ int node3(const Geom &g, int e, int i1, int i2, int i
 // masked: fixed DoFs read as zero (the P of H_c = P H P + (I - P)); sub:
 // a vector subtracted entry by entry (x - x0 of the limiting term).  Split in
 // a load phase (registers) and a store phase (LDS) so that a caller can issue
-// other loads in between; the loop has a compile-time trip count so that all
-// of a lane's loads are issued before the first one is waited for.
+// other loads in between.  A lane takes one node and its three components
+// (EPB NP <= 256 at the base tile shape), so the node's place is worked out
+// once, and every load of the lane is issued before the first is waited for.
 template <int P, int NQ, int T2 = 2>
 struct Gath3 {
-    static constexpr int NIT = (S3<P, NQ, T2>::EPB * 3 * S3<P, NQ>::NP + BLOCK - 1) / BLOCK;
-    double val[NIT];
-    bool fix[NIT];
+    static constexpr int NIT = (S3<P, NQ, T2>::EPB * S3<P, NQ>::NP + BLOCK - 1) / BLOCK;
+    double val[NIT][3];
+    bool fix[NIT][3];
 };
+
+// Element of the block and local node of this lane's node `it`.
+template <int P, int NQ, int T2>
+__device__ __forceinline__ void gather3_node(int it, int &el, int &i)
+{
+    constexpr int NP = S3<P, NQ>::NP;
+    const int idx = threadIdx.x + it * BLOCK;
+    if (S3<P, NQ, T2>::EPB == 1) {
+        el = 0;
+        i = idx;
+    } else {
+        el = idx / NP;
+        i = idx % NP;
+    }
+}
 
 template <int P, int NQ, int T2, bool SUB>
 __device__ __forceinline__ void gather3_box(const Geom &g, const double *__restrict__ vec,
-                                            const double *__restrict__ sub, int e0, int n,
+                                            const double *__restrict__ sub, int e0, int nel,
                                             bool bmask, Gath3<P, NQ, T2> &r)
 {
     using S = S3<P, NQ>;
     constexpr int NI = S::NI, NP = S::NP, NIT = Gath3<P, NQ, T2>::NIT;
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
-        const int idx = threadIdx.x + it * BLOCK;
-        const bool in = idx < n;
-        const int i = idx % NP;
-        const int rr = idx / NP;  // el*3 + c
-        const int c = rr % 3, el = rr / 3;
+        int el, i;
+        gather3_node<P, NQ, T2>(it, el, i);
+        const bool in = (int)threadIdx.x + it * BLOCK < nel * NP;
         const int i1 = i % NI, i2 = (i / NI) % NI, i3 = i / (NI * NI);
         int ex, ey, ez;
         box_elem<3>(g, e0 + el, ex, ey, ez);
         const int gx = ex * P + i1, gy = ey * P + i2, gz = ez * P + i3;
         // lanes past the end read node 0 and are dropped
-        const size_t at = in ? (size_t)c * g.nx + gx + g.M[0] * (gy + g.M[1] * gz) : 0;
-        double v = vec[at];
-        if (SUB) v -= sub[at];
-        r.val[it] = v;
-        r.fix[it] = !in || (bmask && box_boundary(g, gx, gy, gz));
+        const uint32_t at = in ? (uint32_t)(gx + g.M[0] * (gy + g.M[1] * gz)) : 0u;
+        const bool fix = bmask && box_boundary(g, gx, gy, gz);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            double v = vec[at + (uint32_t)(c * g.nx)];
+            if (SUB) v -= sub[at + (uint32_t)(c * g.nx)];
+            r.val[it][c] = v;
+            r.fix[it][c] = fix;
+        }
     }
 }
 
@@ -134,32 +152,35 @@ __device__ __forceinline__ void gather3_load(const Geom &g, const double *__rest
 {
     using S = S3<P, NQ>;
     constexpr int NI = S::NI, NP = S::NP, NIT = Gath3<P, NQ, T2>::NIT;
-    const int n = nel * 3 * NP;
     if (!g.e2n && !(masked && g.ess_mode == 2)) {
         // box mesh without a mask array: branch-free, so that every load of
         // the lane is issued before any is waited for
         const bool bmask = masked && g.ess_mode == 0;
         if (sub)
-            gather3_box<P, NQ, T2, true>(g, vec, sub, e0, n, bmask, r);
+            gather3_box<P, NQ, T2, true>(g, vec, sub, e0, nel, bmask, r);
         else
-            gather3_box<P, NQ, T2, false>(g, vec, sub, e0, n, bmask, r);
+            gather3_box<P, NQ, T2, false>(g, vec, sub, e0, nel, bmask, r);
         return;
     }
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
-        const int idx = threadIdx.x + it * BLOCK;
-        r.val[it] = 0.0;
-        r.fix[it] = false;
-        if (idx < n) {
-            const int i = idx % NP;
-            const int rr = idx / NP;  // el*3 + c
-            const int c = rr % 3, el = rr / 3;
+        int el, i;
+        gather3_node<P, NQ, T2>(it, el, i);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            r.val[it][c] = 0.0;
+            r.fix[it][c] = false;
+        }
+        if ((int)threadIdx.x + it * BLOCK < nel * NP) {
             const int i1 = i % NI, i2 = (i / NI) % NI, i3 = i / (NI * NI);
             int gx, gy, gz;
             const int node = node3<P>(g, e0 + el, i1, i2, i3, gx, gy, gz);
-            r.val[it] = vec[(size_t)c * g.nx + node];
-            if (sub) r.val[it] -= sub[(size_t)c * g.nx + node];
-            r.fix[it] = masked && is_fixed(g, c, node, gx, gy, gz);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                r.val[it][c] = vec[(size_t)c * g.nx + node];
+                if (sub) r.val[it][c] -= sub[(size_t)c * g.nx + node];
+                r.fix[it][c] = masked && is_fixed(g, c, node, gx, gy, gz);
+            }
         }
     }
 }
@@ -167,12 +188,16 @@ __device__ __forceinline__ void gather3_load(const Geom &g, const double *__rest
 template <int P, int NQ, typename CT, int T2 = 2>
 __device__ __forceinline__ void gather3_store(const Gath3<P, NQ, T2> &r, int nel, CT *sX)
 {
-    constexpr int NIT = Gath3<P, NQ, T2>::NIT;
-    const int n = nel * 3 * S3<P, NQ>::NP;
+    constexpr int NIT = Gath3<P, NQ, T2>::NIT, NP = S3<P, NQ>::NP;
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
-        const int idx = threadIdx.x + it * BLOCK;
-        if (idx < n) sX[idx] = r.fix[it] ? (CT)0 : (CT)r.val[it];
+        int el, i;
+        gather3_node<P, NQ, T2>(it, el, i);
+        if ((int)threadIdx.x + it * BLOCK < nel * NP) {
+            CT *o = sX + el * 3 * NP + i;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) o[c * NP] = r.fix[it][c] ? (CT)0 : (CT)r.val[it][c];
+        }
     }
 }
 
@@ -190,10 +215,11 @@ __device__ __forceinline__ void gather3(const Geom &g, const double *__restrict_
 // with VAL also the value of component c, plane el*NR + 9 + c).
 // Forward sweeps of axes 1 and 2: X -> R1 -> R2, ending with a barrier.
 template <int P, int NQ, typename CT>
-__device__ __forceinline__ void forward3_head(const Tables &tb, const CT *X, CT *R1, CT *R2, int nel)
+__device__ __forceinline__ void forward3_head(const Tab &tables, const CT *X, CT *R1, CT *R2, int nel)
 {
     using S = S3<P, NQ>;
     constexpr int NI = S::NI, NP = S::NP, L1 = S::L1, L2 = S::L2, NQ2 = S::NQ2;
+    Tab tb = tables.again();
     // axis 1: pencils (r, i3, i2), r = el*3 + c
     for (int pen = threadIdx.x; pen < nel * 3 * NI * NI; pen += BLOCK) {
         const int i23 = pen % (NI * NI), r = pen / (NI * NI);
@@ -215,6 +241,7 @@ __device__ __forceinline__ void forward3_head(const Tables &tb, const CT *X, CT 
         }
     }
     __syncthreads();
+    tb = tables.again();
     // axis 2: pencils (r, i3, q1)
     for (int pen = threadIdx.x; pen < nel * 3 * NI * NQ; pen += BLOCK) {
         const int q1 = pen % NQ, i3 = (pen / NQ) % NI, r = pen / (NQ * NI);
@@ -245,11 +272,12 @@ __device__ __forceinline__ void forward3_head(const Tables &tb, const CT *X, CT 
 }
 
 template <int P, int NQ, typename CT, int NR = 9, bool VAL = false>
-__device__ __forceinline__ void forward3(const Tables &tb, const CT *X, CT *R1, CT *R2, CT *RY, int nel)
+__device__ __forceinline__ void forward3(const Tab &tables, const CT *X, CT *R1, CT *R2, CT *RY, int nel)
 {
     using S = S3<P, NQ>;
     constexpr int NI = S::NI, L2 = S::L2, NQ2 = S::NQ2, NQ3 = S::NQ3;
-    forward3_head<P, NQ, CT>(tb, X, R1, R2, nel);
+    forward3_head<P, NQ, CT>(tables, X, R1, R2, nel);
+    const Tab tb = tables.again();
     // axis 3: pencils (r, q2, q1) -> J at the NQ points of the pencil
     for (int pen = threadIdx.x; pen < nel * 3 * NQ2; pen += BLOCK) {
         const int q12 = pen % NQ2, r = pen / NQ2;
@@ -289,24 +317,26 @@ __device__ __forceinline__ void forward3(const Tables &tb, const CT *X, CT *R1, 
 // [c][ez*NI+i3][ey*NI+i2][ex*NI+i1], in which the node gather reads runs of
 // neighbouring addresses.
 template <int P>
-__device__ __forceinline__ long ev_index3(const Geom &g, int e, int c, int i1, int i2, int i3)
+__device__ __forceinline__ uint32_t ev_index3(const Geom &g, int e, int c, int i1, int i2, int i3)
 {
+    // the E-vector has fewer than 2^31 entries (checked when a mesh is taken)
     constexpr int NI = P + 1, NP = NI * NI * NI;
-    if (g.e2n) return ((long)e * 3 + c) * NP + i1 + NI * (i2 + NI * i3);
+    if (g.e2n) return (e * 3 + c) * NP + i1 + NI * (i2 + NI * i3);
     int ex, ey, ez;
     box_elem<3>(g, e, ex, ey, ez);
-    const long EX = (long)g.nel[0] * NI, EY = (long)g.nel[1] * NI;
-    return (long)c * g.ne * NP + ((long)(ez * NI + i3) * EY + (ey * NI + i2)) * EX + ex * NI + i1;
+    const int EX = g.nel[0] * NI, EY = g.nel[1] * NI;
+    return c * (g.ne * NP) + ((ez * NI + i3) * EY + (ey * NI + i2)) * EX + ex * NI + i1;
 }
 
 // Backward sweeps of axes 2 and 1: R2 (the axis-3 contractions) -> R1 ->
 // E-vector.  Called after a barrier that ends the writes of R2.
 template <int P, int NQ, typename CT, typename OT, bool CW = false>
-__device__ __forceinline__ void backward3_tail(const Tables &tb, const Geom &g, int e0, CT *R2,
+__device__ __forceinline__ void backward3_tail(const Tab &tables, const Geom &g, int e0, CT *R2,
                                                CT *R1, int nel, OT *__restrict__ out)
 {
     using S = S3<P, NQ>;
     constexpr int NI = S::NI, L1 = S::L1, L2 = S::L2, NQ2 = S::NQ2;
+    Tab tb = tables.again();
     // axis 2: pencils (r, i3, q1)
     for (int pen = threadIdx.x; pen < nel * 3 * NI * NQ; pen += BLOCK) {
         const int q1 = pen % NQ, i3 = (pen / NQ) % NI, r = pen / (NQ * NI);
@@ -333,6 +363,7 @@ __device__ __forceinline__ void backward3_tail(const Tables &tb, const Geom &g, 
         }
     }
     __syncthreads();
+    tb = tables.again();
     // axis 1: pencils (r, i3, i2) -> NI consecutive outputs
     if (!CW) {
         for (int pen = threadIdx.x; pen < nel * 3 * NI * NI; pen += BLOCK) {
@@ -394,11 +425,12 @@ __device__ __forceinline__ void backward3_tail(const Tables &tb, const Geom &g, 
 // Backward (transposed) sweeps RY -> R2 -> R1 -> E-vector:
 //   y_c(i) = sum_q sum_b RY[c][b](q) d w_i/d xbar_b (q)  (+ RY[9+c](q) w_i(q) with VAL).
 template <int P, int NQ, typename CT, typename OT, int NR = 9, bool VAL = false, bool CW = false>
-__device__ __forceinline__ void backward3(const Tables &tb, const Geom &g, int e0, const CT *RY, CT *R2,
+__device__ __forceinline__ void backward3(const Tab &tables, const Geom &g, int e0, const CT *RY, CT *R2,
                                  CT *R1, int nel, OT *__restrict__ out)
 {
     using S = S3<P, NQ>;
     constexpr int NI = S::NI, L1 = S::L1, L2 = S::L2, NQ2 = S::NQ2, NQ3 = S::NQ3;
+    const Tab tb = tables.again();
     // axis 3: pencils (r, q2, q1)
     for (int pen = threadIdx.x; pen < nel * 3 * NQ2; pen += BLOCK) {
         const int q12 = pen % NQ2, r = pen / NQ2;
@@ -432,7 +464,7 @@ __device__ __forceinline__ void backward3(const Tables &tb, const Geom &g, int e
         }
     }
     __syncthreads();
-    backward3_tail<P, NQ, CT, OT, CW>(tb, g, e0, R2, R1, nel, out);
+    backward3_tail<P, NQ, CT, OT, CW>(tables, g, e0, R2, R1, nel, out);
 }
 
 // J[c*3+b] = d x_c / d xbar_b at point q of element el, left in RY by forward3.
@@ -445,18 +477,19 @@ __device__ __forceinline__ void point_J3(const CT *RY, int el, int q, CT *J)
 }
 
 // Product of the 1D quadrature weights at point q.
+// (sw: the 1D weights in LDS).
 template <int NQ>
-__device__ __forceinline__ double qweight3(const Tables &tb, int q)
+__device__ __forceinline__ double qweight3(const double *sw, int q)
 {
     const int q1 = q % NQ, q2 = (q / NQ) % NQ, q3 = q / (NQ * NQ);
-    return tab_w<NQ>(tb, q1) * tab_w<NQ>(tb, q2) * tab_w<NQ>(tb, q3);
+    return sw[q1] * sw[q2] * sw[q3];
 }
 
 // z = w_q det W: the weight of point q in the integral over the target element.
 template <int NQ>
-__device__ __forceinline__ double point_weight3(const Tables &tb, const Target &tg, int q)
+__device__ __forceinline__ double point_weight3(const double *sw, const Target &tg, int q)
 {
-    return qweight3<NQ>(tb, q) * tg.detW;
+    return qweight3<NQ>(sw, q) * tg.detW;
 }
 
 // ------------------------------------------------------------------------
@@ -552,10 +585,10 @@ __device__ __forceinline__ TT qdata_at(const TT *__restrict__ he, int q, int s)
 // v_c(q) become 2 w_q lim v_c(q), a mass-like operator with no stored data
 // (lim = coef det W / delta^2 folds the target volume factor in).
 template <int NQ, typename CT, int NR>
-__device__ __forceinline__ void lim_point3(const Tables &tb, const Geom &g, int el, int q, CT *RY)
+__device__ __forceinline__ void lim_point3(const double *sw, const Geom &g, int el, int q, CT *RY)
 {
     constexpr int NQ3 = NQ * NQ * NQ;
-    const CT f = (CT)(2.0 * g.lim * qweight3<NQ>(tb, q));
+    const CT f = (CT)(2.0 * g.lim * qweight3<NQ>(sw, q));
 #pragma unroll
     for (int c = 0; c < 3; ++c) RY[(el * NR + 9 + c) * NQ3 + q] *= f;
 }
@@ -563,7 +596,7 @@ __device__ __forceinline__ void lim_point3(const Tables &tb, const Geom &g, int 
 // Values of x - x0 (limiting term) at the points of the block's elements,
 // into U[el][c][q]: forward sweeps with value planes on the difference.
 template <int P, int NQ, typename L3>
-__device__ __forceinline__ void lim_values3(const Geom &g, const Tables &tb, const double *__restrict__ x,
+__device__ __forceinline__ void lim_values3(const Geom &g, const Tab &tb, const double *__restrict__ x,
                                    int e0, int nel, L3 &L, double *U)
 {
     using S = S3<P, NQ>;
@@ -584,7 +617,7 @@ __device__ __forceinline__ void lim_values3(const Geom &g, const Tables &tb, con
 // MF: forward sweeps on the matrix cores (forward3_mfma) instead of the
 // pencil sweeps (classes with n_q <= 5, without the limiting term).
 template <int P, int NQ, bool LIM = false, bool MF = false>
-__device__ __forceinline__ void b3_energy(const Geom &g, const Tables &tb, const Target &tg,
+__device__ __forceinline__ void b3_energy(const Geom &g, const Tab &tb, const Target &tg,
                                  const double *__restrict__ x, double *__restrict__ part, int e0,
                                  int nel)
 {
@@ -597,6 +630,8 @@ __device__ __forceinline__ void b3_energy(const Geom &g, const Tables &tb, const
     constexpr int NRED = 3 * (BLOCK / 64), NMF = MF ? 2 * NQ * S::NI : 0;
     __shared__ double red[NRED > NMF ? NRED : NMF];
     double *mft = red;
+    __shared__ double sw[NQ];
+    weights_to_lds<NQ>(tb, sw);
     if (LIM) lim_values3<P, NQ>(g, tb, x, e0, nel, L, U);
     if (MF) mfma_tables<S::NI, NQ>(tb, mft);
     gather3<P, NQ>(g, x, e0, nel, L.X, false);
@@ -611,7 +646,7 @@ __device__ __forceinline__ void b3_energy(const Geom &g, const Tables &tb, const
         double J[9];
         point_J3<P, NQ, double, NR>(L.RY, el, q, J);
         dmin = fmin(dmin, det_only<3>(J));
-        const double z = point_weight3<NQ>(tb, tg, q);
+        const double z = point_weight3<NQ>(sw, tg, q);
         double mu, Pm[9];
         if (metric_first<3>(tg, J, z, &mu, Pm))
             esum += z * mu;
@@ -624,7 +659,7 @@ __device__ __forceinline__ void b3_energy(const Geom &g, const Tables &tb, const
                 const double u = U[(el * 3 + c) * S::NQ3 + q];
                 y2 += u * u;
             }
-            esum += qweight3<NQ>(tb, q) * g.lim * y2;
+            esum += qweight3<NQ>(sw, q) * g.lim * y2;
         }
     }
     block_energy3(esum, dmin, bad, red);
@@ -644,7 +679,7 @@ __device__ __forceinline__ void b3_energy(const Geom &g, const Tables &tb, const
 // (the same terms in the same order as b3_energy: bitwise its partials, and
 // the gradient bitwise that of EN = false).
 template <int P, int NQ, bool LIM = false, bool EN = false, bool MF = false>
-__device__ __forceinline__ void b3_gradient(const Geom &g, const Tables &tb, const Target &tg,
+__device__ __forceinline__ void b3_gradient(const Geom &g, const Tab &tb, const Target &tg,
                                    const double *__restrict__ x, double *__restrict__ gE,
                                    double *__restrict__ bad, int e0, int nel)
 {
@@ -657,6 +692,8 @@ __device__ __forceinline__ void b3_gradient(const Geom &g, const Tables &tb, con
     constexpr int NRED = 3 * (BLOCK / 64), NMF = MF ? 2 * NQ * S::NI : 0;
     __shared__ double red[NRED > NMF ? NRED : NMF];
     double *mft = red;
+    __shared__ double sw[NQ];
+    weights_to_lds<NQ>(tb, sw);
     if (LIM) lim_values3<P, NQ>(g, tb, x, e0, nel, L, U);
     if (MF) mfma_tables<S::NI, NQ>(tb, mft);
     gather3<P, NQ>(g, x, e0, nel, L.X, false);
@@ -671,7 +708,7 @@ __device__ __forceinline__ void b3_gradient(const Geom &g, const Tables &tb, con
         double J[9], Pm[9], mu;
         point_J3<P, NQ, double, NR>(L.RY, el, q, J);
         if (EN) dmin = fmin(dmin, det_only<3>(J));
-        const double z = point_weight3<NQ>(tb, tg, q);
+        const double z = point_weight3<NQ>(sw, tg, q);
         if (!metric_first<3>(tg, J, z, &mu, Pm)) {
             nbad += 1.0;
 #pragma unroll
@@ -686,7 +723,7 @@ __device__ __forceinline__ void b3_gradient(const Geom &g, const Tables &tb, con
                 const double u = U[(el * 3 + c) * S::NQ3 + q];
                 y2 += u * u;
             }
-            esum += qweight3<NQ>(tb, q) * g.lim * y2;
+            esum += qweight3<NQ>(sw, q) * g.lim * y2;
         }
 #pragma unroll
         for (int k = 0; k < 9; ++k) L.RY[(el * NR + k) * S::NQ3 + q] = Pm[k];
@@ -694,7 +731,7 @@ __device__ __forceinline__ void b3_gradient(const Geom &g, const Tables &tb, con
 #pragma unroll
             for (int c = 0; c < 3; ++c)
                 L.RY[(el * NR + 9 + c) * S::NQ3 + q] =
-                    2.0 * qweight3<NQ>(tb, q) * g.lim * U[(el * 3 + c) * S::NQ3 + q];
+                    2.0 * qweight3<NQ>(sw, q) * g.lim * U[(el * 3 + c) * S::NQ3 + q];
         }
     }
     __syncthreads();
@@ -715,7 +752,7 @@ __device__ __forceinline__ void b3_gradient(const Geom &g, const Tables &tb, con
 // Hessian setup (Sec. 3.4): per point the packed z * H_A tensor, stored
 // element-major in the 16-byte-run layout of qdata_store.
 template <int P, int NQ, typename TT, bool MF = false>
-__device__ __forceinline__ void b3_setup(const Geom &g, const Tables &tb, const Target &tg,
+__device__ __forceinline__ void b3_setup(const Geom &g, const Tab &tb, const Target &tg,
                                 const double *__restrict__ x, TT *__restrict__ H,
                                 double *__restrict__ bad, int e0, int nel)
 {
@@ -723,6 +760,8 @@ __device__ __forceinline__ void b3_setup(const Geom &g, const Tables &tb, const 
     __shared__ Lds3<P, NQ, double> L;
     __shared__ double red[BLOCK / 64];
     __shared__ double mft[MF ? 2 * NQ * S::NI : 1];
+    __shared__ double sw[NQ];
+    weights_to_lds<NQ>(tb, sw);
     if (MF) mfma_tables<S::NI, NQ>(tb, mft);
     gather3<P, NQ>(g, x, e0, nel, L.X, false);
     __syncthreads();
@@ -735,7 +774,7 @@ __device__ __forceinline__ void b3_setup(const Geom &g, const Tables &tb, const 
         const int el = idx / S::NQ3, q = idx % S::NQ3;
         double J[9], Hp[45];
         point_J3<P, NQ>(L.RY, el, q, J);
-        const double z = point_weight3<NQ>(tb, tg, q);
+        const double z = point_weight3<NQ>(sw, tg, q);
         if (!metric_second<3>(tg, J, z, Hp)) {
             nbad += 1.0;
 #pragma unroll
@@ -754,7 +793,7 @@ __device__ __forceinline__ void b3_setup(const Geom &g, const Tables &tb, const 
 // Point stage of the action at point q of element el: Y = H : (grad v) from
 // the point's stored tensor hr, in place of the gradient planes of RY.
 template <int P, int NQ, typename TT, typename CT, int NR, bool LIM>
-__device__ __forceinline__ void apply_point3(const Tables &tb, const Geom &g, const TT *hr, int el,
+__device__ __forceinline__ void apply_point3(const double *sw, const Geom &g, const TT *hr, int el,
                                              int q, CT *RY)
 {
     constexpr int NQ3 = S3<P, NQ>::NQ3;
@@ -770,7 +809,7 @@ __device__ __forceinline__ void apply_point3(const Tables &tb, const Geom &g, co
         for (int c = 0; c < 9; ++c) s += hv[sym_index<9>(r, c)] * J[c];
         RY[(el * NR + r) * NQ3 + q] = s;
     }
-    if (LIM) lim_point3<NQ, CT, NR>(tb, g, el, q, RY);
+    if (LIM) lim_point3<NQ, CT, NR>(sw, g, el, q, RY);
 }
 
 // Hessian action, element part (Sec. 3.4, eq. eq_vm_pa_hess):
@@ -781,7 +820,7 @@ __device__ __forceinline__ void apply_point3(const Tables &tb, const Geom &g, co
 // accumulation).  This is the point-pass body; b3_apply chooses between it
 // and the layer-chunked body (b3_apply_layers).
 template <int P, int NQ, typename TT, typename CT, bool LIM = false, int T2 = 2>
-__device__ __forceinline__ void b3_apply_points(const Geom &g, const Tables &tb,
+__device__ __forceinline__ void b3_apply_points(const Geom &g, const Tab &tb,
                                                 const TT *__restrict__ H,
                                                 const double *__restrict__ v,
                                                 CT *__restrict__ yE, int e0, int nel)
@@ -802,6 +841,8 @@ __device__ __forceinline__ void b3_apply_points(const Geom &g, const Tables &tb,
     constexpr bool PF = !ONE && T2 == 2 &&
                         (sizeof(TT) == 4 || 3 * sizeof(Lds3<P, NQ, CT, NR, T2>) > LDS_PER_CU);
     __shared__ Lds3<P, NQ, CT, NR, T2> L;
+    __shared__ double sw[LIM ? NQ : 1];
+    if (LIM) weights_to_lds<NQ>(tb, sw);
     // v loads first, then the tensor loads, then v to LDS: waiting for v
     // leaves the tensor loads in flight
     Gath3<P, NQ, T2> gv;
@@ -826,7 +867,7 @@ __device__ __forceinline__ void b3_apply_points(const Geom &g, const Tables &tb,
             const int idx = threadIdx.x + k * BLOCK;
             if (k + 1 < PASSES) load_pass(k + 1, hraw[(k + 1) & 1]);
             if (idx < npts)
-                apply_point3<P, NQ, TT, CT, NR, LIM>(tb, g, hraw[k & 1], idx / S::NQ3,
+                apply_point3<P, NQ, TT, CT, NR, LIM>(sw, g, hraw[k & 1], idx / S::NQ3,
                                                      idx % S::NQ3, L.RY);
         }
     } else {
@@ -857,7 +898,7 @@ __device__ __forceinline__ void b3_apply_points(const Geom &g, const Tables &tb,
                 for (int c = 0; c < 9; ++c) s += hv[sym_index<9>(r, c)] * J[c];
                 L.RY[(el * NR + r) * S::NQ3 + q] = s;
             }
-            if (LIM) lim_point3<NQ, CT, NR>(tb, g, el, q, L.RY);
+            if (LIM) lim_point3<NQ, CT, NR>(sw, g, el, q, L.RY);
         }
     }
     __syncthreads();
@@ -940,7 +981,7 @@ __device__ __forceinline__ void mul_winv(const Target &t, const CT *in, CT *out,
 // Every sum runs in the order of the unchunked sweeps (q3 ascending), so the
 // result is bitwise that of forward3 / point stage / backward3.
 template <int P, int NQ, typename TT, typename CT, bool COMPACT>
-__device__ __forceinline__ void b3_apply_layers(const Geom &g, const Tables &tb, const Target &tg,
+__device__ __forceinline__ void b3_apply_layers(const Geom &g, const Tab &tb, const Target &tg,
                                                 const TT *__restrict__ Hq,
                                                 const double *__restrict__ v,
                                                 CT *__restrict__ yE, int e0, int nel)
@@ -987,6 +1028,7 @@ __device__ __forceinline__ void b3_apply_layers(const Geom &g, const Tables &tb,
 #pragma unroll
     for (int ch = 0; ch < NCH; ++ch) {
         const int nl = (ch + 1) * CH <= NQ ? CH : NQ - ch * CH;  // layers of this chunk
+        Tab tl = tb.again();
         // axis 3, forward: J[c][b] at this chunk's layers (plane c*3+b of RY)
         if (pen) {
             const CT *t = A.R2 + c * 3 * L2 + q12;
@@ -1004,7 +1046,7 @@ __device__ __forceinline__ void b3_apply_layers(const Geom &g, const Tables &tb,
                     CT a0 = 0, a1 = 0, a2 = 0;
 #pragma unroll
                     for (int k = 0; k < NI; ++k) {
-                        const CT b3 = tabB<CT>(tb, q * NI + k), g3 = tabG<CT>(tb, q * NI + k);
+                        const CT b3 = tabB<CT>(tl, q * NI + k), g3 = tabG<CT>(tl, q * NI + k);
                         a0 += b3 * t0[k];
                         a1 += b3 * t1[k];
                         a2 += g3 * t2[k];
@@ -1052,6 +1094,7 @@ __device__ __forceinline__ void b3_apply_layers(const Geom &g, const Tables &tb,
         }
         if (ch + 1 < NCH) load_chunk(ch + 1);
         __syncthreads();
+        tl = tb.again();
         // axis 3, transposed: this chunk's layers added into the accumulators
         if (pen) {
             const CT *y = B.RY + (c * 3) * CN + q12;
@@ -1062,7 +1105,7 @@ __device__ __forceinline__ void b3_apply_layers(const Geom &g, const Tables &tb,
                     const CT y0 = y[l * NQ2], y1 = y[CN + l * NQ2], y2 = y[2 * CN + l * NQ2];
 #pragma unroll
                     for (int k = 0; k < NI; ++k) {
-                        const CT b3 = tabB<CT>(tb, q * NI + k), g3 = tabG<CT>(tb, q * NI + k);
+                        const CT b3 = tabB<CT>(tl, q * NI + k), g3 = tabG<CT>(tl, q * NI + k);
                         acc0[k] += b3 * y0;
                         acc1[k] += b3 * y1;
                         acc2[k] += g3 * y2;
@@ -1116,7 +1159,7 @@ __device__ __forceinline__ bool compact_point3(const Target &tg, const double *J
 }
 
 template <int P, int NQ, typename TT, bool MF = false>
-__device__ __forceinline__ void b3_setupc(const Geom &g, const Tables &tb, const Target &tg,
+__device__ __forceinline__ void b3_setupc(const Geom &g, const Tab &tb, const Target &tg,
                                  const double *__restrict__ x, TT *__restrict__ Q,
                                  double *__restrict__ bad, int e0, int nel)
 {
@@ -1124,6 +1167,8 @@ __device__ __forceinline__ void b3_setupc(const Geom &g, const Tables &tb, const
     __shared__ Lds3<P, NQ, double> L;
     __shared__ double red[BLOCK / 64];
     __shared__ double mft[MF ? 2 * NQ * S::NI : 1];
+    __shared__ double sw[NQ];
+    weights_to_lds<NQ>(tb, sw);
     if (MF) mfma_tables<S::NI, NQ>(tb, mft);
     gather3<P, NQ>(g, x, e0, nel, L.X, false);
     __syncthreads();
@@ -1137,7 +1182,7 @@ __device__ __forceinline__ void b3_setupc(const Geom &g, const Tables &tb, const
         double J[9];
         point_J3<P, NQ>(L.RY, el, q, J);
         TT hs[NC3];
-        if (!compact_point3<TT>(tg, J, point_weight3<NQ>(tb, tg, q), hs)) nbad += 1.0;
+        if (!compact_point3<TT>(tg, J, point_weight3<NQ>(sw, tg, q), hs)) nbad += 1.0;
         qdata_store<TT, NC3, S::NQ3>(Q + (size_t)(e0 + el) * QLay<TT, NC3, S::NQ3>::STRIDE, q, hs);
     }
     const double b = block_sum(nbad, red);
@@ -1145,7 +1190,7 @@ __device__ __forceinline__ void b3_setupc(const Geom &g, const Tables &tb, const
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM = false, int T2 = 2>
-__device__ __forceinline__ void b3_applyc_points(const Geom &g, const Tables &tb,
+__device__ __forceinline__ void b3_applyc_points(const Geom &g, const Tab &tb,
                                                  const Target &tg, const TT *__restrict__ Q,
                                                  const double *__restrict__ v,
                                                  CT *__restrict__ yE, int e0, int nel)
@@ -1163,6 +1208,8 @@ __device__ __forceinline__ void b3_applyc_points(const Geom &g, const Tables &tb
     constexpr bool ONE = PASSES == 1;
     constexpr bool PF = !ONE;
     __shared__ Lds3<P, NQ, CT, NR, T2> L;
+    __shared__ double sw[LIM ? NQ : 1];
+    if (LIM) weights_to_lds<NQ>(tb, sw);
     Gath3<P, NQ, T2> gv;
     gather3_load<P, NQ, T2>(g, v, e0, nel, true, gv);
     const int npts = nel * S::NQ3;
@@ -1199,7 +1246,7 @@ __device__ __forceinline__ void b3_applyc_points(const Geom &g, const Tables &tb
             }
 #pragma unroll
             for (int r = 0; r < 9; ++r) L.RY[(el * NR + r) * S::NQ3 + q] = Y[r];
-            if (LIM) lim_point3<NQ, CT, NR>(tb, g, el, q, L.RY);
+            if (LIM) lim_point3<NQ, CT, NR>(sw, g, el, q, L.RY);
         }
     }
     __syncthreads();
@@ -1221,7 +1268,7 @@ constexpr bool apply_layers3()
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM = false, int T2 = 2>
-__device__ __forceinline__ void b3_apply(const Geom &g, const Tables &tb, const TT *__restrict__ H,
+__device__ __forceinline__ void b3_apply(const Geom &g, const Tab &tb, const TT *__restrict__ H,
                                 const double *__restrict__ v, CT *__restrict__ yE, int e0, int nel)
 {
     if constexpr (apply_layers3<P, NQ, T2, LIM, CT, false>())
@@ -1231,7 +1278,7 @@ __device__ __forceinline__ void b3_apply(const Geom &g, const Tables &tb, const 
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM = false, int T2 = 2>
-__device__ __forceinline__ void b3_applyc(const Geom &g, const Tables &tb, const Target &tg,
+__device__ __forceinline__ void b3_applyc(const Geom &g, const Tab &tb, const Target &tg,
                                  const TT *__restrict__ Q, const double *__restrict__ v,
                                  CT *__restrict__ yE, int e0, int nel)
 {
@@ -1279,13 +1326,13 @@ __device__ __forceinline__ void diag_line(const double *Tt, const double *yv, do
 }
 
 template <int P, int NQ, bool LIM>
-__device__ __forceinline__ void diag_contract3(const Tables &tb, const Geom &g, int e0,
+__device__ __forceinline__ void diag_contract3(const Tab &tb, const Geom &g, int e0,
                                       DiagLds3<P, NQ, LIM> &L, int nel, double *__restrict__ dE)
 {
     using S = S3<P, NQ>;
     constexpr int NI = S::NI, NQ3 = S::NQ3, NP = S::NP, NPR = DiagLds3<P, NQ, LIM>::NPR;
     for (int k = threadIdx.x; k < NQ * NI; k += BLOCK) {
-        const double b = tb.B[k], gg = tb.G[k];
+        const double b = tb.t->B[k], gg = tb.t->G[k];
         L.T[0][k] = b * b;
         L.T[1][k] = b * gg;
         L.T[2][k] = gg * gg;
@@ -1351,23 +1398,28 @@ __device__ __forceinline__ void diag_contract3(const Tables &tb, const Geom &g, 
 
 // the limiting pair's planes: 2 w_q lim for each component
 template <int P, int NQ, bool LIM>
-__device__ __forceinline__ void diag_lim3(const Tables &tb, const Geom &g, DiagLds3<P, NQ, LIM> &L, int el,
+__device__ __forceinline__ void diag_lim3(const double *sw, const Geom &g, DiagLds3<P, NQ, LIM> &L, int el,
                                  int q)
 {
     if (!LIM) return;
     constexpr int NQ3 = S3<P, NQ>::NQ3, NPR = DiagLds3<P, NQ, LIM>::NPR;
-    const double f = 2.0 * g.lim * qweight3<NQ>(tb, q);
+    const double f = 2.0 * g.lim * qweight3<NQ>(sw, q);
 #pragma unroll
     for (int a = 0; a < 3; ++a) L.sQ[((el * NPR + 6) * 3 + a) * NQ3 + q] = f;
 }
 
 template <int P, int NQ, typename TT, bool LIM = false>
-__device__ __forceinline__ void b3_diag(const Geom &g, const Tables &tb, const TT *__restrict__ H,
+__device__ __forceinline__ void b3_diag(const Geom &g, const Tab &tb, const TT *__restrict__ H,
                                double *__restrict__ dE, int e0, int nel)
 {
     using S = S3<P, NQ>;
     constexpr int NPR = DiagLds3<P, NQ, LIM>::NPR;
     __shared__ DiagLds3<P, NQ, LIM> L;
+    __shared__ double sw[LIM ? NQ : 1];
+    if (LIM) {
+        weights_to_lds<NQ>(tb, sw);
+        __syncthreads();
+    }
     for (int idx = threadIdx.x; idx < nel * S::NQ3; idx += BLOCK) {
         const int el = idx / S::NQ3, q = idx % S::NQ3;
         const TT *h = H + (size_t)(e0 + el) * QLay<TT, 45, S::NQ3>::STRIDE;
@@ -1380,14 +1432,14 @@ __device__ __forceinline__ void b3_diag(const Geom &g, const Tables &tb, const T
                 L.sQ[((el * NPR + pr) * 3 + a) * S::NQ3 + q] =
                     f * (double)qdata_at<TT, 45, S::NQ3>(h, q, sym_index<9>(a * 3 + n, a * 3 + p));
         }
-        diag_lim3<P, NQ, LIM>(tb, g, L, el, q);
+        diag_lim3<P, NQ, LIM>(sw, g, L, el, q);
     }
     diag_contract3<P, NQ, LIM>(tb, g, e0, L, nel, dE);
 }
 
 // The diagonal's LDS planes of one point from its compact data (b3_diagc).
 template <int P, int NQ, typename TT, bool LIM>
-__device__ __forceinline__ void diagc_point3(const Tables &tb, const Geom &g, const Target &tg,
+__device__ __forceinline__ void diagc_point3(const double *sw, const Geom &g, const Target &tg,
                                     const TT *hr, DiagLds3<P, NQ, LIM> &L, int el, int q)
 {
     using S = S3<P, NQ>;
@@ -1430,7 +1482,7 @@ __device__ __forceinline__ void diagc_point3(const Tables &tb, const Geom &g, co
                 L.sQ[((el * NPR + pr) * 3 + a) * S::NQ3 + q] = f * hv;
             }
         }
-        diag_lim3<P, NQ, LIM>(tb, g, L, el, q);
+        diag_lim3<P, NQ, LIM>(sw, g, L, el, q);
     }
 }
 
@@ -1438,16 +1490,21 @@ __device__ __forceinline__ void diagc_point3(const Tables &tb, const Geom &g, co
 // term vanishes, so H[an,ap] = c_id (W^-1 W^-T)_np + c_tc (Tw_an Cw_ap +
 // Cw_an Tw_ap) + c_cc Cw_an Cw_ap with Tw = T W^{-T}, Cw = C W^{-T}.
 template <int P, int NQ, typename TT, bool LIM = false>
-__device__ __forceinline__ void b3_diagc(const Geom &g, const Tables &tb, const Target &tg,
+__device__ __forceinline__ void b3_diagc(const Geom &g, const Tab &tb, const Target &tg,
                                 const TT *__restrict__ Q, double *__restrict__ dE, int e0, int nel)
 {
     using S = S3<P, NQ>;
     __shared__ DiagLds3<P, NQ, LIM> L;
+    __shared__ double sw[LIM ? NQ : 1];
+    if (LIM) {
+        weights_to_lds<NQ>(tb, sw);
+        __syncthreads();
+    }
     for (int idx = threadIdx.x; idx < nel * S::NQ3; idx += BLOCK) {
         const int el = idx / S::NQ3, q = idx % S::NQ3;
         TT hr[NC3];
         qdata_load<TT, NC3, S::NQ3>(Q + (size_t)(e0 + el) * QLay<TT, NC3, S::NQ3>::STRIDE, q, hr);
-        diagc_point3<P, NQ, TT, LIM>(tb, g, tg, hr, L, el, q);
+        diagc_point3<P, NQ, TT, LIM>(sw, g, tg, hr, L, el, q);
     }
     diag_contract3<P, NQ, LIM>(tb, g, e0, L, nel, dE);
 }
@@ -1462,7 +1519,7 @@ __device__ __forceinline__ void b3_diagc(const Geom &g, const Tables &tb, const 
 // pass of the workgroup.  H, bad and dE are bitwise those of b3_setup then
 // b3_diag.
 template <int P, int NQ, typename TT, bool LIM>
-__device__ __forceinline__ void b3_setupd(const Geom &g, const Tables &tb, const Target &tg,
+__device__ __forceinline__ void b3_setupd(const Geom &g, const Tab &tb, const Target &tg,
                                  const double *__restrict__ x, TT *__restrict__ H,
                                  double *__restrict__ dE, double *__restrict__ bad, int e0,
                                  int nel)
@@ -1476,6 +1533,8 @@ __device__ __forceinline__ void b3_setupd(const Geom &g, const Tables &tb, const
     };
     __shared__ Buf L;
     __shared__ double red[BLOCK / 64];
+    __shared__ double sw[NQ];
+    weights_to_lds<NQ>(tb, sw);
     gather3<P, NQ>(g, x, e0, nel, L.s.X, false);
     __syncthreads();
     forward3<P, NQ>(tb, L.s.X, L.s.R1, L.s.R2, L.s.RY, nel);
@@ -1487,7 +1546,7 @@ __device__ __forceinline__ void b3_setupd(const Geom &g, const Tables &tb, const
     double nbad = 0.0;
     if (act) {
         double Hp[45];
-        const double z = point_weight3<NQ>(tb, tg, q);
+        const double z = point_weight3<NQ>(sw, tg, q);
         if (!metric_second<3>(tg, J, z, Hp)) {
             nbad = 1.0;
 #pragma unroll
@@ -1507,7 +1566,7 @@ __device__ __forceinline__ void b3_setupd(const Geom &g, const Tables &tb, const
                 L.d.sQ[((el * NPR + pr) * 3 + a) * S::NQ3 + q] =
                     f * (double)hs[sym_index<9>(a * 3 + n, a * 3 + p)];
         }
-        diag_lim3<P, NQ, LIM>(tb, g, L.d, el, q);
+        diag_lim3<P, NQ, LIM>(sw, g, L.d, el, q);
     }
     diag_contract3<P, NQ, LIM>(tb, g, e0, L.d, nel, dE);
     const double b = block_sum(nbad, red);
@@ -1518,7 +1577,7 @@ __device__ __forceinline__ void b3_setupd(const Geom &g, const Tables &tb, const
 // stored, give the diagonal's planes as b3_diagc computes them from the
 // stored data.  Q, bad and dE are bitwise those of b3_setupc then b3_diagc.
 template <int P, int NQ, typename TT, bool LIM>
-__device__ __forceinline__ void b3_setupcd(const Geom &g, const Tables &tb, const Target &tg,
+__device__ __forceinline__ void b3_setupcd(const Geom &g, const Tab &tb, const Target &tg,
                                   const double *__restrict__ x, TT *__restrict__ Q,
                                   double *__restrict__ dE, double *__restrict__ bad, int e0,
                                   int nel)
@@ -1531,6 +1590,8 @@ __device__ __forceinline__ void b3_setupcd(const Geom &g, const Tables &tb, cons
     };
     __shared__ Buf L;
     __shared__ double red[BLOCK / 64];
+    __shared__ double sw[NQ];
+    weights_to_lds<NQ>(tb, sw);
     gather3<P, NQ>(g, x, e0, nel, L.s.X, false);
     __syncthreads();
     forward3<P, NQ>(tb, L.s.X, L.s.R1, L.s.R2, L.s.RY, nel);
@@ -1542,9 +1603,9 @@ __device__ __forceinline__ void b3_setupcd(const Geom &g, const Tables &tb, cons
     double nbad = 0.0;
     if (act) {
         TT hs[NC3];
-        if (!compact_point3<TT>(tg, J, point_weight3<NQ>(tb, tg, q), hs)) nbad = 1.0;
+        if (!compact_point3<TT>(tg, J, point_weight3<NQ>(sw, tg, q), hs)) nbad = 1.0;
         qdata_store<TT, NC3, S::NQ3>(Q + (size_t)(e0 + el) * QLay<TT, NC3, S::NQ3>::STRIDE, q, hs);
-        diagc_point3<P, NQ, TT, LIM>(tb, g, tg, hs, L.d, el, q);
+        diagc_point3<P, NQ, TT, LIM>(sw, g, tg, hs, L.d, el, q);
     }
     diag_contract3<P, NQ, LIM>(tb, g, e0, L.d, nel, dE);
     const double b = block_sum(nbad, red);
@@ -1559,88 +1620,99 @@ __device__ __forceinline__ void b3_setupcd(const Geom &g, const Tables &tb, cons
 // ------------------------------------------------------------------------
 
 template <int P, int NQ, bool LIM, bool MF = false>
-__global__ __launch_bounds__(BLOCK) void k3_energy(Geom g, Tables tb, Target tg, const double *__restrict__ x, double *__restrict__ part)
+__global__ __launch_bounds__(BLOCK) void k3_energy(Geom g, Tables tba, Target tg, const double *__restrict__ x, double *__restrict__ part)
 {
+    const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S3<P, NQ>::EPB;
     const int e0 = xcd_block(blockIdx.x, gridDim.x) * EPB;
     b3_energy<P, NQ, LIM, MF>(g, tb, tg, x, part, e0, min(EPB, g.ne - e0));
 }
 
 template <int P, int NQ, bool LIM, bool EN = false, bool MF = false>
-__global__ __launch_bounds__(BLOCK) void k3_gradient(Geom g, Tables tb, Target tg, const double *__restrict__ x, double *__restrict__ gE, double *__restrict__ bad)
+__global__ __launch_bounds__(BLOCK) void k3_gradient(Geom g, Tables tba, Target tg, const double *__restrict__ x, double *__restrict__ gE, double *__restrict__ bad)
 {
+    const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S3<P, NQ>::EPB;
     const int e0 = xcd_block(blockIdx.x, gridDim.x) * EPB;
     b3_gradient<P, NQ, LIM, EN, MF>(g, tb, tg, x, gE, bad, e0, min(EPB, g.ne - e0));
 }
 
 template <int P, int NQ, typename TT, bool MF = false>
-__global__ __launch_bounds__(BLOCK) void k3_setup(Geom g, Tables tb, Target tg, const double *__restrict__ x, TT *__restrict__ H, double *__restrict__ bad)
+__global__ __launch_bounds__(BLOCK) void k3_setup(Geom g, Tables tba, Target tg, const double *__restrict__ x, TT *__restrict__ H, double *__restrict__ bad)
 {
+    const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S3<P, NQ>::EPB;
     const int e0 = xcd_block(blockIdx.x, gridDim.x) * EPB;
     b3_setup<P, NQ, TT, MF>(g, tb, tg, x, H, bad, e0, min(EPB, g.ne - e0));
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM, int T2 = 2>
-__global__ __launch_bounds__(BLOCK) void k3_apply(Geom g, Tables tb, const TT *__restrict__ H, const double *__restrict__ v, CT *__restrict__ yE)
+__global__ __launch_bounds__(BLOCK) void k3_apply(Geom g, Tables tba, const TT *__restrict__ H, const double *__restrict__ v, CT *__restrict__ yE)
 {
+    const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S3<P, NQ, T2>::EPB;
     const int e0 = xcd_block(blockIdx.x, gridDim.x) * EPB;
     b3_apply<P, NQ, TT, CT, LIM, T2>(g, tb, H, v, yE, e0, min(EPB, g.ne - e0));
 }
 
 template <int P, int NQ, typename TT, bool MF = false>
-__global__ __launch_bounds__(BLOCK) void k3_setupc(Geom g, Tables tb, Target tg, const double *__restrict__ x, TT *__restrict__ Q, double *__restrict__ bad)
+__global__ __launch_bounds__(BLOCK) void k3_setupc(Geom g, Tables tba, Target tg, const double *__restrict__ x, TT *__restrict__ Q, double *__restrict__ bad)
 {
+    const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S3<P, NQ>::EPB;
     const int e0 = xcd_block(blockIdx.x, gridDim.x) * EPB;
     b3_setupc<P, NQ, TT, MF>(g, tb, tg, x, Q, bad, e0, min(EPB, g.ne - e0));
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM, int T2 = 2>
-__global__ __launch_bounds__(BLOCK) void k3_applyc(Geom g, Tables tb, Target tg, const TT *__restrict__ Q, const double *__restrict__ v, CT *__restrict__ yE)
+__global__ __launch_bounds__(BLOCK) void k3_applyc(Geom g, Tables tba, Target tg, const TT *__restrict__ Q, const double *__restrict__ v, CT *__restrict__ yE)
 {
+    const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S3<P, NQ, T2>::EPB;
     const int e0 = xcd_block(blockIdx.x, gridDim.x) * EPB;
     b3_applyc<P, NQ, TT, CT, LIM, T2>(g, tb, tg, Q, v, yE, e0, min(EPB, g.ne - e0));
 }
 
 template <int P, int NQ, typename TT, bool LIM>
-__global__ __launch_bounds__(BLOCK) void k3_diag(Geom g, Tables tb, const TT *__restrict__ H, double *__restrict__ dE)
+__global__ __launch_bounds__(BLOCK) void k3_diag(Geom g, Tables tba, const TT *__restrict__ H, double *__restrict__ dE)
 {
+    const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S3<P, NQ>::EPB;
     const int e0 = xcd_block(blockIdx.x, gridDim.x) * EPB;
     b3_diag<P, NQ, TT, LIM>(g, tb, H, dE, e0, min(EPB, g.ne - e0));
 }
 
 template <int P, int NQ, typename TT, bool LIM>
-__global__ __launch_bounds__(BLOCK) void k3_setupd(Geom g, Tables tb, Target tg, const double *__restrict__ x, TT *__restrict__ H, double *__restrict__ dE, double *__restrict__ bad)
+__global__ __launch_bounds__(BLOCK) void k3_setupd(Geom g, Tables tba, Target tg, const double *__restrict__ x, TT *__restrict__ H, double *__restrict__ dE, double *__restrict__ bad)
 {
+    const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S3<P, NQ>::EPB;
     const int e0 = xcd_block(blockIdx.x, gridDim.x) * EPB;
     b3_setupd<P, NQ, TT, LIM>(g, tb, tg, x, H, dE, bad, e0, min(EPB, g.ne - e0));
 }
 
 template <int P, int NQ, typename TT, bool LIM>
-__global__ __launch_bounds__(BLOCK) void k3_setupcd(Geom g, Tables tb, Target tg, const double *__restrict__ x, TT *__restrict__ Q, double *__restrict__ dE, double *__restrict__ bad)
+__global__ __launch_bounds__(BLOCK) void k3_setupcd(Geom g, Tables tba, Target tg, const double *__restrict__ x, TT *__restrict__ Q, double *__restrict__ dE, double *__restrict__ bad)
 {
+    const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S3<P, NQ>::EPB;
     const int e0 = xcd_block(blockIdx.x, gridDim.x) * EPB;
     b3_setupcd<P, NQ, TT, LIM>(g, tb, tg, x, Q, dE, bad, e0, min(EPB, g.ne - e0));
 }
 
 template <int P, int NQ, typename TT, bool LIM>
-__global__ __launch_bounds__(BLOCK) void k3_diagc(Geom g, Tables tb, Target tg, const TT *__restrict__ Q, double *__restrict__ dE)
+__global__ __launch_bounds__(BLOCK) void k3_diagc(Geom g, Tables tba, Target tg, const TT *__restrict__ Q, double *__restrict__ dE)
 {
+    const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S3<P, NQ>::EPB;
     const int e0 = xcd_block(blockIdx.x, gridDim.x) * EPB;
     b3_diagc<P, NQ, TT, LIM>(g, tb, tg, Q, dE, e0, min(EPB, g.ne - e0));
 }
 
 template <int P, int NQ, bool LIM = false>
-__global__ __launch_bounds__(BLOCK) void kb3_energy(Tables tb, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ part)
+__global__ __launch_bounds__(BLOCK) void kb3_energy(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ part)
 {
+    const Tab tb = kernel_tables<0>();
     constexpr int EPB = S3<P, NQ>::EPB;
     const Tile t = tiles[blockIdx.x];
     if (gate && !gate[t.slot]) return;
@@ -1649,8 +1721,9 @@ __global__ __launch_bounds__(BLOCK) void kb3_energy(Tables tb, const Tile *__res
 }
 
 template <int P, int NQ, bool LIM = false, bool EN = false>
-__global__ __launch_bounds__(BLOCK) void kb3_gradient(Tables tb, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ bad)
+__global__ __launch_bounds__(BLOCK) void kb3_gradient(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ bad)
 {
+    const Tab tb = kernel_tables<0>();
     constexpr int EPB = S3<P, NQ>::EPB;
     const Tile t = tiles[blockIdx.x];
     if (gate && !gate[t.slot]) return;
@@ -1659,8 +1732,9 @@ __global__ __launch_bounds__(BLOCK) void kb3_gradient(Tables tb, const Tile *__r
 }
 
 template <int P, int NQ, typename TT>
-__global__ __launch_bounds__(BLOCK) void kb3_setup(Tables tb, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ bad)
+__global__ __launch_bounds__(BLOCK) void kb3_setup(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ bad)
 {
+    const Tab tb = kernel_tables<0>();
     constexpr int EPB = S3<P, NQ>::EPB;
     const Tile t = tiles[blockIdx.x];
     if (gate && !gate[t.slot]) return;
@@ -1669,8 +1743,9 @@ __global__ __launch_bounds__(BLOCK) void kb3_setup(Tables tb, const Tile *__rest
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM = false, int T2 = 2>
-__global__ __launch_bounds__(BLOCK) void kb3_apply(Tables tb, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
+__global__ __launch_bounds__(BLOCK) void kb3_apply(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
 {
+    const Tab tb = kernel_tables<0>();
     constexpr int EPB = S3<P, NQ, T2>::EPB;
     const Tile t = tiles[blockIdx.x];
     if (gate && !gate[t.slot]) return;
@@ -1679,8 +1754,9 @@ __global__ __launch_bounds__(BLOCK) void kb3_apply(Tables tb, const Tile *__rest
 }
 
 template <int P, int NQ, typename TT>
-__global__ __launch_bounds__(BLOCK) void kb3_setupc(Tables tb, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ bad)
+__global__ __launch_bounds__(BLOCK) void kb3_setupc(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ bad)
 {
+    const Tab tb = kernel_tables<0>();
     constexpr int EPB = S3<P, NQ>::EPB;
     const Tile t = tiles[blockIdx.x];
     if (gate && !gate[t.slot]) return;
@@ -1689,8 +1765,9 @@ __global__ __launch_bounds__(BLOCK) void kb3_setupc(Tables tb, const Tile *__res
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM = false, int T2 = 2>
-__global__ __launch_bounds__(BLOCK) void kb3_applyc(Tables tb, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
+__global__ __launch_bounds__(BLOCK) void kb3_applyc(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
 {
+    const Tab tb = kernel_tables<0>();
     constexpr int EPB = S3<P, NQ, T2>::EPB;
     const Tile t = tiles[blockIdx.x];
     if (gate && !gate[t.slot]) return;
@@ -1708,8 +1785,9 @@ constexpr bool tile_ok3()
 }
 
 template <int P, int NQ, typename TT, bool LIM = false>
-__global__ __launch_bounds__(BLOCK) void kb3_diag(Tables tb, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate)
+__global__ __launch_bounds__(BLOCK) void kb3_diag(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate)
 {
+    const Tab tb = kernel_tables<0>();
     constexpr int EPB = S3<P, NQ>::EPB;
     const Tile t = tiles[blockIdx.x];
     if (gate && !gate[t.slot]) return;
@@ -1718,8 +1796,9 @@ __global__ __launch_bounds__(BLOCK) void kb3_diag(Tables tb, const Tile *__restr
 }
 
 template <int P, int NQ, typename TT, bool LIM = false>
-__global__ __launch_bounds__(BLOCK) void kb3_diagc(Tables tb, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate)
+__global__ __launch_bounds__(BLOCK) void kb3_diagc(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate)
 {
+    const Tab tb = kernel_tables<0>();
     constexpr int EPB = S3<P, NQ>::EPB;
     const Tile t = tiles[blockIdx.x];
     if (gate && !gate[t.slot]) return;

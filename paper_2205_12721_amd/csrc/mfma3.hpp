@@ -34,13 +34,13 @@ __device__ __forceinline__ dvec4 mfma_f64(double a, double b, dvec4 c)
 // compile-time constants only).  Called before a barrier that precedes the
 // sweeps.
 template <int NI, int NQ>
-__device__ __forceinline__ void mfma_tables(const Tables &tb, double *sT)
+__device__ __forceinline__ void mfma_tables(const Tab &tb, double *sT)
 {
 #pragma unroll
     for (int k = 0; k < NQ * NI; ++k)
         if (threadIdx.x == k) {
-            sT[k] = tb.B[k];
-            sT[NQ * NI + k] = tb.G[k];
+            sT[k] = tabB<double>(tb, k);
+            sT[NQ * NI + k] = tabG<double>(tb, k);
         }
 }
 

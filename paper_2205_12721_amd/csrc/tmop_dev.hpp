@@ -38,9 +38,11 @@ inline FastDiv make_fastdiv(int d)
     return f;
 }
 
+// The shift by s = 31 + l as a high half of (2 n) m (2 n < 2^32) and a 32-bit
+// shift by l: three instructions instead of a 64-bit product and shift.
 __host__ __device__ __forceinline__ int fdiv(int n, FastDiv f)
 {
-    return (int)(((uint64_t)(uint32_t)n * f.m) >> f.s);
+    return (int)((uint32_t)(((uint64_t)((uint32_t)n << 1) * f.m) >> 32) >> (f.s - 31));
 }
 
 // Mesh geometry passed by value to every kernel.
@@ -104,8 +106,7 @@ __device__ __forceinline__ void box_coords(const Geom &g, int node, int gc[3])
 
 // 1D tables: B[q][i] = l_i(chi_q), G[q][i] = l_i'(chi_q), w[q] (Sec. 3.1, eq. eq_B_G_1D).
 // Bf, Gf: the same tables rounded to FP32 for the mixed-precision action.
-// Kernels take Tables by value, so the entries they index with compile-time
-// constants are read from the kernel arguments into scalar registers.
+// Kernels take Tables by value and read the entries through Tab.
 struct Tables {
     double B[MAXNQ * MAXNI];
     double G[MAXNQ * MAXNI];
@@ -114,31 +115,63 @@ struct Tables {
     float Gf[MAXNQ * MAXNI];
 };
 
+// A kernel's view of its Tables argument: a pointer to it in the kernel
+// argument segment (constant address space), so that entries indexed with
+// compile-time constants are scalar loads.  Every contraction stage starts
+// from again(), whose pointer the compiler cannot relate to the earlier ones:
+// the stage loads the 16 to 90 entries it uses afresh from the scalar cache.
+// Read through one pointer, the entries stayed live from stage to stage, more
+// than the 102 scalar registers hold, and were parked in vector lanes: 149
+// v_readlane / v_writelane of the 1170 vector instructions of the compact
+// FP64 action at Q3 (n_q = 5), 208 of the 1301 of the gradient with energy.
+// These kernels wait for the vector issue (one FP64 or 32-bit instruction of
+// a wave takes four cycles), so each instruction that is not a multiply-add
+// costs.
+struct Tab {
+    const __attribute__((address_space(4))) Tables *t;
+    __device__ __forceinline__ Tab again() const
+    {
+        Tab r = *this;
+        asm volatile("" : "+s"(r.t));
+        return r;
+    }
+};
+
+// The Tables argument of a kernel that starts OFF bytes into its arguments.
+template <size_t OFF>
+__device__ __forceinline__ Tab kernel_tables()
+{
+    static_assert(OFF % alignof(Tables) == 0, "offset of the Tables argument");
+    typedef const __attribute__((address_space(4))) char *Bytes;
+    return Tab{(const __attribute__((address_space(4))) Tables
+                    *)((Bytes)__builtin_amdgcn_kernarg_segment_ptr() + OFF)};
+}
+
 template <typename CT>
-__device__ inline CT tabB(const Tables &t, int k);
+__device__ inline CT tabB(const Tab &t, int k);
 template <>
-__device__ inline double tabB<double>(const Tables &t, int k) { return t.B[k]; }
+__device__ inline double tabB<double>(const Tab &t, int k) { return t.t->B[k]; }
 template <>
-__device__ inline float tabB<float>(const Tables &t, int k) { return t.Bf[k]; }
-// 1D weight w[i] for a run-time i, selected with compile-time indices only:
-// indexing the by-value Tables argument with a run-time index would make the
-// compiler copy the whole structure to scratch memory.
+__device__ inline float tabB<float>(const Tab &t, int k) { return t.t->Bf[k]; }
+template <typename CT>
+__device__ inline CT tabG(const Tab &t, int k);
+template <>
+__device__ inline double tabG<double>(const Tab &t, int k) { return t.t->G[k]; }
+template <>
+__device__ inline float tabG<float>(const Tab &t, int k) { return t.t->Gf[k]; }
+
+// The 1D weights to LDS, where a lane reads the entries of its point's
+// indices (selecting them from scalar registers took three instructions per
+// entry and axis).  Called before the barrier that ends the gather.
 template <int NQ>
-__device__ __forceinline__ double tab_w(const Tables &t, int i)
+__device__ __forceinline__ void weights_to_lds(const Tab &t, double *sw)
 {
     double w = 0.0;
 #pragma unroll
     for (int k = 0; k < NQ; ++k)
-        if (i == k) w = t.w[k];
-    return w;
+        if ((int)threadIdx.x == k) w = t.t->w[k];
+    if (threadIdx.x < NQ) sw[threadIdx.x] = w;
 }
-
-template <typename CT>
-__device__ inline CT tabG(const Tables &t, int k);
-template <>
-__device__ inline double tabG<double>(const Tables &t, int k) { return t.G[k]; }
-template <>
-__device__ inline float tabG<float>(const Tables &t, int k) { return t.Gf[k]; }
 
 // Constant target: W^{-1} (row-major) and det W; ideal != 0 means W = I.
 struct Target {
