@@ -285,14 +285,14 @@ __device__ __forceinline__ void b2_energy(const Geom &g, const Tab &tb, const Ta
     double esum = 0.0, dmin = 1.0e300, bad = 0.0;
     for (int idx = threadIdx.x; idx < nel * S::NQ2; idx += BLOCK) {
         const int el = idx / S::NQ2, q = idx % S::NQ2;
-        double J[4], Pm[4], mu;
+        double J[4], Pm[4], mu, detA;
         point_J2<P, NQ, double, NR>(L.RY, el, q, J);
-        dmin = fmin(dmin, det_only<2>(J));
         const double z = qweight2<NQ>(sw, q) * tg.detW;
-        if (metric_first<2>(tg, J, z, &mu, Pm))
+        if (metric_first<2>(tg, J, z, &mu, Pm, &detA))
             esum += z * mu;
         else
             bad += 1.0;
+        dmin = fmin(dmin, detA);
         if (LIM) {
             const double u0 = U[(el * 2) * S::NQ2 + q], u1 = U[(el * 2 + 1) * S::NQ2 + q];
             esum += qweight2<NQ>(sw, q) * g.lim * (u0 * u0 + u1 * u1);
@@ -326,11 +326,12 @@ __device__ __forceinline__ void b2_gradient(const Geom &g, const Tab &tb, const 
     double nbad = 0.0, esum = 0.0, dmin = 1.0e300;
     for (int idx = threadIdx.x; idx < nel * S::NQ2; idx += BLOCK) {
         const int el = idx / S::NQ2, q = idx % S::NQ2;
-        double J[4], Pm[4], mu;
+        double J[4], Pm[4], mu, detA;
         point_J2<P, NQ, double, NR>(L.RY, el, q, J);
-        if (EN) dmin = fmin(dmin, det_only<2>(J));
         const double z = qweight2<NQ>(sw, q) * tg.detW;
-        if (!metric_first<2>(tg, J, z, &mu, Pm)) {
+        const bool ok = metric_first<2>(tg, J, z, &mu, Pm, &detA);
+        if (EN) dmin = fmin(dmin, detA);
+        if (!ok) {
             nbad += 1.0;
 #pragma unroll
             for (int k = 0; k < 4; ++k) Pm[k] = 0.0;
@@ -494,7 +495,7 @@ __device__ __forceinline__ void b2_setupc(const Geom &g, const Tab &tb, const Ta
             double I1 = 0.0;
 #pragma unroll
             for (int k = 0; k < 4; ++k) I1 += T[k] * T[k];
-            const MetricCoef m = metric_coef(tg.metric, I1, tau);
+            const MetricCoef m = metric_coef<2>(tg.metric, I1, tau);
 #pragma unroll
             for (int k = 0; k < 4; ++k) out[k] = T[k];
             out[4] = z * m.c_id;

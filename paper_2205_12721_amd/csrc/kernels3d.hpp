@@ -645,13 +645,13 @@ __device__ __forceinline__ void b3_energy(const Geom &g, const Tab &tb, const Ta
         const int el = idx / S::NQ3, q = idx % S::NQ3;
         double J[9];
         point_J3<P, NQ, double, NR>(L.RY, el, q, J);
-        dmin = fmin(dmin, det_only<3>(J));
         const double z = point_weight3<NQ>(sw, tg, q);
-        double mu, Pm[9];
-        if (metric_first<3>(tg, J, z, &mu, Pm))
+        double mu, Pm[9], detA;
+        if (metric_first<3>(tg, J, z, &mu, Pm, &detA))
             esum += z * mu;
         else
             bad += 1.0;
+        dmin = fmin(dmin, detA);
         if (LIM) {
             double y2 = 0.0;
 #pragma unroll
@@ -705,11 +705,12 @@ __device__ __forceinline__ void b3_gradient(const Geom &g, const Tab &tb, const 
     double nbad = 0.0, esum = 0.0, dmin = 1.0e300;
     for (int idx = threadIdx.x; idx < nel * S::NQ3; idx += BLOCK) {
         const int el = idx / S::NQ3, q = idx % S::NQ3;
-        double J[9], Pm[9], mu;
+        double J[9], Pm[9], mu, detA;
         point_J3<P, NQ, double, NR>(L.RY, el, q, J);
-        if (EN) dmin = fmin(dmin, det_only<3>(J));
         const double z = point_weight3<NQ>(sw, tg, q);
-        if (!metric_first<3>(tg, J, z, &mu, Pm)) {
+        const bool ok = metric_first<3>(tg, J, z, &mu, Pm, &detA);
+        if (EN) dmin = fmin(dmin, detA);
+        if (!ok) {
             nbad += 1.0;
 #pragma unroll
             for (int k = 0; k < 9; ++k) Pm[k] = 0.0;
@@ -1142,7 +1143,7 @@ __device__ __forceinline__ bool compact_point3(const Target &tg, const double *J
         double I1 = 0.0;
 #pragma unroll
         for (int k = 0; k < 9; ++k) I1 += T[k] * T[k];
-        const MetricCoef m = metric_coef(tg.metric, I1, tau);
+        const MetricCoef m = metric_coef<3>(tg.metric, I1, tau);
 #pragma unroll
         for (int k = 0; k < 9; ++k) out[k] = T[k];
         out[9] = z * m.c_id;

@@ -371,32 +371,43 @@ struct MetricCoef {
 // inlining, so every kernel that evaluates a metric at a point rounds the
 // same way (the one-pass kernels give bitwise the results of the separate
 // ones).
+// tau^{-1/3} for tau > 0: tau = m 2^{3k} with m in [1/8, 8), an FP32 estimate
+// r0 = 2^{-log2(m)/3} (relative error below 1e-6) and one third-order
+// (Householder) step for r^-3 = m, which leaves e^3 < 1e-18 of the estimate's
+// error: r = r0 (1 + e/3 + 2 e^2 / 9), e = 1 - m r0^3.  Error about 0.7 ulp;
+// 20 vector instructions, where 1 / cbrt(tau) with the library's cube root
+// and an exact division took about 60.  tau = inf is taken as the largest
+// finite value.
+__device__ __forceinline__ double inv_cbrt(double tau)
+{
+    tau = fmin(tau, 1.7976931348623157e308);
+    const int k = (__builtin_amdgcn_frexp_exp(tau) * 21846) >> 16;  // about a third of the exponent
+    const double m = __builtin_amdgcn_ldexp(tau, -3 * k);
+    const float r0f = __builtin_amdgcn_exp2f(-0.33333334f * __builtin_amdgcn_logf((float)m));
+    const double r0 = (double)r0f;
+    const double e = __builtin_fma(-(m * r0), r0 * r0, 1.0);
+    const double r = __builtin_fma(r0 * e, __builtin_fma(e, 2.0 / 9.0, 1.0 / 3.0), r0);
+    return __builtin_amdgcn_ldexp(r, -k);
+}
+
+template <int D>
 __device__ inline MetricCoef metric_coef(int metric, double I1, double tau)
 {
 #pragma clang fp contract(on)
     MetricCoef m;
-    if (metric == 2) {
-        const double it = 1.0 / tau;
-        m.mu = 0.5 * I1 * it - 1.0;
-        m.cT = it;
-        m.cC = -0.5 * I1 * it * it;
-        m.c_id = it;
-        m.c_tc = -it * it;
-        m.c_cc = I1 * it * it * it;
-        m.c_dc = -0.5 * I1 * it * it;
-    } else if (metric == 303) {
-        const double r = 1.0 / cbrt(tau);  // tau^{-1/3}
+    if (D == 3 && metric == 303) {
+        const double r = inv_cbrt(tau);    // tau^{-1/3}
         const double r2 = r * r;           // tau^{-2/3}
         const double r5 = r2 * r2 * r;     // tau^{-5/3}
         const double r8 = r5 * r2 * r;     // tau^{-8/3}
-        m.mu = I1 * r2 / 3.0 - 1.0;
-        m.cT = 2.0 * r2 / 3.0;
-        m.cC = -2.0 * I1 * r5 / 9.0;
-        m.c_id = 2.0 * r2 / 3.0;
-        m.c_tc = -4.0 * r5 / 9.0;
-        m.c_cc = 10.0 * I1 * r8 / 27.0;
-        m.c_dc = -2.0 * I1 * r5 / 9.0;
-    } else if (metric == 55) {
+        m.mu = (I1 * r2 - 3.0) * (1.0 / 3.0);
+        m.cT = (2.0 / 3.0) * r2;
+        m.cC = (-2.0 / 9.0) * (I1 * r5);
+        m.c_id = m.cT;
+        m.c_tc = (-4.0 / 9.0) * r5;
+        m.c_cc = (10.0 / 27.0) * (I1 * r8);
+        m.c_dc = m.cC;
+    } else if (D == 3 || metric == 55) {
         const double dm = tau - 1.0;
         m.mu = dm * dm;
         m.cT = 0.0;
@@ -405,6 +416,15 @@ __device__ inline MetricCoef metric_coef(int metric, double I1, double tau)
         m.c_tc = 0.0;
         m.c_cc = 2.0;
         m.c_dc = 2.0 * dm;
+    } else if (metric == 2) {
+        const double it = 1.0 / tau;
+        m.mu = 0.5 * I1 * it - 1.0;
+        m.cT = it;
+        m.cC = -0.5 * I1 * it * it;
+        m.c_id = it;
+        m.c_tc = -it * it;
+        m.c_cc = I1 * it * it * it;
+        m.c_dc = -0.5 * I1 * it * it;
     } else if (metric == 7) {
         const double it = 1.0 / tau, it2 = it * it, it3 = it2 * it;
         m.mu = I1 * (1.0 + it2) - 4.0;
@@ -435,7 +455,7 @@ __device__ inline double metric_value(int metric, const double *T, const double 
                                       double tau, const MetricCoef &m)
 {
 #pragma clang fp contract(on)
-    if (metric != 7 && metric != 9) return m.mu;
+    if (D == 3 || (metric != 7 && metric != 9)) return m.mu;
     const double it = 1.0 / tau;
     double s = 0.0;
 #pragma unroll
@@ -518,27 +538,30 @@ __device__ inline double dcof(const double *T, int r, int s)
     }
 }
 
-// mu and z * P with P = dmu/dT W^{-T}.  Returns false if tau <= 0.
+// mu and z * P with P = dmu/dT W^{-T}; *detA = det A (also when the return is
+// false, which tells det T <= 0).
 template <int D>
 __device__ inline bool metric_first(const Target &t, const double *A, double z, double *mu,
-                                    double *P)
+                                    double *P, double *detA)
 {
 #pragma clang fp contract(on)
     double T[D * D], C[D * D];
     apply_winv<D>(t, A, T);
     const double tau = det_cof<D>(T, C);
+    *detA = t.ideal ? tau : det_only<D>(A);
     if (!(tau > 0.0)) return false;
     double I1 = 0.0;
 #pragma unroll
     for (int k = 0; k < D * D; ++k) I1 += T[k] * T[k];
-    const MetricCoef m = metric_coef(t.metric, I1, tau);
+    const MetricCoef m = metric_coef<D>(t.metric, I1, tau);
     *mu = metric_value<D>(t.metric, T, C, I1, tau, m);
+    const double zT = z * m.cT, zC = z * m.cC;
     double dmu[D * D];
 #pragma unroll
-    for (int k = 0; k < D * D; ++k) dmu[k] = m.cT * T[k] + m.cC * C[k];
+    for (int k = 0; k < D * D; ++k) dmu[k] = zT * T[k] + zC * C[k];
     if (t.ideal) {
 #pragma unroll
-        for (int k = 0; k < D * D; ++k) P[k] = z * dmu[k];
+        for (int k = 0; k < D * D; ++k) P[k] = dmu[k];
     } else {
 #pragma unroll
         for (int a = 0; a < D; ++a)
@@ -547,7 +570,7 @@ __device__ inline bool metric_first(const Target &t, const double *A, double z, 
                 double s = 0.0;
 #pragma unroll
                 for (int k = 0; k < D; ++k) s += dmu[a * D + k] * t.Winv[n * D + k];
-                P[a * D + n] = z * s;
+                P[a * D + n] = s;
             }
     }
     return true;
@@ -567,7 +590,7 @@ __device__ inline bool metric_second(const Target &t, const double *A, double z,
     double I1 = 0.0;
 #pragma unroll
     for (int k = 0; k < D2; ++k) I1 += T[k] * T[k];
-    const MetricCoef m = metric_coef(t.metric, I1, tau);
+    const MetricCoef m = metric_coef<D>(t.metric, I1, tau);
     if (t.ideal) {
 #pragma unroll
         for (int r = 0; r < D2; ++r)
