@@ -432,7 +432,9 @@ int tmop_time_apply(tmop_ctx *ctx, const double *v_dev, double *y_dev, int n, do
  * storage, precision), so that contexts and pools created later in the
  * process start with it.  Needs tmop_hessian_setup; leaves y_dev = H v.
  * The tile shape changes no result (every element is computed alike).
- * epb (may be NULL): the chosen elements per workgroup. */
+ * epb (may be NULL): the chosen elements per workgroup.  (With compact storage
+ * the base shape of most hex classes runs in column form, whose workgroups
+ * hold another number of elements; epb names the shape.) */
 int tmop_autotune(tmop_ctx *ctx, const double *v_dev, double *y_dev, int reps, int *epb);
 
 /* Elements per workgroup of the context's current Hessian-action tile. */
@@ -476,8 +478,9 @@ int tmop_set_timing(tmop_ctx *ctx, int enable);
 /* No-allocation evaluation                                                */
 /* ---------------------------------------------------------------------- */
 
-/* Largest number of element tiles (workgroups of the energy kernel, each of
- * max(1, 256 / nq1d^dim) elements) tmop_energy_mindet_noalloc accepts. */
+/* Largest number of element tiles (max(1, 256 / nq1d^dim) elements each; the
+ * energy kernel's workgroups hold one or more) tmop_energy_mindet_noalloc
+ * accepts. */
 #define TMOP_NOALLOC_MAX_TILES 65536
 
 /* For callers that cannot allocate device memory (code under HIP graph

@@ -21,6 +21,7 @@
 #include <cmath>
 #include <cstring>
 #include <map>
+#include <set>
 #include <string>
 #include <vector>
 
@@ -741,20 +742,29 @@ struct ClassKey {
     }
 };
 
+struct TileList {
+    std::vector<Tile> tiles;
+    Tile *d = nullptr;
+    int cap = 0;
+};
+
 struct ClassH {
     ClassKey key{};
     BOps bops{};
     Tables tb{};
-    std::vector<Tile> tiles;
-    Tile *d_tiles = nullptr;
-    int cap = 0;
+    // tile lists by elements per tile (the kernels of a class differ in it)
+    std::map<int, TileList> lists;
     int pbase = 0;
-    // Hessian action tile shape (index into BOps::epb_t) and, when it is not
-    // the base shape, its own tile list
-    int tile = 1;
-    std::vector<Tile> atiles;
-    Tile *d_atiles = nullptr;
-    int acap = 0;
+    int tile = 1;  // Hessian action tile shape (index into BOps::epb_t)
+    int nelem = 0;  // elements of the class's resident meshes
+
+    // elements per tile of the energy and gradient kernels (the energy
+    // partials are counted in these tiles) and of the action
+    int epb_energy() const { return key.lim ? bops.epb : bops.epbE; }
+    int epb_apply(int t) const
+    {
+        return key.lim ? bops.epb : t == 1 ? bops.epbA[key.storage][key.prec] : bops.epb_t[t];
+    }
 };
 
 enum { PH_NEW = 0, PH_ITER = 1, PH_DONE = 2 };
@@ -959,13 +969,32 @@ static void invalidate_graph(tmop_pool *P)
     P->sg_maxj = -1;
 }
 
+static void add_tiles(TileList &l, int slot, int ne, int epb)
+{
+    for (int e = 0; e < ne; e += epb) l.tiles.push_back(Tile{slot, e});
+}
+
+static int upload_tiles(tmop_pool *P, TileList &l)
+{
+    const int n = (int)l.tiles.size();
+    if (n > l.cap) {
+        hipFree(l.d);
+        l.d = nullptr;
+        l.cap = std::max(n, 2 * l.cap);
+        PHIP(hipMalloc((void **)&l.d, sizeof(Tile) * l.cap));
+    }
+    if (n)
+        PHIP(hipMemcpyAsync(l.d, l.tiles.data(), sizeof(Tile) * n, hipMemcpyHostToDevice, P->s));
+    return TMOP_OK;
+}
+
 // Rebuild tile lists, vector tiles, ranges and partial layout for the used slots.
 static int pool_rebuild(tmop_pool *P)
 {
     invalidate_graph(P);
     for (auto &kv : P->classes) {
-        kv.second.tiles.clear();
-        kv.second.atiles.clear();
+        kv.second.nelem = 0;
+        for (auto &l : kv.second.lists) l.second.tiles.clear();
     }
     // element tiles per class
     for (int si = 0; si < P->max_slots; ++si) {
@@ -988,33 +1017,21 @@ static int pool_rebuild(tmop_pool *P)
             it = P->classes.emplace(k, c).first;
         }
         ClassH &c = it->second;
-        for (int e = 0; e < s.ne; e += c.bops.epb) c.tiles.push_back(Tile{si, e});
-        if (c.tile != 1)
-            for (int e = 0; e < s.ne; e += c.bops.epb_t[c.tile]) c.atiles.push_back(Tile{si, e});
+        c.nelem += s.ne;
+        for (int epb : std::set<int>{c.bops.epb, c.epb_energy(), c.bops.epbS[s.storage][s.prec],
+                                     c.epb_apply(c.tile)})
+            add_tiles(c.lists[epb], si, s.ne, epb);
     }
     int pb = 0;
     P->rg.assign(P->max_slots, SlotRange{0, 0, 1, 0, 0});
     for (auto &kv : P->classes) {
         ClassH &c = kv.second;
         c.pbase = pb;
-        const int nt = (int)c.tiles.size();
-        if (nt > c.cap) {
-            hipFree(c.d_tiles);
-            c.d_tiles = nullptr;
-            c.cap = std::max(nt, 2 * c.cap);
-            PHIP(hipMalloc((void **)&c.d_tiles, sizeof(Tile) * c.cap));
-        }
-        if (nt) PHIP(hipMemcpyAsync(c.d_tiles, c.tiles.data(), sizeof(Tile) * nt, hipMemcpyHostToDevice, P->s));
-        const int na = (int)c.atiles.size();
-        if (na > c.acap) {
-            hipFree(c.d_atiles);
-            c.d_atiles = nullptr;
-            c.acap = std::max(na, 2 * c.acap);
-            PHIP(hipMalloc((void **)&c.d_atiles, sizeof(Tile) * c.acap));
-        }
-        if (na) PHIP(hipMemcpyAsync(c.d_atiles, c.atiles.data(), sizeof(Tile) * na, hipMemcpyHostToDevice, P->s));
+        for (auto &l : c.lists) PCHK(upload_tiles(P, l.second));
+        const std::vector<Tile> &et = c.lists[c.epb_energy()].tiles;
+        const int nt = (int)et.size();
         for (int t = 0; t < nt; ++t) {
-            SlotRange &r = P->rg[c.tiles[t].slot];
+            SlotRange &r = P->rg[et[t].slot];
             if (r.ecount == 0) {
                 r.ebase = pb + t;
                 r.estride = nt;
@@ -1079,31 +1096,29 @@ static void launch_elem(tmop_pool *P, int which, const int *gate, int vin)
 {
     for (auto &kv : P->classes) {
         ClassH &c = kv.second;
-        const int nt = (int)c.tiles.size();
-        if (!nt) continue;
+        if (!c.nelem) continue;
         const int st = c.key.storage, pr = c.key.prec;
-        if (c.key.lim) {
-            BLaunch f = which == 0   ? c.bops.energyL
-                        : which == 1 ? c.bops.gradientL
-                        : which == 2 ? c.bops.setup[st][pr]
-                        : which == 3 ? c.bops.applyL[st][pr]
-                        : which == 4 ? c.bops.diagL[st][pr]
-                                     : c.bops.gradientEL;
-            f(nt, P->s, c.tb, c.d_tiles, P->d_slots, gate, vin, P->d_part + c.pbase);
-            continue;
-        }
-        if (which == 3 && c.tile != 1) {
-            c.bops.apply_t[st][pr][c.tile]((int)c.atiles.size(), P->s, c.tb, c.d_atiles, P->d_slots,
-                                          gate, vin, nullptr);
-            continue;
-        }
-        BLaunch f = which == 0   ? c.bops.energy
-                    : which == 1 ? c.bops.gradient
-                    : which == 2 ? c.bops.setup[st][pr]
-                    : which == 3 ? c.bops.apply[st][pr]
-                    : which == 4 ? c.bops.diag[st][pr]
-                                 : c.bops.gradientE;
-        f(nt, P->s, c.tb, c.d_tiles, P->d_slots, gate, vin, P->d_part + c.pbase);
+        const int epb = which == 2   ? c.bops.epbS[st][pr]
+                        : which == 3 ? c.epb_apply(c.tile)
+                        : which == 4 ? c.bops.epb
+                                     : c.epb_energy();
+        BLaunch f;
+        if (c.key.lim)
+            f = which == 0   ? c.bops.energyL
+                : which == 1 ? c.bops.gradientL
+                : which == 2 ? c.bops.setup[st][pr]
+                : which == 3 ? c.bops.applyL[st][pr]
+                : which == 4 ? c.bops.diagL[st][pr]
+                             : c.bops.gradientEL;
+        else
+            f = which == 0   ? c.bops.energy
+                : which == 1 ? c.bops.gradient
+                : which == 2 ? c.bops.setup[st][pr]
+                : which == 3 ? c.bops.apply_t[st][pr][c.tile]
+                : which == 4 ? c.bops.diag[st][pr]
+                             : c.bops.gradientE;
+        const TileList &l = c.lists[epb];
+        f((int)l.tiles.size(), P->s, c.tb, l.d, P->d_slots, gate, vin, P->d_part + c.pbase);
     }
 }
 
@@ -1609,8 +1624,7 @@ extern "C" int tmop_pool_destroy(tmop_pool *P)
     if (P->s) hipStreamSynchronize(P->s);
     invalidate_graph(P);
     for (auto &kv : P->classes) {
-        hipFree(kv.second.d_tiles);
-        hipFree(kv.second.d_atiles);
+        for (auto &l : kv.second.lists) hipFree(l.second.d);
     }
     hipFree(P->arena);
     hipFree(P->d_slots);
@@ -1942,34 +1956,31 @@ extern "C" int tmop_pool_autotune(tmop_pool *P, int reps)
     PHIP(hipEventCreate(&e1));
     for (auto &kv : P->classes) {
         ClassH &c = kv.second;
-        if (c.tiles.empty() || c.key.lim) continue;
+        if (!c.nelem || c.key.lim) continue;
         const int st = c.key.storage, pr = c.key.prec;
         int best = -1;
         float tbest = 0.f;
         float tmin[3] = {0.f, 0.f, 0.f};
+        // tile lists of every shape for the class's resident meshes
+        for (int t = 0; t < 3; ++t) {
+            if (c.bops.epb_t[t] == 0) continue;
+            TileList &l = c.lists[c.epb_apply(t)];
+            if (!l.tiles.empty()) continue;
+            for (int si = 0; si < P->max_slots; ++si) {
+                const SlotH &s = P->slots[si];
+                if (s.used && s.dim == c.key.dim && s.p == c.key.p && s.nq == c.key.nq &&
+                    s.storage == st && s.prec == pr && s.lim == c.key.lim)
+                    add_tiles(l, si, s.ne, c.epb_apply(t));
+            }
+            PCHK(upload_tiles(P, l));
+        }
         // three rounds over the shapes, each shape's best round counts
         for (int round = 0; round < 3; ++round) {
             for (int t = 0; t < 3; ++t) {
                 if (c.bops.epb_t[t] == 0) continue;
-                const Tile *dl = c.d_tiles;
-                int n = (int)c.tiles.size();
-                if (t != 1) {
-                    // tile list of this shape for the class's resident meshes
-                    std::vector<Tile> tl;
-                    for (const Tile &b : c.tiles)
-                        if (b.e0 == 0)  // first tile of each resident mesh of the class
-                            for (int e = 0; e < P->slots[b.slot].ne; e += c.bops.epb_t[t])
-                                tl.push_back(Tile{b.slot, e});
-                    n = (int)tl.size();
-                    if (n > c.acap) {
-                        hipFree(c.d_atiles);
-                        c.d_atiles = nullptr;
-                        c.acap = std::max(n, 2 * c.acap);
-                        PHIP(hipMalloc((void **)&c.d_atiles, sizeof(Tile) * c.acap));
-                    }
-                    PHIP(hipMemcpyAsync(c.d_atiles, tl.data(), sizeof(Tile) * n, hipMemcpyHostToDevice, P->s));
-                    dl = c.d_atiles;
-                }
+                const TileList &l = c.lists[c.epb_apply(t)];
+                const int n = (int)l.tiles.size();
+                const Tile *dl = l.d;
                 BLaunch f = c.bops.apply_t[st][pr][t];
                 for (int k = 0; k < 2; ++k) f(n, P->s, c.tb, dl, P->d_slots, nullptr, 0, nullptr);
                 PHIP(hipEventRecord(e0, P->s));

@@ -251,7 +251,7 @@ struct tmop_ctx {
     int dim = 0, p = 0, nq = 0, ni = 0, np = 0, nqe = 0, ne = 0, nx = 0, ndof = 0;
     int precision = TMOP_FP64;
     int storage = TMOP_HESS_TENSOR;
-    int grid = 0;
+    int grid = 0, gridE = 0;  // workgroups; of energy and gradient without limiting term and MFMA
     hipStream_t s = nullptr;
     void *H = nullptr;
     size_t H_bytes = 0;
@@ -406,6 +406,7 @@ extern "C" int tmop_create(tmop_ctx **out, const tmop_mesh_desc *m, const tmop_p
     c->storage = prm->hess_storage;
     c->s = (hipStream_t)stream;
     c->grid = (int)((ne + ops.epb - 1) / ops.epb);
+    c->gridE = (int)((ne + ops.epbE - 1) / ops.epbE);
     const int tt = tuned_tile(d, p, nq, c->storage, c->precision);
     if (tt >= 0 && ops.epb_t[tt] > 0) c->tile = tt;
 
@@ -440,7 +441,7 @@ extern "C" int tmop_create(tmop_ctx **out, const tmop_mesh_desc *m, const tmop_p
     const size_t tbytes = c->precision == TMOP_MIXED ? 4 : 8;
     c->H_bytes = (size_t)ne * qdata_stride(S, nqe, (int)tbytes) * tbytes;
     c->eV_bytes = (size_t)ne * d * np * 8;
-    c->part_len = std::max(3 * std::max(c->grid, 1024), 2 * MR_MAX_PARTIALS + 1024) + 64;
+    c->part_len = std::max(3 * std::max(std::max(c->grid, c->gridE), 1024), 2 * MR_MAX_PARTIALS + 1024) + 64;
     hipError_t e = hipSuccess;
 #define ALLOC(ptr, bytes)                                       \
     if (e == hipSuccess) e = hipMalloc((void **)&(ptr), (bytes));
@@ -512,10 +513,16 @@ static bool use_mfma(const tmop_ctx *c)
     return c->sweeps == TMOP_SWEEPS_MFMA && c->g.lim == 0.0;
 }
 
+// Workgroups of the energy and gradient kernels, i.e. their energy partials.
+static int energy_grid(const tmop_ctx *c)
+{
+    return use_mfma(c) || c->g.lim != 0.0 ? c->grid : c->gridE;
+}
+
 static int energy_mindet_impl(tmop_ctx *c, const double *x, double *F, double *mindet)
 {
     (use_mfma(c) ? c->ops.energyM : c->ops.energy)(c->grid, c->s, c->g, c->tb, c->tg, x, c->part);
-    launch_reduce3(c->part, c->grid, c->scal, c->s);
+    launch_reduce3(c->part, energy_grid(c), c->scal, c->s);
     HIPCHK(hipMemcpyAsync(c->hscal, c->scal, 3 * sizeof(double), hipMemcpyDeviceToHost, c->s));
     HIPCHK(hipStreamSynchronize(c->s));
     const double bad = c->hscal[2];
@@ -561,7 +568,7 @@ static int energy_gradient_impl(tmop_ctx *c, const double *x, double *F, double 
 {
     (use_mfma(c) ? c->ops.gradientEM : c->ops.gradientE)(c->grid, c->s, c->g, c->tb, c->tg, x,
                                                          (double *)c->eV, c->part);
-    launch_reduce3(c->part, c->grid, c->scal, c->s);
+    launch_reduce3(c->part, energy_grid(c), c->scal, c->s);
     launch_gather(c->g, c->csr_ptr, c->csr_ent, c->eV, false, g, 0, nullptr, c->s);
     launch_dot(c->ndof, g, g, c->part, c->scal + 8, c->s);
     HIPCHK(hipMemcpyAsync(c->hscal, c->scal, 9 * sizeof(double), hipMemcpyDeviceToHost, c->s));
@@ -599,15 +606,15 @@ static void setup_impl(tmop_ctx *c, const double *x)
     const bool mixed = c->precision == TMOP_MIXED;
     if (c->storage == TMOP_HESS_COMPACT) {
         if (mixed)
-            c->ops.setupc32(c->grid, c->s, c->g, c->tb, c->tg, x, (float *)c->H, c->part);
+            c->ops.setupc32(c->grid, c->s, c->g, c->tb, c->tg, x, (float *)c->H);
         else
             (use_mfma(c) ? c->ops.setupcM64 : c->ops.setupc64)(c->grid, c->s, c->g, c->tb, c->tg,
-                                                               x, (double *)c->H, c->part);
+                                                               x, (double *)c->H);
     } else if (mixed)
-        c->ops.setup32(c->grid, c->s, c->g, c->tb, c->tg, x, (float *)c->H, c->part);
+        c->ops.setup32(c->grid, c->s, c->g, c->tb, c->tg, x, (float *)c->H);
     else
         (use_mfma(c) ? c->ops.setupM64 : c->ops.setup64)(c->grid, c->s, c->g, c->tb, c->tg, x,
-                                                         (double *)c->H, c->part);
+                                                         (double *)c->H);
     c->have_setup = true;
     c->have_diag = false;
 }
@@ -668,11 +675,11 @@ static bool setup_diag_impl(tmop_ctx *c, const double *x)
     if (c->precision == TMOP_MIXED) {
         const auto f = cp ? c->ops.setupcd32 : c->ops.setupd32;
         if (!f) return false;
-        f(c->grid, c->s, c->g, c->tb, c->tg, x, (float *)c->H, (double *)c->eV, c->part);
+        f(c->grid, c->s, c->g, c->tb, c->tg, x, (float *)c->H, (double *)c->eV);
     } else {
         const auto f = cp ? c->ops.setupcd64 : c->ops.setupd64;
         if (!f) return false;
-        f(c->grid, c->s, c->g, c->tb, c->tg, x, (double *)c->H, (double *)c->eV, c->part);
+        f(c->grid, c->s, c->g, c->tb, c->tg, x, (double *)c->H, (double *)c->eV);
     }
     c->have_setup = true;
     c->have_diag = false;
@@ -1370,8 +1377,9 @@ extern "C" int tmop_energy_mindet_noalloc(const tmop_mesh_desc *m, const tmop_pa
     double *part = nullptr;
     CHK(scratch_on_current_device(&part));
     const hipStream_t s = (hipStream_t)stream;
+    // (the energy kernel's workgroups hold at least ops.epb elements)
     ops.energy((int)grid, s, g, tb, tg, x, part);
-    launch_reduce3(part, (int)grid, out, s);
+    launch_reduce3(part, (int)((ne + ops.epbE - 1) / ops.epbE), out, s);
     HIPCHK(hipGetLastError());
     return TMOP_OK;
 }

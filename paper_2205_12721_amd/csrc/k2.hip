@@ -4,6 +4,72 @@
 
 namespace tmop {
 
+// The kernels without the limiting term (quads have one form of each).
+template <int P, int NQ>
+struct plain_k2 {
+    static constexpr int epbE = S2<P, NQ>::EPB;
+    static dim3 grid(const Geom &g) { return dim3((g.ne + epbE - 1) / epbE); }
+    static void energy(hipStream_t s, const Geom &g, const Tables &t, const Target &w,
+                       const double *x, double *part)
+    {
+        hipLaunchKernelGGL((k2_energy<P, NQ, false>), grid(g), dim3(BLOCK), 0, s, g, t, w, x, part);
+    }
+    template <bool EN>
+    static void gradient(hipStream_t s, const Geom &g, const Tables &t, const Target &w,
+                         const double *x, double *gE, double *part)
+    {
+        hipLaunchKernelGGL((k2_gradient<P, NQ, false, EN>), grid(g), dim3(BLOCK), 0, s, g, t, w, x,
+                           gE, part);
+    }
+    template <typename TT>
+    static void setupc(hipStream_t s, const Geom &g, const Tables &t, const Target &w,
+                       const double *x, TT *Q)
+    {
+        hipLaunchKernelGGL((k2_setupc<P, NQ, TT>), grid(g), dim3(BLOCK), 0, s, g, t, w, x, Q);
+    }
+    template <typename TT>
+    static void applyc(hipStream_t s, const Geom &g, const Tables &t, const Target &w, const TT *Q,
+                       const double *v, TT *yE)
+    {
+        hipLaunchKernelGGL((k2_applyc<P, NQ, TT, TT, false>), grid(g), dim3(BLOCK), 0, s, g, t, w,
+                           Q, v, yE);
+    }
+};
+
+template <int P, int NQ>
+struct plain_kb2 {
+    static constexpr int epbE = S2<P, NQ>::EPB;
+    template <typename TT>
+    static constexpr int epbS() { return epbE; }
+    template <typename TT>
+    static constexpr int epbA() { return epbE; }
+    static void energy(int n, hipStream_t s, const Tables &t, const Tile *tl, const SlotDev *sl,
+                       const int *gt, int vin, double *part)
+    {
+        hipLaunchKernelGGL((kb2_energy<P, NQ>), dim3(n), dim3(BLOCK), 0, s, t, tl, sl, gt, vin, part);
+    }
+    template <bool EN>
+    static void gradient(int n, hipStream_t s, const Tables &t, const Tile *tl, const SlotDev *sl,
+                         const int *gt, int vin, double *part)
+    {
+        hipLaunchKernelGGL((kb2_gradient<P, NQ, false, EN>), dim3(n), dim3(BLOCK), 0, s, t, tl, sl,
+                           gt, vin, part);
+    }
+    template <typename TT>
+    static void setupc(int n, hipStream_t s, const Tables &t, const Tile *tl, const SlotDev *sl,
+                       const int *gt, int vin)
+    {
+        hipLaunchKernelGGL((kb2_setupc<P, NQ, TT>), dim3(n), dim3(BLOCK), 0, s, t, tl, sl, gt, vin);
+    }
+    template <typename TT, typename CT>
+    static void applyc(int n, hipStream_t s, const Tables &t, const Tile *tl, const SlotDev *sl,
+                       const int *gt, int vin)
+    {
+        hipLaunchKernelGGL((kb2_applyc<P, NQ, TT, CT>), dim3(n), dim3(BLOCK), 0, s, t, tl, sl, gt,
+                           vin);
+    }
+};
+
 bool ops2(int p, int nq, Ops *out)
 {
 #define TMOP_CASE(P, NQ) \

@@ -310,7 +310,7 @@ __device__ __forceinline__ void b2_energy(const Geom &g, const Tab &tb, const Ta
 template <int P, int NQ, bool LIM = false, bool EN = false>
 __device__ __forceinline__ void b2_gradient(const Geom &g, const Tab &tb, const Target &tg,
                                    const double *__restrict__ x, double *__restrict__ gE,
-                                   double *__restrict__ bad, int e0, int nel)
+                                   double *__restrict__ part, int e0, int nel)
 {
     using S = S2<P, NQ>;
     constexpr int NR = Planes2<LIM>::NR;
@@ -332,7 +332,7 @@ __device__ __forceinline__ void b2_gradient(const Geom &g, const Tab &tb, const 
         const bool ok = metric_first<2>(tg, J, z, &mu, Pm, &detA);
         if (EN) dmin = fmin(dmin, detA);
         if (!ok) {
-            nbad += 1.0;
+            if (EN) nbad += 1.0;
 #pragma unroll
             for (int k = 0; k < 4; ++k) Pm[k] = 0.0;
         } else if (EN) {
@@ -356,37 +356,31 @@ __device__ __forceinline__ void b2_gradient(const Geom &g, const Tab &tb, const 
     if (EN) {
         block_energy3(esum, dmin, nbad, red);
         if (threadIdx.x == 0) {
-            bad[blockIdx.x] = esum;
-            bad[gridDim.x + blockIdx.x] = dmin;
-            bad[2 * gridDim.x + blockIdx.x] = nbad;
+            part[blockIdx.x] = esum;
+            part[gridDim.x + blockIdx.x] = dmin;
+            part[2 * gridDim.x + blockIdx.x] = nbad;
         }
-    } else {
-        const double b = block_sum(nbad, red);
-        if (threadIdx.x == 0) bad[blockIdx.x] = b;
     }
 }
 
 template <int P, int NQ, typename TT>
 __device__ __forceinline__ void b2_setup(const Geom &g, const Tab &tb, const Target &tg,
                                 const double *__restrict__ x, TT *__restrict__ H,
-                                double *__restrict__ bad, int e0, int nel)
+                                int e0, int nel)
 {
     using S = S2<P, NQ>;
     __shared__ Lds2<P, NQ, double> L;
-    __shared__ double red[BLOCK / 64];
     __shared__ double sw[NQ];
     weights_to_lds<NQ>(tb, sw);
     gather2<P, NQ>(g, x, e0, nel, L.X, false);
     __syncthreads();
     forward2<P, NQ, double>(tb, L.X, L.R1, L.RY, nel);
-    double nbad = 0.0;
     for (int idx = threadIdx.x; idx < nel * S::NQ2; idx += BLOCK) {
         const int el = idx / S::NQ2, q = idx % S::NQ2;
         double J[4], Hp[10];
         point_J2<P, NQ>(L.RY, el, q, J);
         const double z = qweight2<NQ>(sw, q) * tg.detW;
         if (!metric_second<2>(tg, J, z, Hp)) {
-            nbad += 1.0;
 #pragma unroll
             for (int k = 0; k < 10; ++k) Hp[k] = 0.0;
         }
@@ -394,8 +388,6 @@ __device__ __forceinline__ void b2_setup(const Geom &g, const Tab &tb, const Tar
 #pragma unroll
         for (int k = 0; k < 10; ++k) h[k * S::NQ2] = (TT)Hp[k];
     }
-    const double b = block_sum(nbad, red);
-    if (threadIdx.x == 0) bad[blockIdx.x] = b;
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM = false>
@@ -473,17 +465,15 @@ __device__ __forceinline__ void mul_winv2(const Target &t, const CT *in, CT *out
 template <int P, int NQ, typename TT>
 __device__ __forceinline__ void b2_setupc(const Geom &g, const Tab &tb, const Target &tg,
                                  const double *__restrict__ x, TT *__restrict__ Q,
-                                 double *__restrict__ bad, int e0, int nel)
+                                 int e0, int nel)
 {
     using S = S2<P, NQ>;
     __shared__ Lds2<P, NQ, double> L;
-    __shared__ double red[BLOCK / 64];
     __shared__ double sw[NQ];
     weights_to_lds<NQ>(tb, sw);
     gather2<P, NQ>(g, x, e0, nel, L.X, false);
     __syncthreads();
     forward2<P, NQ, double>(tb, L.X, L.R1, L.RY, nel);
-    double nbad = 0.0;
     for (int idx = threadIdx.x; idx < nel * S::NQ2; idx += BLOCK) {
         const int el = idx / S::NQ2, q = idx % S::NQ2;
         double J[4], T[4], C[4], out[NC2];
@@ -503,7 +493,6 @@ __device__ __forceinline__ void b2_setupc(const Geom &g, const Tab &tb, const Ta
             out[6] = z * m.c_cc;
             out[7] = z * m.c_dc;
         } else {
-            nbad += 1.0;
 #pragma unroll
             for (int k = 0; k < NC2; ++k) out[k] = 0.0;
         }
@@ -511,8 +500,6 @@ __device__ __forceinline__ void b2_setupc(const Geom &g, const Tab &tb, const Ta
 #pragma unroll
         for (int k = 0; k < NC2; ++k) h[k * S::NQ2] = (TT)out[k];
     }
-    const double b = block_sum(nbad, red);
-    if (threadIdx.x == 0) bad[blockIdx.x] = b;
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM = false>
@@ -723,21 +710,21 @@ __global__ __launch_bounds__(BLOCK) void k2_energy(Geom g, Tables tba, Target tg
 }
 
 template <int P, int NQ, bool LIM, bool EN = false>
-__global__ __launch_bounds__(BLOCK) void k2_gradient(Geom g, Tables tba, Target tg, const double *__restrict__ x, double *__restrict__ gE, double *__restrict__ bad)
+__global__ __launch_bounds__(BLOCK) void k2_gradient(Geom g, Tables tba, Target tg, const double *__restrict__ x, double *__restrict__ gE, double *__restrict__ part)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S2<P, NQ>::EPB;
     const int e0 = blockIdx.x * EPB;
-    b2_gradient<P, NQ, LIM, EN>(g, tb, tg, x, gE, bad, e0, min(EPB, g.ne - e0));
+    b2_gradient<P, NQ, LIM, EN>(g, tb, tg, x, gE, part, e0, min(EPB, g.ne - e0));
 }
 
 template <int P, int NQ, typename TT>
-__global__ __launch_bounds__(BLOCK) void k2_setup(Geom g, Tables tba, Target tg, const double *__restrict__ x, TT *__restrict__ H, double *__restrict__ bad)
+__global__ __launch_bounds__(BLOCK) void k2_setup(Geom g, Tables tba, Target tg, const double *__restrict__ x, TT *__restrict__ H)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S2<P, NQ>::EPB;
     const int e0 = blockIdx.x * EPB;
-    b2_setup<P, NQ, TT>(g, tb, tg, x, H, bad, e0, min(EPB, g.ne - e0));
+    b2_setup<P, NQ, TT>(g, tb, tg, x, H, e0, min(EPB, g.ne - e0));
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM>
@@ -750,12 +737,12 @@ __global__ __launch_bounds__(BLOCK) void k2_apply(Geom g, Tables tba, const TT *
 }
 
 template <int P, int NQ, typename TT>
-__global__ __launch_bounds__(BLOCK) void k2_setupc(Geom g, Tables tba, Target tg, const double *__restrict__ x, TT *__restrict__ Q, double *__restrict__ bad)
+__global__ __launch_bounds__(BLOCK) void k2_setupc(Geom g, Tables tba, Target tg, const double *__restrict__ x, TT *__restrict__ Q)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S2<P, NQ>::EPB;
     const int e0 = blockIdx.x * EPB;
-    b2_setupc<P, NQ, TT>(g, tb, tg, x, Q, bad, e0, min(EPB, g.ne - e0));
+    b2_setupc<P, NQ, TT>(g, tb, tg, x, Q, e0, min(EPB, g.ne - e0));
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM>
@@ -797,25 +784,25 @@ __global__ __launch_bounds__(BLOCK) void kb2_energy(Tables tba, const Tile *__re
 }
 
 template <int P, int NQ, bool LIM = false, bool EN = false>
-__global__ __launch_bounds__(BLOCK) void kb2_gradient(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ bad)
+__global__ __launch_bounds__(BLOCK) void kb2_gradient(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ part)
 {
     const Tab tb = kernel_tables<0>();
     constexpr int EPB = S2<P, NQ>::EPB;
     const Tile t = tiles[blockIdx.x];
     if (gate && !gate[t.slot]) return;
     const SlotDev &s = slots[t.slot];
-    b2_gradient<P, NQ, LIM, EN>(s.g, tb, s.tg, s.vec[vin], (double *)s.eV, bad, t.e0, min(EPB, s.g.ne - t.e0));
+    b2_gradient<P, NQ, LIM, EN>(s.g, tb, s.tg, s.vec[vin], (double *)s.eV, part, t.e0, min(EPB, s.g.ne - t.e0));
 }
 
 template <int P, int NQ, typename TT>
-__global__ __launch_bounds__(BLOCK) void kb2_setup(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ bad)
+__global__ __launch_bounds__(BLOCK) void kb2_setup(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
 {
     const Tab tb = kernel_tables<0>();
     constexpr int EPB = S2<P, NQ>::EPB;
     const Tile t = tiles[blockIdx.x];
     if (gate && !gate[t.slot]) return;
     const SlotDev &s = slots[t.slot];
-    b2_setup<P, NQ, TT>(s.g, tb, s.tg, s.vec[vin], (TT *)s.H, bad, t.e0, min(EPB, s.g.ne - t.e0));
+    b2_setup<P, NQ, TT>(s.g, tb, s.tg, s.vec[vin], (TT *)s.H, t.e0, min(EPB, s.g.ne - t.e0));
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM = false>
@@ -830,14 +817,14 @@ __global__ __launch_bounds__(BLOCK) void kb2_apply(Tables tba, const Tile *__res
 }
 
 template <int P, int NQ, typename TT>
-__global__ __launch_bounds__(BLOCK) void kb2_setupc(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ bad)
+__global__ __launch_bounds__(BLOCK) void kb2_setupc(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
 {
     const Tab tb = kernel_tables<0>();
     constexpr int EPB = S2<P, NQ>::EPB;
     const Tile t = tiles[blockIdx.x];
     if (gate && !gate[t.slot]) return;
     const SlotDev &s = slots[t.slot];
-    b2_setupc<P, NQ, TT>(s.g, tb, s.tg, s.vec[vin], (TT *)s.H, bad, t.e0, min(EPB, s.g.ne - t.e0));
+    b2_setupc<P, NQ, TT>(s.g, tb, s.tg, s.vec[vin], (TT *)s.H, t.e0, min(EPB, s.g.ne - t.e0));
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM = false>

@@ -671,17 +671,17 @@ __device__ __forceinline__ void b3_energy(const Geom &g, const Tab &tb, const Ta
 }
 
 // Gradient E-vector (Sec. 3.3, eq. eq_vm_pa_grad): per point z P, then the
-// transposed contractions.  bad[blockIdx] counts points with det T <= 0.
+// transposed contractions (P = 0 at points with det T <= 0).
 // LIM adds 2 w_q lim (x - x0)_c(q) wbar_i(q) through the value planes.
 // EN: also the energy partials of b3_energy (the point stage evaluates mu
 // anyway): the sums, the min det and the count of points with det T <= 0 go
-// to the planes bad[blockIdx], bad[grid + blockIdx], bad[2 grid + blockIdx]
+// to the planes part[blockIdx], part[grid + blockIdx], part[2 grid + blockIdx]
 // (the same terms in the same order as b3_energy: bitwise its partials, and
 // the gradient bitwise that of EN = false).
 template <int P, int NQ, bool LIM = false, bool EN = false, bool MF = false>
 __device__ __forceinline__ void b3_gradient(const Geom &g, const Tab &tb, const Target &tg,
                                    const double *__restrict__ x, double *__restrict__ gE,
-                                   double *__restrict__ bad, int e0, int nel)
+                                   double *__restrict__ part, int e0, int nel)
 {
     using S = S3<P, NQ>;
     constexpr int NR = Planes3<LIM>::NR;
@@ -711,7 +711,7 @@ __device__ __forceinline__ void b3_gradient(const Geom &g, const Tab &tb, const 
         const bool ok = metric_first<3>(tg, J, z, &mu, Pm, &detA);
         if (EN) dmin = fmin(dmin, detA);
         if (!ok) {
-            nbad += 1.0;
+            if (EN) nbad += 1.0;
 #pragma unroll
             for (int k = 0; k < 9; ++k) Pm[k] = 0.0;
         } else if (EN) {
@@ -740,13 +740,10 @@ __device__ __forceinline__ void b3_gradient(const Geom &g, const Tab &tb, const 
     if (EN) {
         block_energy3(esum, dmin, nbad, red);
         if (threadIdx.x == 0) {
-            bad[blockIdx.x] = esum;
-            bad[gridDim.x + blockIdx.x] = dmin;
-            bad[2 * gridDim.x + blockIdx.x] = nbad;
+            part[blockIdx.x] = esum;
+            part[gridDim.x + blockIdx.x] = dmin;
+            part[2 * gridDim.x + blockIdx.x] = nbad;
         }
-    } else {
-        const double b = block_sum(nbad, red);
-        if (threadIdx.x == 0) bad[blockIdx.x] = b;
     }
 }
 
@@ -754,12 +751,10 @@ __device__ __forceinline__ void b3_gradient(const Geom &g, const Tab &tb, const 
 // element-major in the 16-byte-run layout of qdata_store.
 template <int P, int NQ, typename TT, bool MF = false>
 __device__ __forceinline__ void b3_setup(const Geom &g, const Tab &tb, const Target &tg,
-                                const double *__restrict__ x, TT *__restrict__ H,
-                                double *__restrict__ bad, int e0, int nel)
+                                const double *__restrict__ x, TT *__restrict__ H, int e0, int nel)
 {
     using S = S3<P, NQ>;
     __shared__ Lds3<P, NQ, double> L;
-    __shared__ double red[BLOCK / 64];
     __shared__ double mft[MF ? 2 * NQ * S::NI : 1];
     __shared__ double sw[NQ];
     weights_to_lds<NQ>(tb, sw);
@@ -770,14 +765,12 @@ __device__ __forceinline__ void b3_setup(const Geom &g, const Tab &tb, const Tar
         forward3_mfma<P, NQ>(mft, L.X, L.R1, L.R2, L.RY, nel);
     else
         forward3<P, NQ>(tb, L.X, L.R1, L.R2, L.RY, nel);
-    double nbad = 0.0;
     for (int idx = threadIdx.x; idx < nel * S::NQ3; idx += BLOCK) {
         const int el = idx / S::NQ3, q = idx % S::NQ3;
         double J[9], Hp[45];
         point_J3<P, NQ>(L.RY, el, q, J);
         const double z = point_weight3<NQ>(sw, tg, q);
         if (!metric_second<3>(tg, J, z, Hp)) {
-            nbad += 1.0;
 #pragma unroll
             for (int k = 0; k < 45; ++k) Hp[k] = 0.0;
         }
@@ -787,8 +780,6 @@ __device__ __forceinline__ void b3_setup(const Geom &g, const Tab &tb, const Tar
         for (int k = 0; k < 45; ++k) hs[k] = (TT)Hp[k];
         qdata_store<TT, 45, S::NQ3>(H + (size_t)(e0 + el) * QL::STRIDE, q, hs);
     }
-    const double b = block_sum(nbad, red);
-    if (threadIdx.x == 0) bad[blockIdx.x] = b;
 }
 
 // Point stage of the action at point q of element el: Y = H : (grad v) from
@@ -920,6 +911,7 @@ constexpr int NC3 = 13;
 template <typename CT>
 __device__ __forceinline__ void cof3(const CT *T, CT *C)
 {
+#pragma clang fp contract(on)
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
@@ -932,6 +924,7 @@ __device__ __forceinline__ void cof3(const CT *T, CT *C)
 template <typename CT>
 __device__ __forceinline__ void compact_action3(const CT *T, CT ca, CT cb, CT cc, CT cd, const CT *M, CT *Y)
 {
+#pragma clang fp contract(on)
     CT C[9];
     cof3(T, C);
     CT tm = 0, cm = 0;
@@ -945,10 +938,11 @@ __device__ __forceinline__ void compact_action3(const CT *T, CT ca, CT cb, CT cc
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
             const int i1 = (i + 1) % 3, i2 = (i + 2) % 3, j1 = (j + 1) % 3, j2 = (j + 2) % 3;
-            const CT dC = T[i1 * 3 + j1] * M[i2 * 3 + j2] + M[i1 * 3 + j1] * T[i2 * 3 + j2] -
-                          T[i1 * 3 + j2] * M[i2 * 3 + j1] - M[i1 * 3 + j2] * T[i2 * 3 + j1];
+            const int lo = min(i1 * 3 + j1, i2 * 3 + j2), hi = max(i1 * 3 + j1, i2 * 3 + j2);
+            const CT dC = T[hi] * M[lo] + T[lo] * M[hi] - T[i1 * 3 + j2] * M[i2 * 3 + j1] -
+                          M[i1 * 3 + j2] * T[i2 * 3 + j1];
             const int r = i * 3 + j;
-            Y[r] = ca * M[r] + cb * (T[r] * cm + C[r] * tm) + cc * C[r] * cm + cd * dC;
+            Y[r] = ca * M[r] + cb * (C[r] * tm + T[r] * cm) + cc * C[r] * cm + cd * dC;
         }
 }
 
@@ -1161,12 +1155,10 @@ __device__ __forceinline__ bool compact_point3(const Target &tg, const double *J
 
 template <int P, int NQ, typename TT, bool MF = false>
 __device__ __forceinline__ void b3_setupc(const Geom &g, const Tab &tb, const Target &tg,
-                                 const double *__restrict__ x, TT *__restrict__ Q,
-                                 double *__restrict__ bad, int e0, int nel)
+                                 const double *__restrict__ x, TT *__restrict__ Q, int e0, int nel)
 {
     using S = S3<P, NQ>;
     __shared__ Lds3<P, NQ, double> L;
-    __shared__ double red[BLOCK / 64];
     __shared__ double mft[MF ? 2 * NQ * S::NI : 1];
     __shared__ double sw[NQ];
     weights_to_lds<NQ>(tb, sw);
@@ -1177,17 +1169,14 @@ __device__ __forceinline__ void b3_setupc(const Geom &g, const Tab &tb, const Ta
         forward3_mfma<P, NQ>(mft, L.X, L.R1, L.R2, L.RY, nel);
     else
         forward3<P, NQ>(tb, L.X, L.R1, L.R2, L.RY, nel);
-    double nbad = 0.0;
     for (int idx = threadIdx.x; idx < nel * S::NQ3; idx += BLOCK) {
         const int el = idx / S::NQ3, q = idx % S::NQ3;
         double J[9];
         point_J3<P, NQ>(L.RY, el, q, J);
         TT hs[NC3];
-        if (!compact_point3<TT>(tg, J, point_weight3<NQ>(sw, tg, q), hs)) nbad += 1.0;
+        compact_point3<TT>(tg, J, point_weight3<NQ>(sw, tg, q), hs);
         qdata_store<TT, NC3, S::NQ3>(Q + (size_t)(e0 + el) * QLay<TT, NC3, S::NQ3>::STRIDE, q, hs);
     }
-    const double b = block_sum(nbad, red);
-    if (threadIdx.x == 0) bad[blockIdx.x] = b;
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM = false, int T2 = 2>
@@ -1517,13 +1506,11 @@ __device__ __forceinline__ void b3_diagc(const Geom &g, const Tab &tb, const Tar
 // read back from HBM by b3_diag.  The diagonal's buffers overlay the sweeps'
 // (every lane holds its J before the barrier that hands the memory over), so
 // the workgroup needs no more LDS than b3_diag.  Classes whose points fit one
-// pass of the workgroup.  H, bad and dE are bitwise those of b3_setup then
-// b3_diag.
+// pass of the workgroup.  H and dE are bitwise those of b3_setup then b3_diag.
 template <int P, int NQ, typename TT, bool LIM>
 __device__ __forceinline__ void b3_setupd(const Geom &g, const Tab &tb, const Target &tg,
                                  const double *__restrict__ x, TT *__restrict__ H,
-                                 double *__restrict__ dE, double *__restrict__ bad, int e0,
-                                 int nel)
+                                 double *__restrict__ dE, int e0, int nel)
 {
     using S = S3<P, NQ>;
     static_assert(S::EPB * S::NQ3 <= BLOCK, "one pass over the workgroup's points");
@@ -1533,7 +1520,6 @@ __device__ __forceinline__ void b3_setupd(const Geom &g, const Tab &tb, const Ta
         DiagLds3<P, NQ, LIM> d;
     };
     __shared__ Buf L;
-    __shared__ double red[BLOCK / 64];
     __shared__ double sw[NQ];
     weights_to_lds<NQ>(tb, sw);
     gather3<P, NQ>(g, x, e0, nel, L.s.X, false);
@@ -1544,12 +1530,10 @@ __device__ __forceinline__ void b3_setupd(const Geom &g, const Tab &tb, const Ta
     double J[9];
     if (act) point_J3<P, NQ>(L.s.RY, el, q, J);
     __syncthreads();
-    double nbad = 0.0;
     if (act) {
         double Hp[45];
         const double z = point_weight3<NQ>(sw, tg, q);
         if (!metric_second<3>(tg, J, z, Hp)) {
-            nbad = 1.0;
 #pragma unroll
             for (int k = 0; k < 45; ++k) Hp[k] = 0.0;
         }
@@ -1570,18 +1554,15 @@ __device__ __forceinline__ void b3_setupd(const Geom &g, const Tab &tb, const Ta
         diag_lim3<P, NQ, LIM>(sw, g, L.d, el, q);
     }
     diag_contract3<P, NQ, LIM>(tb, g, e0, L.d, nel, dE);
-    const double b = block_sum(nbad, red);
-    if (threadIdx.x == 0) bad[blockIdx.x] = b;
 }
 
 // The same for compact storage: the setup's compact values, rounded to TT as
 // stored, give the diagonal's planes as b3_diagc computes them from the
-// stored data.  Q, bad and dE are bitwise those of b3_setupc then b3_diagc.
+// stored data.  Q and dE are bitwise those of b3_setupc then b3_diagc.
 template <int P, int NQ, typename TT, bool LIM>
 __device__ __forceinline__ void b3_setupcd(const Geom &g, const Tab &tb, const Target &tg,
                                   const double *__restrict__ x, TT *__restrict__ Q,
-                                  double *__restrict__ dE, double *__restrict__ bad, int e0,
-                                  int nel)
+                                  double *__restrict__ dE, int e0, int nel)
 {
     using S = S3<P, NQ>;
     static_assert(S::EPB * S::NQ3 <= BLOCK, "one pass over the workgroup's points");
@@ -1590,7 +1571,6 @@ __device__ __forceinline__ void b3_setupcd(const Geom &g, const Tab &tb, const T
         DiagLds3<P, NQ, LIM> d;
     };
     __shared__ Buf L;
-    __shared__ double red[BLOCK / 64];
     __shared__ double sw[NQ];
     weights_to_lds<NQ>(tb, sw);
     gather3<P, NQ>(g, x, e0, nel, L.s.X, false);
@@ -1601,16 +1581,13 @@ __device__ __forceinline__ void b3_setupcd(const Geom &g, const Tab &tb, const T
     double J[9];
     if (act) point_J3<P, NQ>(L.s.RY, el, q, J);
     __syncthreads();
-    double nbad = 0.0;
     if (act) {
         TT hs[NC3];
-        if (!compact_point3<TT>(tg, J, point_weight3<NQ>(sw, tg, q), hs)) nbad = 1.0;
+        compact_point3<TT>(tg, J, point_weight3<NQ>(sw, tg, q), hs);
         qdata_store<TT, NC3, S::NQ3>(Q + (size_t)(e0 + el) * QLay<TT, NC3, S::NQ3>::STRIDE, q, hs);
         diagc_point3<P, NQ, TT, LIM>(sw, g, tg, hs, L.d, el, q);
     }
     diag_contract3<P, NQ, LIM>(tb, g, e0, L.d, nel, dE);
-    const double b = block_sum(nbad, red);
-    if (threadIdx.x == 0) bad[blockIdx.x] = b;
 }
 
 // ------------------------------------------------------------------------
@@ -1630,21 +1607,21 @@ __global__ __launch_bounds__(BLOCK) void k3_energy(Geom g, Tables tba, Target tg
 }
 
 template <int P, int NQ, bool LIM, bool EN = false, bool MF = false>
-__global__ __launch_bounds__(BLOCK) void k3_gradient(Geom g, Tables tba, Target tg, const double *__restrict__ x, double *__restrict__ gE, double *__restrict__ bad)
+__global__ __launch_bounds__(BLOCK) void k3_gradient(Geom g, Tables tba, Target tg, const double *__restrict__ x, double *__restrict__ gE, double *__restrict__ part)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S3<P, NQ>::EPB;
     const int e0 = xcd_block(blockIdx.x, gridDim.x) * EPB;
-    b3_gradient<P, NQ, LIM, EN, MF>(g, tb, tg, x, gE, bad, e0, min(EPB, g.ne - e0));
+    b3_gradient<P, NQ, LIM, EN, MF>(g, tb, tg, x, gE, part, e0, min(EPB, g.ne - e0));
 }
 
 template <int P, int NQ, typename TT, bool MF = false>
-__global__ __launch_bounds__(BLOCK) void k3_setup(Geom g, Tables tba, Target tg, const double *__restrict__ x, TT *__restrict__ H, double *__restrict__ bad)
+__global__ __launch_bounds__(BLOCK) void k3_setup(Geom g, Tables tba, Target tg, const double *__restrict__ x, TT *__restrict__ H)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S3<P, NQ>::EPB;
     const int e0 = xcd_block(blockIdx.x, gridDim.x) * EPB;
-    b3_setup<P, NQ, TT, MF>(g, tb, tg, x, H, bad, e0, min(EPB, g.ne - e0));
+    b3_setup<P, NQ, TT, MF>(g, tb, tg, x, H, e0, min(EPB, g.ne - e0));
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM, int T2 = 2>
@@ -1657,12 +1634,12 @@ __global__ __launch_bounds__(BLOCK) void k3_apply(Geom g, Tables tba, const TT *
 }
 
 template <int P, int NQ, typename TT, bool MF = false>
-__global__ __launch_bounds__(BLOCK) void k3_setupc(Geom g, Tables tba, Target tg, const double *__restrict__ x, TT *__restrict__ Q, double *__restrict__ bad)
+__global__ __launch_bounds__(BLOCK) void k3_setupc(Geom g, Tables tba, Target tg, const double *__restrict__ x, TT *__restrict__ Q)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S3<P, NQ>::EPB;
     const int e0 = xcd_block(blockIdx.x, gridDim.x) * EPB;
-    b3_setupc<P, NQ, TT, MF>(g, tb, tg, x, Q, bad, e0, min(EPB, g.ne - e0));
+    b3_setupc<P, NQ, TT, MF>(g, tb, tg, x, Q, e0, min(EPB, g.ne - e0));
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM, int T2 = 2>
@@ -1684,21 +1661,21 @@ __global__ __launch_bounds__(BLOCK) void k3_diag(Geom g, Tables tba, const TT *_
 }
 
 template <int P, int NQ, typename TT, bool LIM>
-__global__ __launch_bounds__(BLOCK) void k3_setupd(Geom g, Tables tba, Target tg, const double *__restrict__ x, TT *__restrict__ H, double *__restrict__ dE, double *__restrict__ bad)
+__global__ __launch_bounds__(BLOCK) void k3_setupd(Geom g, Tables tba, Target tg, const double *__restrict__ x, TT *__restrict__ H, double *__restrict__ dE)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S3<P, NQ>::EPB;
     const int e0 = xcd_block(blockIdx.x, gridDim.x) * EPB;
-    b3_setupd<P, NQ, TT, LIM>(g, tb, tg, x, H, dE, bad, e0, min(EPB, g.ne - e0));
+    b3_setupd<P, NQ, TT, LIM>(g, tb, tg, x, H, dE, e0, min(EPB, g.ne - e0));
 }
 
 template <int P, int NQ, typename TT, bool LIM>
-__global__ __launch_bounds__(BLOCK) void k3_setupcd(Geom g, Tables tba, Target tg, const double *__restrict__ x, TT *__restrict__ Q, double *__restrict__ dE, double *__restrict__ bad)
+__global__ __launch_bounds__(BLOCK) void k3_setupcd(Geom g, Tables tba, Target tg, const double *__restrict__ x, TT *__restrict__ Q, double *__restrict__ dE)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S3<P, NQ>::EPB;
     const int e0 = xcd_block(blockIdx.x, gridDim.x) * EPB;
-    b3_setupcd<P, NQ, TT, LIM>(g, tb, tg, x, Q, dE, bad, e0, min(EPB, g.ne - e0));
+    b3_setupcd<P, NQ, TT, LIM>(g, tb, tg, x, Q, dE, e0, min(EPB, g.ne - e0));
 }
 
 template <int P, int NQ, typename TT, bool LIM>
@@ -1722,25 +1699,25 @@ __global__ __launch_bounds__(BLOCK) void kb3_energy(Tables tba, const Tile *__re
 }
 
 template <int P, int NQ, bool LIM = false, bool EN = false>
-__global__ __launch_bounds__(BLOCK) void kb3_gradient(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ bad)
+__global__ __launch_bounds__(BLOCK) void kb3_gradient(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ part)
 {
     const Tab tb = kernel_tables<0>();
     constexpr int EPB = S3<P, NQ>::EPB;
     const Tile t = tiles[blockIdx.x];
     if (gate && !gate[t.slot]) return;
     const SlotDev &s = slots[t.slot];
-    b3_gradient<P, NQ, LIM, EN>(s.g, tb, s.tg, s.vec[vin], (double *)s.eV, bad, t.e0, min(EPB, s.g.ne - t.e0));
+    b3_gradient<P, NQ, LIM, EN>(s.g, tb, s.tg, s.vec[vin], (double *)s.eV, part, t.e0, min(EPB, s.g.ne - t.e0));
 }
 
 template <int P, int NQ, typename TT>
-__global__ __launch_bounds__(BLOCK) void kb3_setup(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ bad)
+__global__ __launch_bounds__(BLOCK) void kb3_setup(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
 {
     const Tab tb = kernel_tables<0>();
     constexpr int EPB = S3<P, NQ>::EPB;
     const Tile t = tiles[blockIdx.x];
     if (gate && !gate[t.slot]) return;
     const SlotDev &s = slots[t.slot];
-    b3_setup<P, NQ, TT>(s.g, tb, s.tg, s.vec[vin], (TT *)s.H, bad, t.e0, min(EPB, s.g.ne - t.e0));
+    b3_setup<P, NQ, TT>(s.g, tb, s.tg, s.vec[vin], (TT *)s.H, t.e0, min(EPB, s.g.ne - t.e0));
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM = false, int T2 = 2>
@@ -1755,14 +1732,14 @@ __global__ __launch_bounds__(BLOCK) void kb3_apply(Tables tba, const Tile *__res
 }
 
 template <int P, int NQ, typename TT>
-__global__ __launch_bounds__(BLOCK) void kb3_setupc(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ bad)
+__global__ __launch_bounds__(BLOCK) void kb3_setupc(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
 {
     const Tab tb = kernel_tables<0>();
     constexpr int EPB = S3<P, NQ>::EPB;
     const Tile t = tiles[blockIdx.x];
     if (gate && !gate[t.slot]) return;
     const SlotDev &s = slots[t.slot];
-    b3_setupc<P, NQ, TT>(s.g, tb, s.tg, s.vec[vin], (TT *)s.H, bad, t.e0, min(EPB, s.g.ne - t.e0));
+    b3_setupc<P, NQ, TT>(s.g, tb, s.tg, s.vec[vin], (TT *)s.H, t.e0, min(EPB, s.g.ne - t.e0));
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM = false, int T2 = 2>

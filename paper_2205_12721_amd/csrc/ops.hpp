@@ -11,17 +11,22 @@ namespace tmop {
 
 struct Ops {
     int epb;  // elements per workgroup
+    // elements per workgroup (so energy partials) of energy and gradientE
+    // without the limiting term and the matrix-core sweeps; these two, the
+    // compact setup and the compact action of the base shape work out their
+    // own grids (column form) and take no grid from the caller then
+    int epbE;
     void (*energy)(int grid, hipStream_t, const Geom &, const Tables &, const Target &,
                    const double *x, double *part);
     void (*gradient)(int grid, hipStream_t, const Geom &, const Tables &, const Target &,
-                     const double *x, double *gE, double *bad);
+                     const double *x, double *gE, double *part);
     // gradient E-vector plus the energy partials (three planes of grid
     // entries in part, as energy writes them)
     decltype(gradient) gradientE;
     void (*setup64)(int grid, hipStream_t, const Geom &, const Tables &, const Target &,
-                    const double *x, double *H, double *bad);
+                    const double *x, double *H);
     void (*setup32)(int grid, hipStream_t, const Geom &, const Tables &, const Target &,
-                    const double *x, float *H, double *bad);
+                    const double *x, float *H);
     void (*apply64)(int grid, hipStream_t, const Geom &, const Tables &, const double *H,
                     const double *v, double *yE);
     void (*apply32)(int grid, hipStream_t, const Geom &, const Tables &, const float *H,
@@ -32,9 +37,9 @@ struct Ops {
                    double *dE);
     // compact quadrature data (T and four weighted metric coefficients)
     void (*setupc64)(int grid, hipStream_t, const Geom &, const Tables &, const Target &,
-                     const double *x, double *Q, double *bad);
+                     const double *x, double *Q);
     void (*setupc32)(int grid, hipStream_t, const Geom &, const Tables &, const Target &,
-                     const double *x, float *Q, double *bad);
+                     const double *x, float *Q);
     void (*applyc64)(int grid, hipStream_t, const Geom &, const Tables &, const Target &,
                      const double *Q, const double *v, double *yE);
     void (*applyc32)(int grid, hipStream_t, const Geom &, const Tables &, const Target &,
@@ -62,9 +67,9 @@ struct Ops {
     // one pass; null where the class has no such kernel (quads, more than one
     // pass of points per workgroup)
     void (*setupd64)(int grid, hipStream_t, const Geom &, const Tables &, const Target &,
-                     const double *x, double *H, double *dE, double *bad);
+                     const double *x, double *H, double *dE);
     void (*setupd32)(int grid, hipStream_t, const Geom &, const Tables &, const Target &,
-                     const double *x, float *H, double *dE, double *bad);
+                     const double *x, float *H, double *dE);
     decltype(setupd64) setupcd64;  // the same for compact storage
     decltype(setupd32) setupcd32;
 };
@@ -77,6 +82,9 @@ typedef void (*BLaunch)(int grid, hipStream_t, const Tables &, const Tile *, con
 
 struct BOps {
     int epb;
+    // elements per tile of the kernels that may run in column form (without
+    // the limiting term): energy and gradient, setup, base-shape action
+    int epbE, epbS[2][2], epbA[2][2];
     BLaunch energy, gradient;
     // gradient plus the energy partials of energy (same three planes)
     BLaunch gradientE, gradientEL;
@@ -149,20 +157,18 @@ bool bops3_p4(int nq, BOps *out);
     {                                                                                          \
         BOps o;                                                                                \
         o.epb = SZ<P, NQ>::EPB;                                                                \
+        o.epbE = plain_##K<P, NQ>::epbE;                                                       \
         o.energy = [](int grid, hipStream_t s, const Tables &t, const Tile *tl, const SlotDev *sl, \
                       const int *gt, int vin, double *part) {                                  \
-            hipLaunchKernelGGL((K##_energy<P, NQ>), dim3(grid), dim3(BLOCK), 0, s, t, tl, sl, gt, \
-                               vin, part);                                                     \
+            plain_##K<P, NQ>::energy(grid, s, t, tl, sl, gt, vin, part);                       \
         };                                                                                     \
         o.gradient = [](int grid, hipStream_t s, const Tables &t, const Tile *tl,               \
                         const SlotDev *sl, const int *gt, int vin, double *part) {             \
-            hipLaunchKernelGGL((K##_gradient<P, NQ>), dim3(grid), dim3(BLOCK), 0, s, t, tl, sl, \
-                               gt, vin, part);                                                 \
+            plain_##K<P, NQ>::template gradient<false>(grid, s, t, tl, sl, gt, vin, part);     \
         };                                                                                     \
         o.gradientE = [](int grid, hipStream_t s, const Tables &t, const Tile *tl,              \
                          const SlotDev *sl, const int *gt, int vin, double *part) {            \
-            hipLaunchKernelGGL((K##_gradient<P, NQ, false, true>), dim3(grid), dim3(BLOCK), 0, s, t, tl, \
-                               sl, gt, vin, part);                                             \
+            plain_##K<P, NQ>::template gradient<true>(grid, s, t, tl, sl, gt, vin, part);      \
         };                                                                                     \
         o.gradientEL = [](int grid, hipStream_t s, const Tables &t, const Tile *tl,             \
                           const SlotDev *sl, const int *gt, int vin, double *part) {           \
@@ -187,15 +193,18 @@ bool bops3_p4(int nq, BOps *out);
     }
 
 #define TMOP_BOPS_PREC(K, P, NQ, IDX, TT, CT)                                                  \
+    o.epbS[0][IDX] = o.epb;                                                                    \
+    o.epbS[1][IDX] = plain_##K<P, NQ>::template epbS<TT>();                                    \
+    o.epbA[0][IDX] = o.epb;                                                                    \
+    o.epbA[1][IDX] = plain_##K<P, NQ>::template epbA<TT>();                                    \
     o.setup[0][IDX] = [](int grid, hipStream_t s, const Tables &t, const Tile *tl,             \
-                         const SlotDev *sl, const int *gt, int vin, double *part) {            \
+                         const SlotDev *sl, const int *gt, int vin, double *) {                \
         hipLaunchKernelGGL((K##_setup<P, NQ, TT>), dim3(grid), dim3(BLOCK), 0, s, t, tl, sl, gt, \
-                           vin, part);                                                         \
+                           vin);                                                               \
     };                                                                                         \
     o.setup[1][IDX] = [](int grid, hipStream_t s, const Tables &t, const Tile *tl,             \
-                         const SlotDev *sl, const int *gt, int vin, double *part) {            \
-        hipLaunchKernelGGL((K##_setupc<P, NQ, TT>), dim3(grid), dim3(BLOCK), 0, s, t, tl, sl,   \
-                           gt, vin, part);                                                     \
+                         const SlotDev *sl, const int *gt, int vin, double *) {                \
+        plain_##K<P, NQ>::template setupc<TT>(grid, s, t, tl, sl, gt, vin);                    \
     };                                                                                         \
     o.apply[0][IDX] = [](int grid, hipStream_t s, const Tables &t, const Tile *tl,             \
                          const SlotDev *sl, const int *gt, int vin, double *) {                \
@@ -204,8 +213,7 @@ bool bops3_p4(int nq, BOps *out);
     };                                                                                         \
     o.apply[1][IDX] = [](int grid, hipStream_t s, const Tables &t, const Tile *tl,             \
                          const SlotDev *sl, const int *gt, int vin, double *) {                \
-        hipLaunchKernelGGL((K##_applyc<P, NQ, TT, CT>), dim3(grid), dim3(BLOCK), 0, s, t, tl,   \
-                           sl, gt, vin);                                                       \
+        plain_##K<P, NQ>::template applyc<TT, CT>(grid, s, t, tl, sl, gt, vin);                \
     };                                                                                         \
     o.diag[0][IDX] = [](int grid, hipStream_t s, const Tables &t, const Tile *tl,              \
                         const SlotDev *sl, const int *gt, int, double *) {                     \
@@ -245,20 +253,21 @@ bool ops3_p4(int nq, Ops *out);
     {                                                                                            \
         Ops o;                                                                                   \
         o.epb = SZ<P, NQ>::EPB;                                                                  \
+        o.epbE = plain_##K<P, NQ>::epbE;                                                         \
         o.energy = [](int grid, hipStream_t s, const Geom &g, const Tables &t, const Target &w, \
                       const double *x, double *part) {                                          \
             if (g.lim != 0.0) {                                                                   \
                 hipLaunchKernelGGL((K##_energy<P, NQ, true>), dim3(grid), dim3(BLOCK), 0, s, g, t, w, x, part); \
             } else {                                                                         \
-                hipLaunchKernelGGL((K##_energy<P, NQ, false>), dim3(grid), dim3(BLOCK), 0, s, g, t, w, x, part); \
+                plain_##K<P, NQ>::energy(s, g, t, w, x, part);                               \
             }                                                                      \
         };                                                                                       \
         o.gradient = [](int grid, hipStream_t s, const Geom &g, const Tables &t,                \
-                        const Target &w, const double *x, double *gE, double *bad) {            \
+                        const Target &w, const double *x, double *gE, double *part) {           \
             if (g.lim != 0.0) {                                                                   \
-                hipLaunchKernelGGL((K##_gradient<P, NQ, true>), dim3(grid), dim3(BLOCK), 0, s, g, t, w, x, gE, bad); \
+                hipLaunchKernelGGL((K##_gradient<P, NQ, true>), dim3(grid), dim3(BLOCK), 0, s, g, t, w, x, gE, part); \
             } else {                                                                         \
-                hipLaunchKernelGGL((K##_gradient<P, NQ, false>), dim3(grid), dim3(BLOCK), 0, s, g, t, w, x, gE, bad); \
+                plain_##K<P, NQ>::template gradient<false>(s, g, t, w, x, gE, part); \
             }                                                                      \
         };                                                                                       \
         o.gradientE = [](int grid, hipStream_t s, const Geom &g, const Tables &t,               \
@@ -266,18 +275,18 @@ bool ops3_p4(int nq, Ops *out);
             if (g.lim != 0.0) {                                                                   \
                 hipLaunchKernelGGL((K##_gradient<P, NQ, true, true>), dim3(grid), dim3(BLOCK), 0, s, g, t, w, x, gE, part); \
             } else {                                                                         \
-                hipLaunchKernelGGL((K##_gradient<P, NQ, false, true>), dim3(grid), dim3(BLOCK), 0, s, g, t, w, x, gE, part); \
+                plain_##K<P, NQ>::template gradient<true>(s, g, t, w, x, gE, part); \
             }                                                                      \
         };                                                                                       \
         o.setup64 = [](int grid, hipStream_t s, const Geom &g, const Tables &t, const Target &w, \
-                       const double *x, double *H, double *bad) {                                \
+                       const double *x, double *H) {                                             \
             hipLaunchKernelGGL((K##_setup<P, NQ, double>), dim3(grid), dim3(BLOCK), 0, s, g, t, \
-                               w, x, H, bad);                                                   \
+                               w, x, H);                                                        \
         };                                                                                       \
         o.setup32 = [](int grid, hipStream_t s, const Geom &g, const Tables &t, const Target &w, \
-                       const double *x, float *H, double *bad) {                                 \
+                       const double *x, float *H) {                                              \
             hipLaunchKernelGGL((K##_setup<P, NQ, float>), dim3(grid), dim3(BLOCK), 0, s, g, t,  \
-                               w, x, H, bad);                                                   \
+                               w, x, H);                                                        \
         };                                                                                       \
         o.apply64 = [](int grid, hipStream_t s, const Geom &g, const Tables &t, const double *H, \
                        const double *v, double *yE) {                                            \
@@ -311,22 +320,20 @@ bool ops3_p4(int nq, Ops *out);
                 hipLaunchKernelGGL((K##_diag<P, NQ, float, false>), dim3(grid), dim3(BLOCK), 0, s, g, t, H, dE); \
             }                                                                      \
         };                                                                                       \
-        o.setupc64 = [](int grid, hipStream_t s, const Geom &g, const Tables &t,                \
-                        const Target &w, const double *x, double *Q, double *bad) {             \
-            hipLaunchKernelGGL((K##_setupc<P, NQ, double>), dim3(grid), dim3(BLOCK), 0, s, g, t,\
-                               w, x, Q, bad);                                                   \
+        o.setupc64 = [](int, hipStream_t s, const Geom &g, const Tables &t, const Target &w,     \
+                        const double *x, double *Q) {                                               \
+            plain_##K<P, NQ>::setupc(s, g, t, w, x, Q);                                          \
         };                                                                                       \
-        o.setupc32 = [](int grid, hipStream_t s, const Geom &g, const Tables &t,                \
-                        const Target &w, const double *x, float *Q, double *bad) {              \
-            hipLaunchKernelGGL((K##_setupc<P, NQ, float>), dim3(grid), dim3(BLOCK), 0, s, g, t, \
-                               w, x, Q, bad);                                                   \
+        o.setupc32 = [](int, hipStream_t s, const Geom &g, const Tables &t, const Target &w,     \
+                        const double *x, float *Q) {                                               \
+            plain_##K<P, NQ>::setupc(s, g, t, w, x, Q);                                          \
         };                                                                                       \
         o.applyc64 = [](int grid, hipStream_t s, const Geom &g, const Tables &t,                \
                         const Target &w, const double *Q, const double *v, double *yE) {        \
             if (g.lim != 0.0) {                                                                   \
                 hipLaunchKernelGGL((K##_applyc<P, NQ, double, double, true>), dim3(grid), dim3(BLOCK), 0, s, g, t, w, Q, v, yE); \
             } else {                                                                         \
-                hipLaunchKernelGGL((K##_applyc<P, NQ, double, double, false>), dim3(grid), dim3(BLOCK), 0, s, g, t, w, Q, v, yE); \
+                plain_##K<P, NQ>::applyc(s, g, t, w, Q, v, yE); \
             }                                                                      \
         };                                                                                       \
         o.applyc32 = [](int grid, hipStream_t s, const Geom &g, const Tables &t,                \
@@ -334,7 +341,7 @@ bool ops3_p4(int nq, Ops *out);
             if (g.lim != 0.0) {                                                                   \
                 hipLaunchKernelGGL((K##_applyc<P, NQ, float, float, true>), dim3(grid), dim3(BLOCK), 0, s, g, t, w, Q, v, yE); \
             } else {                                                                         \
-                hipLaunchKernelGGL((K##_applyc<P, NQ, float, float, false>), dim3(grid), dim3(BLOCK), 0, s, g, t, w, Q, v, yE); \
+                plain_##K<P, NQ>::applyc(s, g, t, w, Q, v, yE); \
             }                                                                      \
         };                                                                                       \
         o.diagc64 = [](int grid, hipStream_t s, const Geom &g, const Tables &t, const Target &w,\

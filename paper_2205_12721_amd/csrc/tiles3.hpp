@@ -3,10 +3,116 @@
 // tables; shapes that do not exist for a class (tile_ok3) are never
 // instantiated.
 #pragma once
+#include "cols3.hpp"
 #include "kernels3d.hpp"
 #include "ops.hpp"
 
 namespace tmop {
+
+// The kernels without the limiting term that have a column form, in the form
+// and with the workgroup of ColForm.
+template <int P, int NQ>
+struct plain_k3 {
+    using F = ColForm<P, NQ>;
+    using CE = C3<P, NQ, F::energy>;
+    static constexpr int epbE = CE::EPB;
+    static dim3 grid(const Geom &g, int epb) { return dim3((g.ne + epb - 1) / epb); }
+    static void energy(hipStream_t s, const Geom &g, const Tables &t, const Target &w,
+                       const double *x, double *part)
+    {
+        hipLaunchKernelGGL((k3c_energy<CE, false, true>), grid(g, epbE), dim3(CE::WL), 0, s, g, t,
+                           w, x, (double *)nullptr, part);
+    }
+    template <bool EN>
+    static void gradient(hipStream_t s, const Geom &g, const Tables &t, const Target &w,
+                         const double *x, double *gE, double *part)
+    {
+        hipLaunchKernelGGL((k3c_energy<CE, true, EN>), grid(g, epbE), dim3(CE::WL), 0, s, g, t, w,
+                           x, gE, part);
+    }
+    template <typename TT>
+    static void setupc(hipStream_t s, const Geom &g, const Tables &t, const Target &w,
+                       const double *x, TT *Q)
+    {
+        if constexpr (F::setupc > 0) {
+            using C = C3<P, NQ, F::setupc>;
+            hipLaunchKernelGGL((k3c_setupc<C, TT>), grid(g, C::EPB), dim3(C::WL), 0, s, g, t, w, x,
+                               Q);
+        } else {
+            hipLaunchKernelGGL((k3_setupc<P, NQ, TT>), grid(g, S3<P, NQ>::EPB), dim3(BLOCK), 0, s,
+                               g, t, w, x, Q);
+        }
+    }
+    template <typename TT>
+    static void applyc(hipStream_t s, const Geom &g, const Tables &t, const Target &w, const TT *Q,
+                       const double *v, TT *yE)
+    {
+        if constexpr (F::template applyc<TT>() > 0) {
+            using C = C3<P, NQ, F::template applyc<TT>()>;
+            hipLaunchKernelGGL((k3c_applyc<C, TT, TT, F::template reread<TT>()>), grid(g, C::EPB),
+                               dim3(C::WL), 0, s, g, t, w, Q, v, yE);
+        } else {
+            hipLaunchKernelGGL((k3_applyc<P, NQ, TT, TT, false>), grid(g, S3<P, NQ>::EPB),
+                               dim3(BLOCK), 0, s, g, t, w, Q, v, yE);
+        }
+    }
+};
+
+// The same for the batched kernels (n tiles of epbE, epbS, epbA elements).
+template <int P, int NQ>
+struct plain_kb3 {
+    using F = ColForm<P, NQ>;
+    using CE = C3<P, NQ, F::energy>;
+    static constexpr int epbE = CE::EPB;
+    template <typename TT>
+    static constexpr int epbS()
+    {
+        return F::setupc > 0 ? F::setupc / (NQ * NQ) : S3<P, NQ>::EPB;
+    }
+    template <typename TT>
+    static constexpr int epbA()
+    {
+        return F::template applyc<TT>() > 0 ? F::template applyc<TT>() / (NQ * NQ) : S3<P, NQ>::EPB;
+    }
+    static void energy(int n, hipStream_t s, const Tables &t, const Tile *tl, const SlotDev *sl,
+                       const int *gt, int vin, double *part)
+    {
+        hipLaunchKernelGGL((kb3c_energy<CE, false, true>), dim3(n), dim3(CE::WL), 0, s, t, tl, sl,
+                           gt, vin, part);
+    }
+    template <bool EN>
+    static void gradient(int n, hipStream_t s, const Tables &t, const Tile *tl, const SlotDev *sl,
+                         const int *gt, int vin, double *part)
+    {
+        hipLaunchKernelGGL((kb3c_energy<CE, true, EN>), dim3(n), dim3(CE::WL), 0, s, t, tl, sl, gt,
+                           vin, part);
+    }
+    template <typename TT>
+    static void setupc(int n, hipStream_t s, const Tables &t, const Tile *tl, const SlotDev *sl,
+                       const int *gt, int vin)
+    {
+        if constexpr (F::setupc > 0) {
+            using C = C3<P, NQ, F::setupc>;
+            hipLaunchKernelGGL((kb3c_setupc<C, TT>), dim3(n), dim3(C::WL), 0, s, t, tl, sl, gt, vin);
+        } else {
+            hipLaunchKernelGGL((kb3_setupc<P, NQ, TT>), dim3(n), dim3(BLOCK), 0, s, t, tl, sl, gt,
+                               vin);
+        }
+    }
+    template <typename TT, typename CT>
+    static void applyc(int n, hipStream_t s, const Tables &t, const Tile *tl, const SlotDev *sl,
+                       const int *gt, int vin)
+    {
+        if constexpr (F::template applyc<TT>() > 0) {
+            using C = C3<P, NQ, F::template applyc<TT>()>;
+            hipLaunchKernelGGL((kb3c_applyc<C, TT, CT, F::template reread<TT>()>), dim3(n),
+                               dim3(C::WL), 0, s, t, tl, sl, gt, vin);
+        } else {
+            hipLaunchKernelGGL((kb3_applyc<P, NQ, TT, CT>), dim3(n), dim3(BLOCK), 0, s, t, tl, sl,
+                               gt, vin);
+        }
+    }
+};
 
 template <int P, int NQ, int T2, int IDX>
 inline void fill_tile3(Ops &o)
@@ -23,16 +129,22 @@ inline void fill_tile3(Ops &o)
             hipLaunchKernelGGL((k3_apply<P, NQ, float, float, false, T2>), dim3(grid),
                                dim3(BLOCK), 0, s, g, t, H, v, yE);
         };
-        o.applyc64_t[IDX] = [](int grid, hipStream_t s, const Geom &g, const Tables &t,
-                               const Target &w, const double *Q, const double *v, double *yE) {
-            hipLaunchKernelGGL((k3_applyc<P, NQ, double, double, false, T2>), dim3(grid),
-                               dim3(BLOCK), 0, s, g, t, w, Q, v, yE);
-        };
-        o.applyc32_t[IDX] = [](int grid, hipStream_t s, const Geom &g, const Tables &t,
-                               const Target &w, const float *Q, const double *v, float *yE) {
-            hipLaunchKernelGGL((k3_applyc<P, NQ, float, float, false, T2>), dim3(grid),
-                               dim3(BLOCK), 0, s, g, t, w, Q, v, yE);
-        };
+        if constexpr (T2 == 2) {
+            // the base shape: plain_k3, which chooses the column form
+            o.applyc64_t[IDX] = o.applyc64;
+            o.applyc32_t[IDX] = o.applyc32;
+        } else {
+            o.applyc64_t[IDX] = [](int grid, hipStream_t s, const Geom &g, const Tables &t,
+                                   const Target &w, const double *Q, const double *v, double *yE) {
+                hipLaunchKernelGGL((k3_applyc<P, NQ, double, double, false, T2>), dim3(grid),
+                                   dim3(BLOCK), 0, s, g, t, w, Q, v, yE);
+            };
+            o.applyc32_t[IDX] = [](int grid, hipStream_t s, const Geom &g, const Tables &t,
+                                   const Target &w, const float *Q, const double *v, float *yE) {
+                hipLaunchKernelGGL((k3_applyc<P, NQ, float, float, false, T2>), dim3(grid),
+                                   dim3(BLOCK), 0, s, g, t, w, Q, v, yE);
+            };
+        }
     } else {
         o.epb_t[IDX] = 0;
         o.apply64_t[IDX] = nullptr;
@@ -53,9 +165,9 @@ inline void fill_mfma3(Ops &o)
                                t, w, x, part);
         };
         o.gradientM = [](int grid, hipStream_t s, const Geom &g, const Tables &t,
-                         const Target &w, const double *x, double *gE, double *bad) {
+                         const Target &w, const double *x, double *gE, double *part) {
             hipLaunchKernelGGL((k3_gradient<P, NQ, false, false, true>), dim3(grid), dim3(BLOCK),
-                               0, s, g, t, w, x, gE, bad);
+                               0, s, g, t, w, x, gE, part);
         };
         o.gradientEM = [](int grid, hipStream_t s, const Geom &g, const Tables &t,
                           const Target &w, const double *x, double *gE, double *part) {
@@ -63,14 +175,14 @@ inline void fill_mfma3(Ops &o)
                                0, s, g, t, w, x, gE, part);
         };
         o.setupM64 = [](int grid, hipStream_t s, const Geom &g, const Tables &t,
-                        const Target &w, const double *x, double *H, double *bad) {
+                        const Target &w, const double *x, double *H) {
             hipLaunchKernelGGL((k3_setup<P, NQ, double, true>), dim3(grid), dim3(BLOCK), 0, s, g,
-                               t, w, x, H, bad);
+                               t, w, x, H);
         };
         o.setupcM64 = [](int grid, hipStream_t s, const Geom &g, const Tables &t,
-                         const Target &w, const double *x, double *Q, double *bad) {
+                         const Target &w, const double *x, double *Q) {
             hipLaunchKernelGGL((k3_setupc<P, NQ, double, true>), dim3(grid), dim3(BLOCK), 0, s,
-                               g, t, w, x, Q, bad);
+                               g, t, w, x, Q);
         };
     } else {
         o.energyM = nullptr;
@@ -88,40 +200,40 @@ inline void fill_setupd3(Ops &o)
 {
     if constexpr (S3<P, NQ>::EPB * S3<P, NQ>::NQ3 <= BLOCK) {
         o.setupd64 = [](int grid, hipStream_t s, const Geom &g, const Tables &t, const Target &w,
-                        const double *x, double *H, double *dE, double *bad) {
+                        const double *x, double *H, double *dE) {
             if (g.lim != 0.0)
                 hipLaunchKernelGGL((k3_setupd<P, NQ, double, true>), dim3(grid), dim3(BLOCK), 0, s,
-                                   g, t, w, x, H, dE, bad);
+                                   g, t, w, x, H, dE);
             else
                 hipLaunchKernelGGL((k3_setupd<P, NQ, double, false>), dim3(grid), dim3(BLOCK), 0, s,
-                                   g, t, w, x, H, dE, bad);
+                                   g, t, w, x, H, dE);
         };
         o.setupd32 = [](int grid, hipStream_t s, const Geom &g, const Tables &t, const Target &w,
-                        const double *x, float *H, double *dE, double *bad) {
+                        const double *x, float *H, double *dE) {
             if (g.lim != 0.0)
                 hipLaunchKernelGGL((k3_setupd<P, NQ, float, true>), dim3(grid), dim3(BLOCK), 0, s,
-                                   g, t, w, x, H, dE, bad);
+                                   g, t, w, x, H, dE);
             else
                 hipLaunchKernelGGL((k3_setupd<P, NQ, float, false>), dim3(grid), dim3(BLOCK), 0, s,
-                                   g, t, w, x, H, dE, bad);
+                                   g, t, w, x, H, dE);
         };
         o.setupcd64 = [](int grid, hipStream_t s, const Geom &g, const Tables &t, const Target &w,
-                         const double *x, double *Q, double *dE, double *bad) {
+                         const double *x, double *Q, double *dE) {
             if (g.lim != 0.0)
                 hipLaunchKernelGGL((k3_setupcd<P, NQ, double, true>), dim3(grid), dim3(BLOCK), 0, s,
-                                   g, t, w, x, Q, dE, bad);
+                                   g, t, w, x, Q, dE);
             else
                 hipLaunchKernelGGL((k3_setupcd<P, NQ, double, false>), dim3(grid), dim3(BLOCK), 0,
-                                   s, g, t, w, x, Q, dE, bad);
+                                   s, g, t, w, x, Q, dE);
         };
         o.setupcd32 = [](int grid, hipStream_t s, const Geom &g, const Tables &t, const Target &w,
-                         const double *x, float *Q, double *dE, double *bad) {
+                         const double *x, float *Q, double *dE) {
             if (g.lim != 0.0)
                 hipLaunchKernelGGL((k3_setupcd<P, NQ, float, true>), dim3(grid), dim3(BLOCK), 0, s,
-                                   g, t, w, x, Q, dE, bad);
+                                   g, t, w, x, Q, dE);
             else
                 hipLaunchKernelGGL((k3_setupcd<P, NQ, float, false>), dim3(grid), dim3(BLOCK), 0, s,
-                                   g, t, w, x, Q, dE, bad);
+                                   g, t, w, x, Q, dE);
         };
     } else {
         o.setupd64 = nullptr;
@@ -156,16 +268,21 @@ inline void fill_btile3(BOps &o)
             hipLaunchKernelGGL((kb3_apply<P, NQ, float, float, false, T2>), dim3(grid), dim3(BLOCK), 0,
                                s, t, tl, sl, gt, vin);
         };
-        o.apply_t[1][0][IDX] = [](int grid, hipStream_t s, const Tables &t, const Tile *tl,
-                                  const SlotDev *sl, const int *gt, int vin, double *) {
-            hipLaunchKernelGGL((kb3_applyc<P, NQ, double, double, false, T2>), dim3(grid), dim3(BLOCK),
-                               0, s, t, tl, sl, gt, vin);
-        };
-        o.apply_t[1][1][IDX] = [](int grid, hipStream_t s, const Tables &t, const Tile *tl,
-                                  const SlotDev *sl, const int *gt, int vin, double *) {
-            hipLaunchKernelGGL((kb3_applyc<P, NQ, float, float, false, T2>), dim3(grid), dim3(BLOCK), 0,
-                               s, t, tl, sl, gt, vin);
-        };
+        if constexpr (T2 == 2) {
+            o.apply_t[1][0][IDX] = o.apply[1][0];
+            o.apply_t[1][1][IDX] = o.apply[1][1];
+        } else {
+            o.apply_t[1][0][IDX] = [](int grid, hipStream_t s, const Tables &t, const Tile *tl,
+                                      const SlotDev *sl, const int *gt, int vin, double *) {
+                hipLaunchKernelGGL((kb3_applyc<P, NQ, double, double, false, T2>), dim3(grid),
+                                   dim3(BLOCK), 0, s, t, tl, sl, gt, vin);
+            };
+            o.apply_t[1][1][IDX] = [](int grid, hipStream_t s, const Tables &t, const Tile *tl,
+                                      const SlotDev *sl, const int *gt, int vin, double *) {
+                hipLaunchKernelGGL((kb3_applyc<P, NQ, float, float, false, T2>), dim3(grid),
+                                   dim3(BLOCK), 0, s, t, tl, sl, gt, vin);
+            };
+        }
     } else {
         o.epb_t[IDX] = 0;
         for (int a = 0; a < 2; ++a)
