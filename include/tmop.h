@@ -487,8 +487,8 @@ int tmop_set_timing(tmop_ctx *ctx, int enable);
  * capture, tight serving loops, harnesses that forbid hipMalloc): the
  * energy and min det of tmop_energy_mindet without a context, with no device
  * or pinned allocation by the library.  The per-workgroup partial sums go to
- * a fixed 1.5 MiB device array of the library (3 x TMOP_NOALLOC_MAX_TILES
- * doubles; each GPU the library runs on holds its own copy until the process
+ * a fixed device array of the library of about 1.5 MiB (3 x TMOP_NOALLOC_MAX_TILES
+ * doubles and the scratch of their reduction; each GPU the library runs on holds its own copy until the process
  * ends).  m: a structured box (elem_to_node must be NULL, else
  * TMOP_ERR_UNSUPPORTED; ess fields ignored); prm: metric, nq1d, target and
  * quad_rule as for tmop_create (precision and storage ignored: the energy is

@@ -261,7 +261,9 @@ struct tmop_ctx {
     double *part = nullptr;
     int part_len = 0;
     double *scal = nullptr;   // device scalars
-    double *hscal = nullptr;  // pinned host mirror
+    double *hscal = nullptr;  // pinned host memory
+    double *hscal_dev = nullptr;  // its device address (kernels write results there)
+    double *esl = nullptr;        // scratch of the energy reductions
     int32_t *csr_ptr = nullptr, *csr_ent = nullptr;
     double *diag = nullptr, *minv = nullptr;
     bool have_diag = false;
@@ -323,6 +325,7 @@ extern "C" int tmop_workspace_bytes(const tmop_mesh_desc *m, const tmop_params *
     size_t b = align256((size_t)ne * qdata_stride(S, nqe, (int)tb) * tb);
     b += align256((size_t)ne * d * np * 8);
     b += align256(sizeof(double) * (3 * ((ne + 0) + 1024) + 64));
+    b += align256(sizeof(double) * ENERGY_SCRATCH);
     b += 2 * align256((size_t)d * nx * 8);  // diag, minv
     if (m->elem_to_node) b += align256((nx + 1) * 4) + align256((size_t)ne * np * 4);
     if (with_solver) b += SV_COUNT * align256((size_t)d * nx * 8);
@@ -353,6 +356,7 @@ static void free_ctx(tmop_ctx *c)
     hipFree(c->eV);
     hipFree(c->part);
     hipFree(c->scal);
+    hipFree(c->esl);
     if (c->hscal) hipHostFree(c->hscal);
     hipFree(c->csr_ptr);
     hipFree(c->csr_ent);
@@ -449,12 +453,14 @@ extern "C" int tmop_create(tmop_ctx **out, const tmop_mesh_desc *m, const tmop_p
     ALLOC(c->eV, c->eV_bytes);
     ALLOC(c->part, sizeof(double) * c->part_len);
     ALLOC(c->scal, sizeof(double) * 64);
+    ALLOC(c->esl, sizeof(double) * ENERGY_SCRATCH);
     ALLOC(c->diag, sizeof(double) * c->ndof);
     ALLOC(c->minv, sizeof(double) * c->ndof);
     ALLOC(c->mst, 2 * sizeof(MinresState));
     ALLOC(c->mhist, MR_MAX_BASIS * sizeof(MrHist));
 #undef ALLOC
     if (e == hipSuccess) e = hipHostMalloc((void **)&c->hscal, sizeof(double) * 64, 0);
+    if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&c->hscal_dev, c->hscal, 0);
     if (e == hipSuccess) e = hipHostMalloc((void **)&c->hmst, 2 * sizeof(MinresState), 0);
     if (e != hipSuccess) {
         free_ctx(c);
@@ -522,8 +528,8 @@ static int energy_grid(const tmop_ctx *c)
 static int energy_mindet_impl(tmop_ctx *c, const double *x, double *F, double *mindet)
 {
     (use_mfma(c) ? c->ops.energyM : c->ops.energy)(c->grid, c->s, c->g, c->tb, c->tg, x, c->part);
-    launch_reduce3(c->part, energy_grid(c), c->scal, c->s);
-    HIPCHK(hipMemcpyAsync(c->hscal, c->scal, 3 * sizeof(double), hipMemcpyDeviceToHost, c->s));
+    // the last kernel writes the results to the pinned host memory itself
+    launch_energy_reduce(c->part, energy_grid(c), c->esl, c->hscal_dev, c->s);
     HIPCHK(hipStreamSynchronize(c->s));
     const double bad = c->hscal[2];
     if (mindet) *mindet = c->hscal[1];
@@ -568,10 +574,8 @@ static int energy_gradient_impl(tmop_ctx *c, const double *x, double *F, double 
 {
     (use_mfma(c) ? c->ops.gradientEM : c->ops.gradientE)(c->grid, c->s, c->g, c->tb, c->tg, x,
                                                          (double *)c->eV, c->part);
-    launch_reduce3(c->part, energy_grid(c), c->scal, c->s);
-    launch_gather(c->g, c->csr_ptr, c->csr_ent, c->eV, false, g, 0, nullptr, c->s);
-    launch_dot(c->ndof, g, g, c->part, c->scal + 8, c->s);
-    HIPCHK(hipMemcpyAsync(c->hscal, c->scal, 9 * sizeof(double), hipMemcpyDeviceToHost, c->s));
+    launch_gather_norm(c->g, c->csr_ptr, c->csr_ent, (const double *)c->eV, g, c->part,
+                       energy_grid(c), c->esl, c->hscal_dev, c->s);
     HIPCHK(hipStreamSynchronize(c->s));
     const double bad = c->hscal[2];
     *md = c->hscal[1];
@@ -1308,7 +1312,7 @@ extern "C" int tmop_set_lanczos_bank_limit(tmop_ctx *c, size_t max_bytes)
 // hipGetSymbolAddress returns on that device.
 // ---------------------------------------------------------------------------
 
-static __device__ __align__(256) double scratch[3 * TMOP_NOALLOC_MAX_TILES];
+static __device__ __align__(256) double scratch[3 * TMOP_NOALLOC_MAX_TILES + 3 * NSLICE];
 
 namespace {
 
@@ -1379,7 +1383,8 @@ extern "C" int tmop_energy_mindet_noalloc(const tmop_mesh_desc *m, const tmop_pa
     const hipStream_t s = (hipStream_t)stream;
     // (the energy kernel's workgroups hold at least ops.epb elements)
     ops.energy((int)grid, s, g, tb, tg, x, part);
-    launch_reduce3(part, (int)((ne + ops.epbE - 1) / ops.epbE), out, s);
+    launch_energy_reduce(part, (int)((ne + ops.epbE - 1) / ops.epbE),
+                         part + 3 * TMOP_NOALLOC_MAX_TILES, out, s);
     HIPCHK(hipGetLastError());
     return TMOP_OK;
 }

@@ -3,6 +3,8 @@
 // reductions, and the vector work of Newton and of preconditioned MINRES.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "tmop_dev.hpp"
 #include "gather.hpp"
 #include "vec.hpp"
@@ -68,23 +70,48 @@ void launch_gather(const Geom &g, const int32_t *csr_ptr, const int32_t *csr_ent
 // Reductions
 // ------------------------------------------------------------------------
 
-// Final reduce of the element kernels' partials: out[0] = sum part[0:nb],
-// out[1] = min part[nb:2nb], out[2] = sum part[2nb:3nb].
-__global__ __launch_bounds__(VBLOCK) void k_reduce3(const double *__restrict__ part, int nb,
-                                                    double *__restrict__ out)
+// Sum of part[0..nb) by one wave (lane l adds l, l+64, ... in that order,
+// 16 loads in flight, then a butterfly): the same bits in every workgroup.
+__device__ inline double wave_sum_partials(const double *__restrict__ part, int nb)
 {
-    __shared__ double red[VBLOCK / 64];
-    double s = 0.0, m = 1.0e300, b = 0.0;
-    // loads in batches of RU strides, each lane's sums in the order of k
-    constexpr int RU = 8;
-    int k = threadIdx.x;
-    for (; k + (RU - 1) * VBLOCK < nb; k += RU * VBLOCK) {
+    constexpr int RU = 16;
+    const int l = threadIdx.x & 63;
+    double s = 0.0;
+    for (int k0 = 0; k0 < nb; k0 += 64 * RU) {
+        double t[RU];
+#pragma unroll
+        for (int r = 0; r < RU; ++r) {
+            const int k = k0 + r * 64 + l;
+            t[r] = k < nb ? part[k] : 0.0;
+        }
+#pragma unroll
+        for (int r = 0; r < RU; ++r) s += t[r];
+    }
+    return wave_sum(s);
+}
+
+// The energy partials of an element kernel (nb sums, nb minima, nb counts of
+// points with det T <= 0, one of each per workgroup) are reduced in slices of
+// ESLICE, each by VBLOCK lanes in a fixed order, and the slices' results by
+// one workgroup (energy_final): the same bits whichever kernel does the
+// slices.  One workgroup for all of them read 1.5 MB in 24 us at 64^3 Q2.
+__device__ __forceinline__ void energy_slice(const double *__restrict__ part, int nb, int slice,
+                                             double &s, double &m, double &b, double *red)
+{
+    constexpr int RU = ESLICE / VBLOCK;
+    const int len = energy_slice_len(nb), k1 = min(nb, (slice + 1) * len);
+    s = 0.0;
+    m = 1.0e300;
+    b = 0.0;
+    for (int k0 = slice * len; k0 < k1; k0 += ESLICE) {
         double a[RU], c[RU], d[RU];
 #pragma unroll
         for (int u = 0; u < RU; ++u) {
-            a[u] = part[k + u * VBLOCK];
-            c[u] = part[nb + k + u * VBLOCK];
-            d[u] = part[2 * nb + k + u * VBLOCK];
+            const int k = k0 + u * VBLOCK + (int)threadIdx.x;
+            const bool in = k < k1;
+            a[u] = in ? part[k] : 0.0;
+            c[u] = in ? part[nb + k] : 1.0e300;
+            d[u] = in ? part[2 * (size_t)nb + k] : 0.0;
         }
 #pragma unroll
         for (int u = 0; u < RU; ++u) {
@@ -93,18 +120,184 @@ __global__ __launch_bounds__(VBLOCK) void k_reduce3(const double *__restrict__ p
             b += d[u];
         }
     }
-    for (; k < nb; k += VBLOCK) {
-        s += part[k];
-        m = fmin(m, part[nb + k]);
-        b += part[2 * nb + k];
+    block_energy3(s, m, b, red);
+}
+
+// Sums and minimum of the slices' results (planes of NSLICE in sl), wave 0.
+__device__ __forceinline__ void energy_final(const double *__restrict__ sl, int ns, double &s,
+                                             double &m, double &b)
+{
+    const int l = threadIdx.x & 63;
+    s = l < ns ? sl[l] : 0.0;
+    m = l < ns ? sl[NSLICE + l] : 1.0e300;
+    b = l < ns ? sl[2 * NSLICE + l] : 0.0;
+    for (int k = l + 64; k < ns; k += 64) {
+        s += sl[k];
+        m = fmin(m, sl[NSLICE + k]);
+        b += sl[2 * NSLICE + k];
     }
-    s = block_sum(s, red);
-    m = block_min(m, red);
-    b = block_sum(b, red);
+    s = wave_sum(s);
+    m = wave_min(m);
+    b = wave_sum(b);
+}
+
+// Slice 0 in a workgroup of more than VBLOCK lanes, the rest idle: the bits of
+// energy_slice.
+__device__ __forceinline__ void energy_slice_wide(const double *__restrict__ part, int nb,
+                                                  double &s, double &m, double &b, double *red)
+{
+    constexpr int RU = ESLICE / VBLOCK, NW = VBLOCK / 64;
+    s = 0.0;
+    m = 1.0e300;
+    b = 0.0;
+    if (threadIdx.x < VBLOCK) {
+#pragma unroll
+        for (int u = 0; u < RU; ++u) {
+            const int k = u * VBLOCK + (int)threadIdx.x;
+            if (k < nb) {
+                s += part[k];
+                m = fmin(m, part[nb + k]);
+                b += part[2 * nb + k];
+            }
+        }
+        s = wave_sum(s);
+        m = wave_min(m);
+        b = wave_sum(b);
+        if ((threadIdx.x & 63) == 0) {
+            const int w = threadIdx.x >> 6;
+            red[w] = s;
+            red[NW + w] = m;
+            red[2 * NW + w] = b;
+        }
+    }
+    __syncthreads();
     if (threadIdx.x == 0) {
+        double a = 0.0, c = red[NW], e = 0.0;
+        for (int k = 0; k < NW; ++k) a += red[k];
+        for (int k = 1; k < NW; ++k) c = fmin(c, red[NW + k]);
+        for (int k = 0; k < NW; ++k) e += red[2 * NW + k];
+        s = a;
+        m = c;
+        b = e;
+    }
+}
+
+// One slice per workgroup: its results to sl, or (one slice) to out.
+__global__ __launch_bounds__(VBLOCK) void k_energy_slices(const double *__restrict__ part, int nb,
+                                                          double *__restrict__ sl,
+                                                          double *__restrict__ out)
+{
+    __shared__ double red[3 * (VBLOCK / 64)];
+    double s, m, b;
+    energy_slice(part, nb, blockIdx.x, s, m, b, red);
+    if (threadIdx.x == 0) {
+        if (gridDim.x == 1) {
+            out[0] = s;
+            out[1] = m;
+            out[2] = b;
+        } else {
+            sl[blockIdx.x] = s;
+            sl[NSLICE + blockIdx.x] = m;
+            sl[2 * NSLICE + blockIdx.x] = b;
+        }
+    }
+}
+
+// The slices' results, and with dot the sum of nd dot partials, to out[0..2]
+// and out[8].
+__global__ __launch_bounds__(VBLOCK) void k_energy_final(const double *__restrict__ sl, int ns,
+                                                         const double *__restrict__ dot, int nd,
+                                                         double *__restrict__ out)
+{
+    if (threadIdx.x < 64) {
+        double s, m, b;
+        energy_final(sl, ns, s, m, b);
+        if (threadIdx.x == 0) {
+            out[0] = s;
+            out[1] = m;
+            out[2] = b;
+        }
+    } else if (threadIdx.x < 128 && dot) {
+        const double d = wave_sum_partials(dot, nd);
+        if (threadIdx.x == 64) out[8] = d;
+    }
+}
+
+// out = G^T eV with fixed DoFs 0 (a gradient), the partial sums of its
+// squares, and the energy slices of the first ns workgroups: one pass in
+// place of the gather, the reduction of the energy partials, and a dot
+// product that reads the gradient again.
+template <int DIM>
+__global__ __launch_bounds__(VBLOCK) void k_gather_norm(Geom g, const int32_t *__restrict__ ptr,
+                                                        const int32_t *__restrict__ ent,
+                                                        const double *__restrict__ eV,
+                                                        double *__restrict__ out,
+                                                        const double *__restrict__ part, int nb,
+                                                        double *__restrict__ sl, int ns,
+                                                        double *__restrict__ dot)
+{
+    __shared__ double red[3 * (VBLOCK / 64)];
+    double q = 0.0;
+    for (int node = xcd_block(blockIdx.x, gridDim.x) * VBLOCK + threadIdx.x; node < g.nx;
+         node += gridDim.x * VBLOCK) {
+        double a[DIM];
+        bool fixed[DIM];
+        gather_node<DIM, double>(g, ptr, ent, eV, node, a, fixed);
+#pragma unroll
+        for (int c = 0; c < DIM; ++c) {
+            out[(size_t)c * g.nx + node] = a[c];
+            q += a[c] * a[c];
+        }
+    }
+    q = block_sum(q, red);
+    if (threadIdx.x == 0) dot[blockIdx.x] = q;
+    if ((int)blockIdx.x < ns) {
+        double s, m, b;
+        energy_slice(part, nb, blockIdx.x, s, m, b, red);
+        if (threadIdx.x == 0) {
+            sl[blockIdx.x] = s;
+            sl[NSLICE + blockIdx.x] = m;
+            sl[2 * NSLICE + blockIdx.x] = b;
+        }
+    }
+}
+
+// The same by one workgroup that also writes the results (out[0..2], out[8]),
+// for meshes of at most GN_ONE_NODES nodes and one energy slice: one launch
+// less where a launch is what the call costs.
+template <int DIM>
+__global__ __launch_bounds__(1024) void k_gather_norm_one(Geom g, const int32_t *__restrict__ ptr,
+                                                          const int32_t *__restrict__ ent,
+                                                          const double *__restrict__ eV,
+                                                          double *__restrict__ grad,
+                                                          const double *__restrict__ part, int nb,
+                                                          double *__restrict__ out)
+{
+    __shared__ double red[3 * (VBLOCK / 64)], redq[16];
+    double q = 0.0;
+    for (int node = threadIdx.x; node < g.nx; node += 1024) {
+        double a[DIM];
+        bool fixed[DIM];
+        gather_node<DIM, double>(g, ptr, ent, eV, node, a, fixed);
+#pragma unroll
+        for (int c = 0; c < DIM; ++c) {
+            grad[(size_t)c * g.nx + node] = a[c];
+            q += a[c] * a[c];
+        }
+    }
+    q = wave_sum(q);
+    if ((threadIdx.x & 63) == 0) redq[threadIdx.x >> 6] = q;
+    // the slice as VBLOCK lanes reduce it (the other waves add nothing, and
+    // only the first BLOCK / 64 waves' results are read)
+    double s, m, b;
+    energy_slice_wide(part, nb, s, m, b, red);
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+        for (int k = 0; k < 16; ++k) t += redq[k];
         out[0] = s;
         out[1] = m;
         out[2] = b;
+        out[8] = t;
     }
 }
 
@@ -138,9 +331,39 @@ __global__ __launch_bounds__(VBLOCK) void k_reduce_max(const double *__restrict_
     if (threadIdx.x == 0) *out = s;
 }
 
-void launch_reduce3(const double *part, int nb, double *out, hipStream_t s)
+void launch_energy_reduce(const double *part, int nb, double *sl, double *out, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_reduce3, dim3(1), dim3(VBLOCK), 0, s, part, nb, out);
+    const int ns = energy_slices(nb);
+    hipLaunchKernelGGL(k_energy_slices, dim3(ns), dim3(VBLOCK), 0, s, part, nb, sl, out);
+    if (ns > 1)
+        hipLaunchKernelGGL(k_energy_final, dim3(1), dim3(VBLOCK), 0, s, sl, ns,
+                           (const double *)nullptr, 0, out);
+}
+
+void launch_gather_norm(const Geom &g, const int32_t *csr_ptr, const int32_t *csr_ent,
+                        const double *eV, double *grad, const double *part, int nb, double *sl,
+                        double *out, hipStream_t s)
+{
+    const int ns = energy_slices(nb);
+    if (g.nx <= GN_ONE_NODES && ns == 1) {
+        if (g.dim == 3)
+            hipLaunchKernelGGL(k_gather_norm_one<3>, dim3(1), dim3(1024), 0, s, g, csr_ptr,
+                               csr_ent, eV, grad, part, nb, out);
+        else
+            hipLaunchKernelGGL(k_gather_norm_one<2>, dim3(1), dim3(1024), 0, s, g, csr_ptr,
+                               csr_ent, eV, grad, part, nb, out);
+        return;
+    }
+    // at least one workgroup per slice (general meshes may have fewer nodes)
+    const int grid = std::max(vgrid((long)g.nx, 1024), ns);
+    double *dot = sl + 3 * NSLICE;
+    if (g.dim == 3)
+        hipLaunchKernelGGL(k_gather_norm<3>, dim3(grid), dim3(VBLOCK), 0, s, g, csr_ptr, csr_ent,
+                           eV, grad, part, nb, sl, ns, dot);
+    else
+        hipLaunchKernelGGL(k_gather_norm<2>, dim3(grid), dim3(VBLOCK), 0, s, g, csr_ptr, csr_ent,
+                           eV, grad, part, nb, sl, ns, dot);
+    hipLaunchKernelGGL(k_energy_final, dim3(1), dim3(VBLOCK), 0, s, sl, ns, dot, grid, out);
 }
 
 void launch_reduce_sum(const double *part, int nb, double *out, hipStream_t s)
@@ -250,26 +473,6 @@ void launch_jacobi(long n, const double *d, const double *dmax, double *minv, hi
 // propagates).  Work of iteration j is skipped when j > stop (set when the
 // residual estimate drops below rtol*beta1 or the Lanczos vector vanishes).
 // ------------------------------------------------------------------------
-
-// Sum of part[0..nb) by one wave (lane l adds l, l+64, ... in that order,
-// 16 loads in flight, then a butterfly): the same bits in every workgroup.
-__device__ inline double wave_sum_partials(const double *__restrict__ part, int nb)
-{
-    constexpr int RU = 16;
-    const int l = threadIdx.x & 63;
-    double s = 0.0;
-    for (int k0 = 0; k0 < nb; k0 += 64 * RU) {
-        double t[RU];
-#pragma unroll
-        for (int r = 0; r < RU; ++r) {
-            const int k = k0 + r * 64 + l;
-            t[r] = k < nb ? part[k] : 0.0;
-        }
-#pragma unroll
-        for (int r = 0; r < RU; ++r) s += t[r];
-    }
-    return wave_sum(s);
-}
 
 // Sums of pa[0..na) (wave 0) and, when pb is given, pb[0..nb) (wave 1), to
 // every thread of the workgroup after one barrier.  Called at most once per

@@ -30,7 +30,28 @@ constexpr int MR_MAX_BASIS = 256;
 
 void launch_gather(const Geom &g, const int32_t *csr_ptr, const int32_t *csr_ent, const void *eV,
                    bool fp32, double *out, int fix_mode, const double *src, hipStream_t s);
-void launch_reduce3(const double *part, int nb, double *out, hipStream_t s);
+// Energy partials are reduced in slices of ESLICE, or of a multiple of it so
+// that there are at most NSLICE slices (vec.hip).  Scratch of
+// launch_energy_reduce: 3 NSLICE doubles; of launch_gather_norm:
+// ENERGY_SCRATCH.
+constexpr int ESLICE = 1024;
+constexpr int NSLICE = 2048;
+constexpr int ENERGY_SCRATCH = 3 * NSLICE + NSLICE;
+inline __host__ __device__ int energy_slice_len(int nb)
+{
+    const int n = (nb + ESLICE - 1) / ESLICE;
+    return ESLICE * ((n + NSLICE - 1) / NSLICE);
+}
+inline int energy_slices(int nb) { return (nb + energy_slice_len(nb) - 1) / energy_slice_len(nb); }
+// Up to 4 nodes per lane of one workgroup.
+constexpr int GN_ONE_NODES = 4096;
+// F, min det, count of points with det T <= 0 from nb energy partials: to out[0..2].
+void launch_energy_reduce(const double *part, int nb, double *sl, double *out, hipStream_t s);
+// The gradient G^T eV (fixed DoFs 0) to grad, the reduced energy partials to
+// out[0..2] and |grad|^2 to out[8].
+void launch_gather_norm(const Geom &g, const int32_t *csr_ptr, const int32_t *csr_ent,
+                        const double *eV, double *grad, const double *part, int nb, double *sl,
+                        double *out, hipStream_t s);
 void launch_reduce_sum(const double *part, int nb, double *out, hipStream_t s);
 int reduce_blocks(long n);
 void launch_dot(long n, const double *a, const double *b, double *part, double *out,
