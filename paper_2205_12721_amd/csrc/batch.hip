@@ -758,12 +758,28 @@ struct ClassH {
     int tile = 1;  // Hessian action tile shape (index into BOps::epb_t)
     int nelem = 0;  // elements of the class's resident meshes
 
-    // elements per tile of the energy and gradient kernels (the energy
-    // partials are counted in these tiles) and of the action
-    int epb_energy() const { return key.lim ? bops.epb : bops.epbE; }
+    // the column form of the setup or the base-shape action, where it is the
+    // one to use
+    const BCol *setup_col() const
+    {
+        const BCol &k = bops.setupc_col[key.prec];
+        return key.storage && !key.lim && k.use(nelem) ? &k : nullptr;
+    }
+    const BCol *apply_col(int t) const
+    {
+        const BCol &k = bops.applyc_col[key.prec];
+        return t == 1 && key.storage && !key.lim && k.use(nelem) ? &k : nullptr;
+    }
+    int epb_setup() const { return setup_col() ? setup_col()->epb : bops.epb; }
     int epb_apply(int t) const
     {
-        return key.lim ? bops.epb : t == 1 ? bops.epbA[key.storage][key.prec] : bops.epb_t[t];
+        return key.lim ? bops.epb : apply_col(t) ? apply_col(t)->epb : bops.epb_t[t];
+    }
+    BLaunch apply_launch(int t) const
+    {
+        return key.lim        ? bops.applyL[key.storage][key.prec]
+               : apply_col(t) ? apply_col(t)->launch
+                              : bops.apply_t[key.storage][key.prec][t];
     }
 };
 
@@ -1018,8 +1034,12 @@ static int pool_rebuild(tmop_pool *P)
         }
         ClassH &c = it->second;
         c.nelem += s.ne;
-        for (int epb : std::set<int>{c.bops.epb, c.epb_energy(), c.bops.epbS[s.storage][s.prec],
-                                     c.epb_apply(c.tile)})
+    }
+    for (int si = 0; si < P->max_slots; ++si) {
+        const SlotH &s = P->slots[si];
+        if (!s.used) continue;
+        ClassH &c = P->classes.at(ClassKey{s.dim, s.p, s.nq, s.storage, s.prec, s.lim});
+        for (int epb : std::set<int>{c.bops.epb, c.epb_setup(), c.epb_apply(c.tile)})
             add_tiles(c.lists[epb], si, s.ne, epb);
     }
     int pb = 0;
@@ -1028,7 +1048,7 @@ static int pool_rebuild(tmop_pool *P)
         ClassH &c = kv.second;
         c.pbase = pb;
         for (auto &l : c.lists) PCHK(upload_tiles(P, l.second));
-        const std::vector<Tile> &et = c.lists[c.epb_energy()].tiles;
+        const std::vector<Tile> &et = c.lists[c.bops.epb].tiles;
         const int nt = (int)et.size();
         for (int t = 0; t < nt; ++t) {
             SlotRange &r = P->rg[et[t].slot];
@@ -1098,23 +1118,20 @@ static void launch_elem(tmop_pool *P, int which, const int *gate, int vin)
         ClassH &c = kv.second;
         if (!c.nelem) continue;
         const int st = c.key.storage, pr = c.key.prec;
-        const int epb = which == 2   ? c.bops.epbS[st][pr]
-                        : which == 3 ? c.epb_apply(c.tile)
-                        : which == 4 ? c.bops.epb
-                                     : c.epb_energy();
+        const int epb = which == 2 ? c.epb_setup() : which == 3 ? c.epb_apply(c.tile) : c.bops.epb;
         BLaunch f;
-        if (c.key.lim)
+        if (which == 2)
+            f = c.setup_col() ? c.setup_col()->launch : c.bops.setup[st][pr];
+        else if (which == 3)
+            f = c.apply_launch(c.tile);
+        else if (c.key.lim)
             f = which == 0   ? c.bops.energyL
                 : which == 1 ? c.bops.gradientL
-                : which == 2 ? c.bops.setup[st][pr]
-                : which == 3 ? c.bops.applyL[st][pr]
                 : which == 4 ? c.bops.diagL[st][pr]
                              : c.bops.gradientEL;
         else
             f = which == 0   ? c.bops.energy
                 : which == 1 ? c.bops.gradient
-                : which == 2 ? c.bops.setup[st][pr]
-                : which == 3 ? c.bops.apply_t[st][pr][c.tile]
                 : which == 4 ? c.bops.diag[st][pr]
                              : c.bops.gradientE;
         const TileList &l = c.lists[epb];
@@ -1981,7 +1998,7 @@ extern "C" int tmop_pool_autotune(tmop_pool *P, int reps)
                 const TileList &l = c.lists[c.epb_apply(t)];
                 const int n = (int)l.tiles.size();
                 const Tile *dl = l.d;
-                BLaunch f = c.bops.apply_t[st][pr][t];
+                BLaunch f = c.apply_launch(t);
                 for (int k = 0; k < 2; ++k) f(n, P->s, c.tb, dl, P->d_slots, nullptr, 0, nullptr);
                 PHIP(hipEventRecord(e0, P->s));
                 for (int k = 0; k < reps; ++k) f(n, P->s, c.tb, dl, P->d_slots, nullptr, 0, nullptr);

@@ -410,7 +410,8 @@ extern "C" int tmop_create(tmop_ctx **out, const tmop_mesh_desc *m, const tmop_p
     c->storage = prm->hess_storage;
     c->s = (hipStream_t)stream;
     c->grid = (int)((ne + ops.epb - 1) / ops.epb);
-    c->gridE = (int)((ne + ops.epbE - 1) / ops.epbE);
+    const int epbE = ops.energy_epb((int)ne);
+    c->gridE = (int)((ne + epbE - 1) / epbE);
     const int tt = tuned_tile(d, p, nq, c->storage, c->precision);
     if (tt >= 0 && ops.epb_t[tt] > 0) c->tile = tt;
 
@@ -1383,7 +1384,8 @@ extern "C" int tmop_energy_mindet_noalloc(const tmop_mesh_desc *m, const tmop_pa
     const hipStream_t s = (hipStream_t)stream;
     // (the energy kernel's workgroups hold at least ops.epb elements)
     ops.energy((int)grid, s, g, tb, tg, x, part);
-    launch_energy_reduce(part, (int)((ne + ops.epbE - 1) / ops.epbE),
+    const int epbE = ops.energy_epb((int)ne);
+    launch_energy_reduce(part, (int)((ne + epbE - 1) / epbE),
                          part + 3 * TMOP_NOALLOC_MAX_TILES, out, s);
     HIPCHK(hipGetLastError());
     return TMOP_OK;

@@ -563,28 +563,39 @@ __device__ __forceinline__ void c3_applyc(const Geom &g, const Tab &tb, const Ta
 }
 
 // ------------------------------------------------------------------------
-// Which kernels run in column form, and with how many lanes per workgroup (0:
-// the pencil form).  One wave per workgroup needs no barriers but leaves lanes
-// idle where 64 is not near a multiple of n_q^2; the LDS of a workgroup limits
-// the large ones.  Each entry is the fastest of 64, 128 and 256 lanes on
-// meshes of 8 to 110 thousand elements (n = 16 to 48 per side), the pencil
-// form where it was faster:
-//   energy, gradient with energy (us, pencil -> column): p1 n_q3 40^3 31 / 49
-//   -> 17 / 28; p2 n_q4 40^3 78 / 119 -> 41 / 75; p3 n_q5 24^3 37 / 57 -> 23 /
-//   43; p4 n_q6 24^3 65 / 108 -> 45 / 91; p4 n_q7 20^3 62 / 103 -> 36 / 70;
-//   p2 n_q9 20^3 85 / 133 -> 36 / 70.  At n_q = 3 one wave would hold 7
-//   elements (8% faster at p = 2), fewer than the 9 of the pencil form, so
-//   that the no-allocation energy would accept smaller meshes than it did.
-//   Compact setup: p2 n_q4 105 -> 84, p3 n_q5 39 -> 33, p4 n_q6 88 -> 72; the
-//   column form is slower where its stores end runs inside 128-byte lines
-//   (p1 n_q9 118 -> 143, p2 n_q5 100 -> 117).
+// Which kernels run in column form, with how many lanes per workgroup (0: the
+// pencil form only) and from how many elements on.
+//
+// Lanes: one wave per workgroup needs no barriers but leaves lanes idle where
+// 64 is not near a multiple of n_q^2, and the LDS limits large workgroups.
+// Each entry is the fastest of 64, 128 and 256 lanes on meshes of n = 16 to 48
+// elements per side, us, pencil -> column:
+//   energy, gradient with energy: p1 n_q3 40^3 31 / 49 -> 17 / 28; p2 n_q4 40^3
+//   78 / 119 -> 41 / 75; p3 n_q5 24^3 37 / 57 -> 23 / 43; p4 n_q6 24^3 65 /
+//   108 -> 45 / 91; p4 n_q7 20^3 62 / 103 -> 36 / 70; p2 n_q9 20^3 85 / 133 ->
+//   36 / 70.  At n_q = 3 one wave would hold 7 elements (8% faster at p = 2),
+//   fewer than the 9 of the pencil form, so that the no-allocation energy
+//   would accept smaller meshes than it did.
+//   Compact setup: p2 n_q4 105 -> 84, p3 n_q5 39 -> 33, p4 n_q6 88 -> 72; slower
+//   where its stores end runs inside 128-byte lines (p1 n_q9 118 -> 143, p2
+//   n_q5 100 -> 117, p4 n_q9 140 -> 152).
 //   Compact action in FP64: p1 n_q3 41 -> 36, p2 n_q3 63 -> 49, p2 n_q4 111 ->
 //   103, p3 n_q4 34 -> 28 with the column re-read from LDS (kept in registers
 //   it takes more than the 256 of two waves per SIMD, 36); from n_q = 5 at p >=
 //   3 on equal or slower, and with 9 points the layer-chunked form is faster.
 //   In FP32, where a column takes half the registers: p2 n_q4 55 -> 49, p2
-//   n_q9 71 -> 63, p3 n_q6 50 -> 39, p4 n_q6 58 -> 52 (re-read), p4 n_q5 38 ->
-//   37.
+//   n_q9 71 -> 63, p3 n_q6 50 -> 39, p4 n_q6 58 -> 52 (re-read).
+//
+// Elements: a column's points are walked one after the other, so a workgroup
+// takes longer, and on a mesh of few workgroups per CU that is the kernel's
+// time (9^3 elements p3 n_q5: gradient 7.9 us pencil, 9.1 column; FP32 action
+// 5.3 / 8.4).  The lines lie where the two meet, counted in workgroups of the
+// pencil form (256 CUs): energy and gradient about 1024 (16^3 p2 n_q4, 1024:
+// 10.6 -> 9.2; 12^3, 432: 7.2 -> 8.2), at p = 4 with n_q <= 6 4096; compact
+// setup 4096, n_q = 6 8192 (20^3 p3, 8000: 30.0 -> 33.9; 24^3: 70 -> 63), n_q >= 7
+// 1024; FP64 action 1024, n_q = 5 2048; FP32 action 1536 for n_q <= 4 and n_q =
+// 9 at p <= 2, n_q = 5 and p = 4 n_q <= 7 8192 (p2 n_q5 20^3, 4000: 15.6 -> 17.1;
+// 32^3: 54 -> 47), else 4096.
 // ------------------------------------------------------------------------
 template <int P, int NQ>
 struct ColForm {
@@ -594,18 +605,32 @@ struct ColForm {
                                             : 64;
     static constexpr int setupc = NQ <= 4 ? 64
                                   : NQ == 5 ? (P == 2 ? 0 : 64)
-                                  : NQ == 9 ? (P <= 2 ? 0 : P == 3 ? 256 : 128)
+                                  : NQ == 9 ? (P == 3 ? 256 : 0)
                                             : 128;
     template <typename TT>
     static constexpr int applyc()
     {
-        if (sizeof(TT) == 8) return P <= 2 && NQ <= 4 ? 64 : P == 2 && NQ == 5 ? 128 : P == 3 && NQ == 4 ? 64 : 0;
-        return P == 2 && NQ == 3 ? 256 : NQ <= 4 ? (P == 3 ? 128 : 64) : NQ == 5 ? 128 : 256;
+        if (sizeof(TT) == 8)
+            return NQ <= 4 ? 64 : P == 2 && NQ == 5 ? 128 : 0;
+        if ((P == 2 && NQ == 3) || (P == 4 && NQ == 5)) return 0;
+        return NQ <= 4 ? (P == 3 ? 128 : 64) : NQ == 5 ? 128 : 256;
     }
     template <typename TT>
     static constexpr bool reread()
     {
         return sizeof(TT) == 8 ? P == 3 : P == 4 || (P == 3 && NQ == 4);
+    }
+    // smallest element counts
+    static constexpr int EPB0 = S3<P, NQ>::EPB;
+    static constexpr int energy_min = EPB0 * (P == 4 && NQ <= 6 ? 4096 : 1024);
+    static constexpr int setupc_min = EPB0 * (NQ >= 7 ? 1024 : NQ == 6 ? 8192 : 4096);
+    template <typename TT>
+    static constexpr int applyc_min()
+    {
+        if (sizeof(TT) == 8) return EPB0 * (NQ == 5 ? 2048 : 1024);
+        return EPB0 * (NQ <= 4 || (NQ == 9 && P <= 2) ? 1536
+                       : NQ == 5 || (P == 4 && NQ <= 7) ? 8192
+                                                        : 4096);
     }
 };
 
@@ -635,16 +660,6 @@ __global__ __launch_bounds__(C::WL) __attribute__((amdgpu_waves_per_eu(2))) void
     const Tab tb = kernel_tables<sizeof(Geom)>();
     const int e0 = xcd_block(blockIdx.x, gridDim.x) * C::EPB;
     c3_applyc<C, TT, CT, RD>(g, tb, tg, Q, v, yE, e0, min(C::EPB, g.ne - e0));
-}
-
-template <class C, bool GRAD, bool EN>
-__global__ __launch_bounds__(C::WL) __attribute__((amdgpu_waves_per_eu(2))) void kb3c_energy(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ part)
-{
-    const Tab tb = kernel_tables<0>();
-    const Tile t = tiles[blockIdx.x];
-    if (gate && !gate[t.slot]) return;
-    const SlotDev &s = slots[t.slot];
-    c3_energy<C, GRAD, EN>(s.g, tb, s.tg, s.vec[vin], (double *)s.eV, part, t.e0, min(C::EPB, s.g.ne - t.e0));
 }
 
 template <class C, typename TT>

@@ -7,8 +7,9 @@ namespace tmop {
 // The kernels without the limiting term (quads have one form of each).
 template <int P, int NQ>
 struct plain_k2 {
-    static constexpr int epbE = S2<P, NQ>::EPB;
-    static dim3 grid(const Geom &g) { return dim3((g.ne + epbE - 1) / epbE); }
+    static constexpr int EPB = S2<P, NQ>::EPB;
+    static int energy_epb(int) { return EPB; }
+    static dim3 grid(const Geom &g) { return dim3((g.ne + EPB - 1) / EPB); }
     static void energy(hipStream_t s, const Geom &g, const Tables &t, const Target &w,
                        const double *x, double *part)
     {
@@ -33,40 +34,6 @@ struct plain_k2 {
     {
         hipLaunchKernelGGL((k2_applyc<P, NQ, TT, TT, false>), grid(g), dim3(BLOCK), 0, s, g, t, w,
                            Q, v, yE);
-    }
-};
-
-template <int P, int NQ>
-struct plain_kb2 {
-    static constexpr int epbE = S2<P, NQ>::EPB;
-    template <typename TT>
-    static constexpr int epbS() { return epbE; }
-    template <typename TT>
-    static constexpr int epbA() { return epbE; }
-    static void energy(int n, hipStream_t s, const Tables &t, const Tile *tl, const SlotDev *sl,
-                       const int *gt, int vin, double *part)
-    {
-        hipLaunchKernelGGL((kb2_energy<P, NQ>), dim3(n), dim3(BLOCK), 0, s, t, tl, sl, gt, vin, part);
-    }
-    template <bool EN>
-    static void gradient(int n, hipStream_t s, const Tables &t, const Tile *tl, const SlotDev *sl,
-                         const int *gt, int vin, double *part)
-    {
-        hipLaunchKernelGGL((kb2_gradient<P, NQ, false, EN>), dim3(n), dim3(BLOCK), 0, s, t, tl, sl,
-                           gt, vin, part);
-    }
-    template <typename TT>
-    static void setupc(int n, hipStream_t s, const Tables &t, const Tile *tl, const SlotDev *sl,
-                       const int *gt, int vin)
-    {
-        hipLaunchKernelGGL((kb2_setupc<P, NQ, TT>), dim3(n), dim3(BLOCK), 0, s, t, tl, sl, gt, vin);
-    }
-    template <typename TT, typename CT>
-    static void applyc(int n, hipStream_t s, const Tables &t, const Tile *tl, const SlotDev *sl,
-                       const int *gt, int vin)
-    {
-        hipLaunchKernelGGL((kb2_applyc<P, NQ, TT, CT>), dim3(n), dim3(BLOCK), 0, s, t, tl, sl, gt,
-                           vin);
     }
 };
 

@@ -11,11 +11,12 @@ namespace tmop {
 
 struct Ops {
     int epb;  // elements per workgroup
-    // elements per workgroup (so energy partials) of energy and gradientE
-    // without the limiting term and the matrix-core sweeps; these two, the
-    // compact setup and the compact action of the base shape work out their
-    // own grids (column form) and take no grid from the caller then
-    int epbE;
+    // elements per workgroup (so energy partials) of energy and gradientE on a
+    // mesh of ne elements, without the limiting term and the matrix-core
+    // sweeps.  Without the limiting term these, gradient, the compact setup
+    // and the compact action in the base shape work out their own form and
+    // grid and ignore the caller's.
+    int (*energy_epb)(int ne);
     void (*energy)(int grid, hipStream_t, const Geom &, const Tables &, const Target &,
                    const double *x, double *part);
     void (*gradient)(int grid, hipStream_t, const Geom &, const Tables &, const Target &,
@@ -80,11 +81,19 @@ struct Ops {
 typedef void (*BLaunch)(int grid, hipStream_t, const Tables &, const Tile *, const SlotDev *,
                         const int *gate, int vin, double *part);
 
+// A batched kernel in column form: elements per tile, the fewest elements of
+// a class from which it is used (none: never), its launcher.
+struct BCol {
+    int epb = 0, min_elems = 0;
+    BLaunch launch = nullptr;
+    bool use(int ne) const { return launch && ne >= min_elems; }
+};
+
 struct BOps {
     int epb;
-    // elements per tile of the kernels that may run in column form (without
-    // the limiting term): energy and gradient, setup, base-shape action
-    int epbE, epbS[2][2], epbA[2][2];
+    // column form of the compact setup and of the compact action in the base
+    // shape, by precision [fp64/fp32] (without the limiting term)
+    BCol setupc_col[2], applyc_col[2];
     BLaunch energy, gradient;
     // gradient plus the energy partials of energy (same three planes)
     BLaunch gradientE, gradientEL;
@@ -157,18 +166,20 @@ bool bops3_p4(int nq, BOps *out);
     {                                                                                          \
         BOps o;                                                                                \
         o.epb = SZ<P, NQ>::EPB;                                                                \
-        o.epbE = plain_##K<P, NQ>::epbE;                                                       \
         o.energy = [](int grid, hipStream_t s, const Tables &t, const Tile *tl, const SlotDev *sl, \
                       const int *gt, int vin, double *part) {                                  \
-            plain_##K<P, NQ>::energy(grid, s, t, tl, sl, gt, vin, part);                       \
+            hipLaunchKernelGGL((K##_energy<P, NQ>), dim3(grid), dim3(BLOCK), 0, s, t, tl, sl, gt, \
+                               vin, part);                                                     \
         };                                                                                     \
         o.gradient = [](int grid, hipStream_t s, const Tables &t, const Tile *tl,               \
                         const SlotDev *sl, const int *gt, int vin, double *part) {             \
-            plain_##K<P, NQ>::template gradient<false>(grid, s, t, tl, sl, gt, vin, part);     \
+            hipLaunchKernelGGL((K##_gradient<P, NQ>), dim3(grid), dim3(BLOCK), 0, s, t, tl, sl, \
+                               gt, vin, part);                                                 \
         };                                                                                     \
         o.gradientE = [](int grid, hipStream_t s, const Tables &t, const Tile *tl,              \
                          const SlotDev *sl, const int *gt, int vin, double *part) {            \
-            plain_##K<P, NQ>::template gradient<true>(grid, s, t, tl, sl, gt, vin, part);      \
+            hipLaunchKernelGGL((K##_gradient<P, NQ, false, true>), dim3(grid), dim3(BLOCK), 0, s, t, tl, \
+                               sl, gt, vin, part);                                             \
         };                                                                                     \
         o.gradientEL = [](int grid, hipStream_t s, const Tables &t, const Tile *tl,             \
                           const SlotDev *sl, const int *gt, int vin, double *part) {           \
@@ -193,10 +204,6 @@ bool bops3_p4(int nq, BOps *out);
     }
 
 #define TMOP_BOPS_PREC(K, P, NQ, IDX, TT, CT)                                                  \
-    o.epbS[0][IDX] = o.epb;                                                                    \
-    o.epbS[1][IDX] = plain_##K<P, NQ>::template epbS<TT>();                                    \
-    o.epbA[0][IDX] = o.epb;                                                                    \
-    o.epbA[1][IDX] = plain_##K<P, NQ>::template epbA<TT>();                                    \
     o.setup[0][IDX] = [](int grid, hipStream_t s, const Tables &t, const Tile *tl,             \
                          const SlotDev *sl, const int *gt, int vin, double *) {                \
         hipLaunchKernelGGL((K##_setup<P, NQ, TT>), dim3(grid), dim3(BLOCK), 0, s, t, tl, sl, gt, \
@@ -204,7 +211,8 @@ bool bops3_p4(int nq, BOps *out);
     };                                                                                         \
     o.setup[1][IDX] = [](int grid, hipStream_t s, const Tables &t, const Tile *tl,             \
                          const SlotDev *sl, const int *gt, int vin, double *) {                \
-        plain_##K<P, NQ>::template setupc<TT>(grid, s, t, tl, sl, gt, vin);                    \
+        hipLaunchKernelGGL((K##_setupc<P, NQ, TT>), dim3(grid), dim3(BLOCK), 0, s, t, tl, sl,  \
+                           gt, vin);                                                           \
     };                                                                                         \
     o.apply[0][IDX] = [](int grid, hipStream_t s, const Tables &t, const Tile *tl,             \
                          const SlotDev *sl, const int *gt, int vin, double *) {                \
@@ -213,7 +221,8 @@ bool bops3_p4(int nq, BOps *out);
     };                                                                                         \
     o.apply[1][IDX] = [](int grid, hipStream_t s, const Tables &t, const Tile *tl,             \
                          const SlotDev *sl, const int *gt, int vin, double *) {                \
-        plain_##K<P, NQ>::template applyc<TT, CT>(grid, s, t, tl, sl, gt, vin);                \
+        hipLaunchKernelGGL((K##_applyc<P, NQ, TT, CT>), dim3(grid), dim3(BLOCK), 0, s, t, tl,   \
+                           sl, gt, vin);                                                       \
     };                                                                                         \
     o.diag[0][IDX] = [](int grid, hipStream_t s, const Tables &t, const Tile *tl,              \
                         const SlotDev *sl, const int *gt, int, double *) {                     \
@@ -253,7 +262,7 @@ bool ops3_p4(int nq, Ops *out);
     {                                                                                            \
         Ops o;                                                                                   \
         o.epb = SZ<P, NQ>::EPB;                                                                  \
-        o.epbE = plain_##K<P, NQ>::epbE;                                                         \
+        o.energy_epb = plain_##K<P, NQ>::energy_epb;                                             \
         o.energy = [](int grid, hipStream_t s, const Geom &g, const Tables &t, const Target &w, \
                       const double *x, double *part) {                                          \
             if (g.lim != 0.0) {                                                                   \

@@ -10,25 +10,34 @@
 namespace tmop {
 
 // The kernels without the limiting term that have a column form, in the form
-// and with the workgroup of ColForm.
+// and with the workgroup that ColForm gives for the mesh.
 template <int P, int NQ>
 struct plain_k3 {
     using F = ColForm<P, NQ>;
     using CE = C3<P, NQ, F::energy>;
-    static constexpr int epbE = CE::EPB;
+    static constexpr int EPB0 = S3<P, NQ>::EPB;
     static dim3 grid(const Geom &g, int epb) { return dim3((g.ne + epb - 1) / epb); }
+    static int energy_epb(int ne) { return ne >= F::energy_min ? CE::EPB : EPB0; }
     static void energy(hipStream_t s, const Geom &g, const Tables &t, const Target &w,
                        const double *x, double *part)
     {
-        hipLaunchKernelGGL((k3c_energy<CE, false, true>), grid(g, epbE), dim3(CE::WL), 0, s, g, t,
-                           w, x, (double *)nullptr, part);
+        if (g.ne >= F::energy_min)
+            hipLaunchKernelGGL((k3c_energy<CE, false, true>), grid(g, CE::EPB), dim3(CE::WL), 0, s,
+                               g, t, w, x, (double *)nullptr, part);
+        else
+            hipLaunchKernelGGL((k3_energy<P, NQ, false>), grid(g, EPB0), dim3(BLOCK), 0, s, g, t, w,
+                               x, part);
     }
     template <bool EN>
     static void gradient(hipStream_t s, const Geom &g, const Tables &t, const Target &w,
                          const double *x, double *gE, double *part)
     {
-        hipLaunchKernelGGL((k3c_energy<CE, true, EN>), grid(g, epbE), dim3(CE::WL), 0, s, g, t, w,
-                           x, gE, part);
+        if (g.ne >= F::energy_min)
+            hipLaunchKernelGGL((k3c_energy<CE, true, EN>), grid(g, CE::EPB), dim3(CE::WL), 0, s, g,
+                               t, w, x, gE, part);
+        else
+            hipLaunchKernelGGL((k3_gradient<P, NQ, false, EN>), grid(g, EPB0), dim3(BLOCK), 0, s, g,
+                               t, w, x, gE, part);
     }
     template <typename TT>
     static void setupc(hipStream_t s, const Geom &g, const Tables &t, const Target &w,
@@ -36,83 +45,61 @@ struct plain_k3 {
     {
         if constexpr (F::setupc > 0) {
             using C = C3<P, NQ, F::setupc>;
-            hipLaunchKernelGGL((k3c_setupc<C, TT>), grid(g, C::EPB), dim3(C::WL), 0, s, g, t, w, x,
-                               Q);
-        } else {
-            hipLaunchKernelGGL((k3_setupc<P, NQ, TT>), grid(g, S3<P, NQ>::EPB), dim3(BLOCK), 0, s,
-                               g, t, w, x, Q);
+            if (g.ne >= F::setupc_min) {
+                hipLaunchKernelGGL((k3c_setupc<C, TT>), grid(g, C::EPB), dim3(C::WL), 0, s, g, t, w,
+                                   x, Q);
+                return;
+            }
         }
+        hipLaunchKernelGGL((k3_setupc<P, NQ, TT>), grid(g, EPB0), dim3(BLOCK), 0, s, g, t, w, x, Q);
     }
     template <typename TT>
     static void applyc(hipStream_t s, const Geom &g, const Tables &t, const Target &w, const TT *Q,
                        const double *v, TT *yE)
     {
-        if constexpr (F::template applyc<TT>() > 0) {
-            using C = C3<P, NQ, F::template applyc<TT>()>;
-            hipLaunchKernelGGL((k3c_applyc<C, TT, TT, F::template reread<TT>()>), grid(g, C::EPB),
-                               dim3(C::WL), 0, s, g, t, w, Q, v, yE);
-        } else {
-            hipLaunchKernelGGL((k3_applyc<P, NQ, TT, TT, false>), grid(g, S3<P, NQ>::EPB),
-                               dim3(BLOCK), 0, s, g, t, w, Q, v, yE);
+        constexpr int WL = F::template applyc<TT>();
+        if constexpr (WL > 0) {
+            using C = C3<P, NQ, WL>;
+            if (g.ne >= F::template applyc_min<TT>()) {
+                hipLaunchKernelGGL((k3c_applyc<C, TT, TT, F::template reread<TT>()>),
+                                   grid(g, C::EPB), dim3(C::WL), 0, s, g, t, w, Q, v, yE);
+                return;
+            }
         }
+        hipLaunchKernelGGL((k3_applyc<P, NQ, TT, TT, false>), grid(g, EPB0), dim3(BLOCK), 0, s, g, t,
+                           w, Q, v, yE);
     }
 };
 
-// The same for the batched kernels (n tiles of epbE, epbS, epbA elements).
-template <int P, int NQ>
-struct plain_kb3 {
+// Column form of the batched compact setup and action, by precision; taken
+// for a class whose resident meshes have at least so many elements together.
+// (Energy and gradient keep the pencil form there: a solve's energy is summed
+// by tiles, and is to have the same bits alone and with others.)
+template <int P, int NQ, typename TT, int IDX>
+inline void fill_bcol3(BOps &o)
+{
     using F = ColForm<P, NQ>;
-    using CE = C3<P, NQ, F::energy>;
-    static constexpr int epbE = CE::EPB;
-    template <typename TT>
-    static constexpr int epbS()
-    {
-        return F::setupc > 0 ? F::setupc / (NQ * NQ) : S3<P, NQ>::EPB;
+    constexpr int WS = F::setupc, WA = F::template applyc<TT>();
+    if constexpr (WS > 0) {
+        using C = C3<P, NQ, WS>;
+        o.setupc_col[IDX] = BCol{C::EPB, F::setupc_min,
+                                 [](int n, hipStream_t s, const Tables &t, const Tile *tl,
+                                    const SlotDev *sl, const int *gt, int vin, double *) {
+                                     hipLaunchKernelGGL((kb3c_setupc<C, TT>), dim3(n), dim3(C::WL),
+                                                        0, s, t, tl, sl, gt, vin);
+                                 }};
     }
-    template <typename TT>
-    static constexpr int epbA()
-    {
-        return F::template applyc<TT>() > 0 ? F::template applyc<TT>() / (NQ * NQ) : S3<P, NQ>::EPB;
+    if constexpr (WA > 0) {
+        using C = C3<P, NQ, WA>;
+        o.applyc_col[IDX] =
+            BCol{C::EPB, F::template applyc_min<TT>(),
+                 [](int n, hipStream_t s, const Tables &t, const Tile *tl, const SlotDev *sl,
+                    const int *gt, int vin, double *) {
+                     hipLaunchKernelGGL((kb3c_applyc<C, TT, TT, F::template reread<TT>()>), dim3(n),
+                                        dim3(C::WL), 0, s, t, tl, sl, gt, vin);
+                 }};
     }
-    static void energy(int n, hipStream_t s, const Tables &t, const Tile *tl, const SlotDev *sl,
-                       const int *gt, int vin, double *part)
-    {
-        hipLaunchKernelGGL((kb3c_energy<CE, false, true>), dim3(n), dim3(CE::WL), 0, s, t, tl, sl,
-                           gt, vin, part);
-    }
-    template <bool EN>
-    static void gradient(int n, hipStream_t s, const Tables &t, const Tile *tl, const SlotDev *sl,
-                         const int *gt, int vin, double *part)
-    {
-        hipLaunchKernelGGL((kb3c_energy<CE, true, EN>), dim3(n), dim3(CE::WL), 0, s, t, tl, sl, gt,
-                           vin, part);
-    }
-    template <typename TT>
-    static void setupc(int n, hipStream_t s, const Tables &t, const Tile *tl, const SlotDev *sl,
-                       const int *gt, int vin)
-    {
-        if constexpr (F::setupc > 0) {
-            using C = C3<P, NQ, F::setupc>;
-            hipLaunchKernelGGL((kb3c_setupc<C, TT>), dim3(n), dim3(C::WL), 0, s, t, tl, sl, gt, vin);
-        } else {
-            hipLaunchKernelGGL((kb3_setupc<P, NQ, TT>), dim3(n), dim3(BLOCK), 0, s, t, tl, sl, gt,
-                               vin);
-        }
-    }
-    template <typename TT, typename CT>
-    static void applyc(int n, hipStream_t s, const Tables &t, const Tile *tl, const SlotDev *sl,
-                       const int *gt, int vin)
-    {
-        if constexpr (F::template applyc<TT>() > 0) {
-            using C = C3<P, NQ, F::template applyc<TT>()>;
-            hipLaunchKernelGGL((kb3c_applyc<C, TT, CT, F::template reread<TT>()>), dim3(n),
-                               dim3(C::WL), 0, s, t, tl, sl, gt, vin);
-        } else {
-            hipLaunchKernelGGL((kb3_applyc<P, NQ, TT, CT>), dim3(n), dim3(BLOCK), 0, s, t, tl, sl,
-                               gt, vin);
-        }
-    }
-};
+}
 
 template <int P, int NQ, int T2, int IDX>
 inline void fill_tile3(Ops &o)
@@ -268,21 +255,16 @@ inline void fill_btile3(BOps &o)
             hipLaunchKernelGGL((kb3_apply<P, NQ, float, float, false, T2>), dim3(grid), dim3(BLOCK), 0,
                                s, t, tl, sl, gt, vin);
         };
-        if constexpr (T2 == 2) {
-            o.apply_t[1][0][IDX] = o.apply[1][0];
-            o.apply_t[1][1][IDX] = o.apply[1][1];
-        } else {
-            o.apply_t[1][0][IDX] = [](int grid, hipStream_t s, const Tables &t, const Tile *tl,
-                                      const SlotDev *sl, const int *gt, int vin, double *) {
-                hipLaunchKernelGGL((kb3_applyc<P, NQ, double, double, false, T2>), dim3(grid),
-                                   dim3(BLOCK), 0, s, t, tl, sl, gt, vin);
-            };
-            o.apply_t[1][1][IDX] = [](int grid, hipStream_t s, const Tables &t, const Tile *tl,
-                                      const SlotDev *sl, const int *gt, int vin, double *) {
-                hipLaunchKernelGGL((kb3_applyc<P, NQ, float, float, false, T2>), dim3(grid),
-                                   dim3(BLOCK), 0, s, t, tl, sl, gt, vin);
-            };
-        }
+        o.apply_t[1][0][IDX] = [](int grid, hipStream_t s, const Tables &t, const Tile *tl,
+                                  const SlotDev *sl, const int *gt, int vin, double *) {
+            hipLaunchKernelGGL((kb3_applyc<P, NQ, double, double, false, T2>), dim3(grid), dim3(BLOCK),
+                               0, s, t, tl, sl, gt, vin);
+        };
+        o.apply_t[1][1][IDX] = [](int grid, hipStream_t s, const Tables &t, const Tile *tl,
+                                  const SlotDev *sl, const int *gt, int vin, double *) {
+            hipLaunchKernelGGL((kb3_applyc<P, NQ, float, float, false, T2>), dim3(grid), dim3(BLOCK), 0,
+                               s, t, tl, sl, gt, vin);
+        };
     } else {
         o.epb_t[IDX] = 0;
         for (int a = 0; a < 2; ++a)
@@ -293,6 +275,8 @@ inline void fill_btile3(BOps &o)
 template <int P, int NQ>
 inline void fill_tiles_kb3(BOps &o)
 {
+    fill_bcol3<P, NQ, double, 0>(o);
+    fill_bcol3<P, NQ, float, 1>(o);
     fill_btile3<P, NQ, 1, 0>(o);
     fill_btile3<P, NQ, 2, 1>(o);
     fill_btile3<P, NQ, 4, 2>(o);

@@ -1,13 +1,15 @@
-"""Hex kernels in column form (energy, gradient, compact setup and action)
-against the oracle where their workgroups end: a single element, a mesh with
-every kind of remainder of the elements per workgroup (2 to 32 by class), a
-sheared constant target, general connectivity with a mask.  Tolerances as in
-the parity tests: 1e-11 in FP64, 2e-6 for the FP32 action.
+"""Hex energy, gradient, compact setup and action against the oracle where
+their workgroups end: a single element, a mesh with every kind of remainder of
+the elements per workgroup (2 to 32 by class), a sheared constant target,
+general connectivity with a mask, and meshes of many elements, which the
+kernels in column form take.  Tolerances as in the parity tests: 1e-11 in
+FP64, 2e-6 for the FP32 action.
 """
 import numpy as np
 import pytest
 
 import oracle
+from oracle import basis
 from paper_2205_12721_amd import inputs
 from tests.gpu_common import TOL64, log, make_case, rel, to_dev, to_host
 
@@ -63,3 +65,116 @@ def test_sheared_target_and_general_mesh(p, nq):
                   num_nodes=pb.nx, ess=torch.as_tensor(mask.astype(np.uint8)).cuda())
     _check(ctx, pbm, x, 37)
     ctx.close()
+
+
+def _min_det(pb, x):
+    """min det A over the quadrature points in extended precision: where the
+    determinant is a thousandth of its terms and less, the oracle's own
+    rounding (4.5e-16 of 1.3e-4 in one piece below, p = 4, n_q = 9) is more than
+    1e-12 of it."""
+    ld = np.longdouble
+    t, z = basis.gl_rule(pb.nq1d)[0].astype(ld), np.asarray(basis.gll_nodes(pb.p), dtype=ld)
+    n = len(z)
+    B = np.ones((len(t), n), ld)
+    G = np.zeros((len(t), n), ld)
+    for i in range(n):
+        others = [j for j in range(n) if j != i]
+        for j in others:
+            B[:, i] *= (t - z[j]) / (z[i] - z[j])
+        for m in others:
+            w = np.full(len(t), 1 / (z[i] - z[m]))
+            for j in others:
+                if j != m:
+                    w = w * (t - z[j]) / (z[i] - z[j])
+            G[:, i] += w
+    low = []
+    for nodes in pb.e2n:
+        U = x.astype(ld).reshape(3, -1)[:, nodes].reshape(3, n, n, n)
+        A = []
+        for M in ((B, B, G), (B, G, B), (G, B, B)):
+            W = U
+            for T in M:
+                W = np.tensordot(W, T, axes=(1, 1))
+            A.append(W)
+        a, b, c = A
+        low.append((a[0] * (b[1] * c[2] - b[2] * c[1]) - a[1] * (b[0] * c[2] - b[2] * c[0])
+                    + a[2] * (b[0] * c[1] - b[1] * c[0])).min())
+    return float(min(low))
+
+
+# elements that put every kernel of a class in column form (where it has one);
+# primes, so that the last workgroup is a ragged one for every elements per
+# workgroup
+MANY = {2: 50021, 3: 40009, 4: 16411, 5: 16411, 6: 8219, 7: 8209, 9: 4111}
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("p,nq", CLASSES)
+def test_many_elements(p, nq, precision):
+    """A general mesh of separate pieces (three different ones of 12 elements in
+    turn, single elements at the end), each piece against the oracle."""
+    import torch
+    from paper_2205_12721_amd.tmop import Context
+    log("case", p, nq, precision)
+    ne = MANY[nq]
+    pieces = [make_case(3, (3, 2, 2), p, nq, "smooth", 0.05, seed=41 + k, constrain=None)
+              for k in range(3)]
+    pieces.append(make_case(3, (1, 1, 1), p, nq, "interior_jitter", 0.03, seed=44, constrain=None))
+    vs = [inputs.gaussian_vector(pb.ndof, 45 + k) for k, (pb, _) in enumerate(pieces)]
+    order = [k % 3 for k in range(ne // 12)] + [3] * (ne % 12)
+    nxs = np.array([pieces[k][0].nx for k in order])
+    off = np.concatenate([[0], np.cumsum(nxs)])
+    e2n = np.concatenate([pieces[k][0].e2n + o for k, o in zip(order, off)]).astype(np.int32)
+    assert e2n.shape[0] == ne
+
+    def joined(parts):
+        parts = [a.reshape(3, -1) for a in parts]
+        return np.concatenate([parts[k] for k in order], axis=1).ravel()
+
+    x = joined([x for _, x in pieces])
+    v = joined(vs)
+    count = np.bincount(order, minlength=4)
+    ctx = Context(3, None, p, nq, storage="compact", precision=precision,
+                  elem_to_node=torch.as_tensor(e2n).cuda(), num_nodes=int(off[-1]), ess="none")
+    xd = to_dev(x)
+    F, md, gd, _ = ctx.energy_gradient(xd)
+    assert (F, md) == ctx.energy_mindet(xd)
+    F0 = sum(int(n) * pb.energy(y) for n, (pb, y) in zip(count, pieces))
+    md0 = min(_min_det(pb, y) for n, (pb, y) in zip(count, pieces) if n)
+    assert abs(F - F0) <= TOL64 * F0
+    assert abs(md - md0) <= 1e-12 * md0
+    assert rel(to_host(gd), joined([pb.gradient(y) for pb, y in pieces])) <= TOL64
+    ctx.hessian_setup(xd)
+    assert rel(to_host(ctx.hessian_apply(to_dev(v))),
+               joined([pb.hvp(y, w) for (pb, y), w in zip(pieces, vs)])) <= (
+                   2e-6 if precision == "mixed" else TOL64)
+    ctx.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("p,ns,nq", [(1, (37, 37, 37), 2), (1, (30, 37, 37), 3), (1, (26, 26, 25), 4),
+                                     (2, (26, 26, 25), 4), (2, (26, 26, 25), 5), (3, (26, 26, 25), 4),
+                                     (3, (21, 20, 20), 6), (4, (21, 20, 20), 7)])
+def test_many_elements_box(p, ns, nq, precision):
+    """The box's own numbering against the same mesh as an element list (which
+    differ in the order in which a node's up to 8 terms are added)."""
+    import torch
+    from oracle import mesh
+    from paper_2205_12721_amd.tmop import Context
+    log("case", p, ns, nq, precision)
+    e2n, nx = mesh.box_topology(3, ns, p)
+    x, _ = inputs.perturbed_box(3, ns, p, basis.gll_nodes(p), 48, recipe="interior_jitter", amp=0.02)
+    v = to_dev(inputs.gaussian_vector(3 * nx, 49))
+    xd = to_dev(x)
+    box = Context(3, ns, p, nq, storage="compact", precision=precision, ess="none")
+    gen = Context(3, None, p, nq, storage="compact", precision=precision,
+                  elem_to_node=torch.as_tensor(e2n).cuda(), num_nodes=nx, ess="none")
+    a, b = box.energy_gradient(xd), gen.energy_gradient(xd)
+    assert a[:2] == b[:2] and a[1] > 0
+    assert rel(to_host(a[2]), to_host(b[2])) <= TOL64
+    box.hessian_setup(xd)
+    gen.hessian_setup(xd)
+    assert rel(to_host(box.hessian_apply(v)), to_host(gen.hessian_apply(v))) <= (
+        2e-6 if precision == "mixed" else TOL64)
+    box.close()
+    gen.close()
