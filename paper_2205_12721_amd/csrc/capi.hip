@@ -190,6 +190,9 @@ int internal_tables(int p, int nq, Tables *tb, int rule)
     for (int k = 0; k < MAXNQ * MAXNI; ++k) {
         tb->Bf[k] = (float)tb->B[k];
         tb->Gf[k] = (float)tb->G[k];
+        tb->D[0][k] = tb->B[k] * tb->B[k];
+        tb->D[1][k] = tb->B[k] * tb->G[k];
+        tb->D[2][k] = tb->G[k] * tb->G[k];
     }
     return TMOP_OK;
 }

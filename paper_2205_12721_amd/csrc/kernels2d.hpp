@@ -380,7 +380,7 @@ __device__ __forceinline__ void b2_setup(const Geom &g, const Tab &tb, const Tar
         double J[4], Hp[10];
         point_J2<P, NQ>(L.RY, el, q, J);
         const double z = qweight2<NQ>(sw, q) * tg.detW;
-        if (!metric_second<2>(tg, J, z, Hp)) {
+        if (!metric_second<2>(tg, J, z, [&](int r, int s, double v) { Hp[sym_index<4>(r, s)] = v; })) {
 #pragma unroll
             for (int k = 0; k < 10; ++k) Hp[k] = 0.0;
         }

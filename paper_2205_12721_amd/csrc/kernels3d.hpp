@@ -540,32 +540,46 @@ __device__ __forceinline__ void qdata_load(const TT *__restrict__ he, int q, TT 
 // Where a run's (a plane's) data ends inside a 128-byte line, the lanes of
 // its last PR (PP) points also write zeros into the padding points that fill
 // that line, so that the wave writing the line's data writes all of it.
+// put() takes the values k = 0, 1, .. NS-1 of point q in turn and stores each 16
+// bytes when they are complete, so that few values wait in registers.
 template <typename TT, int NS, int NQT>
-__device__ __forceinline__ void qdata_store(TT *__restrict__ he, int q, const TT *in)
-{
+struct QPut {
     using L = QLay<TT, NS, NQT>;
-    constexpr int TB = (int)sizeof(TT);
-    constexpr int PR = (NQT * 16) % 128 ? (128 - (NQT * 16) % 128) / 16 : 0;
-    constexpr int PP = (NQT * TB) % 128 ? (128 - (NQT * TB) % 128) / TB : 0;
+    static constexpr int TB = (int)sizeof(TT);
+    static constexpr int PR = (NQT * 16) % 128 ? (128 - (NQT * 16) % 128) / 16 : 0;
+    static constexpr int PP = (NQT * TB) % 128 ? (128 - (NQT * TB) % 128) / TB : 0;
     static_assert(PR <= L::NQP - NQT && PP <= L::NQP - NQT, "padding within the block");
-#pragma unroll
-    for (int r = 0; r < L::NV; ++r) {
-        Vec16<TT> w;
-#pragma unroll
-        for (int k = 0; k < L::VEC; ++k) w.v[k] = in[r * L::VEC + k];
-        *(Vec16<TT> *)(he + (r * L::NQP + q) * L::VEC) = w;
+    TT *he;
+    int q;
+    Vec16<TT> w;
+    __device__ __forceinline__ QPut(TT *he, int q) : he(he), q(q) {}
+    __device__ __forceinline__ void put(int k, TT v)
+    {
+        if (k >= L::TAIL) {
+            TT *a = he + (L::TAIL + (k - L::TAIL)) * L::NQP + q;
+            *a = v;
+            if (PP && q >= NQT - PP) a[PP] = (TT)0;
+            return;
+        }
+        w.v[k % L::VEC] = v;
+        if (k % L::VEC != L::VEC - 1) return;
+        Vec16<TT> *a = (Vec16<TT> *)(he + ((k / L::VEC) * L::NQP + q) * L::VEC);
+        *a = w;
         if (PR && q >= NQT - PR) {
             Vec16<TT> z;
 #pragma unroll
-            for (int k = 0; k < L::VEC; ++k) z.v[k] = (TT)0;
-            *(Vec16<TT> *)(he + (r * L::NQP + q + PR) * L::VEC) = z;
+            for (int j = 0; j < L::VEC; ++j) z.v[j] = (TT)0;
+            a[PR] = z;
         }
     }
+};
+
+template <typename TT, int NS, int NQT>
+__device__ __forceinline__ void qdata_store(TT *__restrict__ he, int q, const TT *in)
+{
+    QPut<TT, NS, NQT> o(he, q);
 #pragma unroll
-    for (int s = L::TAIL; s < NS; ++s) {
-        he[L::TAIL * L::NQP + (s - L::TAIL) * L::NQP + q] = in[s];
-        if (PP && q >= NQT - PP) he[L::TAIL * L::NQP + (s - L::TAIL) * L::NQP + q + PP] = (TT)0;
-    }
+    for (int k = 0; k < NS; ++k) o.put(k, in[k]);
 }
 
 // one value s (diagonal kernels read a subset)
@@ -767,18 +781,17 @@ __device__ __forceinline__ void b3_setup(const Geom &g, const Tab &tb, const Tar
         forward3<P, NQ>(tb, L.X, L.R1, L.R2, L.RY, nel);
     for (int idx = threadIdx.x; idx < nel * S::NQ3; idx += BLOCK) {
         const int el = idx / S::NQ3, q = idx % S::NQ3;
-        double J[9], Hp[45];
+        double J[9];
         point_J3<P, NQ>(L.RY, el, q, J);
         const double z = point_weight3<NQ>(sw, tg, q);
-        if (!metric_second<3>(tg, J, z, Hp)) {
-#pragma unroll
-            for (int k = 0; k < 45; ++k) Hp[k] = 0.0;
-        }
         using QL = QLay<TT, 45, S::NQ3>;
-        TT hs[45];
+        QPut<TT, 45, S::NQ3> out(H + (size_t)(e0 + el) * QL::STRIDE, q);
+        if (!metric_second<3>(tg, J, z, [&](int r, int s, double v) {
+                out.put(sym_index<9>(r, s), (TT)v);
+            })) {
 #pragma unroll
-        for (int k = 0; k < 45; ++k) hs[k] = (TT)Hp[k];
-        qdata_store<TT, 45, S::NQ3>(H + (size_t)(e0 + el) * QL::STRIDE, q, hs);
+            for (int k = 0; k < 45; ++k) out.put(k, (TT)0);
+        }
     }
 }
 
@@ -1285,34 +1298,32 @@ __device__ __forceinline__ void b3_applyc(const Geom &g, const Tab &tb, const Ta
 // doubled) are first placed in LDS planes sQ[el][pair][a][q].  With the
 // limiting term a seventh "pair" holds 2 w_q lim, contracted with BB on every
 // axis (the diagonal of the mass-like term, eq. eq_pa_limiting).
+//
+// Three sweeps for all pairs together, each in place: a lane owns a line of
+// every plane of one component, and its n_i outputs go where its n_q inputs
+// were.  After axis 2 only the number of derivative factors on axis 1 tells
+// pairs apart, so their sums are three planes, and one after axis 1.  (A pass
+// of three sweeps per pair had 18 barriers, of which axis 1's added to a sum
+// in LDS, and read a product table entry per multiply-add from LDS; here an
+// entry is a scalar operand that serves one to four lines.  Setup + diagonal
+// with its gather, us: p3 n_q5 24^3 compact 127 -> 86, tensor 170 -> 150; p2
+// n_q4 64^3 compact 978 -> 648; p4 n_q6 24^3 compact 279 -> 160; diagonal alone
+// 85 -> 54, 94 -> 79, 641 -> 422, 198 -> 99.  LDS traffic and the lanes that
+// the shorter stages leave idle bound it.)
 template <int P, int NQ, bool LIM = false>
 struct DiagLds3 {
     using S = S3<P, NQ>;
     static constexpr int NPR = LIM ? 7 : 6;
-    double T[3][NQ * S::NI];  // B B, B G, G G at (chi_q, node i)
     double sQ[S::EPB * NPR * 3 * S::NQ3];
-    double U2[S::EPB * 3 * S::NI * NQ * NQ];
-    double U1[S::EPB * 3 * S::NI * S::NI * NQ];
-    double sD[S::EPB * 3 * S::NP];
 };
 
 // pair pr < 6: (n, p) = (0,0) (0,1) (0,2) (1,1) (1,2) (2,2); pr = 6: value term
 __device__ constexpr int diag_pn(int pr) { return pr < 3 ? 0 : (pr < 5 ? 1 : 2); }
 __device__ constexpr int diag_pp(int pr) { return pr < 3 ? pr : (pr < 5 ? pr - 2 : 2); }
-
-// One 1D line of the diagonal contraction: out[i] = sum_q Tt[q*NI + i] y[q],
-// Tt the product table of the axis in LDS; every lane reads the same entry at
-// once (a broadcast).
-template <int NQ, int NI>
-__device__ __forceinline__ void diag_line(const double *Tt, const double *yv, double *out)
+// its number of derivative factors on axis k
+__device__ constexpr int diag_order(int pr, int k)
 {
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-        double s = 0.0;
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) s += Tt[q * NI + i] * yv[q];
-        out[i] = s;
-    }
+    return pr == 6 ? 0 : (diag_pn(pr) == k) + (diag_pp(pr) == k);
 }
 
 template <int P, int NQ, bool LIM>
@@ -1320,69 +1331,80 @@ __device__ __forceinline__ void diag_contract3(const Tab &tb, const Geom &g, int
                                       DiagLds3<P, NQ, LIM> &L, int nel, double *__restrict__ dE)
 {
     using S = S3<P, NQ>;
-    constexpr int NI = S::NI, NQ3 = S::NQ3, NP = S::NP, NPR = DiagLds3<P, NQ, LIM>::NPR;
-    for (int k = threadIdx.x; k < NQ * NI; k += BLOCK) {
-        const double b = tb.t->B[k], gg = tb.t->G[k];
-        L.T[0][k] = b * b;
-        L.T[1][k] = b * gg;
-        L.T[2][k] = gg * gg;
+    constexpr int NI = S::NI, NQ2 = S::NQ2, NQ3 = S::NQ3, NP = S::NP;
+    constexpr int NPR = DiagLds3<P, NQ, LIM>::NPR, PL = 3 * NQ3;  // from a pair's plane to the next
+    __syncthreads();  // sQ ready
+    // axis 3: lines (r = el*3 + a, q2, q1), q3 -> i3
+    {
+        const Tab t = tb.again();
+        for (int pen = threadIdx.x; pen < nel * 3 * NQ2; pen += BLOCK) {
+            const int q21 = pen % NQ2, r = pen / NQ2;
+            double *y = L.sQ + ((r / 3) * NPR * 3 + r % 3) * NQ3 + q21;
+            double o[NPR][NI] = {};
+#pragma unroll
+            for (int q = 0; q < NQ; ++q)
+#pragma unroll
+                for (int pr = 0; pr < NPR; ++pr) {
+                    const double v = y[pr * PL + q * NQ2];
+#pragma unroll
+                    for (int i = 0; i < NI; ++i)
+                        o[pr][i] += t.t->D[diag_order(pr, 2)][q * NI + i] * v;
+                }
+#pragma unroll
+            for (int pr = 0; pr < NPR; ++pr)
+#pragma unroll
+                for (int i = 0; i < NI; ++i) y[pr * PL + i * NQ2] = o[pr][i];
+        }
     }
-    for (int k = threadIdx.x; k < nel * 3 * NP; k += BLOCK) L.sD[k] = 0.0;
-    // one pass per pair as three pencil sweeps: a lane loads one 1D line from
-    // LDS and produces the n_i outputs of that line
-    for (int pr = 0; pr < NPR; ++pr) {
-        const int n = diag_pn(pr), p = diag_pp(pr);
-        // number of derivative factors on each axis
-        const bool val = pr == 6;
-        const int t1 = val ? 0 : (n == 0) + (p == 0), t2 = val ? 0 : (n == 1) + (p == 1),
-                  t3 = val ? 0 : (n == 2) + (p == 2);
-        // sQ and sD ready; later pairs need no barrier here (their axis-3 pass
-        // writes U2 only, which the previous pair's axis-1 pass does not read)
-        if (pr == 0) __syncthreads();
-        // axis 3: pencils (r = el*3 + a, q2, q1) -> U2[r][i3][q2][q1]
-        for (int pen = threadIdx.x; pen < nel * 3 * NQ * NQ; pen += BLOCK) {
-            const int q21 = pen % (NQ * NQ), r = pen / (NQ * NQ);
-            const int el = r / 3, a = r % 3;
-            const double *y = L.sQ + ((el * NPR + pr) * 3 + a) * NQ3 + q21;
-            double yv[NQ];
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) yv[q] = y[q * NQ * NQ];
-            double o[NI];
-            diag_line<NQ, NI>(L.T[t3], yv, o);
-#pragma unroll
-            for (int i = 0; i < NI; ++i) L.U2[(r * NI + i) * NQ * NQ + q21] = o[i];
-        }
-        __syncthreads();
-        // axis 2: pencils (r, i3, q1) -> U1[r][i3][i2][q1]
+    __syncthreads();
+    // axis 2: lines (r, i3, q1), q2 -> i2; plane k for axis-1 order 2 - k
+    {
+        const Tab t = tb.again();
         for (int pen = threadIdx.x; pen < nel * 3 * NI * NQ; pen += BLOCK) {
-            const int q1 = pen % NQ, ri3 = pen / NQ;
-            const double *y = L.U2 + ri3 * NQ * NQ + q1;
-            double yv[NQ];
+            const int q1 = pen % NQ, i3 = (pen / NQ) % NI, r = pen / (NQ * NI);
+            double *y = L.sQ + ((r / 3) * NPR * 3 + r % 3) * NQ3 + i3 * NQ2 + q1;
+            double o[3][NI] = {};
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) yv[q] = y[q * NQ];
-            double o[NI];
-            diag_line<NQ, NI>(L.T[t2], yv, o);
+            for (int q = 0; q < NQ; ++q)
 #pragma unroll
-            for (int i = 0; i < NI; ++i) L.U1[(ri3 * NI + i) * NQ + q1] = o[i];
+                for (int pr = 0; pr < NPR; ++pr) {
+                    const double v = y[pr * PL + q * NQ];
+#pragma unroll
+                    for (int i = 0; i < NI; ++i)
+                        o[2 - diag_order(pr, 0)][i] += t.t->D[diag_order(pr, 1)][q * NI + i] * v;
+                }
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+#pragma unroll
+                for (int i = 0; i < NI; ++i) y[k * PL + i * NQ] = o[k][i];
         }
-        __syncthreads();
-        // axis 1: pencils (r, i3, i2) -> the n_i diagonal entries of the line,
-        // each written by one lane
+    }
+    __syncthreads();
+    // axis 1: lines (r, i3, i2), q1 -> i1, into the first plane
+    {
+        const Tab t = tb.again();
         for (int pen = threadIdx.x; pen < nel * 3 * NI * NI; pen += BLOCK) {
-            const double *y = L.U1 + pen * NQ;
-            double yv[NQ];
+            const int i2 = pen % NI, i3 = (pen / NI) % NI, r = pen / (NI * NI);
+            double *y = L.sQ + ((r / 3) * NPR * 3 + r % 3) * NQ3 + i3 * NQ2 + i2 * NQ;
+            double o[NI] = {};
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) yv[q] = y[q];
-            double o[NI];
-            diag_line<NQ, NI>(L.T[t1], yv, o);
+            for (int q = 0; q < NQ; ++q)
 #pragma unroll
-            for (int i = 0; i < NI; ++i) L.sD[pen * NI + i] += o[i];
+                for (int k = 0; k < 3; ++k) {
+                    const double v = y[k * PL + q];
+#pragma unroll
+                    for (int i = 0; i < NI; ++i) o[i] += t.t->D[2 - k][q * NI + i] * v;
+                }
+#pragma unroll
+            for (int i = 0; i < NI; ++i) y[i] = o[i];
         }
     }
     __syncthreads();
     for (int k = threadIdx.x; k < nel * 3 * NP; k += BLOCK) {
         const int i = k % NP, r = k / NP;
-        dE[ev_index3<P>(g, e0 + r / 3, r % 3, i % NI, (i / NI) % NI, i / (NI * NI))] = L.sD[k];
+        const int i1 = i % NI, i2 = (i / NI) % NI, i3 = i / (NI * NI);
+        dE[ev_index3<P>(g, e0 + r / 3, r % 3, i1, i2, i3)] =
+            L.sQ[((r / 3) * NPR * 3 + r % 3) * NQ3 + i3 * NQ2 + i2 * NQ + i1];
     }
 }
 
@@ -1531,25 +1553,25 @@ __device__ __forceinline__ void b3_setupd(const Geom &g, const Tab &tb, const Ta
     if (act) point_J3<P, NQ>(L.s.RY, el, q, J);
     __syncthreads();
     if (act) {
-        double Hp[45];
         const double z = point_weight3<NQ>(sw, tg, q);
-        if (!metric_second<3>(tg, J, z, Hp)) {
-#pragma unroll
-            for (int k = 0; k < 45; ++k) Hp[k] = 0.0;
-        }
         using QL = QLay<TT, 45, S::NQ3>;
-        TT hs[45];
+        QPut<TT, 45, S::NQ3> out(H + (size_t)(e0 + el) * QL::STRIDE, q);
+        // the entries go out as they are computed: 111 registers, four
+        // workgroups on a CU, where holding all 45 took 151 and three (p3 n_q5
+        // 24^3, setup alone 142 -> 129 us; a fill of its 641 MB takes 100)
+        const auto emit = [&](int r, int s, double v) {
+            const TT h = (TT)v;
+            out.put(sym_index<9>(r, s), h);
+            if (r / 3 == s / 3) {
+                const int n = r % 3, p = s % 3, pr = n == 0 ? p : n + p + 1;
+                L.d.sQ[((el * NPR + pr) * 3 + r / 3) * S::NQ3 + q] = (n == p ? 1.0 : 2.0) * (double)h;
+            }
+        };
+        if (!metric_second<3>(tg, J, z, emit)) {
 #pragma unroll
-        for (int k = 0; k < 45; ++k) hs[k] = (TT)Hp[k];
-        qdata_store<TT, 45, S::NQ3>(H + (size_t)(e0 + el) * QL::STRIDE, q, hs);
+            for (int r = 0; r < 9; ++r)
 #pragma unroll
-        for (int pr = 0; pr < 6; ++pr) {
-            const int n = diag_pn(pr), p = diag_pp(pr);
-            const double f = (n == p) ? 1.0 : 2.0;
-#pragma unroll
-            for (int a = 0; a < 3; ++a)
-                L.d.sQ[((el * NPR + pr) * 3 + a) * S::NQ3 + q] =
-                    f * (double)hs[sym_index<9>(a * 3 + n, a * 3 + p)];
+                for (int s = r; s < 9; ++s) emit(r, s, 0.0);
         }
         diag_lim3<P, NQ, LIM>(sw, g, L.d, el, q);
     }

@@ -113,6 +113,7 @@ struct Tables {
     double w[MAXNQ];
     float Bf[MAXNQ * MAXNI];
     float Gf[MAXNQ * MAXNI];
+    double D[3][MAXNQ * MAXNI];  // B B, B G, G G (Hessian diagonal)
 };
 
 // A kernel's view of its Tables argument: a pointer to it in the kernel
@@ -577,9 +578,11 @@ __device__ inline bool metric_first(const Target &t, const double *A, double z, 
 }
 
 // z * H_A, packed symmetric (D^2 (D^2+1)/2 entries), where
-// H_A[an][bp] = sum_kl d2mu[ak][bl] Winv_nk Winv_pl.  Returns false if tau <= 0.
-template <int D>
-__device__ inline bool metric_second(const Target &t, const double *A, double z, double *Hp)
+// H_A[an][bp] = sum_kl d2mu[ak][bl] Winv_nk Winv_pl, entry by entry in packed
+// order: emit(r, s, value), r <= s.  Returns false, with nothing emitted, if
+// tau <= 0.
+template <int D, class Emit>
+__device__ __forceinline__ bool metric_second(const Target &t, const double *A, double z, Emit emit)
 {
 #pragma clang fp contract(on)
     constexpr int D2 = D * D;
@@ -599,7 +602,7 @@ __device__ inline bool metric_second(const Target &t, const double *A, double z,
                 double v = m.c_tc * (T[r] * C[s] + C[r] * T[s]) + m.c_cc * C[r] * C[s] +
                            m.c_dc * dcof<D>(T, r, s);
                 if (r == s) v += m.c_id;
-                Hp[sym_index<D2>(r, s)] = z * v;
+                emit(r, s, z * v);
             }
         return true;
     }
@@ -630,7 +633,9 @@ __device__ inline bool metric_second(const Target &t, const double *A, double z,
                 Hg[sym_index<D2>(r, s)] = z * acc;
             }
 #pragma unroll
-        for (int k = 0; k < NS; ++k) Hp[k] = Hg[k];
+        for (int r = 0; r < D2; ++r)
+#pragma unroll
+            for (int s = r; s < D2; ++s) emit(r, s, Hg[sym_index<D2>(r, s)]);
     }
     return true;
 }
