@@ -954,7 +954,8 @@ static int minres_three_term(tmop_ctx *c, const double *minv, double *const P1[2
 // c->mst[0..1] (see vec.hip for the recurrences).  When the max_its + 1
 // preconditioned Lanczos vectors fit in the bank they stay resident and dx
 // is formed once after the loop; otherwise every iteration takes the
-// three-term solution update.
+// three-term solution update.  The smallest meshes take all of it in one
+// launch (unless actions are to be timed one by one).
 static int minres_impl(tmop_ctx *c, const double *b, double *dx, int max_its, double rtol,
                        bool jacobi, int check_every, int *its_out)
 {
@@ -967,7 +968,13 @@ static int minres_impl(tmop_ctx *c, const double *b, double *dx, int max_its, do
     const double *minv = jacobi ? c->minv : nullptr;
     const bool resident = ensure_bank(c, max_its + 1);
     c->tev_used = 0;
-    if (resident) {
+    const auto one = c->ops.minres_one[c->storage == TMOP_HESS_COMPACT][c->precision == TMOP_MIXED];
+    if (resident && one && !c->timing && c->g.lim == 0.0 &&
+        one(c->s, c->g, c->tb, c->tg,
+            MrOne{c->csr_ptr, c->csr_ent, c->H, c->eV, b, minv, c->sv[SV_R1], c->sv[SV_R2], c->bank,
+                  c->bank_stride, dx, c->mst, rtol, max_its})) {
+        // all of it in one launch
+    } else if (resident) {
         // z_{-1} = M^{-1} b is bank vector 0; no w vectors
         mr_init(n, b, minv, c->sv[SV_R1], c->sv[SV_R2], c->bank, nullptr, dx, nullptr, nullptr,
                 nullptr, P1[0], c->mst, rtol, c->s);

@@ -1,5 +1,6 @@
 // Quad kernel instantiations for p = 1..4, n_q = p+1 .. p+3.
 #include "kernels2d.hpp"
+#include "minres_one.hpp"
 #include "ops.hpp"
 
 namespace tmop {
@@ -37,7 +38,7 @@ struct plain_k2 {
     }
 };
 
-bool ops2(int p, int nq, Ops *out)
+static bool ops2_elem(int p, int nq, Ops *out)
 {
 #define TMOP_CASE(P, NQ) \
     if (p == P && nq == NQ) TMOP_OPS_BODY(k2, S2, P, NQ)
@@ -47,6 +48,29 @@ bool ops2(int p, int nq, Ops *out)
     TMOP_CASE(4, 5) TMOP_CASE(4, 6) TMOP_CASE(4, 7)
 #undef TMOP_CASE
     return false;
+}
+
+template <int P, int NQ>
+static bool fill_minres_one2(Ops *o)
+{
+    o->minres_one[0][0] = minres_one2<P, NQ, double, false>;
+    o->minres_one[0][1] = minres_one2<P, NQ, float, false>;
+    o->minres_one[1][0] = minres_one2<P, NQ, double, true>;
+    o->minres_one[1][1] = minres_one2<P, NQ, float, true>;
+    return true;
+}
+
+bool ops2(int p, int nq, Ops *out)
+{
+    if (!ops2_elem(p, nq, out)) return false;
+#define TMOP_CASE(P, NQ) \
+    if (p == P && nq == NQ) return fill_minres_one2<P, NQ>(out);
+    TMOP_CASE(1, 2) TMOP_CASE(1, 3) TMOP_CASE(1, 4)
+    TMOP_CASE(2, 3) TMOP_CASE(2, 4) TMOP_CASE(2, 5)
+    TMOP_CASE(3, 4) TMOP_CASE(3, 5) TMOP_CASE(3, 6)
+    TMOP_CASE(4, 5) TMOP_CASE(4, 6) TMOP_CASE(4, 7)
+#undef TMOP_CASE
+    return true;
 }
 
 bool bops2(int p, int nq, BOps *out)

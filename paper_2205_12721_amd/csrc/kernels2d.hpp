@@ -390,13 +390,16 @@ __device__ __forceinline__ void b2_setup(const Geom &g, const Tab &tb, const Tar
     }
 }
 
-template <int P, int NQ, typename TT, typename CT, bool LIM = false>
+// V: blocks of elements that a workgroup of V x BLOCK lanes takes side by side,
+// lanes (., y) the y-th.
+template <int P, int NQ, typename TT, typename CT, bool LIM = false, int V = 1>
 __device__ __forceinline__ void b2_apply(const Geom &g, const Tab &tb, const TT *__restrict__ H,
                                 const double *__restrict__ v, CT *__restrict__ yE, int e0, int nel)
 {
     using S = S2<P, NQ>;
     constexpr int NR = Planes2<LIM>::NR;
-    __shared__ Lds2<P, NQ, CT, NR> L;
+    __shared__ Lds2<P, NQ, CT, NR> Ls[V];
+    Lds2<P, NQ, CT, NR> &L = Ls[V == 1 ? 0 : threadIdx.y];
     __shared__ double sw[LIM ? NQ : 1];
     if (LIM) weights_to_lds<NQ>(tb, sw);
     gather2<P, NQ>(g, v, e0, nel, L.X, true);
@@ -502,14 +505,15 @@ __device__ __forceinline__ void b2_setupc(const Geom &g, const Tab &tb, const Ta
     }
 }
 
-template <int P, int NQ, typename TT, typename CT, bool LIM = false>
+template <int P, int NQ, typename TT, typename CT, bool LIM = false, int V = 1>
 __device__ __forceinline__ void b2_applyc(const Geom &g, const Tab &tb, const Target &tg,
                                  const TT *__restrict__ Q, const double *__restrict__ v,
                                  CT *__restrict__ yE, int e0, int nel)
 {
     using S = S2<P, NQ>;
     constexpr int NR = Planes2<LIM>::NR;
-    __shared__ Lds2<P, NQ, CT, NR> L;
+    __shared__ Lds2<P, NQ, CT, NR> Ls[V];
+    Lds2<P, NQ, CT, NR> &L = Ls[V == 1 ? 0 : threadIdx.y];
     __shared__ double sw[LIM ? NQ : 1];
     if (LIM) weights_to_lds<NQ>(tb, sw);
     gather2<P, NQ>(g, v, e0, nel, L.X, true);

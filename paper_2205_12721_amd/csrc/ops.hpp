@@ -9,6 +9,8 @@
 
 namespace tmop {
 
+struct MrOne;  // minres_one.hpp
+
 struct Ops {
     int epb;  // elements per workgroup
     // elements per workgroup (so energy partials) of energy and gradientE on a
@@ -73,6 +75,11 @@ struct Ops {
                      const double *x, float *H, double *dE);
     decltype(setupd64) setupcd64;  // the same for compact storage
     decltype(setupd32) setupcd32;
+    // the whole MINRES solve in one workgroup [storage][precision]; false,
+    // with nothing launched, for a mesh too large for it.  Null where there
+    // is none; without the limiting term.
+    bool (*minres_one[2][2])(hipStream_t, const Geom &, const Tables &, const Target &,
+                             const MrOne &) = {};
 };
 
 // Batched launchers (grid = number of tiles); every batched element kernel

@@ -7,6 +7,7 @@
 
 #include "tmop_dev.hpp"
 #include "gather.hpp"
+#include "minres_dev.hpp"
 #include "vec.hpp"
 
 namespace tmop {
@@ -541,69 +542,10 @@ __global__ __launch_bounds__(VBLOCK) void k_mr_start(long n, MinresState *st, do
         }
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        MinresState &o = st[0];
-        o.tmp = bb;
-        o.beta1 = b1;
-        o.beta = b1;
-        o.oldb = 0.0;
-        o.alpha = 0.0;
-        o.dbar = 0.0;
-        o.eps = 0.0;
-        o.oldeps = 0.0;
-        o.phibar = b1;
-        o.phi = 0.0;
-        o.cs = -1.0;
-        o.sn = 0.0;
-        o.gamma = 1.0;
-        o.delta = 0.0;
-        o.rtol = rtol;
-        o.its = 0;
-        o.stop = (b1 > 0.0 && bb >= 0.0) ? 0x7fffffff : -1;
-        o.indefinite_precond = bb < 0.0 ? 1 : 0;
+        const MinresState o = mr_state0(bb, rtol);
+        st[0] = o;
         st[1] = o;
     }
-}
-
-// Scalars of the update of iteration jm (Givens rotation of the Lanczos
-// tridiagonal matrix) from the state before it, alpha_jm and beta_{jm+1}^2.
-struct MrUpd {
-    MinresState o;  // state after the update
-    double ig, oldeps, delta, phi;
-};
-
-__device__ inline MrUpd mr_scalars(const MinresState &sin, int jm, double alpha, double bb)
-{
-    MrUpd u;
-    const double beta = sqrt(fmax(bb, 0.0));
-    u.oldeps = sin.eps;
-    u.delta = sin.cs * sin.dbar + sin.sn * alpha;
-    const double gbar = sin.sn * sin.dbar - sin.cs * alpha;
-    const double eps = sin.sn * beta;
-    const double dbar = -sin.cs * beta;
-    const double gamma = fmax(hypot(gbar, beta), 2.2250738585072014e-308);
-    const double cs = gbar / gamma, sn = beta / gamma;
-    u.phi = cs * sin.phibar;
-    const double phibar = sn * sin.phibar;
-    u.ig = 1.0 / gamma;
-    MinresState o = sin;
-    o.tmp = bb;
-    o.alpha = alpha;
-    o.oldb = sin.beta;
-    o.beta = beta;
-    o.oldeps = u.oldeps;
-    o.eps = eps;
-    o.dbar = dbar;
-    o.delta = u.delta;
-    o.gamma = gamma;
-    o.cs = cs;
-    o.sn = sn;
-    o.phi = u.phi;
-    o.phibar = phibar;
-    o.its = jm + 1;
-    if (bb < 0.0) o.indefinite_precond = 1;
-    if (phibar <= sin.rtol * sin.beta1 || beta == 0.0) o.stop = jm;
-    u.o = o;
-    return u;
 }
 
 // Iteration j after the element kernel ran on z_{j-1} (the Lanczos vector

@@ -27,6 +27,21 @@ struct MrHist {
 };
 // Most updates one combination can take (one lane per coefficient).
 constexpr int MR_MAX_BASIS = 256;
+// A MINRES solve in one launch (minres_one.hpp): dx = H_c^{-1} b with the Lanczos vectors z_j in
+// bank (as in minres_resident), at most max_its iterations.  mst[0] and
+// mst[1] get the final state.
+struct MrOne {
+    const int32_t *ptr, *ent;
+    const void *H;
+    void *eV;
+    const double *b, *minv;
+    double *r1, *r2, *bank;
+    long stride;
+    double *dx;
+    MinresState *mst;
+    double rtol;
+    int max_its;
+};
 
 void launch_gather(const Geom &g, const int32_t *csr_ptr, const int32_t *csr_ent, const void *eV,
                    bool fp32, double *out, int fix_mode, const double *src, hipStream_t s);
