@@ -31,6 +31,7 @@
 #include <rocprofiler-sdk-roctx/roctx.h>
 
 #include "gather.hpp"
+#include "minres_dev.hpp"
 #include "vec.hpp"
 
 namespace tmop {
@@ -46,7 +47,7 @@ constexpr int BZIN = BNV;
 static_assert(BNV < NVEC, "too many vectors per slot");
 
 constexpr int VB = 256;      // threads per vector block
-constexpr int VCH = 8 * VB;  // DoFs per vector tile
+constexpr int VCH = 3 * VB;  // DoFs per vector tile
 
 struct VTile {
     int slot;
@@ -374,16 +375,43 @@ __global__ __launch_bounds__(VB) void kv_mr_gather_upd(
 {
     VT_PROLOGUE
     __shared__ double red[VB / 64];
+    const Geom &g = S.g;
+    const ET *__restrict__ eV = (const ET *)S.eV;
     const BState sp = st[2 * t.slot + (par ^ 1)];
+    const SlotRange r = rg[t.slot];
+    // G^T with one lane per node for all components (the copy positions are
+    // worked out once per node and the loads of every component are in
+    // flight together): the slot's nodes are split evenly over its vector
+    // tiles (the tiles of a slot are consecutive VCH-DoF chunks from 0).
+    // The lane's first node (hexes: its only one) is loaded before the partial
+    // sums are, and those before the state says whether they are needed.
+    const int ntile = (DIM * g.nx + VCH - 1) / VCH, jt = t.start / VCH;
+    const int npt = (g.nx + ntile - 1) / ntile;
+    const int nb = jt * npt, ne = nb + npt < g.nx ? nb + npt : g.nx;
+    const int node0 = nb + (int)threadIdx.x;
+    double *__restrict__ r1 = S.vec[vr1];
+    // the element kernel's input, z_{j-1} (vzc names its buffer when the
+    // slot has no bank)
+    const double *__restrict__ zc = S.vec[BZIN];
+    ET sv[DIM];
+    double zv[DIM], qv[DIM];
+    int gc[3];
+    const auto load = [&](int node) {
+        box_coords<DIM>(g, node, gc);
+        gather_box_all<DIM, ET>(g, eV, gc, sv);
+#pragma unroll
+        for (int c = 0; c < DIM; ++c) {
+            zv[c] = zc[(size_t)c * g.nx + node];
+            qv[c] = r1[(size_t)c * g.nx + node];
+        }
+    };
+    if (node0 < ne) load(node0);
+    double alpha, bb;
+    sum_partials(p1prev + r.vbegin, r.vcount, p2 + r.vbegin, r.vcount, alpha, bb);
     const bool upd = !sp.first && !bs_skip(sp);
     BUpd u{};
     u.o = sp;
-    if (upd) {
-        const SlotRange r = rg[t.slot];
-        const double alpha = seg_sum(p1prev, r.vbegin, r.vcount, red);
-        const double bb = seg_sum(p2, r.vbegin, r.vcount, red);
-        u = bs_update(sp, alpha, bb);
-    }
+    if (upd) u = bs_update(sp, alpha, bb);
     u.o.first = 0;
     const bool gat = !bs_skip(u.o);
     const bool res = S.bank != nullptr;
@@ -402,43 +430,28 @@ __global__ __launch_bounds__(VB) void kv_mr_gather_upd(
     }
     const bool vupd = upd && !res;
     if (!vupd && !gat) return;
-    const Geom &g = S.g;
-    const ET *__restrict__ eV = (const ET *)S.eV;
     const double sc = u.o.beta > 0.0 ? 1.0 / u.o.beta : 0.0;
     const double cr = u.o.j >= 1 ? u.o.beta / u.o.oldb : 0.0;
-    // the element kernel's input, z_{j-1} (vzc names its buffer when the
-    // slot has no bank)
-    const double *__restrict__ zc = S.vec[BZIN], *__restrict__ zp = S.vec[vzp];
-    const double *__restrict__ w1 = S.vec[vw1], *__restrict__ w2 = S.vec[vw2];
-    double *__restrict__ r1 = S.vec[vr1], *__restrict__ x = S.vec[BDX];
-    double *__restrict__ wo = S.vec[vwout];
-    if (vupd)
+    if (vupd) {
+        const double *__restrict__ zp = S.vec[vzp], *__restrict__ w1 = S.vec[vw1];
+        const double *__restrict__ w2 = S.vec[vw2];
+        double *__restrict__ x = S.vec[BDX], *__restrict__ wo = S.vec[vwout];
         for (int i = i0; i < i1; i += VB) {
             const double wn = (sprev * zp[i] - u.oldeps * w1[i] - u.delta * w2[i]) * u.ig;
             wo[i] = wn;
             x[i] += u.phi * wn;
         }
+    }
     if (!gat) return;
-    // G^T with one lane per node for all components (the copy positions are
-    // worked out once per node and the loads of every component are in
-    // flight together): the slot's nodes are split evenly over its vector
-    // tiles (the tiles of a slot are consecutive VCH-DoF chunks from 0)
     double acc = 0.0;
-    const int ntile = (DIM * g.nx + VCH - 1) / VCH, jt = t.start / VCH;
-    const int npt = (g.nx + ntile - 1) / ntile;
-    const int nb = jt * npt, ne = nb + npt < g.nx ? nb + npt : g.nx;
-    for (int node = nb + (int)threadIdx.x; node < ne; node += VB) {
-        int gc[3];
-        box_coords<DIM>(g, node, gc);
-        ET sv[DIM];
-        gather_box_all<DIM, ET>(g, eV, gc, sv);
+    for (int node = node0; node < ne; node += VB) {
+        if (node != node0) load(node);
 #pragma unroll
         for (int c = 0; c < DIM; ++c) {
-            const size_t i = (size_t)c * g.nx + node;
-            const double vi = sc * zc[i];
+            const double vi = sc * zv[c];
             double h = is_fixed(g, c, node, gc[0], gc[1], gc[2]) ? vi : sc * (double)sv[c];
-            if (u.o.j >= 1) h -= cr * r1[i];
-            r1[i] = h;
+            if (u.o.j >= 1) h -= cr * qv[c];
+            r1[(size_t)c * g.nx + node] = h;
             acc += vi * h;
         }
     }
@@ -457,26 +470,42 @@ __global__ __launch_bounds__(VB) void kv_mr_l2(const VTile *__restrict__ vt,
                                                SlotDev *wslots)
 {
     VT_PROLOGUE
-    const BState &s = st[2 * t.slot + par];
-    if (bs_skip(s)) return;
-    __shared__ double red[VB / 64];
+    const BState s = st[2 * t.slot + par];
     const SlotRange r = rg[t.slot];
-    const double alpha = seg_sum(part1, r.vbegin, r.vcount, red);
-    const double c = alpha / s.beta;
+    __shared__ double red[VB / 64];
     const bool useM = jac[t.slot] != 0;
     const double *__restrict__ m = S.vec[BMINV], *__restrict__ r2 = S.vec[vr2];
+    double *__restrict__ hv = S.vec[vhv];
+    // the tile's entries and the partial sums are in flight together, and
+    // neither waits for the state
+    constexpr int PL = VCH / VB;
+    double h[PL], q[PL], mi[PL];
+#pragma unroll
+    for (int k = 0; k < PL; ++k) {
+        const int i = i0 + k * VB;
+        h[k] = i < i1 ? hv[i] : 0.0;
+        q[k] = i < i1 ? r2[i] : 0.0;
+        mi[k] = i < i1 && useM ? m[i] : 1.0;
+    }
+    double alpha, unused;
+    sum_partials(part1 + r.vbegin, r.vcount, nullptr, 0, alpha, unused);
+    if (bs_skip(s)) return;
+    const double c = alpha / s.beta;
     // z_j to bank vector j + 1 (j < maxit here, and the bank holds maxit + 1),
     // else to the buffer vz; it is the next element kernel's input
     double *__restrict__ z = S.bank ? S.bank + (long)(s.j + 1) * S.bstride : S.vec[vz];
-    double *__restrict__ hv = S.vec[vhv];
     if (t.start == 0 && threadIdx.x == 0) wslots[t.slot].vec[BZIN] = z;
     double acc = 0.0;
-    for (int i = i0; i < i1; i += VB) {
-        const double h = hv[i] - c * r2[i];
-        hv[i] = h;
-        const double zi = useM ? m[i] * h : h;
-        z[i] = zi;
-        acc += h * zi;
+#pragma unroll
+    for (int k = 0; k < PL; ++k) {
+        const int i = i0 + k * VB;
+        if (i < i1) {
+            const double hn = h[k] - c * q[k];
+            hv[i] = hn;
+            const double zi = useM ? mi[k] * hn : hn;
+            z[i] = zi;
+            acc += hn * zi;
+        }
     }
     acc = block_sum(acc, red);
     if (threadIdx.x == 0) part2[blockIdx.x] = acc;

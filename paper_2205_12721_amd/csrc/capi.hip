@@ -243,6 +243,8 @@ int internal_target(const tmop_params *prm, int d, Target *tp)
 
 enum { SV_DX, SV_XT, SV_G, SV_GT, SV_R1, SV_R2, SV_Y, SV_V, SV_W, SV_W1, SV_W2, SV_COUNT };
 
+constexpr int HSCAL_PROGRESS = 16;  // entry of tmop_ctx::hscal (minres_watch)
+
 struct tmop_ctx {
     double *x0buf = nullptr;  // reference nodes of the limiting term (library copy)
     int tile = 1;             // Hessian-action tile shape (index into Ops::epb_t)
@@ -839,18 +841,50 @@ static bool ensure_bank(tmop_ctx *c, int nvec)
     return true;
 }
 
+// The word of pinned memory in which the device reports how far a solve is,
+// set to "nothing begun" (no solve of this context is under way here).
+static unsigned long long *minres_watch(tmop_ctx *c)
+{
+    __atomic_store_n((unsigned long long *)(c->hscal + HSCAL_PROGRESS), 0ull, __ATOMIC_RELEASE);
+    return (unsigned long long *)(c->hscal_dev + HSCAL_PROGRESS);
+}
+
+// Before iteration j is launched: waits until the device has begun iteration
+// j - MINRES_AHEAD + 1 at least, so that the queue holds enough to keep it
+// busy and few iterations are launched in vain after the solve has stopped;
+// returns whether it has.  (A copy of the state and a synchronisation every 8
+// iterations emptied the queue: some 24 us each time, 4 iterations launched in
+// vain on average.)
+constexpr int MINRES_AHEAD = 3;
+static bool minres_stopped(tmop_ctx *c, int j)
+{
+    const unsigned long long *w = (const unsigned long long *)(c->hscal + HSCAL_PROGRESS);
+    for (unsigned k = 1;; ++k) {
+        const unsigned long long p = __atomic_load_n(w, __ATOMIC_ACQUIRE);
+        if (p >> 32) return true;
+        if (j < (int)(uint32_t)p + MINRES_AHEAD) return false;
+        __builtin_ia32_pause();
+        if (k % 65536) continue;
+        // nothing left to run, or a failure: the caller's checks tell
+        if (hipPeekAtLastError() != hipSuccess || hipStreamQuery(c->s) != hipErrorNotReady) return false;
+        (void)hipGetLastError();  // "not ready" is no error
+    }
+}
+
 // Iterations with the preconditioned Lanczos vectors resident in the bank:
 // z_j in bank vector j, the update scalars to mhist, dx formed once at the
 // end.  Returns the iterations run.
 static int minres_resident(tmop_ctx *c, const double *minv, double *R1, double *R2,
                            double *const P1[2], double *P2, double *dx, int max_its,
-                           int check_every)
+                           bool early_stop)
 {
     const long n = c->ndof;
     const bool fp32 = c->precision == TMOP_MIXED;
     const int nbg = mr_gather_grid(c->g);
+    unsigned long long *prog = early_stop ? minres_watch(c) : nullptr;
     int J = 0;
     for (int j = 0; j < max_its; ++j) {
+        if (prog && minres_stopped(c, j)) break;
         // S_{j-1} in mst[(j-1)&1], S_j to mst[j&1]
         MinresState *sin = c->mst + ((j + 1) & 1), *sout = c->mst + (j & 1);
         const double *zc = c->bank + (long)j * c->bank_stride;
@@ -863,7 +897,7 @@ static int minres_resident(tmop_ctx *c, const double *minv, double *R1, double *
         // update into R1
         mr_gather_upd(c->g, c->csr_ptr, c->csr_ent, c->eV, fp32, j, sin, sout, P1[(j + 1) & 1],
                       P2, nullptr, zc, nullptr, nullptr, nullptr, nullptr, R1, P1[j & 1],
-                      c->mhist, c->s);
+                      c->mhist, prog, c->s);
         if (rec) {
             (void)hipEventRecord(c->tev[c->tev_used + 2], c->s);
             c->tev_used += 3;
@@ -871,11 +905,6 @@ static int minres_resident(tmop_ctx *c, const double *minv, double *R1, double *
         mr_lanczos2(n, nbg, j, sout, P1[j & 1], R1, R2, minv, znext, P2, c->s);
         std::swap(R1, R2);  // r1 <- r2, r2 <- hv
         J = j + 1;
-        if (check_every > 0 && (j + 1) % check_every == 0 && j + 1 < max_its) {
-            (void)hipMemcpyAsync(c->hmst, sout, sizeof(MinresState), hipMemcpyDeviceToHost, c->s);
-            (void)hipStreamSynchronize(c->s);
-            if (c->hmst->stop != 0x7fffffff) break;
-        }
     }
     // the last update, then dx from the resident vectors (dx = 0 from the
     // start when nothing ran)
@@ -889,7 +918,7 @@ static int minres_resident(tmop_ctx *c, const double *minv, double *R1, double *
 // Iterations with the three-term solution update in every gather (the
 // Lanczos vectors ping-pong between two buffers).  Returns the iterations run.
 static int minres_three_term(tmop_ctx *c, const double *minv, double *const P1[2], double *P2,
-                             double *dx, int max_its, int check_every)
+                             double *dx, int max_its, bool early_stop)
 {
     const long n = c->ndof;
     const bool fp32 = c->precision == TMOP_MIXED;
@@ -898,8 +927,10 @@ static int minres_three_term(tmop_ctx *c, const double *minv, double *const P1[2
     // kernel's input, v_j = z_{j-1} / beta_j); ZP: z_{j-2}, then z_j
     double *R1 = c->sv[SV_R1], *R2 = c->sv[SV_R2], *ZC = c->sv[SV_Y], *ZP = c->sv[SV_V];
     double *W = c->sv[SV_W], *W1 = c->sv[SV_W1], *W2 = c->sv[SV_W2];
+    unsigned long long *prog = early_stop ? minres_watch(c) : nullptr;
     int J = 0;
     for (int j = 0; j < max_its; ++j) {
+        if (prog && minres_stopped(c, j)) break;
         MinresState *sin = c->mst + ((j + 1) & 1), *sout = c->mst + (j & 1);
         const bool rec = c->timing && c->tev_used + 3 <= (int)c->tev.size();
         if (rec) (void)hipEventRecord(c->tev[c->tev_used], c->s);
@@ -908,7 +939,7 @@ static int minres_three_term(tmop_ctx *c, const double *minv, double *const P1[2
         // deferred update of iteration j-1 (formula's w1, w2 = buffers W2, W;
         // new w into W1), then G^T with the first Lanczos update into R1
         mr_gather_upd(c->g, c->csr_ptr, c->csr_ent, c->eV, fp32, j, sin, sout, P1[(j + 1) & 1],
-                      P2, ZP, ZC, W2, W, W1, dx, R1, P1[j & 1], nullptr, c->s);
+                      P2, ZP, ZC, W2, W, W1, dx, R1, P1[j & 1], nullptr, prog, c->s);
         if (rec) {
             (void)hipEventRecord(c->tev[c->tev_used + 2], c->s);
             c->tev_used += 3;
@@ -924,11 +955,6 @@ static int minres_three_term(tmop_ctx *c, const double *minv, double *const P1[2
             W = oW1;
         }
         J = j + 1;
-        if (check_every > 0 && (j + 1) % check_every == 0 && j + 1 < max_its) {
-            (void)hipMemcpyAsync(c->hmst, sout, sizeof(MinresState), hipMemcpyDeviceToHost, c->s);
-            (void)hipStreamSynchronize(c->s);
-            if (c->hmst->stop != 0x7fffffff) break;
-        }
     }
     // the update of the last iteration run
     if (J > 0) {
@@ -957,7 +983,7 @@ static int minres_three_term(tmop_ctx *c, const double *minv, double *const P1[2
 // three-term solution update.  The smallest meshes take all of it in one
 // launch (unless actions are to be timed one by one).
 static int minres_impl(tmop_ctx *c, const double *b, double *dx, int max_its, double rtol,
-                       bool jacobi, int check_every, int *its_out)
+                       bool jacobi, bool early_stop, int *its_out)
 {
     CHK(ensure_solver(c));
     const long n = c->ndof;
@@ -978,11 +1004,11 @@ static int minres_impl(tmop_ctx *c, const double *b, double *dx, int max_its, do
         // z_{-1} = M^{-1} b is bank vector 0; no w vectors
         mr_init(n, b, minv, c->sv[SV_R1], c->sv[SV_R2], c->bank, nullptr, dx, nullptr, nullptr,
                 nullptr, P1[0], c->mst, rtol, c->s);
-        minres_resident(c, minv, c->sv[SV_R1], c->sv[SV_R2], P1, P2, dx, max_its, check_every);
+        minres_resident(c, minv, c->sv[SV_R1], c->sv[SV_R2], P1, P2, dx, max_its, early_stop);
     } else {
         mr_init(n, b, minv, c->sv[SV_R1], c->sv[SV_R2], c->sv[SV_Y], nullptr, dx, c->sv[SV_W],
                 c->sv[SV_W1], c->sv[SV_W2], P1[0], c->mst, rtol, c->s);
-        minres_three_term(c, minv, P1, P2, dx, max_its, check_every);
+        minres_three_term(c, minv, P1, P2, dx, max_its, early_stop);
     }
     HIPCHK(hipGetLastError());
     HIPCHK(hipMemcpyAsync(c->hmst, c->mst, 2 * sizeof(MinresState), hipMemcpyDeviceToHost, c->s));
@@ -1010,7 +1036,7 @@ extern "C" int tmop_minres(tmop_ctx *c, const double *b, double *dx, int max_its
     if (!c || !b || !dx || max_its < 0) return fail(TMOP_ERR_INVALID_ARG, "bad argument");
     if (!c->have_setup) return fail(TMOP_ERR_STATE, "tmop_hessian_setup was not called");
     if (jacobi && !c->have_diag) make_jacobi(c);
-    return minres_impl(c, b, dx, max_its, rtol, jacobi != 0, 8, its);
+    return minres_impl(c, b, dx, max_its, rtol, jacobi != 0, true, its);
 }
 
 static double now_ms()
@@ -1022,7 +1048,7 @@ static double now_ms()
 // One Newton update of x (in place): setup, Jacobi, MINRES, line search.
 // F, gn, g (in c->sv[SV_G]) describe x on entry and are updated on accept.
 static int newton_update(tmop_ctx *c, double *x, double &F, double &gn, int max_minres,
-                         double rtol, int max_halvings, bool jacobi, int check_every,
+                         double rtol, int max_halvings, bool jacobi, bool early_stop,
                          tmop_solve_report *rep)
 {
     TraceRange step_range("tmop newton step");
@@ -1041,7 +1067,7 @@ static int newton_update(tmop_ctx *c, double *x, double &F, double &gn, int max_
     int its = 0;
     {
         TraceRange r("tmop minres");
-        CHK(minres_impl(c, c->sv[SV_G], c->sv[SV_DX], max_minres, rtol, jacobi, check_every, &its));
+        CHK(minres_impl(c, c->sv[SV_G], c->sv[SV_DX], max_minres, rtol, jacobi, early_stop, &its));
     }
     double t2 = now_ms();
     TraceRange ls_range("tmop line search");
@@ -1122,7 +1148,7 @@ extern "C" int tmop_solve(tmop_ctx *c, double *x, const tmop_solve_params *sp,
         if (it == sp->max_newton) break;
         const int its0 = rep->minres_its_total, h0 = rep->halvings_total;
         r = newton_update(c, x, F, gn, sp->max_minres, sp->minres_rtol, sp->max_halvings,
-                          sp->jacobi != 0, 8, rep);
+                          sp->jacobi != 0, true, rep);
         if (r != TMOP_OK) {
             status = r;
             break;
@@ -1151,7 +1177,7 @@ extern "C" int tmop_newton_step(tmop_ctx *c, double *x, int n_minres, int jacobi
     if (r == TMOP_OK) {
         rep->g0_norm = gn;
         // fixed amount of linear work: rtol 0, no early exit checks
-        r = newton_update(c, x, F, gn, n_minres, 0.0, 30, jacobi != 0, 0, rep);
+        r = newton_update(c, x, F, gn, n_minres, 0.0, 30, jacobi != 0, false, rep);
     }
     rep->F = F;
     rep->g_norm = gn;

@@ -5,6 +5,46 @@
 
 namespace tmop {
 
+// Sum of part[0..nb) by one wave (lane l adds l, l+64, ... in that order,
+// 16 loads in flight, then a butterfly): the same bits in every workgroup.
+__device__ inline double wave_sum_partials(const double *__restrict__ part, int nb)
+{
+    constexpr int RU = 16;
+    const int l = threadIdx.x & 63;
+    double s = 0.0;
+    for (int k0 = 0; k0 < nb; k0 += 64 * RU) {
+        double t[RU];
+#pragma unroll
+        for (int r = 0; r < RU; ++r) {
+            const int k = k0 + r * 64 + l;
+            t[r] = k < nb ? part[k] : 0.0;
+        }
+#pragma unroll
+        for (int r = 0; r < RU; ++r) s += t[r];
+    }
+    return wave_sum(s);
+}
+
+// Sums of pa[0..na) (wave 0) and, when pb is given, pb[0..nb) (wave 1), to
+// every thread of the workgroup after one barrier.  Called at most once per
+// kernel, by every thread.
+__device__ inline void sum_partials(const double *__restrict__ pa, int na,
+                                    const double *__restrict__ pb, int nb, double &a, double &b)
+{
+    __shared__ double sh[2];
+    const int w = threadIdx.x >> 6;
+    if (w == 0) {
+        const double t = wave_sum_partials(pa, na);
+        if (threadIdx.x == 0) sh[0] = t;
+    } else if (w == 1 && pb) {
+        const double t = wave_sum_partials(pb, nb);
+        if (threadIdx.x == 64) sh[1] = t;
+    }
+    __syncthreads();
+    a = sh[0];
+    b = pb ? sh[1] : 0.0;
+}
+
 // The state before the first iteration, from <b, M^{-1} b>.
 __device__ inline MinresState mr_state0(double bb, double rtol)
 {

@@ -71,26 +71,6 @@ void launch_gather(const Geom &g, const int32_t *csr_ptr, const int32_t *csr_ent
 // Reductions
 // ------------------------------------------------------------------------
 
-// Sum of part[0..nb) by one wave (lane l adds l, l+64, ... in that order,
-// 16 loads in flight, then a butterfly): the same bits in every workgroup.
-__device__ inline double wave_sum_partials(const double *__restrict__ part, int nb)
-{
-    constexpr int RU = 16;
-    const int l = threadIdx.x & 63;
-    double s = 0.0;
-    for (int k0 = 0; k0 < nb; k0 += 64 * RU) {
-        double t[RU];
-#pragma unroll
-        for (int r = 0; r < RU; ++r) {
-            const int k = k0 + r * 64 + l;
-            t[r] = k < nb ? part[k] : 0.0;
-        }
-#pragma unroll
-        for (int r = 0; r < RU; ++r) s += t[r];
-    }
-    return wave_sum(s);
-}
-
 // The energy partials of an element kernel (nb sums, nb minima, nb counts of
 // points with det T <= 0, one of each per workgroup) are reduced in slices of
 // ESLICE, each by VBLOCK lanes in a fixed order, and the slices' results by
@@ -475,26 +455,6 @@ void launch_jacobi(long n, const double *d, const double *dmax, double *minv, hi
 // residual estimate drops below rtol*beta1 or the Lanczos vector vanishes).
 // ------------------------------------------------------------------------
 
-// Sums of pa[0..na) (wave 0) and, when pb is given, pb[0..nb) (wave 1), to
-// every thread of the workgroup after one barrier.  Called at most once per
-// kernel, by every thread.
-__device__ inline void sum_partials(const double *__restrict__ pa, int na,
-                                    const double *__restrict__ pb, int nb, double &a, double &b)
-{
-    __shared__ double sh[2];
-    const int w = threadIdx.x >> 6;
-    if (w == 0) {
-        const double t = wave_sum_partials(pa, na);
-        if (threadIdx.x == 0) sh[0] = t;
-    } else if (w == 1 && pb) {
-        const double t = wave_sum_partials(pb, nb);
-        if (threadIdx.x == 64) sh[1] = t;
-    }
-    __syncthreads();
-    a = sh[0];
-    b = pb ? sh[1] : 0.0;
-}
-
 __global__ __launch_bounds__(VBLOCK) void k_mr_init(long n, const double *__restrict__ b,
                                                     const double *__restrict__ minv,
                                                     double *__restrict__ r1,
@@ -557,7 +517,8 @@ __global__ __launch_bounds__(VBLOCK) void k_mr_start(long n, MinresState *st, do
 //   place of r1;  part1 = <v_j, hv>.
 // With hist given (the Lanczos vectors kept resident) the update's scalars go
 // to hist[j-1] instead and w, x are not touched: the solution is formed once
-// after the loop (k_mr_combine).
+// after the loop (k_mr_combine).  progress: word of host memory for the
+// iterations begun and whether the solve has stopped, or null.
 template <int DIM, typename ET>
 __global__ __launch_bounds__(VBLOCK) void k_mr_gather_upd(
     Geom g, const int32_t *__restrict__ ptr, const int32_t *__restrict__ ent,
@@ -566,7 +527,7 @@ __global__ __launch_bounds__(VBLOCK) void k_mr_gather_upd(
     const double *__restrict__ p2prev, int nb2, const double *__restrict__ zp,
     const double *__restrict__ zc, const double *__restrict__ w1, const double *__restrict__ w2,
     double *__restrict__ wout, double *__restrict__ x, double *__restrict__ r1hv,
-    double *__restrict__ part, MrHist *__restrict__ hist)
+    double *__restrict__ part, MrHist *__restrict__ hist, unsigned long long *progress)
 {
     __shared__ double red[VBLOCK / 64];
     const int nstride = gridDim.x * VBLOCK;
@@ -585,18 +546,20 @@ __global__ __launch_bounds__(VBLOCK) void k_mr_gather_upd(
             q0[c] = j >= 1 ? r1hv[idx] : 0.0;
         }
     }
+    // nor do the sums wait for the state (they are not used when it says stop)
     const MinresState S = *sin;
+    double alpha = 0.0, bb = 0.0;
+    if (j >= 1) sum_partials(p1prev, nb1, p2prev, nb2, alpha, bb);
     const bool upd = j >= 1 && j - 1 <= S.stop;
     MrUpd u{};
     u.o = S;
-    if (upd) {
-        double alpha, bb;
-        sum_partials(p1prev, nb1, p2prev, nb2, alpha, bb);
-        u = mr_scalars(S, j - 1, alpha, bb);
-    }
+    if (upd) u = mr_scalars(S, j - 1, alpha, bb);
     const double sp = S.beta > 0.0 ? 1.0 / S.beta : 0.0;      // v_{j-1} = sp z_{j-2}
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         *sout = u.o;
+        if (progress)
+            __hip_atomic_store(progress, mr_progress(j + 1, u.o.stop != 0x7fffffff), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_SYSTEM);
         if (hist && upd) hist[j - 1] = MrHist{u.ig, u.oldeps, u.delta, u.phi, sp, {}};
     }
     const bool gat = j <= u.o.stop;
@@ -778,10 +741,12 @@ __global__ __launch_bounds__(VBLOCK) void k_mr_l2(long n, int j, const MinresSta
         rr[k] = i < n ? r2[i] : 0.0;
         mr[k] = i < n && minv ? minv[i] : 1.0;
     }
-    if (j > st->stop) return;
+    const int stop = st->stop;
+    const double beta = st->beta;
     double alpha, unused;
     sum_partials(part1, nb1, nullptr, 0, alpha, unused);
-    const double c = alpha / st->beta;
+    if (j > stop) return;
+    const double c = alpha / beta;
     double s = 0.0;
 #pragma unroll
     for (int k = 0; k < RU; ++k) {
@@ -819,7 +784,7 @@ void mr_gather_upd(const Geom &g, const int32_t *csr_ptr, const int32_t *csr_ent
                    bool fp32, int j, const MinresState *sin, MinresState *sout,
                    const double *p1prev, const double *p2prev, const double *zp, const double *zc,
                    const double *w1, const double *w2, double *wout, double *x, double *r1hv,
-                   double *part, MrHist *hist, hipStream_t s)
+                   double *part, MrHist *hist, unsigned long long *progress, hipStream_t s)
 {
     // one node per lane up to 1024 workgroups; its partials (alpha) number
     // nb1, those of the vector kernels (beta^2) nb2
@@ -827,7 +792,7 @@ void mr_gather_upd(const Geom &g, const int32_t *csr_ptr, const int32_t *csr_ent
 #define TMOP_G(D, T)                                                                          \
     hipLaunchKernelGGL((k_mr_gather_upd<D, T>), dim3(nb1), dim3(VBLOCK), 0, s, g, csr_ptr,    \
                        csr_ent, (const T *)eV, j, sin, sout, p1prev, nb1, p2prev, nb2, zp, zc, \
-                       w1, w2, wout, x, r1hv, part, hist);
+                       w1, w2, wout, x, r1hv, part, hist, progress);
     if (g.dim == 3) {
         if (fp32) {
             TMOP_G(3, float)

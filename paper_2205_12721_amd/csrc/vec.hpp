@@ -83,7 +83,13 @@ void mr_gather_upd(const Geom &g, const int32_t *csr_ptr, const int32_t *csr_ent
                    bool fp32, int j, const MinresState *sin, MinresState *sout,
                    const double *p1prev, const double *p2prev, const double *zp, const double *zc,
                    const double *w1, const double *w2, double *wout, double *x, double *r1hv,
-                   double *part, MrHist *hist, hipStream_t s);
+                   double *part, MrHist *hist, unsigned long long *progress, hipStream_t s);
+// What mr_gather_upd writes to progress: gathers begun, and in the upper half
+// whether the solve has stopped.
+inline __host__ __device__ unsigned long long mr_progress(int begun, bool stopped)
+{
+    return (unsigned long long)begun | ((unsigned long long)stopped << 32);
+}
 // Workgroups of mr_gather_upd, i.e. the count of its partials (nb1 below);
 // at most MR_MAX_PARTIALS.
 int mr_gather_grid(const Geom &g);
