@@ -882,30 +882,51 @@ static int minres_resident(tmop_ctx *c, const double *minv, double *R1, double *
     const bool fp32 = c->precision == TMOP_MIXED;
     const int nbg = mr_gather_grid(c->g);
     unsigned long long *prog = early_stop ? minres_watch(c) : nullptr;
+    // Where the solve waits for launches (up to MR_L2_GRID workgroups), the
+    // element kernel does the second Lanczos update of the iteration before:
+    // two launches per iteration instead of three.
+    const int gridL = (c->g.ne + c->ops.epb - 1) / c->ops.epb;
+    const auto apply_l2 = c->ops.apply_l2[c->storage == TMOP_HESS_COMPACT][fp32];
+    const bool fuse = apply_l2 && !c->g.e2n && c->g.lim == 0.0 && !c->timing && gridL <= MR_L2_GRID;
+    double *R3 = c->sv[SV_W];  // the update's output buffer (the w vectors are not used here)
+    const int nbl = reduce_blocks(n);
     int J = 0;
     for (int j = 0; j < max_its; ++j) {
         if (prog && minres_stopped(c, j)) break;
         // S_{j-1} in mst[(j-1)&1], S_j to mst[j&1]
         MinresState *sin = c->mst + ((j + 1) & 1), *sout = c->mst + (j & 1);
-        const double *zc = c->bank + (long)j * c->bank_stride;
-        double *znext = c->bank + (long)(j + 1) * c->bank_stride;
+        double *zc = c->bank + (long)j * c->bank_stride;
         const bool rec = c->timing && c->tev_used + 3 <= (int)c->tev.size();
         if (rec) (void)hipEventRecord(c->tev[c->tev_used], c->s);
-        apply_elem(c, zc);
+        if (fuse && j > 0) {
+            apply_l2(c->s, c->g, c->tb, c->tg, c->H,
+                     MrL2{R1, R2, minv, R3, zc, P2, P1[(j + 1) & 1], nbg, j - 1, sin}, c->eV);
+            double *t = R1;  // r1 <- r2, r2 <- hv
+            R1 = R2;
+            R2 = R3;
+            R3 = t;
+        } else {
+            apply_elem(c, zc);
+        }
         if (rec) (void)hipEventRecord(c->tev[c->tev_used + 1], c->s);
         // scalars of update j-1 to mhist, then G^T with the first Lanczos
         // update into R1
         mr_gather_upd(c->g, c->csr_ptr, c->csr_ent, c->eV, fp32, j, sin, sout, P1[(j + 1) & 1],
                       P2, nullptr, zc, nullptr, nullptr, nullptr, nullptr, R1, P1[j & 1],
-                      c->mhist, prog, c->s);
+                      c->mhist, prog, fuse ? gridL : nbl, c->s);
         if (rec) {
             (void)hipEventRecord(c->tev[c->tev_used + 2], c->s);
             c->tev_used += 3;
         }
-        mr_lanczos2(n, nbg, j, sout, P1[j & 1], R1, R2, minv, znext, P2, c->s);
-        std::swap(R1, R2);  // r1 <- r2, r2 <- hv
         J = j + 1;
+        if (fuse) continue;
+        mr_lanczos2(n, nbg, j, sout, P1[j & 1], R1, R2, minv, c->bank + (long)J * c->bank_stride, P2,
+                    c->s);
+        std::swap(R1, R2);  // r1 <- r2, r2 <- hv
     }
+    if (fuse && J > 0)
+        mr_lanczos2(n, nbg, J - 1, c->mst + ((J - 1) & 1), P1[(J - 1) & 1], R1, R2, minv,
+                    c->bank + (long)J * c->bank_stride, P2, c->s);
     // the last update, then dx from the resident vectors (dx = 0 from the
     // start when nothing ran)
     if (J > 0)
@@ -939,7 +960,7 @@ static int minres_three_term(tmop_ctx *c, const double *minv, double *const P1[2
         // deferred update of iteration j-1 (formula's w1, w2 = buffers W2, W;
         // new w into W1), then G^T with the first Lanczos update into R1
         mr_gather_upd(c->g, c->csr_ptr, c->csr_ent, c->eV, fp32, j, sin, sout, P1[(j + 1) & 1],
-                      P2, ZP, ZC, W2, W, W1, dx, R1, P1[j & 1], nullptr, prog, c->s);
+                      P2, ZP, ZC, W2, W, W1, dx, R1, P1[j & 1], nullptr, prog, reduce_blocks(n), c->s);
         if (rec) {
             (void)hipEventRecord(c->tev[c->tev_used + 2], c->s);
             c->tev_used += 3;

@@ -50,9 +50,22 @@ static bool ops2_elem(int p, int nq, Ops *out)
     return false;
 }
 
-template <int P, int NQ>
-static bool fill_minres_one2(Ops *o)
+template <int P, int NQ, typename TT, bool COMPACT>
+static void apply_l2_2(hipStream_t s, const Geom &g, const Tables &t, const Target &w, const void *H,
+                       const MrL2 &a, void *yE)
 {
+    constexpr int EPB = S2<P, NQ>::EPB;
+    hipLaunchKernelGGL((k2_apply_l2<P, NQ, TT, COMPACT>), dim3((g.ne + EPB - 1) / EPB), dim3(BLOCK), 0,
+                       s, g, t, w, (const TT *)H, a, (TT *)yE);
+}
+
+template <int P, int NQ>
+static bool fill_minres2(Ops *o)
+{
+    o->apply_l2[0][0] = apply_l2_2<P, NQ, double, false>;
+    o->apply_l2[0][1] = apply_l2_2<P, NQ, float, false>;
+    o->apply_l2[1][0] = apply_l2_2<P, NQ, double, true>;
+    o->apply_l2[1][1] = apply_l2_2<P, NQ, float, true>;
     o->minres_one[0][0] = minres_one2<P, NQ, double, false>;
     o->minres_one[0][1] = minres_one2<P, NQ, float, false>;
     o->minres_one[1][0] = minres_one2<P, NQ, double, true>;
@@ -64,7 +77,7 @@ bool ops2(int p, int nq, Ops *out)
 {
     if (!ops2_elem(p, nq, out)) return false;
 #define TMOP_CASE(P, NQ) \
-    if (p == P && nq == NQ) return fill_minres_one2<P, NQ>(out);
+    if (p == P && nq == NQ) return fill_minres2<P, NQ>(out);
     TMOP_CASE(1, 2) TMOP_CASE(1, 3) TMOP_CASE(1, 4)
     TMOP_CASE(2, 3) TMOP_CASE(2, 4) TMOP_CASE(2, 5)
     TMOP_CASE(3, 4) TMOP_CASE(3, 5) TMOP_CASE(3, 6)

@@ -12,6 +12,7 @@
 //                               component c in plane 4+c
 // with X and RY overlaid (X is dead once the axis-1 sweep has read it).
 #pragma once
+#include "minres_dev.hpp"
 #include "tmop_dev.hpp"
 
 namespace tmop {
@@ -97,6 +98,42 @@ __device__ __forceinline__ void gather2(const Geom &g, const double *__restrict_
 #pragma unroll
         for (int c = 0; c < 2; ++c) sX[(el * 2 + c) * NP + i] = fix[c] ? (CT)0 : (CT)val[c];
     }
+}
+
+// The input of the action, fixed DoFs as zero: a vector, or what MrL2 makes of
+// one (box meshes; false, and nothing to be done, when the solve has stopped).
+template <int P, int NQ, typename CT>
+__device__ __forceinline__ bool gather2_v(const Geom &g, const double *v, int e0, int nel, CT *sX)
+{
+    gather2<P, NQ>(g, v, e0, nel, sX, true);
+    return true;
+}
+
+template <int P, int NQ, typename CT>
+__device__ __forceinline__ bool gather2_v(const Geom &g, const MrL2 &a, int e0, int nel, CT *sX)
+{
+    using S = S2<P, NQ>;
+    constexpr int NI = S::NI, NP = S::NP;
+    __shared__ double red[BLOCK / 64];
+    const int i = threadIdx.x % NP, el = threadIdx.x / NP;
+    const bool in = (int)threadIdx.x < nel * NP;
+    const int i1 = i % NI, i2 = i / NI;
+    int ex, ey, ez;
+    box_elem<2>(g, in ? e0 + el : 0, ex, ey, ez);
+    const int gx = ex * P + i1, gy = ey * P + i2, node = gx + g.M[0] * gy;
+    const bool own = in && (i1 < P || ex == g.nel[0] - 1) && (i2 < P || ey == g.nel[1] - 1);
+    MrL2Node<2> n;
+    n.load(a, g.nx, node);
+    double ab, z[2], s = 0.0;
+    if (!mr_l2_ratio(a, ab)) return false;
+    n.update(a, g.nx, ab, own, z, s);
+    if (in)
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+            sX[(el * 2 + c) * NP + i] = is_fixed(g, c, node, gx, gy, 0) ? (CT)0 : (CT)z[c];
+    s = block_sum(s, red);
+    if (threadIdx.x == 0) a.part2[blockIdx.x] = s;
+    return true;
 }
 
 // Forward sweeps X -> R1 -> RY: J (plane el*NR + c*2 + b), with VAL also the
@@ -392,9 +429,9 @@ __device__ __forceinline__ void b2_setup(const Geom &g, const Tab &tb, const Tar
 
 // V: blocks of elements that a workgroup of V x BLOCK lanes takes side by side,
 // lanes (., y) the y-th.
-template <int P, int NQ, typename TT, typename CT, bool LIM = false, int V = 1>
+template <int P, int NQ, typename TT, typename CT, bool LIM = false, int V = 1, class VS = const double *>
 __device__ __forceinline__ void b2_apply(const Geom &g, const Tab &tb, const TT *__restrict__ H,
-                                const double *__restrict__ v, CT *__restrict__ yE, int e0, int nel)
+                                const VS v, CT *__restrict__ yE, int e0, int nel)
 {
     using S = S2<P, NQ>;
     constexpr int NR = Planes2<LIM>::NR;
@@ -402,7 +439,7 @@ __device__ __forceinline__ void b2_apply(const Geom &g, const Tab &tb, const TT 
     Lds2<P, NQ, CT, NR> &L = Ls[V == 1 ? 0 : threadIdx.y];
     __shared__ double sw[LIM ? NQ : 1];
     if (LIM) weights_to_lds<NQ>(tb, sw);
-    gather2<P, NQ>(g, v, e0, nel, L.X, true);
+    if (!gather2_v<P, NQ>(g, v, e0, nel, L.X)) return;
     __syncthreads();
     forward2<P, NQ, CT, NR, LIM>(tb, L.X, L.R1, L.RY, nel);
     for (int idx = threadIdx.x; idx < nel * S::NQ2; idx += BLOCK) {
@@ -505,9 +542,9 @@ __device__ __forceinline__ void b2_setupc(const Geom &g, const Tab &tb, const Ta
     }
 }
 
-template <int P, int NQ, typename TT, typename CT, bool LIM = false, int V = 1>
+template <int P, int NQ, typename TT, typename CT, bool LIM = false, int V = 1, class VS = const double *>
 __device__ __forceinline__ void b2_applyc(const Geom &g, const Tab &tb, const Target &tg,
-                                 const TT *__restrict__ Q, const double *__restrict__ v,
+                                 const TT *__restrict__ Q, const VS v,
                                  CT *__restrict__ yE, int e0, int nel)
 {
     using S = S2<P, NQ>;
@@ -516,7 +553,7 @@ __device__ __forceinline__ void b2_applyc(const Geom &g, const Tab &tb, const Ta
     Lds2<P, NQ, CT, NR> &L = Ls[V == 1 ? 0 : threadIdx.y];
     __shared__ double sw[LIM ? NQ : 1];
     if (LIM) weights_to_lds<NQ>(tb, sw);
-    gather2<P, NQ>(g, v, e0, nel, L.X, true);
+    if (!gather2_v<P, NQ>(g, v, e0, nel, L.X)) return;
     __syncthreads();
     forward2<P, NQ, CT, NR, LIM>(tb, L.X, L.R1, L.RY, nel);
     for (int idx = threadIdx.x; idx < nel * S::NQ2; idx += BLOCK) {
@@ -756,6 +793,19 @@ __global__ __launch_bounds__(BLOCK) void k2_applyc(Geom g, Tables tba, Target tg
     constexpr int EPB = S2<P, NQ>::EPB;
     const int e0 = blockIdx.x * EPB;
     b2_applyc<P, NQ, TT, CT, LIM>(g, tb, tg, Q, v, yE, e0, min(EPB, g.ne - e0));
+}
+
+// The action on the next Lanczos vector, which it works out (MrL2).
+template <int P, int NQ, typename TT, bool COMPACT>
+__global__ __launch_bounds__(BLOCK) void k2_apply_l2(Geom g, Tables tba, Target tg, const TT *__restrict__ H, MrL2 a, TT *__restrict__ yE)
+{
+    const Tab tb = kernel_tables<sizeof(Geom)>();
+    constexpr int EPB = S2<P, NQ>::EPB;
+    const int e0 = blockIdx.x * EPB, nel = min(EPB, g.ne - e0);
+    if constexpr (COMPACT)
+        b2_applyc<P, NQ, TT, TT, false, 1, MrL2>(g, tb, tg, H, a, yE, e0, nel);
+    else
+        b2_apply<P, NQ, TT, TT, false, 1, MrL2>(g, tb, H, a, yE, e0, nel);
 }
 
 template <int P, int NQ, typename TT, bool LIM>

@@ -24,6 +24,7 @@
 // backward: RY(Y) -> R2 -> R1 -> E-vector.
 #pragma once
 #include "mfma3.hpp"
+#include "minres_dev.hpp"
 #include "tmop_dev.hpp"
 
 namespace tmop {
@@ -210,6 +211,66 @@ __device__ __forceinline__ void gather3(const Geom &g, const double *__restrict_
     gather3_load<P, NQ>(g, vec, e0, nel, masked, r, sub);
     gather3_store<P, NQ, CT>(r, nel, sX);
 }
+
+// The input of the action, fixed DoFs as zero, in a load phase and a phase that
+// puts it into LDS: a vector, or what MrL2 makes of one (box meshes; store is
+// false, and nothing to be done, when the solve has stopped).
+template <int P, int NQ, int T2, class VS>
+struct GathV3 {
+    Gath3<P, NQ, T2> r;
+    __device__ __forceinline__ void load(const Geom &g, const double *v, int e0, int nel)
+    {
+        gather3_load<P, NQ, T2>(g, v, e0, nel, true, r);
+    }
+    template <typename CT>
+    __device__ __forceinline__ bool store(const Geom &, const double *, int, int nel, CT *sX)
+    {
+        gather3_store<P, NQ, CT, T2>(r, nel, sX);
+        return true;
+    }
+};
+
+template <int P, int NQ, int T2>
+struct GathV3<P, NQ, T2, MrL2> {
+    using S = S3<P, NQ>;
+    static_assert(T2 == 2 && S::EPB * S::NP <= BLOCK, "one node per lane");
+    MrL2Node<3> n;
+    int gx, gy, gz;
+    bool in, own;
+    __device__ __forceinline__ void load(const Geom &g, const MrL2 &a, int e0, int nel)
+    {
+        constexpr int NI = S::NI, NP = S::NP;
+        const int el = threadIdx.x / NP, i = threadIdx.x % NP;
+        in = (int)threadIdx.x < nel * NP;
+        const int i1 = i % NI, i2 = (i / NI) % NI, i3 = i / (NI * NI);
+        int ex, ey, ez;
+        box_elem<3>(g, in ? e0 + el : 0, ex, ey, ez);
+        gx = ex * P + i1;
+        gy = ey * P + i2;
+        gz = ez * P + i3;
+        own = in && (i1 < P || ex == g.nel[0] - 1) && (i2 < P || ey == g.nel[1] - 1) &&
+              (i3 < P || ez == g.nel[2] - 1);
+        n.load(a, g.nx, gx + g.M[0] * (gy + g.M[1] * gz));
+    }
+    template <typename CT>
+    __device__ __forceinline__ bool store(const Geom &g, const MrL2 &a, int, int, CT *sX)
+    {
+        constexpr int NP = S::NP;
+        __shared__ double red[BLOCK / 64];
+        double ab, z[3], s = 0.0;
+        if (!mr_l2_ratio(a, ab)) return false;
+        n.update(a, g.nx, ab, own, z, s);
+        if (in) {
+            const int el = threadIdx.x / NP, i = threadIdx.x % NP;
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+                sX[(el * 3 + c) * NP + i] = is_fixed(g, c, (int)n.at, gx, gy, gz) ? (CT)0 : (CT)z[c];
+        }
+        s = block_sum(s, red);
+        if (threadIdx.x == 0) a.part2[blockIdx.x] = s;
+        return true;
+    }
+};
 
 // Forward sweeps X -> R1 -> R2 -> RY (J at every point, plane el*NR + c*3 + b;
 // with VAL also the value of component c, plane el*NR + 9 + c).
@@ -824,10 +885,11 @@ __device__ __forceinline__ void apply_point3(const double *sw, const Geom &g, co
 // CT = double (FP64) or float (mixed: FP32 tensor, FP32 arithmetic and
 // accumulation).  This is the point-pass body; b3_apply chooses between it
 // and the layer-chunked body (b3_apply_layers).
-template <int P, int NQ, typename TT, typename CT, bool LIM = false, int T2 = 2>
+template <int P, int NQ, typename TT, typename CT, bool LIM = false, int T2 = 2,
+          class VS = const double *>
 __device__ __forceinline__ void b3_apply_points(const Geom &g, const Tab &tb,
                                                 const TT *__restrict__ H,
-                                                const double *__restrict__ v,
+                                                const VS v,
                                                 CT *__restrict__ yE, int e0, int nel)
 {
     using S = S3<P, NQ, T2>;
@@ -850,8 +912,8 @@ __device__ __forceinline__ void b3_apply_points(const Geom &g, const Tab &tb,
     if (LIM) weights_to_lds<NQ>(tb, sw);
     // v loads first, then the tensor loads, then v to LDS: waiting for v
     // leaves the tensor loads in flight
-    Gath3<P, NQ, T2> gv;
-    gather3_load<P, NQ, T2>(g, v, e0, nel, true, gv);
+    GathV3<P, NQ, T2, VS> gv;
+    gv.load(g, v, e0, nel);
     const int npts = nel * S::NQ3;
     if constexpr (PF) {
         // point data of pass k; lanes past the last point re-read the first
@@ -864,7 +926,7 @@ __device__ __forceinline__ void b3_apply_points(const Geom &g, const Tab &tb,
                                              t % S::NQ3, dst);
         };
         load_pass(0, hraw[0]);
-        gather3_store<P, NQ, CT, T2>(gv, nel, L.X);
+        if (!gv.template store<CT>(g, v, e0, nel, L.X)) return;
         __syncthreads();
         forward3<P, NQ, CT, NR, LIM>(tb, L.X, L.R1, L.R2, L.RY, nel);
 #pragma unroll
@@ -885,7 +947,7 @@ __device__ __forceinline__ void b3_apply_points(const Geom &g, const Tab &tb,
             const int el = t / S::NQ3, q = t % S::NQ3;
             qdata_load<TT, 45, S::NQ3, true>(H + (size_t)(e0 + el) * QL::STRIDE, q, hraw);
         }
-        gather3_store<P, NQ, CT, T2>(gv, nel, L.X);
+        if (!gv.template store<CT>(g, v, e0, nel, L.X)) return;
         __syncthreads();
         forward3<P, NQ, CT, NR, LIM>(tb, L.X, L.R1, L.R2, L.RY, nel);
         for (int idx = threadIdx.x; idx < npts; idx += BLOCK) {
@@ -1192,10 +1254,11 @@ __device__ __forceinline__ void b3_setupc(const Geom &g, const Tab &tb, const Ta
     }
 }
 
-template <int P, int NQ, typename TT, typename CT, bool LIM = false, int T2 = 2>
+template <int P, int NQ, typename TT, typename CT, bool LIM = false, int T2 = 2,
+          class VS = const double *>
 __device__ __forceinline__ void b3_applyc_points(const Geom &g, const Tab &tb,
                                                  const Target &tg, const TT *__restrict__ Q,
-                                                 const double *__restrict__ v,
+                                                 const VS v,
                                                  CT *__restrict__ yE, int e0, int nel)
 {
     using S = S3<P, NQ, T2>;
@@ -1213,8 +1276,8 @@ __device__ __forceinline__ void b3_applyc_points(const Geom &g, const Tab &tb,
     __shared__ Lds3<P, NQ, CT, NR, T2> L;
     __shared__ double sw[LIM ? NQ : 1];
     if (LIM) weights_to_lds<NQ>(tb, sw);
-    Gath3<P, NQ, T2> gv;
-    gather3_load<P, NQ, T2>(g, v, e0, nel, true, gv);
+    GathV3<P, NQ, T2, VS> gv;
+    gv.load(g, v, e0, nel);
     const int npts = nel * S::NQ3;
     auto load_pass = [&](int k, TT *dst) {
         const int i = threadIdx.x + k * BLOCK;
@@ -1223,7 +1286,7 @@ __device__ __forceinline__ void b3_applyc_points(const Geom &g, const Tab &tb,
     };
     TT draw[PF ? 2 : 1][NC3];
     if (ONE || PF) load_pass(0, draw[0]);
-    gather3_store<P, NQ, CT, T2>(gv, nel, L.X);
+    if (!gv.template store<CT>(g, v, e0, nel, L.X)) return;
     __syncthreads();
     forward3<P, NQ, CT, NR, LIM>(tb, L.X, L.R1, L.R2, L.RY, nel);
 #pragma unroll
@@ -1653,6 +1716,19 @@ __global__ __launch_bounds__(BLOCK) void k3_apply(Geom g, Tables tba, const TT *
     constexpr int EPB = S3<P, NQ, T2>::EPB;
     const int e0 = xcd_block(blockIdx.x, gridDim.x) * EPB;
     b3_apply<P, NQ, TT, CT, LIM, T2>(g, tb, H, v, yE, e0, min(EPB, g.ne - e0));
+}
+
+// The action on the next Lanczos vector, which it works out (MrL2).
+template <int P, int NQ, typename TT, bool COMPACT>
+__global__ __launch_bounds__(BLOCK) void k3_apply_l2(Geom g, Tables tba, Target tg, const TT *__restrict__ H, MrL2 a, TT *__restrict__ yE)
+{
+    const Tab tb = kernel_tables<sizeof(Geom)>();
+    constexpr int EPB = S3<P, NQ>::EPB;
+    const int e0 = xcd_block(blockIdx.x, gridDim.x) * EPB, nel = min(EPB, g.ne - e0);
+    if constexpr (COMPACT)
+        b3_applyc_points<P, NQ, TT, TT, false, 2, MrL2>(g, tb, tg, H, a, yE, e0, nel);
+    else
+        b3_apply_points<P, NQ, TT, TT, false, 2, MrL2>(g, tb, H, a, yE, e0, nel);
 }
 
 template <int P, int NQ, typename TT, bool MF = false>

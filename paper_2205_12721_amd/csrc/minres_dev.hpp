@@ -114,4 +114,48 @@ __device__ inline MrUpd mr_scalars(const MinresState &sin, int jm, double alpha,
     return u;
 }
 
+
+// MrL2 at one node: loads first, then (after the sum of alpha) the new values,
+// which every element of the node works out alike and its owner writes.
+template <int D>
+struct MrL2Node {
+    double h[D], q[D], m[D];
+    size_t at;
+    __device__ __forceinline__ void load(const MrL2 &a, int nx, int node)
+    {
+        at = node;
+#pragma unroll
+        for (int c = 0; c < D; ++c) {
+            h[c] = a.hv[at + (size_t)c * nx];
+            q[c] = a.r2[at + (size_t)c * nx];
+            m[c] = a.minv ? a.minv[at + (size_t)c * nx] : 1.0;
+        }
+    }
+    __device__ __forceinline__ void update(const MrL2 &a, int nx, double ab, bool own, double *z,
+                                           double &s) const
+    {
+#pragma unroll
+        for (int c = 0; c < D; ++c) {
+            const double t = h[c] - ab * q[c];
+            z[c] = a.minv ? m[c] * t : t;
+            if (own) {
+                a.hvo[at + (size_t)c * nx] = t;
+                a.z[at + (size_t)c * nx] = z[c];
+                s += t * z[c];
+            }
+        }
+    }
+};
+
+// alpha / beta to every lane; false when the solve stopped before iteration j
+__device__ __forceinline__ bool mr_l2_ratio(const MrL2 &a, double &ab)
+{
+    const int stop = a.st->stop;
+    const double beta = a.st->beta;
+    double alpha, unused;
+    sum_partials(a.part1, a.nb1, nullptr, 0, alpha, unused);
+    ab = alpha / beta;
+    return a.j <= stop;
+}
+
 }  // namespace tmop

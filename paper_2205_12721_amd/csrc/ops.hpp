@@ -9,7 +9,8 @@
 
 namespace tmop {
 
-struct MrOne;  // minres_one.hpp
+struct MrOne;  // vec.hpp
+struct MrL2;
 
 struct Ops {
     int epb;  // elements per workgroup
@@ -75,6 +76,11 @@ struct Ops {
                      const double *x, float *H, double *dE);
     decltype(setupd64) setupcd64;  // the same for compact storage
     decltype(setupd32) setupcd32;
+    // the action on the next Lanczos vector, with the update that gives it, in
+    // the base tile shape [storage][precision]; null where there is none;
+    // without the limiting term, box meshes
+    void (*apply_l2[2][2])(hipStream_t, const Geom &, const Tables &, const Target &, const void *H,
+                           const MrL2 &, void *yE) = {};
     // the whole MINRES solve in one workgroup [storage][precision]; false,
     // with nothing launched, for a mesh too large for it.  Null where there
     // is none; without the limiting term.

@@ -230,9 +230,24 @@ inline void fill_setupd3(Ops &o)
     }
 }
 
+template <int P, int NQ, typename TT, bool COMPACT>
+inline void apply_l2_3(hipStream_t s, const Geom &g, const Tables &t, const Target &w, const void *H,
+                       const MrL2 &a, void *yE)
+{
+    constexpr int EPB = S3<P, NQ>::EPB;
+    hipLaunchKernelGGL((k3_apply_l2<P, NQ, TT, COMPACT>), dim3((g.ne + EPB - 1) / EPB), dim3(BLOCK), 0,
+                       s, g, t, w, (const TT *)H, a, (TT *)yE);
+}
+
 template <int P, int NQ>
 inline void fill_tiles_k3(Ops &o)
 {
+    if constexpr (S3<P, NQ>::NQ3 <= BLOCK) {
+        o.apply_l2[0][0] = apply_l2_3<P, NQ, double, false>;
+        o.apply_l2[0][1] = apply_l2_3<P, NQ, float, false>;
+        o.apply_l2[1][0] = apply_l2_3<P, NQ, double, true>;
+        o.apply_l2[1][1] = apply_l2_3<P, NQ, float, true>;
+    }
     fill_tile3<P, NQ, 1, 0>(o);
     fill_tile3<P, NQ, 2, 1>(o);
     fill_tile3<P, NQ, 4, 2>(o);

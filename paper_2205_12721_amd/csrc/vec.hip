@@ -784,11 +784,11 @@ void mr_gather_upd(const Geom &g, const int32_t *csr_ptr, const int32_t *csr_ent
                    bool fp32, int j, const MinresState *sin, MinresState *sout,
                    const double *p1prev, const double *p2prev, const double *zp, const double *zc,
                    const double *w1, const double *w2, double *wout, double *x, double *r1hv,
-                   double *part, MrHist *hist, unsigned long long *progress, hipStream_t s)
+                   double *part, MrHist *hist, unsigned long long *progress, int nb2, hipStream_t s)
 {
     // one node per lane up to 1024 workgroups; its partials (alpha) number
-    // nb1, those of the vector kernels (beta^2) nb2
-    const int nb1 = mr_gather_grid(g), nb2 = reduce_blocks((long)g.dim * g.nx);
+    // nb1, those of beta^2 nb2
+    const int nb1 = mr_gather_grid(g);
 #define TMOP_G(D, T)                                                                          \
     hipLaunchKernelGGL((k_mr_gather_upd<D, T>), dim3(nb1), dim3(VBLOCK), 0, s, g, csr_ptr,    \
                        csr_ent, (const T *)eV, j, sin, sout, p1prev, nb1, p2prev, nb2, zp, zc, \

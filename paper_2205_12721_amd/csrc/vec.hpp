@@ -27,6 +27,22 @@ struct MrHist {
 };
 // Most updates one combination can take (one lane per coefficient).
 constexpr int MR_MAX_BASIS = 256;
+// The second Lanczos update of iteration j (k_mr_l2), done by the next
+// iteration's element kernel as it gathers its input: z = M^{-1}(hv - alpha /
+// beta r2), alpha the sum of part1[0..nb1).  The new hv goes to hvo, another
+// buffer, since elements share nodes; part2 gets a partial of beta^2 per
+// workgroup.
+struct MrL2 {
+    const double *hv, *r2, *minv;
+    double *hvo, *z, *part2;
+    const double *part1;
+    int nb1, j;
+    const MinresState *st;
+};
+// Most workgroups of an element kernel that does so (each of the next
+// kernel's sums their partials).  Below it the solve waits for launches, some
+// 4 us each: hex 8^3 p3 n_q5 (256 workgroups) 16.2 -> 13.5 us per iteration.
+constexpr int MR_L2_GRID = 1024;
 // A MINRES solve in one launch (minres_one.hpp): dx = H_c^{-1} b with the Lanczos vectors z_j in
 // bank (as in minres_resident), at most max_its iterations.  mst[0] and
 // mst[1] get the final state.
@@ -83,7 +99,7 @@ void mr_gather_upd(const Geom &g, const int32_t *csr_ptr, const int32_t *csr_ent
                    bool fp32, int j, const MinresState *sin, MinresState *sout,
                    const double *p1prev, const double *p2prev, const double *zp, const double *zc,
                    const double *w1, const double *w2, double *wout, double *x, double *r1hv,
-                   double *part, MrHist *hist, unsigned long long *progress, hipStream_t s);
+                   double *part, MrHist *hist, unsigned long long *progress, int nb2, hipStream_t s);
 // What mr_gather_upd writes to progress: gathers begun, and in the upper half
 // whether the solve has stopped.
 inline __host__ __device__ unsigned long long mr_progress(int begun, bool stopped)
