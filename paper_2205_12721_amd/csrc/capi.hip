@@ -268,7 +268,7 @@ struct tmop_ctx {
     double *scal = nullptr;   // device scalars
     double *hscal = nullptr;  // pinned host memory
     double *hscal_dev = nullptr;  // its device address (kernels write results there)
-    double *esl = nullptr;        // scratch of the energy reductions
+    double *esl = nullptr;        // scratch of the energy reductions (the end of part)
     int32_t *csr_ptr = nullptr, *csr_ent = nullptr;
     double *diag = nullptr, *minv = nullptr;
     bool have_diag = false;
@@ -361,7 +361,6 @@ static void free_ctx(tmop_ctx *c)
     hipFree(c->eV);
     hipFree(c->part);
     hipFree(c->scal);
-    hipFree(c->esl);
     if (c->hscal) hipHostFree(c->hscal);
     hipFree(c->csr_ptr);
     hipFree(c->csr_ent);
@@ -457,9 +456,9 @@ extern "C" int tmop_create(tmop_ctx **out, const tmop_mesh_desc *m, const tmop_p
     if (e == hipSuccess) e = hipMalloc((void **)&(ptr), (bytes));
     ALLOC(c->H, c->H_bytes);
     ALLOC(c->eV, c->eV_bytes);
-    ALLOC(c->part, sizeof(double) * c->part_len);
+    ALLOC(c->part, sizeof(double) * (c->part_len + ENERGY_SCRATCH));
+    c->esl = c->part + c->part_len;
     ALLOC(c->scal, sizeof(double) * 64);
-    ALLOC(c->esl, sizeof(double) * ENERGY_SCRATCH);
     ALLOC(c->diag, sizeof(double) * c->ndof);
     ALLOC(c->minv, sizeof(double) * c->ndof);
     ALLOC(c->mst, 2 * sizeof(MinresState));
