@@ -1,27 +1,41 @@
 // Quad kernel instantiations for p = 1..4, n_q = p+1 .. p+3.
+#include "cols2.hpp"
 #include "kernels2d.hpp"
 #include "minres_one.hpp"
 #include "ops.hpp"
 
 namespace tmop {
 
-// The kernels without the limiting term (quads have one form of each).
+// The kernels without the limiting term; energy and gradient in the form that
+// ColForm2 gives for the mesh.
 template <int P, int NQ>
 struct plain_k2 {
     static constexpr int EPB = S2<P, NQ>::EPB;
-    static int energy_epb(int) { return EPB; }
-    static dim3 grid(const Geom &g) { return dim3((g.ne + EPB - 1) / EPB); }
+    using CE = C2<P, NQ, ColForm2<P, NQ>::WL>;
+    static_assert(CE::EPB >= EPB, "the no-allocation energy takes the meshes it took");
+    static bool col(int ne) { return ne >= ColForm2<P, NQ>::energy_min; }
+    static int energy_epb(int ne) { return col(ne) ? CE::EPB : EPB; }
+    static dim3 grid(const Geom &g, int epb = EPB) { return dim3((g.ne + epb - 1) / epb); }
     static void energy(hipStream_t s, const Geom &g, const Tables &t, const Target &w,
                        const double *x, double *part)
     {
-        hipLaunchKernelGGL((k2_energy<P, NQ, false>), grid(g), dim3(BLOCK), 0, s, g, t, w, x, part);
+        if (col(g.ne))
+            hipLaunchKernelGGL((k2c_energy<CE, false, true>), grid(g, CE::EPB), dim3(CE::WL), 0, s, g,
+                               t, w, x, (double *)nullptr, part);
+        else
+            hipLaunchKernelGGL((k2_energy<P, NQ, false>), grid(g), dim3(BLOCK), 0, s, g, t, w, x,
+                               part);
     }
     template <bool EN>
     static void gradient(hipStream_t s, const Geom &g, const Tables &t, const Target &w,
                          const double *x, double *gE, double *part)
     {
-        hipLaunchKernelGGL((k2_gradient<P, NQ, false, EN>), grid(g), dim3(BLOCK), 0, s, g, t, w, x,
-                           gE, part);
+        if (col(g.ne))
+            hipLaunchKernelGGL((k2c_energy<CE, true, EN>), grid(g, CE::EPB), dim3(CE::WL), 0, s, g, t,
+                               w, x, gE, part);
+        else
+            hipLaunchKernelGGL((k2_gradient<P, NQ, false, EN>), grid(g), dim3(BLOCK), 0, s, g, t, w, x,
+                               gE, part);
     }
     template <typename TT>
     static void setupc(hipStream_t s, const Geom &g, const Tables &t, const Target &w,
