@@ -52,15 +52,15 @@ HBM_PEAK_GBS = 8000.0  # MI355X HBM3E peak, GB/s
 # entry names the SHA-256 of the kernel sources (csrc_sha256()) and is
 # reported as null once they differ.  Summary and commands:
 # profiles/hessian_apply_traffic_24cube_q3.md.
-_SHA_C2 = "a40a481d36b6bc943531a4a21cf3d3373af65a4006afbdadefbf6a753cfb6637"
+_SHA_C2 = "3e980f8cef5f819bd4e1afc3c8bbdf50ef75d27ce501b22c7e585d946f72553c"
 TRAFFIC = {
-    ("c2", "tensor_fp64"): {"bytes": 714546511, "elements_per_workgroup": 2,
+    ("c2", "tensor_fp64"): {"bytes": 723345183, "elements_per_workgroup": 2,
                         "csrc_sha256": _SHA_C2},
-    ("c2", "tensor_mixed"): {"bytes": 371956710, "elements_per_workgroup": 2,
+    ("c2", "tensor_mixed"): {"bytes": 369890865, "elements_per_workgroup": 2,
                         "csrc_sha256": _SHA_C2},
-    ("c2", "compact_fp64"): {"bytes": 249300935, "elements_per_workgroup": 2,
+    ("c2", "compact_fp64"): {"bytes": 249297014, "elements_per_workgroup": 2,
                         "csrc_sha256": _SHA_C2},
-    ("c2", "compact_mixed"): {"bytes": 137360473, "elements_per_workgroup": 2,
+    ("c2", "compact_mixed"): {"bytes": 137488831, "elements_per_workgroup": 2,
                         "csrc_sha256": _SHA_C2},
 }
 
@@ -68,9 +68,10 @@ TRAFFIC = {
 # Sources of the device code a single-context Hessian action runs (its element
 # kernels, the node gather and what they include); host-only files (capi.hip,
 # batch.hip) and other element classes' units do not change the measured kernels.
-ACTION_SOURCES = ("gather.hpp", "kernels3d.hpp", "kernels2d.hpp", "k2.hip", "k3_p1.hip", "mfma3.hpp",
-                  "k3_p2.hip", "k3_p3.hip", "k3_p4.hip", "ops.hpp", "tiles3.hpp",
-                  "tmop_dev.hpp", "vec.hip", "vec.hpp")
+ACTION_SOURCES = ("cols.hpp", "cols2.hpp", "cols3.hpp", "gather.hpp", "kernels3d.hpp", "kernels2d.hpp",
+                  "k2.hip", "k3_p1.hip", "mfma3.hpp", "k3_p2.hip", "k3_p3.hip", "k3_p4.hip",
+                  "minres_dev.hpp", "minres_one.hpp", "ops.hpp", "tiles3.hpp", "tmop_dev.hpp", "vec.hip",
+                  "vec.hpp")
 
 
 def csrc_sha256():
