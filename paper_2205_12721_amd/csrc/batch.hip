@@ -46,8 +46,7 @@ enum {
 constexpr int BZIN = BNV;
 static_assert(BNV < NVEC, "too many vectors per slot");
 
-constexpr int VB = 256;      // threads per vector block
-constexpr int VCH = 3 * VB;  // DoFs per vector tile
+constexpr int VB = VTILE_LANES;  // threads per vector block
 
 struct VTile {
     int slot;
@@ -382,11 +381,11 @@ __global__ __launch_bounds__(VB) void kv_mr_gather_upd(
     // G^T with one lane per node for all components (the copy positions are
     // worked out once per node and the loads of every component are in
     // flight together): the slot's nodes are split evenly over its vector
-    // tiles (the tiles of a slot are consecutive VCH-DoF chunks from 0).
-    // The lane's first node (hexes: its only one) is loaded before the partial
-    // sums are, and those before the state says whether they are needed.
-    const int ntile = (DIM * g.nx + VCH - 1) / VCH, jt = t.start / VCH;
-    const int npt = (g.nx + ntile - 1) / ntile;
+    // tiles.  The lane's first node (its only one on hexes of three DoFs per
+    // lane) is loaded before the partial sums are, and those before the state
+    // says whether they are needed.
+    const int jt = pbase + (int)blockIdx.x - r.vbegin;
+    const int npt = (g.nx + r.vcount - 1) / r.vcount;
     const int nb = jt * npt, ne = nb + npt < g.nx ? nb + npt : g.nx;
     const int node0 = nb + (int)threadIdx.x;
     double *__restrict__ r1 = S.vec[vr1];
@@ -476,9 +475,9 @@ __global__ __launch_bounds__(VB) void kv_mr_l2(const VTile *__restrict__ vt,
     const bool useM = jac[t.slot] != 0;
     const double *__restrict__ m = S.vec[BMINV], *__restrict__ r2 = S.vec[vr2];
     double *__restrict__ hv = S.vec[vhv];
-    // the tile's entries and the partial sums are in flight together, and
-    // neither waits for the state
-    constexpr int PL = VCH / VB;
+    // the lane's first entries (three per lane: all of them) and the partial
+    // sums are in flight together, and neither waits for the state
+    constexpr int PL = 3;
     double h[PL], q[PL], mi[PL];
 #pragma unroll
     for (int k = 0; k < PL; ++k) {
@@ -506,6 +505,13 @@ __global__ __launch_bounds__(VB) void kv_mr_l2(const VTile *__restrict__ vt,
             z[i] = zi;
             acc += hn * zi;
         }
+    }
+    for (int i = i0 + PL * VB; i < i1; i += VB) {
+        const double hn = hv[i] - c * r2[i];
+        hv[i] = hn;
+        const double zi = useM ? m[i] * hn : hn;
+        z[i] = zi;
+        acc += hn * zi;
     }
     acc = block_sum(acc, red);
     if (threadIdx.x == 0) part2[blockIdx.x] = acc;
@@ -1099,8 +1105,9 @@ static int pool_rebuild(tmop_pool *P)
             SlotH &s = P->slots[si];
             if (!s.used || s.dim != gd || s.prec != gp) continue;
             s.first_vt = (int)P->vts.size();
-            for (int st = 0; st < s.ndof; st += VCH)
-                P->vts.push_back(VTile{si, st, std::min(VCH, s.ndof - st)});
+            const int ch = vtile_dofs(s.ndof);
+            for (long st = 0; st < s.ndof; st += ch)
+                P->vts.push_back(VTile{si, (int)st, (int)std::min((long)ch, s.ndof - st)});
             s.nvt = (int)P->vts.size() - s.first_vt;
             P->rg[si].vbegin = s.first_vt;
             P->rg[si].vcount = s.nvt;

@@ -59,6 +59,22 @@ struct MrOne {
     int max_its;
 };
 
+// DoFs per vector tile (workgroup of VTILE_LANES lanes) of a pool slot: three per
+// lane, and on large slots so many that the slot has at most VTILE_MAX tiles.
+// Every workgroup of the two MINRES vector kernels sums the partials of all of
+// its slot's tiles, so their reads grow with the square of the tile count: with
+// three per lane throughout, a lockstep position of one 48^3 p = 4 slot (28000
+// tiles) took 1818 us, of one 64^3 p = 2 slot 465, of one 32^3 p = 4 slot 357;
+// so limited they take 941, 396 and 287.
+constexpr int VTILE_LANES = 256;
+constexpr int VTILE_MAX = 1024;
+inline int vtile_dofs(int ndof)
+{
+    const long per = (long)VTILE_LANES * VTILE_MAX;
+    const int k = (int)((ndof + per - 1) / per);
+    return VTILE_LANES * (k > 3 ? k : 3);
+}
+
 void launch_gather(const Geom &g, const int32_t *csr_ptr, const int32_t *csr_ent, const void *eV,
                    bool fp32, double *out, int fix_mode, const double *src, hipStream_t s);
 // Energy partials are reduced in slices of ESLICE, or of a multiple of it so
