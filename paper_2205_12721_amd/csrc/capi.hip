@@ -535,6 +535,8 @@ static int energy_mindet_impl(tmop_ctx *c, const double *x, double *F, double *m
     (use_mfma(c) ? c->ops.energyM : c->ops.energy)(c->grid, c->s, c->g, c->tb, c->tg, x, c->part);
     // the last kernel writes the results to the pinned host memory itself
     launch_energy_reduce(c->part, energy_grid(c), c->esl, c->hscal_dev, c->s);
+    // (a launch that failed leaves the results of the call before)
+    HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(c->s));
     const double bad = c->hscal[2];
     if (mindet) *mindet = c->hscal[1];
@@ -581,6 +583,7 @@ static int energy_gradient_impl(tmop_ctx *c, const double *x, double *F, double 
                                                          (double *)c->eV, c->part);
     launch_gather_norm(c->g, c->csr_ptr, c->csr_ent, (const double *)c->eV, g, c->part,
                        energy_grid(c), c->esl, c->hscal_dev, c->s);
+    HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(c->s));
     const double bad = c->hscal[2];
     *md = c->hscal[1];
@@ -793,6 +796,7 @@ static int ensure_solver(tmop_ctx *c)
 static int dot_host(tmop_ctx *c, const double *a, const double *b, double *out)
 {
     launch_dot(c->ndof, a, b, c->part, c->scal + 8, c->s);
+    HIPCHK(hipGetLastError());
     HIPCHK(hipMemcpyAsync(c->hscal + 8, c->scal + 8, sizeof(double), hipMemcpyDeviceToHost, c->s));
     HIPCHK(hipStreamSynchronize(c->s));
     *out = c->hscal[8];
