@@ -1034,7 +1034,13 @@ static int minres_impl(tmop_ctx *c, const double *b, double *dx, int max_its, do
                 c->sv[SV_W1], c->sv[SV_W2], P1[0], c->mst, rtol, c->s);
         minres_three_term(c, minv, P1, P2, dx, max_its, early_stop);
     }
-    HIPCHK(hipGetLastError());
+    const hipError_t le = hipGetLastError();
+    if (le != hipSuccess) {
+        // what was launched still reports to the progress word, which the
+        // next solve resets and reads
+        (void)hipStreamSynchronize(c->s);
+        HIPCHK(le);
+    }
     HIPCHK(hipMemcpyAsync(c->hmst, c->mst, 2 * sizeof(MinresState), hipMemcpyDeviceToHost, c->s));
     HIPCHK(hipStreamSynchronize(c->s));
     const MinresState &fin = c->hmst[0].its >= c->hmst[1].its ? c->hmst[0] : c->hmst[1];

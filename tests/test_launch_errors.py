@@ -2,6 +2,8 @@
 nothing and one of which can be told to fail) takes the runtime's place before the library is loaded.
 Every launch of an evaluation fails in turn: the call has to say so (TMOP_ERR_HIP), since the results
 it would return are those of the call before, and the next call, whose launches succeed, is accepted.
+A MINRES call has to wait, before it returns with the error, for what it did launch: those kernels
+report their progress to the word that the context's next solve reads.
 """
 import os
 import shutil
@@ -105,6 +107,21 @@ print("done")
 """
 
 
+MINRES = DRIVER + r"""
+for dim, ns, p, nq, bank in [(2, (3, 3), 2, 4, None), (2, (90, 90), 1, 3, None), (2, (90, 90), 1, 3, 0),
+                             (3, (4, 3, 2), 2, 4, None), (3, (24, 24, 24), 1, 3, None),
+                             (3, (17, 17, 17), 2, 5, None)]:
+    h, b, dx = context(dim, ns, p, nq, storage=1)
+    assert L.tmop_hessian_setup(h, P(b)) == OK
+    if bank is not None:
+        assert L.tmop_set_lanczos_bank_limit(h, bank) == OK
+    every_launch("minres %s" % (ns,), lambda: L.tmop_minres(h, P(b), P(dx), 12, 1e-9, 0, None),
+                 after=lambda: rt.fake_syncs_after_failure() >= 1)
+    L.tmop_destroy(h)
+print("done")
+"""
+
+
 def _run(tmp_path, script):
     from paper_2205_12721_amd import tmop
     cc = shutil.which("gcc")
@@ -123,3 +140,7 @@ def _run(tmp_path, script):
 
 def test_failed_launch_of_an_evaluation_is_reported(tmp_path):
     _run(tmp_path, EVALUATIONS)
+
+
+def test_failed_minres_waits_for_what_it_launched(tmp_path):
+    _run(tmp_path, MINRES)
