@@ -23,6 +23,8 @@
 // before any lane writes its output.  Every sum runs in the order of the
 // pencil form, so both give the same bits.
 #pragma once
+#include <climits>
+
 #include "cols.hpp"
 #include "kernels3d.hpp"
 
@@ -534,7 +536,7 @@ __device__ __forceinline__ void c3_applyc(const Geom &g, const Tab &tb, const Ta
 //   would accept smaller meshes than it did.
 //   Compact setup: p2 n_q4 105 -> 84, p3 n_q5 39 -> 33, p4 n_q6 88 -> 72; slower
 //   where its stores end runs inside 128-byte lines (p1 n_q9 118 -> 143, p2
-//   n_q5 100 -> 117, p4 n_q9 140 -> 152).
+//   n_q5 100 -> 117, p4 n_q9 140 -> 152; see also the largest meshes below).
 //   Compact action in FP64: p1 n_q3 41 -> 36, p2 n_q3 63 -> 49, p2 n_q4 111 ->
 //   103, p3 n_q4 34 -> 28 with the column re-read from LDS (kept in registers
 //   it takes more than the 256 of two waves per SIMD, 36); from n_q = 5 at p >=
@@ -548,10 +550,21 @@ __device__ __forceinline__ void c3_applyc(const Geom &g, const Tab &tb, const Ta
 // 5.3 / 8.4).  The lines lie where the two meet, counted in workgroups of the
 // pencil form (256 CUs): energy and gradient about 1024 (16^3 p2 n_q4, 1024:
 // 10.6 -> 9.2; 12^3, 432: 7.2 -> 8.2), at p = 4 with n_q <= 6 4096; compact
-// setup 4096, n_q = 6 8192 (20^3 p3, 8000: 30.0 -> 33.9; 24^3: 70 -> 63), n_q >= 7
-// 1024; FP64 action 1024, n_q = 5 2048; FP32 action 1536 for n_q <= 4 and n_q =
+// setup 4096, n_q = 6 8192 (FP64: only p = 4, from 16384 on: 20^3 35.5 -> 38.2,
+// 25^3 91.4 -> 86.6; p3 25^3 81.8 -> 85.7), n_q >= 7 1024; FP64 action 1024, n_q = 5 2048; FP32 action 1536 for n_q <= 4 and n_q =
 // 9 at p <= 2, n_q = 5 and p = 4 n_q <= 7 8192 (p2 n_q5 20^3, 4000: 15.6 -> 17.1;
 // 32^3: 54 -> 47), else 4096.
+//
+// Largest meshes: the setup stores a column layer by layer, n_q^2 points of 16
+// bytes at a time, so the 128-byte lines at both ends of a layer are written in
+// two parts, some time apart.  The 256 MB last-level cache puts them together;
+// beyond it they reach memory as parts.  Where a layer is a few lines long
+// that costs more than the form saves, in FP64 above all (41.4 against 42.5 us
+// at 42^3 p1 n_q3, 200 MB, but 345 against 632 at 84^3; p2 n_q3 53^3 112 / 168;
+// p1 n_q2 81^3 103 / 150): such classes keep the pencil form, or take the
+// column form up to 256 MB of data (p1 n_q4 FP64 32^3 38.2 -> 35.7, 64^3 288 ->
+// 322; p3 n_q5 FP64 25^3 40.0 -> 38.2, 51^3 411 -> 439), in FP32 320 MB (p1 n_q2
+// 81^3 87 -> 72, 90^3 111 -> 113, 128^3 313 -> 345).
 // ------------------------------------------------------------------------
 template <int P, int NQ>
 struct ColForm {
@@ -559,10 +572,15 @@ struct ColForm {
                                   : NQ == 6 ? (P == 3 ? 256 : 128)
                                   : NQ == 9 ? (P <= 3 ? 256 : 128)
                                             : 64;
-    static constexpr int setupc = NQ <= 4 ? 64
-                                  : NQ == 5 ? (P == 2 ? 0 : 64)
-                                  : NQ == 9 ? (P == 3 ? 256 : 0)
-                                            : 128;
+    template <typename TT>
+    static constexpr int setupc()
+    {
+        if (sizeof(TT) == 8 && (NQ <= 3 || (P == 3 && NQ == 6))) return 0;
+        return NQ <= 4   ? 64
+               : NQ == 5 ? (P == 3 ? 64 : 0)
+               : NQ == 9 ? (P == 3 ? 256 : 0)
+                         : 128;
+    }
     template <typename TT>
     static constexpr int applyc()
     {
@@ -579,7 +597,11 @@ struct ColForm {
     // smallest element counts
     static constexpr int EPB0 = S3<P, NQ>::EPB;
     static constexpr int energy_min = EPB0 * (P == 4 && NQ <= 6 ? 4096 : 1024);
-    static constexpr int setupc_min = EPB0 * (NQ >= 7 ? 1024 : NQ == 6 ? 8192 : 4096);
+    template <typename TT>
+    static constexpr int setupc_min()
+    {
+        return EPB0 * (NQ >= 7 ? 1024 : NQ == 6 ? (sizeof(TT) == 8 ? 16384 : 8192) : 4096);
+    }
     template <typename TT>
     static constexpr int applyc_min()
     {
@@ -587,6 +609,22 @@ struct ColForm {
         return EPB0 * (NQ <= 4 || (NQ == 9 && P <= 2) ? 1536
                        : NQ == 5 || (P == 4 && NQ <= 7) ? 8192
                                                         : 4096);
+    }
+    // largest element counts: no limit, or so many MB of quadrature data (whole
+    // lines of the runs and planes, without what pads them further)
+    template <typename TT, long MB>
+    static constexpr int within()
+    {
+        using L = QLay<TT, NC3, NQ * NQ * NQ>;
+        constexpr long NQ3 = NQ * NQ * NQ, RUN = (NQ3 * 16 + 127) / 128 * 128;
+        constexpr long PLANE = (NQ3 * (long)sizeof(TT) + 127) / 128 * 128;
+        return (int)((MB << 20) / (L::NV * RUN + (NC3 - L::TAIL) * PLANE));
+    }
+    template <typename TT>
+    static constexpr int setupc_max()
+    {
+        if (sizeof(TT) == 8 && (NQ == 5 || (P == 1 && NQ == 4))) return within<TT, 256>();
+        return NQ == 2 ? within<TT, 320>() : INT_MAX;
     }
 };
 

@@ -94,12 +94,12 @@ struct Ops {
 typedef void (*BLaunch)(int grid, hipStream_t, const Tables &, const Tile *, const SlotDev *,
                         const int *gate, int vin, double *part);
 
-// A batched kernel in column form: elements per tile, the fewest elements of
-// a class from which it is used (none: never), its launcher.
+// A batched kernel in column form: elements per tile, the fewest and the most
+// elements of a class with which it is used, its launcher (null: never).
 struct BCol {
-    int epb = 0, min_elems = 0;
+    int epb = 0, min_elems = 0, max_elems = 0;
     BLaunch launch = nullptr;
-    bool use(int ne) const { return launch && ne >= min_elems; }
+    bool use(int ne) const { return launch && ne >= min_elems && ne <= max_elems; }
 };
 
 struct BOps {

@@ -43,9 +43,10 @@ struct plain_k3 {
     static void setupc(hipStream_t s, const Geom &g, const Tables &t, const Target &w,
                        const double *x, TT *Q)
     {
-        if constexpr (F::setupc > 0) {
-            using C = C3<P, NQ, F::setupc>;
-            if (g.ne >= F::setupc_min) {
+        constexpr int WL = F::template setupc<TT>();
+        if constexpr (WL > 0) {
+            using C = C3<P, NQ, WL>;
+            if (g.ne >= F::template setupc_min<TT>() && g.ne <= F::template setupc_max<TT>()) {
                 hipLaunchKernelGGL((k3c_setupc<C, TT>), grid(g, C::EPB), dim3(C::WL), 0, s, g, t, w,
                                    x, Q);
                 return;
@@ -72,17 +73,17 @@ struct plain_k3 {
 };
 
 // Column form of the batched compact setup and action, by precision; taken
-// for a class whose resident meshes have at least so many elements together.
+// for a class whose resident meshes have so many elements together.
 // (Energy and gradient keep the pencil form there: a solve's energy is summed
 // by tiles, and is to have the same bits alone and with others.)
 template <int P, int NQ, typename TT, int IDX>
 inline void fill_bcol3(BOps &o)
 {
     using F = ColForm<P, NQ>;
-    constexpr int WS = F::setupc, WA = F::template applyc<TT>();
+    constexpr int WS = F::template setupc<TT>(), WA = F::template applyc<TT>();
     if constexpr (WS > 0) {
         using C = C3<P, NQ, WS>;
-        o.setupc_col[IDX] = BCol{C::EPB, F::setupc_min,
+        o.setupc_col[IDX] = BCol{C::EPB, F::template setupc_min<TT>(), F::template setupc_max<TT>(),
                                  [](int n, hipStream_t s, const Tables &t, const Tile *tl,
                                     const SlotDev *sl, const int *gt, int vin, double *) {
                                      hipLaunchKernelGGL((kb3c_setupc<C, TT>), dim3(n), dim3(C::WL),
@@ -92,7 +93,7 @@ inline void fill_bcol3(BOps &o)
     if constexpr (WA > 0) {
         using C = C3<P, NQ, WA>;
         o.applyc_col[IDX] =
-            BCol{C::EPB, F::template applyc_min<TT>(),
+            BCol{C::EPB, F::template applyc_min<TT>(), INT_MAX,
                  [](int n, hipStream_t s, const Tables &t, const Tile *tl, const SlotDev *sl,
                     const int *gt, int vin, double *) {
                      hipLaunchKernelGGL((kb3c_applyc<C, TT, TT, F::template reread<TT>()>), dim3(n),
