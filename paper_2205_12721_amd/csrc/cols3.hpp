@@ -552,8 +552,8 @@ __device__ __forceinline__ void c3_applyc(const Geom &g, const Tab &tb, const Ta
 // 10.6 -> 9.2; 12^3, 432: 7.2 -> 8.2), at p = 4 with n_q <= 6 4096; compact
 // setup 4096, n_q = 6 8192 (FP64: only p = 4, from 16384 on: 20^3 35.5 -> 38.2,
 // 25^3 91.4 -> 86.6; p3 25^3 81.8 -> 85.7), n_q >= 7 1024; FP64 action 1024, n_q = 5 2048; FP32 action 1536 for n_q <= 4 and n_q =
-// 9 at p <= 2, n_q = 5 and p = 4 n_q <= 7 8192 (p2 n_q5 20^3, 4000: 15.6 -> 17.1;
-// 32^3: 54 -> 47), else 4096.
+// 9 at p = 1, n_q = 5 and p = 4 n_q <= 7 8192 (p2 n_q5 20^3, 4000: 15.6 -> 17.1;
+// 32^3: 54 -> 47), else 4096 (p2 n_q9 13^3, 2366: 24.2 -> 27.6; 16^3: 35.6 -> 33.5).
 //
 // Largest meshes: the setup stores a column layer by layer, n_q^2 points of 16
 // bytes at a time, so the 128-byte lines at both ends of a layer are written in
@@ -564,7 +564,10 @@ __device__ __forceinline__ void c3_applyc(const Geom &g, const Tab &tb, const Ta
 // p1 n_q2 81^3 103 / 150): such classes keep the pencil form, or take the
 // column form up to 256 MB of data (p1 n_q4 FP64 32^3 38.2 -> 35.7, 64^3 288 ->
 // 322; p3 n_q5 FP64 25^3 40.0 -> 38.2, 51^3 411 -> 439), in FP32 320 MB (p1 n_q2
-// 81^3 87 -> 72, 90^3 111 -> 113, 128^3 313 -> 345).
+// 81^3 87 -> 72, 90^3 111 -> 113, 128^3 313 -> 345).  The action reads the data
+// so; beyond 256 MB n_q = 3, p1 n_q4 and p2 n_q5 in FP64 and p1 n_q3 in FP32 keep
+// the pencil form (p1 n_q3 FP64 42^3 49.2 -> 46.9, 84^3 433 -> 462, FP32 53^3 52.6
+// -> 48.5, 84^3 232 -> 254; p2 n_q5 25^3 47.8 -> 47.2, 51^3 408 -> 421).
 // ------------------------------------------------------------------------
 template <int P, int NQ>
 struct ColForm {
@@ -606,7 +609,7 @@ struct ColForm {
     static constexpr int applyc_min()
     {
         if (sizeof(TT) == 8) return EPB0 * (NQ == 5 ? 2048 : 1024);
-        return EPB0 * (NQ <= 4 || (NQ == 9 && P <= 2) ? 1536
+        return EPB0 * (NQ <= 4 || (NQ == 9 && P == 1) ? 1536
                        : NQ == 5 || (P == 4 && NQ <= 7) ? 8192
                                                         : 4096);
     }
@@ -625,6 +628,13 @@ struct ColForm {
     {
         if (sizeof(TT) == 8 && (NQ == 5 || (P == 1 && NQ == 4))) return within<TT, 256>();
         return NQ == 2 ? within<TT, 320>() : INT_MAX;
+    }
+    template <typename TT>
+    static constexpr int applyc_max()
+    {
+        const bool part = sizeof(TT) == 8 ? NQ == 3 || (P == 1 && NQ == 4) || (P == 2 && NQ == 5)
+                                          : P == 1 && NQ == 3;
+        return part ? within<TT, 256>() : INT_MAX;
     }
 };
 

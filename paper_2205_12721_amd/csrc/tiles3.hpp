@@ -61,7 +61,7 @@ struct plain_k3 {
         constexpr int WL = F::template applyc<TT>();
         if constexpr (WL > 0) {
             using C = C3<P, NQ, WL>;
-            if (g.ne >= F::template applyc_min<TT>()) {
+            if (g.ne >= F::template applyc_min<TT>() && g.ne <= F::template applyc_max<TT>()) {
                 hipLaunchKernelGGL((k3c_applyc<C, TT, TT, F::template reread<TT>()>),
                                    grid(g, C::EPB), dim3(C::WL), 0, s, g, t, w, Q, v, yE);
                 return;
@@ -93,7 +93,7 @@ inline void fill_bcol3(BOps &o)
     if constexpr (WA > 0) {
         using C = C3<P, NQ, WA>;
         o.applyc_col[IDX] =
-            BCol{C::EPB, F::template applyc_min<TT>(), INT_MAX,
+            BCol{C::EPB, F::template applyc_min<TT>(), F::template applyc_max<TT>(),
                  [](int n, hipStream_t s, const Tables &t, const Tile *tl, const SlotDev *sl,
                     const int *gt, int vin, double *) {
                      hipLaunchKernelGGL((kb3c_applyc<C, TT, TT, F::template reread<TT>()>), dim3(n),
