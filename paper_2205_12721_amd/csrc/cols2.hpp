@@ -178,7 +178,7 @@ __device__ __forceinline__ void c2_energy(const Geom &g, const Tab &tb, const Ta
 }
 
 template <class C, bool GRAD, bool EN>
-__global__ __launch_bounds__(C::WL) void k2c_energy(Geom g, Tables tba, Target tg, const double *__restrict__ x, double *__restrict__ gE, double *__restrict__ part)
+__global__ __launch_bounds__(C::WL) void k2c_energy(Geom g, BasisTables tba, Target tg, const double *__restrict__ x, double *__restrict__ gE, double *__restrict__ part)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     const int e0 = xcd_block(blockIdx.x, gridDim.x) * C::EPB;

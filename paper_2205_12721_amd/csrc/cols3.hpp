@@ -643,7 +643,7 @@ struct ColForm {
 // ------------------------------------------------------------------------
 
 template <class C, bool GRAD, bool EN>
-__global__ __launch_bounds__(C::WL) __attribute__((amdgpu_waves_per_eu(2))) void k3c_energy(Geom g, Tables tba, Target tg, const double *__restrict__ x, double *__restrict__ gE, double *__restrict__ part)
+__global__ __launch_bounds__(C::WL) __attribute__((amdgpu_waves_per_eu(2))) void k3c_energy(Geom g, BasisTables tba, Target tg, const double *__restrict__ x, double *__restrict__ gE, double *__restrict__ part)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     const int e0 = xcd_block(blockIdx.x, gridDim.x) * C::EPB;
@@ -651,7 +651,7 @@ __global__ __launch_bounds__(C::WL) __attribute__((amdgpu_waves_per_eu(2))) void
 }
 
 template <class C, typename TT>
-__global__ __launch_bounds__(C::WL) void k3c_setupc(Geom g, Tables tba, Target tg, const double *__restrict__ x, TT *__restrict__ Q)
+__global__ __launch_bounds__(C::WL) void k3c_setupc(Geom g, BasisTables tba, Target tg, const double *__restrict__ x, TT *__restrict__ Q)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     const int e0 = xcd_block(blockIdx.x, gridDim.x) * C::EPB;
@@ -659,7 +659,7 @@ __global__ __launch_bounds__(C::WL) void k3c_setupc(Geom g, Tables tba, Target t
 }
 
 template <class C, typename TT, typename CT, bool RD>
-__global__ __launch_bounds__(C::WL) __attribute__((amdgpu_waves_per_eu(2))) void k3c_applyc(Geom g, Tables tba, Target tg, const TT *__restrict__ Q, const double *__restrict__ v, CT *__restrict__ yE)
+__global__ __launch_bounds__(C::WL) __attribute__((amdgpu_waves_per_eu(2))) void k3c_applyc(Geom g, BasisTables tba, Target tg, const TT *__restrict__ Q, const double *__restrict__ v, CT *__restrict__ yE)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     const int e0 = xcd_block(blockIdx.x, gridDim.x) * C::EPB;
@@ -667,7 +667,7 @@ __global__ __launch_bounds__(C::WL) __attribute__((amdgpu_waves_per_eu(2))) void
 }
 
 template <class C, typename TT>
-__global__ __launch_bounds__(C::WL) void kb3c_setupc(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
+__global__ __launch_bounds__(C::WL) void kb3c_setupc(BasisTables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
 {
     const Tab tb = kernel_tables<0>();
     const Tile t = tiles[blockIdx.x];
@@ -677,7 +677,7 @@ __global__ __launch_bounds__(C::WL) void kb3c_setupc(Tables tba, const Tile *__r
 }
 
 template <class C, typename TT, typename CT, bool RD>
-__global__ __launch_bounds__(C::WL) __attribute__((amdgpu_waves_per_eu(2))) void kb3c_applyc(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
+__global__ __launch_bounds__(C::WL) __attribute__((amdgpu_waves_per_eu(2))) void kb3c_applyc(BasisTables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
 {
     const Tab tb = kernel_tables<0>();
     const Tile t = tiles[blockIdx.x];

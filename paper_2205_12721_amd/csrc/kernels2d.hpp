@@ -742,7 +742,7 @@ __device__ __forceinline__ void b2_diagc(const Geom &g, const Tab &tb, const Tar
 // ------------------------------------------------------------------------
 
 template <int P, int NQ, bool LIM>
-__global__ __launch_bounds__(BLOCK) void k2_energy(Geom g, Tables tba, Target tg, const double *__restrict__ x, double *__restrict__ part)
+__global__ __launch_bounds__(BLOCK) void k2_energy(Geom g, BasisTables tba, Target tg, const double *__restrict__ x, double *__restrict__ part)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S2<P, NQ>::EPB;
@@ -751,7 +751,7 @@ __global__ __launch_bounds__(BLOCK) void k2_energy(Geom g, Tables tba, Target tg
 }
 
 template <int P, int NQ, bool LIM, bool EN = false>
-__global__ __launch_bounds__(BLOCK) void k2_gradient(Geom g, Tables tba, Target tg, const double *__restrict__ x, double *__restrict__ gE, double *__restrict__ part)
+__global__ __launch_bounds__(BLOCK) void k2_gradient(Geom g, BasisTables tba, Target tg, const double *__restrict__ x, double *__restrict__ gE, double *__restrict__ part)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S2<P, NQ>::EPB;
@@ -760,7 +760,7 @@ __global__ __launch_bounds__(BLOCK) void k2_gradient(Geom g, Tables tba, Target 
 }
 
 template <int P, int NQ, typename TT>
-__global__ __launch_bounds__(BLOCK) void k2_setup(Geom g, Tables tba, Target tg, const double *__restrict__ x, TT *__restrict__ H)
+__global__ __launch_bounds__(BLOCK) void k2_setup(Geom g, BasisTables tba, Target tg, const double *__restrict__ x, TT *__restrict__ H)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S2<P, NQ>::EPB;
@@ -769,7 +769,7 @@ __global__ __launch_bounds__(BLOCK) void k2_setup(Geom g, Tables tba, Target tg,
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM>
-__global__ __launch_bounds__(BLOCK) void k2_apply(Geom g, Tables tba, const TT *__restrict__ H, const double *__restrict__ v, CT *__restrict__ yE)
+__global__ __launch_bounds__(BLOCK) void k2_apply(Geom g, BasisTables tba, const TT *__restrict__ H, const double *__restrict__ v, CT *__restrict__ yE)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S2<P, NQ>::EPB;
@@ -778,7 +778,7 @@ __global__ __launch_bounds__(BLOCK) void k2_apply(Geom g, Tables tba, const TT *
 }
 
 template <int P, int NQ, typename TT>
-__global__ __launch_bounds__(BLOCK) void k2_setupc(Geom g, Tables tba, Target tg, const double *__restrict__ x, TT *__restrict__ Q)
+__global__ __launch_bounds__(BLOCK) void k2_setupc(Geom g, BasisTables tba, Target tg, const double *__restrict__ x, TT *__restrict__ Q)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S2<P, NQ>::EPB;
@@ -787,7 +787,7 @@ __global__ __launch_bounds__(BLOCK) void k2_setupc(Geom g, Tables tba, Target tg
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM>
-__global__ __launch_bounds__(BLOCK) void k2_applyc(Geom g, Tables tba, Target tg, const TT *__restrict__ Q, const double *__restrict__ v, CT *__restrict__ yE)
+__global__ __launch_bounds__(BLOCK) void k2_applyc(Geom g, BasisTables tba, Target tg, const TT *__restrict__ Q, const double *__restrict__ v, CT *__restrict__ yE)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S2<P, NQ>::EPB;
@@ -797,7 +797,7 @@ __global__ __launch_bounds__(BLOCK) void k2_applyc(Geom g, Tables tba, Target tg
 
 // The action on the next Lanczos vector, which it works out (MrL2).
 template <int P, int NQ, typename TT, bool COMPACT>
-__global__ __launch_bounds__(BLOCK) void k2_apply_l2(Geom g, Tables tba, Target tg, const TT *__restrict__ H, MrL2 a, TT *__restrict__ yE)
+__global__ __launch_bounds__(BLOCK) void k2_apply_l2(Geom g, BasisTables tba, Target tg, const TT *__restrict__ H, MrL2 a, TT *__restrict__ yE)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S2<P, NQ>::EPB;
@@ -809,7 +809,7 @@ __global__ __launch_bounds__(BLOCK) void k2_apply_l2(Geom g, Tables tba, Target 
 }
 
 template <int P, int NQ, typename TT, bool LIM>
-__global__ __launch_bounds__(BLOCK) void k2_diag(Geom g, Tables tba, const TT *__restrict__ H, double *__restrict__ dE)
+__global__ __launch_bounds__(BLOCK) void k2_diag(Geom g, BasisTables tba, const TT *__restrict__ H, double *__restrict__ dE)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S2<P, NQ>::EPB;
@@ -818,7 +818,7 @@ __global__ __launch_bounds__(BLOCK) void k2_diag(Geom g, Tables tba, const TT *_
 }
 
 template <int P, int NQ, typename TT, bool LIM>
-__global__ __launch_bounds__(BLOCK) void k2_diagc(Geom g, Tables tba, Target tg, const TT *__restrict__ Q, double *__restrict__ dE)
+__global__ __launch_bounds__(BLOCK) void k2_diagc(Geom g, BasisTables tba, Target tg, const TT *__restrict__ Q, double *__restrict__ dE)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S2<P, NQ>::EPB;
@@ -827,7 +827,7 @@ __global__ __launch_bounds__(BLOCK) void k2_diagc(Geom g, Tables tba, Target tg,
 }
 
 template <int P, int NQ, bool LIM = false>
-__global__ __launch_bounds__(BLOCK) void kb2_energy(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ part)
+__global__ __launch_bounds__(BLOCK) void kb2_energy(BasisTables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ part)
 {
     const Tab tb = kernel_tables<0>();
     constexpr int EPB = S2<P, NQ>::EPB;
@@ -838,7 +838,7 @@ __global__ __launch_bounds__(BLOCK) void kb2_energy(Tables tba, const Tile *__re
 }
 
 template <int P, int NQ, bool LIM = false, bool EN = false>
-__global__ __launch_bounds__(BLOCK) void kb2_gradient(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ part)
+__global__ __launch_bounds__(BLOCK) void kb2_gradient(BasisTables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ part)
 {
     const Tab tb = kernel_tables<0>();
     constexpr int EPB = S2<P, NQ>::EPB;
@@ -849,7 +849,7 @@ __global__ __launch_bounds__(BLOCK) void kb2_gradient(Tables tba, const Tile *__
 }
 
 template <int P, int NQ, typename TT>
-__global__ __launch_bounds__(BLOCK) void kb2_setup(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
+__global__ __launch_bounds__(BLOCK) void kb2_setup(BasisTables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
 {
     const Tab tb = kernel_tables<0>();
     constexpr int EPB = S2<P, NQ>::EPB;
@@ -860,7 +860,7 @@ __global__ __launch_bounds__(BLOCK) void kb2_setup(Tables tba, const Tile *__res
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM = false>
-__global__ __launch_bounds__(BLOCK) void kb2_apply(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
+__global__ __launch_bounds__(BLOCK) void kb2_apply(BasisTables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
 {
     const Tab tb = kernel_tables<0>();
     constexpr int EPB = S2<P, NQ>::EPB;
@@ -871,7 +871,7 @@ __global__ __launch_bounds__(BLOCK) void kb2_apply(Tables tba, const Tile *__res
 }
 
 template <int P, int NQ, typename TT>
-__global__ __launch_bounds__(BLOCK) void kb2_setupc(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
+__global__ __launch_bounds__(BLOCK) void kb2_setupc(BasisTables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
 {
     const Tab tb = kernel_tables<0>();
     constexpr int EPB = S2<P, NQ>::EPB;
@@ -882,7 +882,7 @@ __global__ __launch_bounds__(BLOCK) void kb2_setupc(Tables tba, const Tile *__re
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM = false>
-__global__ __launch_bounds__(BLOCK) void kb2_applyc(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
+__global__ __launch_bounds__(BLOCK) void kb2_applyc(BasisTables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
 {
     const Tab tb = kernel_tables<0>();
     constexpr int EPB = S2<P, NQ>::EPB;
@@ -893,7 +893,7 @@ __global__ __launch_bounds__(BLOCK) void kb2_applyc(Tables tba, const Tile *__re
 }
 
 template <int P, int NQ, typename TT, bool LIM = false>
-__global__ __launch_bounds__(BLOCK) void kb2_diag(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate)
+__global__ __launch_bounds__(BLOCK) void kb2_diag(BasisTables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate)
 {
     const Tab tb = kernel_tables<0>();
     constexpr int EPB = S2<P, NQ>::EPB;
@@ -904,7 +904,7 @@ __global__ __launch_bounds__(BLOCK) void kb2_diag(Tables tba, const Tile *__rest
 }
 
 template <int P, int NQ, typename TT, bool LIM = false>
-__global__ __launch_bounds__(BLOCK) void kb2_diagc(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate)
+__global__ __launch_bounds__(BLOCK) void kb2_diagc(BasisTables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate)
 {
     const Tab tb = kernel_tables<0>();
     constexpr int EPB = S2<P, NQ>::EPB;

@@ -1399,7 +1399,7 @@ __device__ __forceinline__ void diag_contract3(const Tab &tb, const Geom &g, int
     __syncthreads();  // sQ ready
     // axis 3: lines (r = el*3 + a, q2, q1), q3 -> i3
     {
-        const Tab t = tb.again();
+        const auto t = products(tb.again());
         for (int pen = threadIdx.x; pen < nel * 3 * NQ2; pen += BLOCK) {
             const int q21 = pen % NQ2, r = pen / NQ2;
             double *y = L.sQ + ((r / 3) * NPR * 3 + r % 3) * NQ3 + q21;
@@ -1411,7 +1411,7 @@ __device__ __forceinline__ void diag_contract3(const Tab &tb, const Geom &g, int
                     const double v = y[pr * PL + q * NQ2];
 #pragma unroll
                     for (int i = 0; i < NI; ++i)
-                        o[pr][i] += t.t->D[diag_order(pr, 2)][q * NI + i] * v;
+                        o[pr][i] += t->D[diag_order(pr, 2)][q * NI + i] * v;
                 }
 #pragma unroll
             for (int pr = 0; pr < NPR; ++pr)
@@ -1422,7 +1422,7 @@ __device__ __forceinline__ void diag_contract3(const Tab &tb, const Geom &g, int
     __syncthreads();
     // axis 2: lines (r, i3, q1), q2 -> i2; plane k for axis-1 order 2 - k
     {
-        const Tab t = tb.again();
+        const auto t = products(tb.again());
         for (int pen = threadIdx.x; pen < nel * 3 * NI * NQ; pen += BLOCK) {
             const int q1 = pen % NQ, i3 = (pen / NQ) % NI, r = pen / (NQ * NI);
             double *y = L.sQ + ((r / 3) * NPR * 3 + r % 3) * NQ3 + i3 * NQ2 + q1;
@@ -1434,7 +1434,7 @@ __device__ __forceinline__ void diag_contract3(const Tab &tb, const Geom &g, int
                     const double v = y[pr * PL + q * NQ];
 #pragma unroll
                     for (int i = 0; i < NI; ++i)
-                        o[2 - diag_order(pr, 0)][i] += t.t->D[diag_order(pr, 1)][q * NI + i] * v;
+                        o[2 - diag_order(pr, 0)][i] += t->D[diag_order(pr, 1)][q * NI + i] * v;
                 }
 #pragma unroll
             for (int k = 0; k < 3; ++k)
@@ -1445,7 +1445,7 @@ __device__ __forceinline__ void diag_contract3(const Tab &tb, const Geom &g, int
     __syncthreads();
     // axis 1: lines (r, i3, i2), q1 -> i1, into the first plane
     {
-        const Tab t = tb.again();
+        const auto t = products(tb.again());
         for (int pen = threadIdx.x; pen < nel * 3 * NI * NI; pen += BLOCK) {
             const int i2 = pen % NI, i3 = (pen / NI) % NI, r = pen / (NI * NI);
             double *y = L.sQ + ((r / 3) * NPR * 3 + r % 3) * NQ3 + i3 * NQ2 + i2 * NQ;
@@ -1456,7 +1456,7 @@ __device__ __forceinline__ void diag_contract3(const Tab &tb, const Geom &g, int
                 for (int k = 0; k < 3; ++k) {
                     const double v = y[k * PL + q];
 #pragma unroll
-                    for (int i = 0; i < NI; ++i) o[i] += t.t->D[2 - k][q * NI + i] * v;
+                    for (int i = 0; i < NI; ++i) o[i] += t->D[2 - k][q * NI + i] * v;
                 }
 #pragma unroll
             for (int i = 0; i < NI; ++i) y[i] = o[i];
@@ -1683,7 +1683,7 @@ __device__ __forceinline__ void b3_setupcd(const Geom &g, const Tab &tb, const T
 // ------------------------------------------------------------------------
 
 template <int P, int NQ, bool LIM, bool MF = false>
-__global__ __launch_bounds__(BLOCK) void k3_energy(Geom g, Tables tba, Target tg, const double *__restrict__ x, double *__restrict__ part)
+__global__ __launch_bounds__(BLOCK) void k3_energy(Geom g, BasisTables tba, Target tg, const double *__restrict__ x, double *__restrict__ part)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S3<P, NQ>::EPB;
@@ -1692,7 +1692,7 @@ __global__ __launch_bounds__(BLOCK) void k3_energy(Geom g, Tables tba, Target tg
 }
 
 template <int P, int NQ, bool LIM, bool EN = false, bool MF = false>
-__global__ __launch_bounds__(BLOCK) void k3_gradient(Geom g, Tables tba, Target tg, const double *__restrict__ x, double *__restrict__ gE, double *__restrict__ part)
+__global__ __launch_bounds__(BLOCK) void k3_gradient(Geom g, BasisTables tba, Target tg, const double *__restrict__ x, double *__restrict__ gE, double *__restrict__ part)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S3<P, NQ>::EPB;
@@ -1701,7 +1701,7 @@ __global__ __launch_bounds__(BLOCK) void k3_gradient(Geom g, Tables tba, Target 
 }
 
 template <int P, int NQ, typename TT, bool MF = false>
-__global__ __launch_bounds__(BLOCK) void k3_setup(Geom g, Tables tba, Target tg, const double *__restrict__ x, TT *__restrict__ H)
+__global__ __launch_bounds__(BLOCK) void k3_setup(Geom g, BasisTables tba, Target tg, const double *__restrict__ x, TT *__restrict__ H)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S3<P, NQ>::EPB;
@@ -1710,7 +1710,7 @@ __global__ __launch_bounds__(BLOCK) void k3_setup(Geom g, Tables tba, Target tg,
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM, int T2 = 2>
-__global__ __launch_bounds__(BLOCK) void k3_apply(Geom g, Tables tba, const TT *__restrict__ H, const double *__restrict__ v, CT *__restrict__ yE)
+__global__ __launch_bounds__(BLOCK) void k3_apply(Geom g, BasisTables tba, const TT *__restrict__ H, const double *__restrict__ v, CT *__restrict__ yE)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S3<P, NQ, T2>::EPB;
@@ -1720,7 +1720,7 @@ __global__ __launch_bounds__(BLOCK) void k3_apply(Geom g, Tables tba, const TT *
 
 // The action on the next Lanczos vector, which it works out (MrL2).
 template <int P, int NQ, typename TT, bool COMPACT>
-__global__ __launch_bounds__(BLOCK) void k3_apply_l2(Geom g, Tables tba, Target tg, const TT *__restrict__ H, MrL2 a, TT *__restrict__ yE)
+__global__ __launch_bounds__(BLOCK) void k3_apply_l2(Geom g, BasisTables tba, Target tg, const TT *__restrict__ H, MrL2 a, TT *__restrict__ yE)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S3<P, NQ>::EPB;
@@ -1732,7 +1732,7 @@ __global__ __launch_bounds__(BLOCK) void k3_apply_l2(Geom g, Tables tba, Target 
 }
 
 template <int P, int NQ, typename TT, bool MF = false>
-__global__ __launch_bounds__(BLOCK) void k3_setupc(Geom g, Tables tba, Target tg, const double *__restrict__ x, TT *__restrict__ Q)
+__global__ __launch_bounds__(BLOCK) void k3_setupc(Geom g, BasisTables tba, Target tg, const double *__restrict__ x, TT *__restrict__ Q)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S3<P, NQ>::EPB;
@@ -1741,7 +1741,7 @@ __global__ __launch_bounds__(BLOCK) void k3_setupc(Geom g, Tables tba, Target tg
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM, int T2 = 2>
-__global__ __launch_bounds__(BLOCK) void k3_applyc(Geom g, Tables tba, Target tg, const TT *__restrict__ Q, const double *__restrict__ v, CT *__restrict__ yE)
+__global__ __launch_bounds__(BLOCK) void k3_applyc(Geom g, BasisTables tba, Target tg, const TT *__restrict__ Q, const double *__restrict__ v, CT *__restrict__ yE)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S3<P, NQ, T2>::EPB;
@@ -1786,7 +1786,7 @@ __global__ __launch_bounds__(BLOCK) void k3_diagc(Geom g, Tables tba, Target tg,
 }
 
 template <int P, int NQ, bool LIM = false>
-__global__ __launch_bounds__(BLOCK) void kb3_energy(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ part)
+__global__ __launch_bounds__(BLOCK) void kb3_energy(BasisTables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ part)
 {
     const Tab tb = kernel_tables<0>();
     constexpr int EPB = S3<P, NQ>::EPB;
@@ -1797,7 +1797,7 @@ __global__ __launch_bounds__(BLOCK) void kb3_energy(Tables tba, const Tile *__re
 }
 
 template <int P, int NQ, bool LIM = false, bool EN = false>
-__global__ __launch_bounds__(BLOCK) void kb3_gradient(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ part)
+__global__ __launch_bounds__(BLOCK) void kb3_gradient(BasisTables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin, double *__restrict__ part)
 {
     const Tab tb = kernel_tables<0>();
     constexpr int EPB = S3<P, NQ>::EPB;
@@ -1808,7 +1808,7 @@ __global__ __launch_bounds__(BLOCK) void kb3_gradient(Tables tba, const Tile *__
 }
 
 template <int P, int NQ, typename TT>
-__global__ __launch_bounds__(BLOCK) void kb3_setup(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
+__global__ __launch_bounds__(BLOCK) void kb3_setup(BasisTables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
 {
     const Tab tb = kernel_tables<0>();
     constexpr int EPB = S3<P, NQ>::EPB;
@@ -1819,7 +1819,7 @@ __global__ __launch_bounds__(BLOCK) void kb3_setup(Tables tba, const Tile *__res
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM = false, int T2 = 2>
-__global__ __launch_bounds__(BLOCK) void kb3_apply(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
+__global__ __launch_bounds__(BLOCK) void kb3_apply(BasisTables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
 {
     const Tab tb = kernel_tables<0>();
     constexpr int EPB = S3<P, NQ, T2>::EPB;
@@ -1830,7 +1830,7 @@ __global__ __launch_bounds__(BLOCK) void kb3_apply(Tables tba, const Tile *__res
 }
 
 template <int P, int NQ, typename TT>
-__global__ __launch_bounds__(BLOCK) void kb3_setupc(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
+__global__ __launch_bounds__(BLOCK) void kb3_setupc(BasisTables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
 {
     const Tab tb = kernel_tables<0>();
     constexpr int EPB = S3<P, NQ>::EPB;
@@ -1841,7 +1841,7 @@ __global__ __launch_bounds__(BLOCK) void kb3_setupc(Tables tba, const Tile *__re
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM = false, int T2 = 2>
-__global__ __launch_bounds__(BLOCK) void kb3_applyc(Tables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
+__global__ __launch_bounds__(BLOCK) void kb3_applyc(BasisTables tba, const Tile *__restrict__ tiles, const SlotDev *__restrict__ slots, const int *__restrict__ gate, int vin)
 {
     const Tab tb = kernel_tables<0>();
     constexpr int EPB = S3<P, NQ, T2>::EPB;

@@ -32,7 +32,7 @@ __device__ __forceinline__ double mr1_sum(double v, double *red, int tid)
 // registers from the gather to the new z.  The scalar recurrence is done by
 // the last wave, which has the least to do in the next element stage.
 template <int P, int NQ, typename TT, bool COMPACT>
-__global__ __launch_bounds__(MR1_LANES) void k2_minres_one(Geom g, Tables tba, Target tg, MrOne a)
+__global__ __launch_bounds__(MR1_LANES) void k2_minres_one(Geom g, BasisTables tba, Target tg, MrOne a)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int DIM = 2, EPB = S2<P, NQ>::EPB;

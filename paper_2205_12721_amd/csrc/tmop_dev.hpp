@@ -106,17 +106,22 @@ __device__ __forceinline__ void box_coords(const Geom &g, int node, int gc[3])
 
 // 1D tables: B[q][i] = l_i(chi_q), G[q][i] = l_i'(chi_q), w[q] (Sec. 3.1, eq. eq_B_G_1D).
 // Bf, Gf: the same tables rounded to FP32 for the mixed-precision action.
-// Kernels take Tables by value and read the entries through Tab.
-struct Tables {
+// Kernels take BasisTables by value and read the entries through Tab; those of
+// the hex diagonal take Tables, whose products are as many bytes again (in
+// every launch's arguments they cost 0.1 to 0.2 us of it: Hessian actions of
+// 35 x 36 quads p2 issued one after the other took 8.4 us instead of 8.2).
+struct BasisTables {
     double B[MAXNQ * MAXNI];
     double G[MAXNQ * MAXNI];
     double w[MAXNQ];
     float Bf[MAXNQ * MAXNI];
     float Gf[MAXNQ * MAXNI];
+};
+struct Tables : BasisTables {
     double D[3][MAXNQ * MAXNI];  // B B, B G, G G (Hessian diagonal)
 };
 
-// A kernel's view of its Tables argument: a pointer to it in the kernel
+// A kernel's view of its tables argument: a pointer to it in the kernel
 // argument segment (constant address space), so that entries indexed with
 // compile-time constants are scalar loads.  Every contraction stage starts
 // from again(), whose pointer the compiler cannot relate to the earlier ones:
@@ -129,7 +134,7 @@ struct Tables {
 // a wave takes four cycles), so each instruction that is not a multiply-add
 // costs.
 struct Tab {
-    const __attribute__((address_space(4))) Tables *t;
+    const __attribute__((address_space(4))) BasisTables *t;
     __device__ __forceinline__ Tab again() const
     {
         Tab r = *this;
@@ -138,14 +143,20 @@ struct Tab {
     }
 };
 
-// The Tables argument of a kernel that starts OFF bytes into its arguments.
+// The tables argument of a kernel that starts OFF bytes into its arguments.
 template <size_t OFF>
 __device__ __forceinline__ Tab kernel_tables()
 {
-    static_assert(OFF % alignof(Tables) == 0, "offset of the Tables argument");
+    static_assert(OFF % alignof(Tables) == 0, "offset of the tables argument");
     typedef const __attribute__((address_space(4))) char *Bytes;
-    return Tab{(const __attribute__((address_space(4))) Tables
+    return Tab{(const __attribute__((address_space(4))) BasisTables
                     *)((Bytes)__builtin_amdgcn_kernarg_segment_ptr() + OFF)};
+}
+
+// The products, in a kernel that takes Tables.
+__device__ __forceinline__ const __attribute__((address_space(4))) Tables *products(const Tab &t)
+{
+    return (const __attribute__((address_space(4))) Tables *)t.t;
 }
 
 template <typename CT>
