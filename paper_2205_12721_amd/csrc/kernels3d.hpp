@@ -212,10 +212,68 @@ __device__ __forceinline__ void gather3(const Geom &g, const double *__restrict_
     gather3_store<P, NQ, CT>(r, nel, sX);
 }
 
+// Gather for the FP64 tensor action at n_q = 5 on larger meshes (flat_apply3): a
+// lane takes one component of one node, (element, component, node) running over
+// the lanes, fixed DoFs as zero.
+template <int P, int NQ, int T2>
+struct GathFlat3 {
+    static constexpr int NP = S3<P, NQ>::NP;
+    static constexpr int NIT = (S3<P, NQ, T2>::EPB * 3 * NP + BLOCK - 1) / BLOCK;
+    double val[NIT];
+    bool fix[NIT];
+    __device__ __forceinline__ void load(const Geom &g, const double *__restrict__ vec, int e0, int nel)
+    {
+        constexpr int NI = S3<P, NQ>::NI;
+        const int n = nel * 3 * NP;
+        if (!g.e2n && g.ess_mode != 2) {
+            // branch-free, so that every load is issued before any is waited for
+            const bool bmask = g.ess_mode == 0;
+#pragma unroll
+            for (int it = 0; it < NIT; ++it) {
+                const int idx = threadIdx.x + it * BLOCK;
+                const bool in = idx < n;
+                const int i = idx % NP, r = idx / NP;  // r = el*3 + c
+                const int c = r % 3, el = r / 3;
+                int ex, ey, ez;
+                box_elem<3>(g, e0 + el, ex, ey, ez);
+                const int gx = ex * P + i % NI, gy = ey * P + (i / NI) % NI, gz = ez * P + i / (NI * NI);
+                // lanes past the end read entry 0 and are dropped
+                const size_t at = in ? (size_t)c * g.nx + gx + g.M[0] * (gy + g.M[1] * gz) : 0;
+                val[it] = vec[at];
+                fix[it] = !in || (bmask && box_boundary(g, gx, gy, gz));
+            }
+            return;
+        }
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) {
+            const int idx = threadIdx.x + it * BLOCK;
+            val[it] = 0.0;
+            fix[it] = true;
+            if (idx < n) {
+                const int i = idx % NP, r = idx / NP;
+                const int c = r % 3, el = r / 3;
+                int gx, gy, gz;
+                const int node = node3<P>(g, e0 + el, i % NI, (i / NI) % NI, i / (NI * NI), gx, gy, gz);
+                val[it] = vec[(size_t)c * g.nx + node];
+                fix[it] = is_fixed(g, c, node, gx, gy, gz);
+            }
+        }
+    }
+    template <typename CT>
+    __device__ __forceinline__ void store(int nel, CT *sX) const
+    {
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) {
+            const int idx = threadIdx.x + it * BLOCK;
+            if (idx < nel * 3 * NP) sX[idx] = fix[it] ? (CT)0 : (CT)val[it];
+        }
+    }
+};
+
 // The input of the action, fixed DoFs as zero, in a load phase and a phase that
 // puts it into LDS: a vector, or what MrL2 makes of one (box meshes; store is
 // false, and nothing to be done, when the solve has stopped).
-template <int P, int NQ, int T2, class VS>
+template <int P, int NQ, int T2, class VS, bool FLAT = false>
 struct GathV3 {
     Gath3<P, NQ, T2> r;
     __device__ __forceinline__ void load(const Geom &g, const double *v, int e0, int nel)
@@ -231,7 +289,22 @@ struct GathV3 {
 };
 
 template <int P, int NQ, int T2>
-struct GathV3<P, NQ, T2, MrL2> {
+struct GathV3<P, NQ, T2, const double *, true> {
+    GathFlat3<P, NQ, T2> r;
+    __device__ __forceinline__ void load(const Geom &g, const double *v, int e0, int nel)
+    {
+        r.load(g, v, e0, nel);
+    }
+    template <typename CT>
+    __device__ __forceinline__ bool store(const Geom &, const double *, int, int nel, CT *sX)
+    {
+        r.template store<CT>(nel, sX);
+        return true;
+    }
+};
+
+template <int P, int NQ, int T2, bool FLAT>
+struct GathV3<P, NQ, T2, MrL2, FLAT> {
     using S = S3<P, NQ>;
     static_assert(T2 == 2 && S::EPB * S::NP <= BLOCK, "one node per lane");
     MrL2Node<3> n;
@@ -886,7 +959,7 @@ __device__ __forceinline__ void apply_point3(const double *sw, const Geom &g, co
 // accumulation).  This is the point-pass body; b3_apply chooses between it
 // and the layer-chunked body (b3_apply_layers).
 template <int P, int NQ, typename TT, typename CT, bool LIM = false, int T2 = 2,
-          class VS = const double *>
+          class VS = const double *, bool FLAT = false>
 __device__ __forceinline__ void b3_apply_points(const Geom &g, const Tab &tb,
                                                 const TT *__restrict__ H,
                                                 const VS v,
@@ -912,7 +985,7 @@ __device__ __forceinline__ void b3_apply_points(const Geom &g, const Tab &tb,
     if (LIM) weights_to_lds<NQ>(tb, sw);
     // v loads first, then the tensor loads, then v to LDS: waiting for v
     // leaves the tensor loads in flight
-    GathV3<P, NQ, T2, VS> gv;
+    GathV3<P, NQ, T2, VS, FLAT> gv;
     gv.load(g, v, e0, nel);
     const int npts = nel * S::NQ3;
     if constexpr (PF) {
@@ -1333,14 +1406,26 @@ constexpr bool apply_layers3()
     return S3<P, NQ>::NQ3 > BLOCK && T2 == 2 && !LIM && sizeof(CT) == 8 && (COMPACT || P >= 4);
 }
 
-template <int P, int NQ, typename TT, typename CT, bool LIM = false, int T2 = 2>
+// Where one node with all components per lane leaves half of the lanes without
+// loads and HBM bounds the action, the flat gather is faster (workgroups; p3
+// 24^3, 6912, 120.8 us -> 120.4; 28^3 192.9 -> 192.2; p2 42^3 586.6 -> 584.1);
+// where a workgroup's own time counts, placing a node once is (p2 20^3, 3990:
+// 63.2 / 63.1; p3 13^3, 1092: 22.9 / 23.2; 6^3 9.65 / 10.0).
+template <int P, int NQ>
+constexpr bool flat_apply3()
+{
+    return NQ == 5 && P <= 3;
+}
+constexpr int FLAT_MIN = 4096;
+
+template <int P, int NQ, typename TT, typename CT, bool LIM = false, int T2 = 2, bool FLAT = false>
 __device__ __forceinline__ void b3_apply(const Geom &g, const Tab &tb, const TT *__restrict__ H,
                                 const double *__restrict__ v, CT *__restrict__ yE, int e0, int nel)
 {
     if constexpr (apply_layers3<P, NQ, T2, LIM, CT, false>())
         b3_apply_layers<P, NQ, TT, CT, false>(g, tb, Target{}, H, v, yE, e0, nel);
     else
-        b3_apply_points<P, NQ, TT, CT, LIM, T2>(g, tb, H, v, yE, e0, nel);
+        b3_apply_points<P, NQ, TT, CT, LIM, T2, const double *, FLAT>(g, tb, H, v, yE, e0, nel);
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM = false, int T2 = 2>
@@ -1709,13 +1794,13 @@ __global__ __launch_bounds__(BLOCK) void k3_setup(Geom g, BasisTables tba, Targe
     b3_setup<P, NQ, TT, MF>(g, tb, tg, x, H, e0, min(EPB, g.ne - e0));
 }
 
-template <int P, int NQ, typename TT, typename CT, bool LIM, int T2 = 2>
+template <int P, int NQ, typename TT, typename CT, bool LIM, int T2 = 2, bool FLAT = false>
 __global__ __launch_bounds__(BLOCK) void k3_apply(Geom g, BasisTables tba, const TT *__restrict__ H, const double *__restrict__ v, CT *__restrict__ yE)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S3<P, NQ, T2>::EPB;
     const int e0 = xcd_block(blockIdx.x, gridDim.x) * EPB;
-    b3_apply<P, NQ, TT, CT, LIM, T2>(g, tb, H, v, yE, e0, min(EPB, g.ne - e0));
+    b3_apply<P, NQ, TT, CT, LIM, T2, FLAT>(g, tb, H, v, yE, e0, min(EPB, g.ne - e0));
 }
 
 // The action on the next Lanczos vector, which it works out (MrL2).

@@ -121,6 +121,21 @@ inline void fill_tile3(Ops &o)
             // the base shape: plain_k3, which chooses the column form
             o.applyc64_t[IDX] = o.applyc64;
             o.applyc32_t[IDX] = o.applyc32;
+            if constexpr (flat_apply3<P, NQ>()) {
+                o.apply64 = [](int grid, hipStream_t s, const Geom &g, const Tables &t,
+                               const double *H, const double *v, double *yE) {
+                    if (g.lim != 0.0)
+                        hipLaunchKernelGGL((k3_apply<P, NQ, double, double, true>), dim3(grid),
+                                           dim3(BLOCK), 0, s, g, t, H, v, yE);
+                    else if (grid >= FLAT_MIN)
+                        hipLaunchKernelGGL((k3_apply<P, NQ, double, double, false, 2, true>),
+                                           dim3(grid), dim3(BLOCK), 0, s, g, t, H, v, yE);
+                    else
+                        hipLaunchKernelGGL((k3_apply<P, NQ, double, double, false>), dim3(grid),
+                                           dim3(BLOCK), 0, s, g, t, H, v, yE);
+                };
+                o.apply64_t[IDX] = o.apply64;
+            }
         } else {
             o.applyc64_t[IDX] = [](int grid, hipStream_t s, const Geom &g, const Tables &t,
                                    const Target &w, const double *Q, const double *v, double *yE) {
