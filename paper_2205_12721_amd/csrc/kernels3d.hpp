@@ -23,6 +23,8 @@
 // Forward:  X -> R1 -> R2 -> RY(J);  point stage RY(J) -> RY(Y) in place;
 // backward: RY(Y) -> R2 -> R1 -> E-vector.
 #pragma once
+#include <type_traits>
+
 #include "mfma3.hpp"
 #include "minres_dev.hpp"
 #include "tmop_dev.hpp"
@@ -706,6 +708,25 @@ struct QPut {
             a[PR] = z;
         }
     }
+    __device__ __forceinline__ void finish() const {}
+};
+
+// The same interface with all values held until finish() stores them together
+// (hold_setup3).
+template <typename TT, int NS, int NQT>
+struct QHold {
+    TT *he;
+    int q;
+    TT v[NS];
+    __device__ __forceinline__ QHold(TT *he, int q) : he(he), q(q) {}
+    __device__ __forceinline__ void put(int k, TT a) { v[k] = a; }
+    __device__ __forceinline__ void finish() const
+    {
+        asm volatile("" ::: "memory");  // no store before the last value
+        QPut<TT, NS, NQT> o(he, q);
+#pragma unroll
+        for (int k = 0; k < NS; ++k) o.put(k, v[k]);
+    }
 };
 
 template <typename TT, int NS, int NQT>
@@ -895,9 +916,32 @@ __device__ __forceinline__ void b3_gradient(const Geom &g, const Tab &tb, const 
     }
 }
 
+// Where an FP64 tensor setup is faster when a point's entries are held and
+// stored together: entries that go out as they are computed leave registers
+// for four workgroups per CU instead of three, which is worth 2 to 10% while
+// the 256 MB last-level cache takes the stores, and costs as much where HBM
+// has to take those of more workgroups at a time.  us, as computed / together:
+// p2 n_q3 29^3 (280 MB) 45.1 / 48.3, p1 n_q3 26^3 32.2 / 33.3, 42^3 160 / 156,
+// 84^3 1221 / 1185; p2 n_q5 16^3 32.7 / 33.6, 25^3 146 / 138, 51^3 1161 / 1086; p3
+// n_q5 19^3 (315 MB) 57.5 / 58.3, 24^3 128.2 / 123.8, 51^3 1209 / 1152; n_q = 4 from
+// 1 GB on, p1 32^3 138 / 137, 64^3 1049 / 1028; with n_q >= 6 or in FP32 they differ
+// by 1%, or the first is faster.  With the diagonal, which takes registers too,
+// only p1 n_q4 (58^3 806 / 788; n_q3 40^3 139.8 / 141.4, 84^3 1302 / 1294).
+template <int P, int NQ, bool DIAG>
+constexpr bool hold_setup3()
+{
+    return DIAG ? P == 1 && NQ == 4 : NQ == 3 || NQ == 5 || (NQ == 4 && P <= 2);
+}
+// elements from which the data is that large
+template <int NQ>
+constexpr int hold_setup3_min()
+{
+    return (int)((NQ == 4 ? 1L << 30 : 320L << 20) / (QLay<double, 45, NQ * NQ * NQ>::STRIDE * 8)) + 1;
+}
+
 // Hessian setup (Sec. 3.4): per point the packed z * H_A tensor, stored
 // element-major in the 16-byte-run layout of qdata_store.
-template <int P, int NQ, typename TT, bool MF = false>
+template <int P, int NQ, typename TT, bool MF = false, bool HOLD = false>
 __device__ __forceinline__ void b3_setup(const Geom &g, const Tab &tb, const Target &tg,
                                 const double *__restrict__ x, TT *__restrict__ H, int e0, int nel)
 {
@@ -919,13 +963,15 @@ __device__ __forceinline__ void b3_setup(const Geom &g, const Tab &tb, const Tar
         point_J3<P, NQ>(L.RY, el, q, J);
         const double z = point_weight3<NQ>(sw, tg, q);
         using QL = QLay<TT, 45, S::NQ3>;
-        QPut<TT, 45, S::NQ3> out(H + (size_t)(e0 + el) * QL::STRIDE, q);
+        using Out = std::conditional_t<HOLD, QHold<TT, 45, S::NQ3>, QPut<TT, 45, S::NQ3>>;
+        Out out(H + (size_t)(e0 + el) * QL::STRIDE, q);
         if (!metric_second<3>(tg, J, z, [&](int r, int s, double v) {
                 out.put(sym_index<9>(r, s), (TT)v);
             })) {
 #pragma unroll
             for (int k = 0; k < 45; ++k) out.put(k, (TT)0);
         }
+        out.finish();
     }
 }
 
@@ -1677,7 +1723,7 @@ __device__ __forceinline__ void b3_diagc(const Geom &g, const Tab &tb, const Tar
 // (every lane holds its J before the barrier that hands the memory over), so
 // the workgroup needs no more LDS than b3_diag.  Classes whose points fit one
 // pass of the workgroup.  H and dE are bitwise those of b3_setup then b3_diag.
-template <int P, int NQ, typename TT, bool LIM>
+template <int P, int NQ, typename TT, bool LIM, bool HOLD = false>
 __device__ __forceinline__ void b3_setupd(const Geom &g, const Tab &tb, const Target &tg,
                                  const double *__restrict__ x, TT *__restrict__ H,
                                  double *__restrict__ dE, int e0, int nel)
@@ -1703,10 +1749,8 @@ __device__ __forceinline__ void b3_setupd(const Geom &g, const Tab &tb, const Ta
     if (act) {
         const double z = point_weight3<NQ>(sw, tg, q);
         using QL = QLay<TT, 45, S::NQ3>;
-        QPut<TT, 45, S::NQ3> out(H + (size_t)(e0 + el) * QL::STRIDE, q);
-        // the entries go out as they are computed: 111 registers, four
-        // workgroups on a CU, where holding all 45 took 151 and three (p3 n_q5
-        // 24^3, setup alone 142 -> 129 us; a fill of its 641 MB takes 100)
+        using Out = std::conditional_t<HOLD, QHold<TT, 45, S::NQ3>, QPut<TT, 45, S::NQ3>>;
+        Out out(H + (size_t)(e0 + el) * QL::STRIDE, q);
         const auto emit = [&](int r, int s, double v) {
             const TT h = (TT)v;
             out.put(sym_index<9>(r, s), h);
@@ -1721,6 +1765,7 @@ __device__ __forceinline__ void b3_setupd(const Geom &g, const Tab &tb, const Ta
 #pragma unroll
                 for (int s = r; s < 9; ++s) emit(r, s, 0.0);
         }
+        out.finish();
         diag_lim3<P, NQ, LIM>(sw, g, L.d, el, q);
     }
     diag_contract3<P, NQ, LIM>(tb, g, e0, L.d, nel, dE);
@@ -1785,13 +1830,13 @@ __global__ __launch_bounds__(BLOCK) void k3_gradient(Geom g, BasisTables tba, Ta
     b3_gradient<P, NQ, LIM, EN, MF>(g, tb, tg, x, gE, part, e0, min(EPB, g.ne - e0));
 }
 
-template <int P, int NQ, typename TT, bool MF = false>
+template <int P, int NQ, typename TT, bool MF = false, bool HOLD = false>
 __global__ __launch_bounds__(BLOCK) void k3_setup(Geom g, BasisTables tba, Target tg, const double *__restrict__ x, TT *__restrict__ H)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S3<P, NQ>::EPB;
     const int e0 = xcd_block(blockIdx.x, gridDim.x) * EPB;
-    b3_setup<P, NQ, TT, MF>(g, tb, tg, x, H, e0, min(EPB, g.ne - e0));
+    b3_setup<P, NQ, TT, MF, HOLD>(g, tb, tg, x, H, e0, min(EPB, g.ne - e0));
 }
 
 template <int P, int NQ, typename TT, typename CT, bool LIM, int T2 = 2, bool FLAT = false>
@@ -1843,13 +1888,13 @@ __global__ __launch_bounds__(BLOCK) void k3_diag(Geom g, Tables tba, const TT *_
     b3_diag<P, NQ, TT, LIM>(g, tb, H, dE, e0, min(EPB, g.ne - e0));
 }
 
-template <int P, int NQ, typename TT, bool LIM>
+template <int P, int NQ, typename TT, bool LIM, bool HOLD = false>
 __global__ __launch_bounds__(BLOCK) void k3_setupd(Geom g, Tables tba, Target tg, const double *__restrict__ x, TT *__restrict__ H, double *__restrict__ dE)
 {
     const Tab tb = kernel_tables<sizeof(Geom)>();
     constexpr int EPB = S3<P, NQ>::EPB;
     const int e0 = xcd_block(blockIdx.x, gridDim.x) * EPB;
-    b3_setupd<P, NQ, TT, LIM>(g, tb, tg, x, H, dE, e0, min(EPB, g.ne - e0));
+    b3_setupd<P, NQ, TT, LIM, HOLD>(g, tb, tg, x, H, dE, e0, min(EPB, g.ne - e0));
 }
 
 template <int P, int NQ, typename TT, bool LIM>

@@ -207,6 +207,9 @@ inline void fill_setupd3(Ops &o)
             if (g.lim != 0.0)
                 hipLaunchKernelGGL((k3_setupd<P, NQ, double, true>), dim3(grid), dim3(BLOCK), 0, s,
                                    g, t, w, x, H, dE);
+            else if (hold_setup3<P, NQ, true>() && g.ne >= hold_setup3_min<NQ>())
+                hipLaunchKernelGGL((k3_setupd<P, NQ, double, false, hold_setup3<P, NQ, true>()>),
+                                   dim3(grid), dim3(BLOCK), 0, s, g, t, w, x, H, dE);
             else
                 hipLaunchKernelGGL((k3_setupd<P, NQ, double, false>), dim3(grid), dim3(BLOCK), 0, s,
                                    g, t, w, x, H, dE);
@@ -264,6 +267,16 @@ inline void fill_tiles_k3(Ops &o)
         o.apply_l2[1][0] = apply_l2_3<P, NQ, double, true>;
         o.apply_l2[1][1] = apply_l2_3<P, NQ, float, true>;
     }
+    if constexpr (hold_setup3<P, NQ, false>())
+        o.setup64 = [](int grid, hipStream_t s, const Geom &g, const Tables &t, const Target &w,
+                       const double *x, double *H) {
+            if (g.ne >= hold_setup3_min<NQ>())
+                hipLaunchKernelGGL((k3_setup<P, NQ, double, false, true>), dim3(grid), dim3(BLOCK),
+                                   0, s, g, t, w, x, H);
+            else
+                hipLaunchKernelGGL((k3_setup<P, NQ, double>), dim3(grid), dim3(BLOCK), 0, s, g, t, w,
+                                   x, H);
+        };
     fill_tile3<P, NQ, 1, 0>(o);
     fill_tile3<P, NQ, 2, 1>(o);
     fill_tile3<P, NQ, 4, 2>(o);
