@@ -244,7 +244,7 @@ __global__ __launch_bounds__(VBLOCK) void k_gather_norm(Geom g, const int32_t *_
 }
 
 // The same by one workgroup that also writes the results (out[0..2], out[8]),
-// for meshes of at most GN_ONE_NODES nodes and one energy slice: one launch
+// for meshes of at most gn_one_nodes nodes and one energy slice: one launch
 // less where a launch is what the call costs.
 template <int DIM>
 __global__ __launch_bounds__(1024) void k_gather_norm_one(Geom g, const int32_t *__restrict__ ptr,
@@ -326,7 +326,7 @@ void launch_gather_norm(const Geom &g, const int32_t *csr_ptr, const int32_t *cs
                         double *out, hipStream_t s)
 {
     const int ns = energy_slices(nb);
-    if (g.nx <= GN_ONE_NODES && ns == 1) {
+    if (g.nx <= gn_one_nodes(g) && ns == 1) {
         if (g.dim == 3)
             hipLaunchKernelGGL(k_gather_norm_one<3>, dim3(1), dim3(1024), 0, s, g, csr_ptr,
                                csr_ent, eV, grad, part, nb, out);

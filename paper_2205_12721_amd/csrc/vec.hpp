@@ -90,8 +90,16 @@ inline __host__ __device__ int energy_slice_len(int nb)
     return ESLICE * ((n + NSLICE - 1) / NSLICE);
 }
 inline int energy_slices(int nb) { return (nb + energy_slice_len(nb) - 1) / energy_slice_len(nb); }
-// Up to 4 nodes per lane of one workgroup.
-constexpr int GN_ONE_NODES = 4096;
+// Most nodes of a mesh whose gradient is gathered by one workgroup of 1024
+// lanes that also sums everything up.  Against one launch more (3 to 4 us) a
+// lane's nodes follow one another, each a chain of dependent loads, on quads of
+// up to 4, on hexes 8 copies, on general meshes through the element lists.
+// Energy + gradient, us, one workgroup / several: box quads p1 1640 nodes 21.8 /
+// 23.1, 2254 (p3) 22.9 / 23.6, 2970 23.5 / 23.1; box hexes p2 729 23.3 / 25.0, p1
+// 1320 25.1 / 24.7, 3360 32.8 / 25.6; element lists: quads p1 650 22.4 / 24.2,
+// 1122 24.5 / 24.5, 4032 32.4 / 24.1; hexes p1 720 26.4 / 28.1, 1320 35.1 / 27.7,
+// 3360 59.4 / 28.8.
+inline int gn_one_nodes(const Geom &g) { return g.dim == 2 && !g.e2n ? 2048 : 1024; }
 // F, min det, count of points with det T <= 0 from nb energy partials: to out[0..2].
 void launch_energy_reduce(const double *part, int nb, double *sl, double *out, hipStream_t s);
 // The gradient G^T eV (fixed DoFs 0) to grad, the reduced energy partials to
