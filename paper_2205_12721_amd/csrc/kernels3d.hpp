@@ -1500,10 +1500,11 @@ __device__ __forceinline__ void b3_applyc(const Geom &g, const Tab &tb, const Ta
 // of three sweeps per pair had 18 barriers, of which axis 1's added to a sum
 // in LDS, and read a product table entry per multiply-add from LDS; here an
 // entry is a scalar operand that serves one to four lines.  Setup + diagonal
-// with its gather, us: p3 n_q5 24^3 compact 127 -> 86, tensor 170 -> 150; p2
-// n_q4 64^3 compact 978 -> 648; p4 n_q6 24^3 compact 279 -> 160; diagonal alone
-// 85 -> 54, 94 -> 79, 641 -> 422, 198 -> 99.  LDS traffic and the lanes that
-// the shorter stages leave idle bound it.)
+// with its gather, us: p3 n_q5 24^3 compact 127 -> 86, tensor, which its stores
+// bound, by 1%; p2 n_q4 64^3 compact 978 -> 648; p4 n_q6 24^3 compact 279 ->
+// 160; diagonal alone 85 -> 54, 94 -> 79, 641 -> 422, 198 -> 99; only p1 n_q3 and
+// n_q4 tensor setups with diagonal are 3 to 5% slower, 58^3 419 -> 432, 759 ->
+// 788.  LDS traffic and the lanes that the shorter stages leave idle bound it.)
 template <int P, int NQ, bool LIM = false>
 struct DiagLds3 {
     using S = S3<P, NQ>;
