@@ -214,7 +214,7 @@ __device__ __forceinline__ void gather3(const Geom &g, const double *__restrict_
     gather3_store<P, NQ, CT>(r, nel, sX);
 }
 
-// Gather for the FP64 tensor action at n_q = 5 on larger meshes (flat_apply3): a
+// Gather for the tensor action at n_q = 5 on larger meshes (flat_apply3): a
 // lane takes one component of one node, (element, component, node) running over
 // the lanes, fixed DoFs as zero.
 template <int P, int NQ, int T2>
@@ -1456,11 +1456,12 @@ constexpr bool apply_layers3()
 // loads and HBM bounds the action, the flat gather is faster (workgroups; p3
 // 24^3, 6912, 120.8 us -> 120.4; 28^3 192.9 -> 192.2; p2 42^3 586.6 -> 584.1);
 // where a workgroup's own time counts, placing a node once is (p2 20^3, 3990:
-// 63.2 / 63.1; p3 13^3, 1092: 22.9 / 23.2; 6^3 9.65 / 10.0).
-template <int P, int NQ>
+// 63.2 / 63.1; p3 13^3, 1092: 22.9 / 23.2; 6^3 9.65 / 10.0).  In FP32 at p = 3
+// only (28^3 104.3 -> 103.3, 38^3 260.7 -> 255.3; p2 42^3 286.7 / 289.7).
+template <int P, int NQ, typename TT>
 constexpr bool flat_apply3()
 {
-    return NQ == 5 && P <= 3;
+    return NQ == 5 && (P == 3 || (P == 2 && sizeof(TT) == 8));
 }
 constexpr int FLAT_MIN = 4096;
 

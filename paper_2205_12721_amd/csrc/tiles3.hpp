@@ -121,7 +121,7 @@ inline void fill_tile3(Ops &o)
             // the base shape: plain_k3, which chooses the column form
             o.applyc64_t[IDX] = o.applyc64;
             o.applyc32_t[IDX] = o.applyc32;
-            if constexpr (flat_apply3<P, NQ>()) {
+            if constexpr (flat_apply3<P, NQ, double>()) {
                 o.apply64 = [](int grid, hipStream_t s, const Geom &g, const Tables &t,
                                const double *H, const double *v, double *yE) {
                     if (g.lim != 0.0)
@@ -135,6 +135,21 @@ inline void fill_tile3(Ops &o)
                                            dim3(BLOCK), 0, s, g, t, H, v, yE);
                 };
                 o.apply64_t[IDX] = o.apply64;
+            }
+            if constexpr (flat_apply3<P, NQ, float>()) {
+                o.apply32 = [](int grid, hipStream_t s, const Geom &g, const Tables &t,
+                               const float *H, const double *v, float *yE) {
+                    if (g.lim != 0.0)
+                        hipLaunchKernelGGL((k3_apply<P, NQ, float, float, true>), dim3(grid),
+                                           dim3(BLOCK), 0, s, g, t, H, v, yE);
+                    else if (grid >= FLAT_MIN)
+                        hipLaunchKernelGGL((k3_apply<P, NQ, float, float, false, 2, true>),
+                                           dim3(grid), dim3(BLOCK), 0, s, g, t, H, v, yE);
+                    else
+                        hipLaunchKernelGGL((k3_apply<P, NQ, float, float, false>), dim3(grid),
+                                           dim3(BLOCK), 0, s, g, t, H, v, yE);
+                };
+                o.apply32_t[IDX] = o.apply32;
             }
         } else {
             o.applyc64_t[IDX] = [](int grid, hipStream_t s, const Geom &g, const Tables &t,

@@ -1,4 +1,4 @@
-"""The FP64 tensor action at n_q = 5 on both sides of the 4096 workgroups (two elements each) from which
+"""The tensor action at n_q = 5 on both sides of the 4096 workgroups (two elements each) from which
 its gather runs over components as well: bitwise the action in another tile shape, which gathers by node,
 with the boundary, a mask and no DoF fixed, on the box and on the same mesh as an element list.
 """
@@ -12,12 +12,12 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("ess", ["boundary", "mask", "none"])
-@pytest.mark.parametrize("p", [2, 3])
+@pytest.mark.parametrize("p,precision", [(2, "fp64"), (3, "fp64"), (3, "mixed")])
 @pytest.mark.parametrize("ns", [(30, 13, 21), (32, 32, 8), (27, 19, 17)])  # 4095, 4096, 4361 (one ragged)
-def test_limit(p, ns, ess):
+def test_limit(p, precision, ns, ess):
     import torch
     from paper_2205_12721_amd.tmop import Context
-    log("case", p, ns, ess)
+    log("case", p, precision, ns, ess)
     e2n, nx = mesh.box_topology(3, ns, p)
     x, _ = inputs.perturbed_box(3, ns, p, basis.gll_nodes(p), 95, recipe="interior_jitter", amp=0.02)
     xd = to_dev(x)
@@ -30,7 +30,7 @@ def test_limit(p, ns, ess):
     if not isinstance(ess, str) or ess == "none":
         ways.append(dict(elem_to_node=torch.as_tensor(e2n).to(torch.int32).cuda(), num_nodes=nx))
     for kw in ways:
-        ctx = Context(3, p=p, nq1d=5, ess=ess, **kw)
+        ctx = Context(3, p=p, nq1d=5, ess=ess, precision=precision, **kw)
         ctx.hessian_setup(xd)
         ctx.set_tile(2)  # the base shape (another may have been tuned before)
         a = ctx.hessian_apply(v)
