@@ -52,15 +52,15 @@ HBM_PEAK_GBS = 8000.0  # MI355X HBM3E peak, GB/s
 # entry names the SHA-256 of the kernel sources (csrc_sha256()) and is
 # reported as null once they differ.  Summary and commands:
 # profiles/hessian_apply_traffic_24cube_q3.md.
-_SHA_C2 = "3e980f8cef5f819bd4e1afc3c8bbdf50ef75d27ce501b22c7e585d946f72553c"
+_SHA_C2 = "ba1aeb4a71c2d1422acb614b353cf10026ee683d28f568d61812e09e00f3ca67"
 TRAFFIC = {
-    ("c2", "tensor_fp64"): {"bytes": 723345183, "elements_per_workgroup": 2,
+    ("c2", "tensor_fp64"): {"bytes": 721965844, "elements_per_workgroup": 2,
                         "csrc_sha256": _SHA_C2},
-    ("c2", "tensor_mixed"): {"bytes": 369890865, "elements_per_workgroup": 2,
+    ("c2", "tensor_mixed"): {"bytes": 370766422, "elements_per_workgroup": 2,
                         "csrc_sha256": _SHA_C2},
-    ("c2", "compact_fp64"): {"bytes": 249297014, "elements_per_workgroup": 2,
+    ("c2", "compact_fp64"): {"bytes": 249297529, "elements_per_workgroup": 2,
                         "csrc_sha256": _SHA_C2},
-    ("c2", "compact_mixed"): {"bytes": 137488831, "elements_per_workgroup": 2,
+    ("c2", "compact_mixed"): {"bytes": 137506217, "elements_per_workgroup": 2,
                         "csrc_sha256": _SHA_C2},
 }
 
